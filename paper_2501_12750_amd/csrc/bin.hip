@@ -633,7 +633,6 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_scatter(JS js, int phase) {
                 if (total > host_ctr->pairs) host_ctr->pairs = total;
                 host_ctr->overflow |= total > capacity ? 1u : 0u;
                 host_ctr->overflow_tiles += n_over;
-                __threadfence_system();
             } else if (host_ctr) {
                 host_ctr->vis_count = vis;
                 host_ctr->bad_bonds = bad;
@@ -648,7 +647,6 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_scatter(JS js, int phase) {
                 host_ctr->rec_culled = 0;
                 host_ctr->lists_stopped = 0;
                 host_ctr->chunks_stopped = 0;
-                __threadfence_system();
             }
         }
     }

@@ -849,6 +849,10 @@ template <int TS, class JS, bool kCount, bool kTwo>
 __global__ void __launch_bounds__(kBlock) k_resolve_tail(JS js, const unsigned long long* ovf, uint32_t* ovf_n,
                                                           int phase) {
     const uint32_t total = *(volatile uint32_t*)ovf_n;
+    // Nothing overflowed (the usual frame): nothing to clear or publish, and
+    // no fences.  The count is the same for every workgroup (it is cleared
+    // only after all of them have taken a ticket, which none does here).
+    if (!kCount && total == 0) return;
     for (uint32_t e = blockIdx.x; e < total; e += gridDim.x) {
         const unsigned long long v = ovf[e];
         const Job& J = js.job((int)(v >> 32));
