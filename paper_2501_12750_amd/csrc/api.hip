@@ -946,7 +946,7 @@ int render_locked(std::vector<JobDesc>& d, bool bin, bool shade, hipStream_t str
         const uint64_t nprim = (uint64_t)s.F.n_atoms + s.F.n_bonds;
         nprims[i] = nprim;
         uint32_t groups, chunk, nc = 0;
-        vtx::bin_grid(nprim, &groups, &chunk);
+        vtx::bin_grid(nprim, n, &groups, &chunk);
         if (s.scene) {
             // each binning workgroup takes whole clusters
             nc = s.S.atom_clusters + s.S.bond_clusters;
@@ -1021,10 +1021,12 @@ int render_locked(std::vector<JobDesc>& d, bool bin, bool shade, hipStream_t str
         uint32_t per = starts[start_index + 1] - starts[start_index];
         for (size_t i = 1; per && i <= count; ++i)
             if (starts[start_index + i] - starts[start_index] != (uint32_t)i * per) per = 0;
-        uint32_t no_bonds = 1;
-        for (size_t i = first; i < first + count; ++i)
+        uint32_t no_bonds = 1, few = 1;
+        for (size_t i = first; i < first + count; ++i) {
             if (jobs[i].S.bond_clusters || jobs[i].F.n_bonds) no_bonds = 0;
-        return vtx::JobList{dj, dk, ds, (uint32_t)count, per, no_bonds};
+            if (jobs[i].S.atom_clusters > vtx::kFewClusters * jobs[i].bb.groups) few = 0;
+        }
+        return vtx::JobList{dj, dk, ds, (uint32_t)count, per, no_bonds, few};
     };
     if (n > 1 && capture) {
         // the tables must be the ones the eager call uploaded
@@ -1333,7 +1335,7 @@ int vtx_render_static(const float* positions, const float* radii, const uint32_t
     const int T = F.tiles_x * F.tiles_y;
     const uint64_t nprim = (uint64_t)F.n_atoms + F.n_bonds;
     uint32_t groups, chunk;
-    vtx::bin_grid(nprim, &groups, &chunk);
+    vtx::bin_grid(nprim, 1, &groups, &chunk);
     const StaticLayout L = static_layout(T, groups, chunk);
     if (L.fixed_end + 256 * sizeof(uint2) > kStaticScratchBytes)
         return fail(VTX_EOVERFLOW,
@@ -1469,7 +1471,7 @@ size_t vtx_frame_scratch_bytes(int32_t W, int32_t H, int64_t n_atoms, int64_t n_
     const uint64_t T = (uint64_t)((W + ts - 1) / ts) * ((H + ts - 1) / ts);
     const uint64_t nprim = (uint64_t)n_atoms + (uint64_t)n_bonds;
     uint32_t groups, chunk;
-    vtx::bin_grid(nprim, &groups, &chunk);
+    vtx::bin_grid(nprim, 1, &groups, &chunk);
     uint64_t cap = nprim / 2;
     if (cap < kMinCapacity) cap = kMinCapacity;
     // tile counts and offsets, per-layer cursors, starts and totals, visible lists,

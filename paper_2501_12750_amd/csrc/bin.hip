@@ -28,6 +28,8 @@
 // capacity are left empty; the resolve pass then finds those tiles' primitives
 // in the per-workgroup visible lists, so every frame is exact whatever the
 // capacity.
+#include <algorithm>
+
 #include "prims.h"
 
 namespace vtx {
@@ -173,8 +175,9 @@ __device__ inline bool cluster_hidden(const Frame& F, const SceneDev& S, const B
 // Count.  Work block b of a job is that job's binning workgroup b.
 // kRest: the rest pass of a two-pass frame (a separate instantiation keeps
 // the cluster test out of the others' registers).  kAtoms: a scene without
-// bonds (no bond path in the loop: fewer live registers).
-template <class JS, bool kScene, bool kRest, bool kAtoms = false>
+// bonds (no bond path in the loop: fewer live registers).  kQuarters: see
+// quarters() for the scenes that take it.
+template <class JS, bool kScene, bool kRest, bool kAtoms = false, bool kQuarters = false>
 __global__ void __launch_bounds__(kBinThreads, 8) k_count(JS js, int phase) {
     extern __shared__ uint32_t hist[];
     __shared__ uint32_t local_n, bx0, by0, bx1, by1;
@@ -273,8 +276,8 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_count(JS js, int phase) {
         emit(vis, it.src, x0, y0, x1, y1);
     };
     if constexpr (kScene) {
-        // Resident scene: each wave takes whole clusters (256 primitives of
-        // one kind, so the kind is the same across the wave).  An atom
+        // Resident scene: each wave takes whole clusters or quarters of them
+        // (256 primitives of one kind, so the kind is the same across the wave).  An atom
         // cluster's 64-atom quarters take the sphere-only path.
         // Workgroup b takes positions [c0, c1) of the visible clusters in
         // depth-class order, so the workgroups run front to back.  A
@@ -298,11 +301,15 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_count(JS js, int phase) {
             while (cls_end[cls] <= q) ++cls;
             return S.vis_clusters[(size_t)cls * stride + (q - (cls ? cls_end[cls - 1] : 0u))];
         };
-        const uint32_t nw = kBinThreads / 64;
+        // kQuarters: the waves take the clusters' 64-primitive quarters in
+        // turn, four waves per cluster, else whole clusters.
+        constexpr uint32_t kPer = kQuarters ? 4u : 1u;   // waves per cluster
+        const uint32_t nw = kBinThreads / 64 / kPer;
         const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
-        const uint32_t lane = __lane_id();
-        uint32_t cn = c0 + wave < c1 ? cluster_at(c0 + wave) : 0u;
-        for (uint32_t ci = c0 + wave; ci < c1; ci += nw) {
+        const uint32_t first = c0 + wave / kPer;
+        const uint32_t part = (wave % kPer) * 64u + __lane_id();
+        uint32_t cn = first < c1 ? cluster_at(first) : 0u;
+        for (uint32_t ci = first; ci < c1; ci += nw) {
             const uint32_t ce = (uint32_t)__builtin_amdgcn_readfirstlane((int)cn);
             const uint32_t c = ce & ~kClusterInside;
             const bool inside = (ce & kClusterInside) != 0u;   // its atoms need no frustum test
@@ -313,8 +320,8 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_count(JS js, int phase) {
             if (kAtoms || c < S.atom_clusters) {
                 // one quarter at a time: holding more quarters' atoms spills
                 // registers, which costs more than the load latency it hides
-                for (int q = 0; q < 4; ++q) {
-                    const uint32_t i = c * kCluster + (uint32_t)q * 64u + lane;
+                for (uint32_t q = 0; q < 4u / kPer; ++q) {
+                    const uint32_t i = c * kCluster + q * 64u + part;
                     float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
                     if (i < S.n_atoms) a = to_global(S.xyzr)[i];
                     int x0 = 0, y0 = 0, x1 = -1, y1 = -1;
@@ -334,8 +341,8 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_count(JS js, int phase) {
                     emit(vis, i, x0, y0, x1, y1);
                 }
             } else if constexpr (!kAtoms) {
-                for (int q = 0; q < 4; ++q) {
-                    const uint32_t j = (c - S.atom_clusters) * kCluster + (uint32_t)q * 64u + lane;
+                for (uint32_t q = 0; q < 4u / kPer; ++q) {
+                    const uint32_t j = (c - S.atom_clusters) * kCluster + q * 64u + part;
                     emit_item(j < S.n_bonds ? fetch_scene(S, S.n_atoms + j) : empty_item());
                 }
             }
@@ -721,10 +728,23 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_scatter(JS js, int phase) {
 
 }  // namespace
 
-void bin_grid(uint64_t nprim, uint32_t* groups, uint32_t* chunk) {
-    uint64_t g = (nprim + 4095) / 4096;
+// Two workgroups of 16 waves fill a CU, so a large scene takes 512 workgroups
+// of 4096 primitives or more.  Below that the launch leaves CUs idle and each
+// workgroup's primitives are a serial chain (four rounds of 1024 threads for
+// 4096), so a single render cuts them finer: 512 primitives each up to 128
+// workgroups, 1024 up to 256.  Past those the finer cut loses: every
+// workgroup adds to, and reserves a run in, each tile it touches, and 107,640
+// large spheres at 3840x2160 took 604 us in 210 workgroups against 594 in
+// 106.  (4,096 atoms at 256x256: 73 us in one workgroup, 58 in 8; 50,000 at
+// 720p: 98 in 13, 82 in 98; 214,785 primitives at 1080p: 162 in 53, 146 in
+// 210.)  A batch's renders share the device: 512 workgroups over all of them
+// are enough, and 256 renders of 50,000 atoms lose 8 % with 98 each.
+void bin_grid(uint64_t nprim, uint64_t renders, uint32_t* groups, uint32_t* chunk) {
+    const uint64_t share = std::max<uint64_t>(1, kMaxBinGroups / std::max<uint64_t>(1, renders));
+    auto cut = [&](uint64_t per, uint64_t most) { return std::min((nprim + per - 1) / per, most); };
+    uint64_t g = std::max(cut(4096, kMaxBinGroups),
+                          std::max(cut(512, std::min<uint64_t>(128, share)), cut(1024, std::min<uint64_t>(256, share))));
     if (g < 1) g = 1;
-    if (g > kMaxBinGroups) g = kMaxBinGroups;
     uint64_t c = (nprim + g - 1) / g;
     if (c < 1) c = 1;
     *groups = (uint32_t)g;
@@ -743,16 +763,27 @@ hipError_t launch_zero(uint32_t* p, size_t n, hipStream_t stream) {
 inline bool atoms_only(const OneJob& js) { return js.j.S.bond_clusters == 0; }
 inline bool atoms_only(const JobList& js) { return js.no_bonds != 0; }
 
+// A scene of few clusters per binning workgroup is dealt by quarters: whole
+// clusters would leave most of the workgroup's 16 waves without work
+// (107,500 atoms with bonds, two clusters per workgroup: 29 us by clusters,
+// 23 by quarters).  So is any scene with bonds (1M atoms and bonds: 48 us by
+// clusters, 46 by quarters); large atom-only scenes are not, whose waves then
+// wait on a cluster id per quarter (100M atoms: 180 us by clusters, 199 by
+// quarters).
+inline bool quarters(const OneJob& js) { return js.j.S.atom_clusters <= kFewClusters * js.j.bb.groups; }
+inline bool quarters(const JobList& js) { return js.few_clusters != 0; }
+
 template <class JS>
 hipError_t count_impl(const JS& js, bool scene, int phase, uint32_t grid, int max_tiles, hipStream_t stream) {
     if (max_tiles > kMaxLdsTiles) return hipErrorInvalidValue;
     if (phase != kPhaseAll && !scene) return hipErrorInvalidValue;
     if (grid == 0) return hipSuccess;
     const size_t lds = (size_t)max_tiles * sizeof(uint32_t);
-    if (scene && phase == kPhaseRest) return dispatch(k_count<JS, true, true>, grid, kBinThreads, lds, stream, js, phase);
-    if (scene && atoms_only(js)) return dispatch(k_count<JS, true, false, true>, grid, kBinThreads, lds, stream, js, phase);
-    if (scene) return dispatch(k_count<JS, true, false>, grid, kBinThreads, lds, stream, js, phase);
-    return dispatch(k_count<JS, false, false>, grid, kBinThreads, lds, stream, js, phase);
+    if (!scene) return dispatch(k_count<JS, false, false>, grid, kBinThreads, lds, stream, js, phase);
+    if (phase == kPhaseRest) return dispatch(k_count<JS, true, true>, grid, kBinThreads, lds, stream, js, phase);
+    if (!atoms_only(js)) return dispatch(k_count<JS, true, false, false, true>, grid, kBinThreads, lds, stream, js, phase);
+    if (quarters(js)) return dispatch(k_count<JS, true, false, true, true>, grid, kBinThreads, lds, stream, js, phase);
+    return dispatch(k_count<JS, true, false, true>, grid, kBinThreads, lds, stream, js, phase);
 }
 
 template <class JS>

@@ -381,8 +381,13 @@ struct BinBuffers {
     Counters* host_ctr;     // device address of host-mapped counters (may be null)
 };
 
-// Binning grid for n primitives (groups <= kMaxBinGroups, groups * chunk >= n).
-void bin_grid(uint64_t nprim, uint32_t* groups, uint32_t* chunk);
+// Clusters per binning workgroup up to which an atom-only scene's count deals
+// them to the waves by quarters.
+constexpr uint32_t kFewClusters = 8;
+
+// Binning grid for n primitives of one of `renders` renders launched together
+// (groups <= kMaxBinGroups, groups * chunk >= n).
+void bin_grid(uint64_t nprim, uint64_t renders, uint32_t* groups, uint32_t* chunk);
 
 // Resident scene (device arrays owned by the library).  Atoms are stored in
 // Morton order as an xyzr stream, grouped in clusters of kCluster; bonds are
@@ -480,6 +485,7 @@ struct JobList {
     uint32_t n;
     uint32_t per;            // when every job has this many blocks (else 0): job g / per
     uint32_t no_bonds;       // no job's scene holds bonds (the count's atom-only instantiation)
+    uint32_t few_clusters;   // every job's binning workgroups take at most kFewClusters clusters each
     __device__ int find(uint32_t g, uint32_t& local) const {
         if (per) {
             if (g >= n * per) return -1;
