@@ -1132,9 +1132,6 @@ int render_locked(std::vector<JobDesc>& d, bool bin, bool shade, hipStream_t str
                                                 count, ws->d_ovf, ws->d_ovf_n, stream));
             }
         }
-        // batches: FP64 depths of the winners the resolve marked (a single
-        // render's resolve writes them itself)
-        if (n > 1) VTX_HIP(vtx::launch_refine(list_of(0, n, 2 * (n + 1)), g_shade, stream));
         for (size_t i = 0; i < n; ++i) {
             ws->slots[i]->dirty = false;
             ws->slots[i]->pending_capacity = ws->slots[i]->bb.capacity;

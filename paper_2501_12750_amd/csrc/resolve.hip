@@ -225,10 +225,6 @@ __device__ inline float refine_depth_at(const Frame& F, const global_t<const flo
     return z > 0.0f && z < INFINITY ? z : z32;
 }
 
-__device__ inline float refine_depth(const Job& J, uint32_t id, int px, int py, float z32) {
-    return refine_depth_at(J.F, to_global(J.pos), to_global(J.rad), to_global(J.bonds), id, px, py, z32);
-}
-
 // Expand a list record into the LDS form.
 __device__ inline Rec make_rec(const Frame& F, const PrimRec& p) {
     Rec r;
@@ -254,9 +250,13 @@ __device__ inline Rec make_rec(const Frame& F, const PrimRec& p) {
 // View-space record of a visible primitive, rebuilt from its source (the
 // tile lists hold only source indices and footprints).  The count pass has
 // culled it already, so the frustum test is not repeated.
-__device__ inline bool source_record(const Job& J, uint32_t src, PrimRec& pr) {
+__device__ inline bool source_record(JobRef R, uint32_t src, PrimRec& pr) {
     double v[6], rr;
-    return item_view<false>(J.F, fetch_src(J, src), pr, v, rr);
+    const Frame F = R.frame();
+    const SceneDev S = R.scene();
+    const Item it = S.xyzr ? fetch_scene(S, src)
+                           : fetch_plain(to_global(R.pos()), to_global(R.rad()), to_global(R.bonds()), F.n_atoms, src);
+    return item_view<false>(F, it, pr, v, rr);
 }
 
 // Resolves tile t of job J, whose list holds n records from offset o
@@ -266,11 +266,11 @@ __device__ inline bool source_record(const Job& J, uint32_t src, PrimRec& pr) {
 // records and their prefix.  Two-pass frames: the front pass also stores the
 // farthest depth of each 16x16 cell of the tile; the rest pass starts from the
 // front pass's depth and id.
-// kInline: the write-out recomputes the marked winners' depths in FP64 itself
-// (single renders); otherwise it leaves them to the refine pass (batches,
-// whose instantiations have no registers to spare for it).
-template <int TS, bool kCount, bool kTail, bool kTwo, bool kInline>
-__device__ inline void resolve_tile(const Job& J, int t, uint32_t n, uint64_t o, int phase_arg) {
+template <int TS, bool kCount, bool kTail, bool kTwo>
+__device__ __forceinline__ void resolve_tile(JobRef R, int t, uint32_t n, uint64_t o, int phase_arg) {
+    const JobRef R0 = R.again();
+    const Frame F = R0.frame();
+    const BinBuffers bb = R0.bins();
     const int phase = kTwo ? phase_arg : (int)kPhaseAll;   // one-pass instantiations drop the two-pass code
     __shared__ unsigned long long keys[TS * TS];
     __shared__ Rec recs[kChunk];
@@ -293,18 +293,17 @@ __device__ inline void resolve_tile(const Job& J, int t, uint32_t n, uint64_t o,
     auto rec_at = [&](uint32_t j) -> const Rec& {
         return *reinterpret_cast<const Rec*>(reinterpret_cast<const char*>(recs) + __umul24(j, (uint32_t)sizeof(Rec)));
     };
-    const Frame F = J.F;
-    uint32_t* __restrict__ const cnt = J.bb.tile_cnt;
-    const global_t<const uint2>* __restrict__ const list = to_global(J.bb.list);
-    const global_t<const uint32_t>* __restrict__ const vis_src = to_global(J.bb.vis_src);
-    const global_t<const uint2>* __restrict__ const vis_rect = to_global(J.bb.vis_rect);
-    const uint32_t* __restrict__ const vis_cnt = J.bb.vis_cnt;
-    const uint2* __restrict__ const vis_box = J.bb.vis_box;
-    const uint32_t chunk = J.bb.chunk, groups = J.bb.groups;
-    uint32_t* __restrict__ const fill = J.bb.tile_fill;
-    Counters* const ctr = J.bb.ctr;
-    global_t<float>* __restrict__ const depth = to_global(J.depth);
-    global_t<uint32_t>* __restrict__ const out_id = to_global(J.id);
+    uint32_t* __restrict__ const cnt = bb.tile_cnt;
+    const global_t<const uint2>* __restrict__ const list = to_global(bb.list);
+    const global_t<const uint32_t>* __restrict__ const vis_src = to_global(bb.vis_src);
+    const global_t<const uint2>* __restrict__ const vis_rect = to_global(bb.vis_rect);
+    const uint32_t* __restrict__ const vis_cnt = bb.vis_cnt;
+    const uint2* __restrict__ const vis_box = bb.vis_box;
+    const uint32_t chunk = bb.chunk, groups = bb.groups;
+    uint32_t* __restrict__ const fill = bb.tile_fill;
+    Counters* const ctr = bb.ctr;
+    global_t<float>* __restrict__ const depth = to_global(R0.depth());
+    global_t<uint32_t>* __restrict__ const out_id = to_global(R0.id());
 
     const int tid = threadIdx.x, lane = __lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -336,7 +335,7 @@ __device__ inline void resolve_tile(const Job& J, int t, uint32_t n, uint64_t o,
         // every wave has read the tile's count (it sets the trip count of the
         // barrier loop below): re-arm it for the next frame's count kernel
         if (tid == 0) cnt[t] = 0;
-        if ((uint32_t)tid < J.bb.layers) fill[(size_t)tid * F.tiles_x * F.tiles_y + t] = 0;
+        if ((uint32_t)tid < bb.layers) fill[(size_t)tid * F.tiles_x * F.tiles_y + t] = 0;
 
         // one (record, pixel) ray test folded into the tile's LDS depth buffer
         auto test_pixel = [&](const Rec& rc, int lx, int ly) {
@@ -390,7 +389,7 @@ __device__ inline void resolve_tile(const Job& J, int t, uint32_t n, uint64_t o,
             const int x1 = min((int)(r.y & 0xFFFF), px0 + TS - 1) - px0;
             const int y1 = min((int)(r.y >> 16), py0 + TS - 1) - py0;
             if (x0 > x1 || y0 > y1) return false;
-            if (!source_record(J, vis_src[k], pr)) return false;
+            if (!source_record(R.again(), vis_src[k], pr)) return false;
             pr.g1.w = (uint32_t)x0 | ((uint32_t)y0 << 8) | ((uint32_t)(x1 - x0 + 1) << 16) |
                       ((uint32_t)(y1 - y0 + 1) << 24);
             return true;
@@ -629,7 +628,7 @@ __device__ inline void resolve_tile(const Job& J, int t, uint32_t n, uint64_t o,
         // Layered lists (resident scenes) run front to back by layer: once
         // every record from a layer on lies behind all block depths of the
         // tile, the rest of the list is culled whole, unread.
-        const uint32_t L = kTail || stats || n <= (uint32_t)kChunk ? 1u : J.bb.layers;   // one chunk: nothing to stop
+        const uint32_t L = kTail || stats || n <= (uint32_t)kChunk ? 1u : bb.layers;   // one chunk: nothing to stop
         if (L > 1 && wave == 0) {
             uint32_t zr = lane < (int)L ? ctr->layer_zlo[phase == kPhaseRest ? 1 : 0][lane] : 0x7F800000u;
 #pragma unroll
@@ -639,7 +638,7 @@ __device__ inline void resolve_tile(const Job& J, int t, uint32_t n, uint64_t o,
             }
             if (lane < (int)L) {
                 lay_zrest[lane] = zr;
-                lay_start[lane] = J.bb.layer_off[(size_t)lane * F.tiles_x * F.tiles_y + t];
+                lay_start[lane] = bb.layer_off[(size_t)lane * F.tiles_x * F.tiles_y + t];
             }
         }
         bool hz_set = false;   // the block depths hold a refresh (uniform)
@@ -666,7 +665,7 @@ __device__ inline void resolve_tile(const Job& J, int t, uint32_t n, uint64_t o,
                 have = base + tid < nsrc && fetch_overflow(base + tid, pr);
             } else {
                 const uint2 e = nxt;
-                have = nxt_ok && source_record(J, e.x, pr);
+                have = nxt_ok && source_record(R.again(), e.x, pr);
                 pr.g1.w = e.y;
                 nxt_ok = base + kChunk + tid < nsrc;
                 if (nxt_ok) nxt = list[o + base + kChunk + tid];
@@ -753,41 +752,69 @@ __device__ inline void resolve_tile(const Job& J, int t, uint32_t n, uint64_t o,
                 if (tid < kCells * kCells) {
                     const int cy = tid / kCells, cx = tid - cy * kCells;
                     const int gx = tx * kCells + cx, gy = ty * kCells + cy;
-                    if (gx < J.bb.hz16_w && gy < (F.H + kHzCell - 1) / kHzCell) {
+                    if (gx < bb.hz16_w && gy < (F.H + kHzCell - 1) / kHzCell) {
                         uint32_t m = 0;
                         for (int by = 0; by < kSub; ++by)
                             for (int bx = 0; bx < kSub; ++bx) m = max(m, hz[(cy * kSub + by) * (TS / 4) + cx * kSub + bx]);
-                        J.bb.hz16[(size_t)gy * J.bb.hz16_w + gx] = m;
+                        bb.hz16[(size_t)gy * bb.hz16_w + gx] = m;
                     }
                 }
             }
         }
 
-        // The G-buffer: the winner of each pixel.  Inline, the last pass
-        // writes the marked winners' depths recomputed in FP64 and plain ids;
-        // otherwise (and in the front pass of a two-pass frame, which the
-        // rest pass continues from) the FP32 depth and the id with its refine
-        // mark, for the refine pass.
-        const bool finish = kInline && phase != kPhaseFront;
+        // The G-buffer: the winner of each pixel.  The last pass gives the
+        // marked winners their depths recomputed in FP64 and plain ids; the
+        // front pass of a two-pass frame, which the rest pass continues from,
+        // keeps the FP32 depths and the marks.
+        const bool finish = phase != kPhaseFront;
+        const JobRef Rr = R.again();
+        const Frame Fr = Rr.frame();
+        auto is_marked = [&](unsigned long long kk) { return kk != ~0ull && (!F.refine_flag || ((uint32_t)kk & kRefineBit)); };
+        auto refined = [&](unsigned long long kk, int i) -> unsigned long long {
+            const uint32_t id = F.refine_flag ? (uint32_t)kk & ~kRefineBit : (uint32_t)kk;
+            const float z = refine_depth_at(Fr, to_global(Rr.pos()), to_global(Rr.rad()), to_global(Rr.bonds()), id, px0 + i % TS, py0 + i / TS,
+                                            __uint_as_float((uint32_t)(kk >> 32)));
+            return ((unsigned long long)__float_as_uint(z) << 32) | id;
+        };
+        // Several pixels per thread: about one winner in five is marked, in
+        // nearly every wave, so the marked pixels are packed into a list first
+        // and only as many waves as they fill run the FP64 code (a trajectory
+        // batch of 256 renders, 32-pixel tiles: 3.98 ms; with a pass of its
+        // own over the ids after the resolve 5.14 ms).  With one pixel per
+        // thread the list's barriers cost more than the waves it saves (1M
+        // atoms and bonds at 1080p, 16-pixel tiles: 86 us packed, 80 not).
+        constexpr bool kPacked = TS * TS > kBlock;
+        if (kPacked && finish) {
+            uint16_t* const todo = reinterpret_cast<uint16_t*>(recs);   // the records are done with
+            static_assert(TS * TS * sizeof(uint16_t) <= sizeof(recs), "one list entry per pixel of the tile");
+            if (tid == 0) wsum[0] = 0u;
+            __syncthreads();
+            for (int i = tid; i < TS * TS; i += kBlock) {   // whole waves: TS * TS is a multiple of kBlock
+                const unsigned long long kk = keys[i];
+                const unsigned long long mm = __ballot(is_marked(kk));
+                uint32_t at = 0;
+                if (mm && lane == 0) at = atomicAdd(&wsum[0], (uint32_t)__popcll(mm));
+                at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+                if (is_marked(kk)) todo[at + (uint32_t)__popcll(mm & __lanemask_lt())] = (uint16_t)i;
+            }
+            __syncthreads();
+            const uint32_t n_todo = wsum[0];
+#pragma unroll 1
+            for (uint32_t e = (uint32_t)tid; e < n_todo; e += kBlock) {
+                const int i = todo[e];
+                keys[i] = refined(keys[i], i);
+            }
+            __syncthreads();
+        }
 #pragma unroll 1
         for (int i = tid; i < TS * TS; i += kBlock) {
             const int ly = i / TS, lx = i - ly * TS;
             if (lx < tw && ly < th) {
-                const unsigned long long kk = keys[i];
+                unsigned long long kk = keys[i];
                 const size_t p = (size_t)(py0 + ly) * F.W + (px0 + lx);
-                float zo = INFINITY;
-                uint32_t io = kBackground;
-                if (kk != ~0ull) {
-                    io = (uint32_t)(kk & 0xFFFFFFFFull);
-                    zo = __uint_as_float((uint32_t)(kk >> 32));
-                    if (finish) {
-                        const bool marked = !F.refine_flag || (io & kRefineBit);
-                        io &= F.refine_flag ? ~kRefineBit : ~0u;
-                        if (marked) zo = refine_depth(J, io, px0 + lx, py0 + ly, zo);
-                    }
-                }
-                depth[p] = zo;
-                out_id[p] = io;
+                if (!kPacked && finish && is_marked(kk)) kk = refined(kk, i);
+                depth[p] = kk == ~0ull ? INFINITY : __uint_as_float((uint32_t)(kk >> 32));
+                out_id[p] = (uint32_t)kk;   // no hit: kBackground, the key's low word
             }
         }
     }
@@ -838,7 +865,21 @@ __global__ void __launch_bounds__(kBlock, kCount ? 1 : 7) k_resolve(JS js, unsig
         if (threadIdx.x == 0) ovf[atomicAdd(ovf_n, 1u)] = ((unsigned long long)ji << 32) | tu;
         return;
     }
-    resolve_tile<TS, kCount, false, kTwo, !JS::kMany>(J, (int)tu, n, o, phase);
+    if (!kTwo && n == 0) {   // nothing to cast or to re-arm: background
+        const int W = J.F.W, H = J.F.H, tiles_x = J.F.tiles_x;
+        const int px0 = ((int)tu % tiles_x) * TS, py0 = ((int)tu / tiles_x) * TS;
+        global_t<float>* __restrict__ const depth = to_global(J.depth);
+        global_t<uint32_t>* __restrict__ const out_id = to_global(J.id);
+        for (int i = threadIdx.x; i < TS * TS; i += kBlock) {
+            const int x = px0 + i % TS, y = py0 + i / TS;
+            if (x < W && y < H) {
+                depth[(size_t)y * W + x] = INFINITY;
+                out_id[(size_t)y * W + x] = kBackground;
+            }
+        }
+        return;
+    }
+    resolve_tile<TS, kCount, false, kTwo>(job_ref(js, ji), (int)tu, n, o, phase);
 }
 
 // Tail launch (a fixed grid, queued right after the main one): resolves the
@@ -857,7 +898,7 @@ __global__ void __launch_bounds__(kBlock) k_resolve_tail(JS js, const unsigned l
         const unsigned long long v = ovf[e];
         const Job& J = js.job((int)(v >> 32));
         const int t = (int)(v & 0xFFFFFFFFull);
-        resolve_tile<TS, kCount, true, kTwo, !JS::kMany>(J, t, J.bb.tile_cnt[t], J.bb.tile_off[t], phase);
+        resolve_tile<TS, kCount, true, kTwo>(job_ref(js, (int)(v >> 32)), t, J.bb.tile_cnt[t], J.bb.tile_off[t], phase);
         __syncthreads();   // the next tile reuses the LDS
     }
     if (threadIdx.x == 0) {
@@ -921,138 +962,6 @@ hipError_t resolve_impl(const JS& js, int tile, int phase, uint32_t grid, unsign
         default: return hipErrorInvalidValue;
     }
 }
-
-// Depth refinement of a batch, over the shade's 16x16 blocks, kRefineBlocks
-// of them per workgroup: a pixel whose winner the resolve marked (kRefineBit
-// in the id, or every hit when the frame has too many primitives for the
-// mark) gets its depth recomputed from the primitive's FP64 data
-// (refine_depth) and its mark cleared; every other pixel keeps the resolve's
-// FP32 depth, which is within the tolerance there (see kGrazeCos).
-constexpr int kRefineBlocks = 16;   // 16x16 blocks per refine workgroup (pixels per thread in flight)
-
-template <class JS>
-__global__ void __launch_bounds__(kBlock, 6) k_refine(JS js, uint32_t nblocks) {
-    __shared__ uint16_t todo[kRefineBlocks * kBlock];
-    __shared__ uint32_t todo_id[kRefineBlocks * kBlock];   // the entry's id as loaded (mark included)
-    __shared__ uint32_t wave_n[kBlock / 64];
-    __shared__ int blk_job[kRefineBlocks];
-    __shared__ uint32_t blk_tile[kRefineBlocks];
-    const int tid = threadIdx.x, wave = tid >> 6;
-    const uint32_t q = (uint32_t)xcd_contiguous(blockIdx.x, gridDim.x);
-    // the id of this thread's pixel in each of the workgroup's blocks, all
-    // loads issued before any is used
-    // (one search for the first block; the others follow it)
-    int ji[kRefineBlocks];
-    uint32_t tu[kRefineBlocks], raw[kRefineBlocks];
-    ji[0] = q * kRefineBlocks < nblocks ? js.find(q * kRefineBlocks, tu[0]) : -1;
-#pragma unroll
-    for (int s = 0; s < kRefineBlocks; ++s) {
-        if (s > 0) {
-            ji[s] = ji[s - 1];
-            tu[s] = tu[s - 1];
-            js.next(ji[s], tu[s]);
-        }
-        raw[s] = kBackground;
-        if (ji[s] >= 0) {
-            const Frame& F = js.job(ji[s]).F;
-            const int tiles_x = (F.W + 15) / 16;
-            const int x = ((int)tu[s] % tiles_x) * 16 + (tid & 15), y = ((int)tu[s] / tiles_x) * 16 + (tid >> 4);
-            if (x < F.W && y < F.H) raw[s] = to_global(js.job(ji[s]).id)[(size_t)y * F.W + x];
-        }
-    }
-    // the marked pixels, packed into a list so that only as many waves as
-    // they fill run the FP64 recomputation
-    uint32_t mine = 0, n_mine = 0;
-#pragma unroll
-    for (int s = 0; s < kRefineBlocks; ++s) {
-        if (ji[s] < 0 || raw[s] == kBackground) continue;
-        if (!js.job(ji[s]).F.refine_flag || (raw[s] & kRefineBit)) {
-            mine |= 1u << s;
-            ++n_mine;
-        }
-    }
-    uint32_t incl = n_mine;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t u = (uint32_t)__shfl_up((int)incl, o);
-        if ((int)__lane_id() >= o) incl += u;
-    }
-    if (__lane_id() == 63) wave_n[wave] = incl;
-    if (tid < kRefineBlocks) {
-        // each entry's job and block, for the threads that take it
-#pragma unroll
-        for (int s = 0; s < kRefineBlocks; ++s)
-            if (tid == s) {
-                blk_job[s] = ji[s];
-                blk_tile[s] = tu[s];
-            }
-    }
-    __syncthreads();
-    uint32_t before = 0, total = 0;
-    for (int w = 0; w < kBlock / 64; ++w) {
-        before += w < wave ? wave_n[w] : 0u;
-        total += wave_n[w];
-    }
-    uint32_t at = before + incl - n_mine;
-#pragma unroll
-    for (int s = 0; s < kRefineBlocks; ++s)
-        if (mine & (1u << s)) {
-            todo_id[at] = raw[s];
-            todo[at++] = (uint16_t)(s * kBlock + tid);
-        }
-    __syncthreads();
-    if (ji[0] >= 0 && ji[kRefineBlocks - 1] == ji[0]) {
-        // all the workgroup's blocks are one job's (the usual case): block s
-        // is that job's block tu[0] + s, and the job's frame is read once,
-        // into scalar registers, rather than per entry
-        const Job& J = js.job(__builtin_amdgcn_readfirstlane(ji[0]));
-        const Frame& F = J.F;
-        const global_t<const float>* __restrict__ const pos = to_global(J.pos);
-        const global_t<const float>* __restrict__ const rad = to_global(J.rad);
-        const global_t<const uint32_t>* __restrict__ const bonds = to_global(J.bonds);
-        global_t<float>* __restrict__ const depth = to_global(J.depth);
-        global_t<uint32_t>* __restrict__ const out_id = to_global(J.id);
-        const int tiles_x = (F.W + 15) / 16, tb0 = __builtin_amdgcn_readfirstlane((int)tu[0]);
-        for (uint32_t e = (uint32_t)tid; e < total; e += kBlock) {
-            const int s = todo[e] / kBlock, t = todo[e] % kBlock;
-            const int tb = tb0 + s;
-            const int px = (tb % tiles_x) * 16 + (t & 15), py = (tb / tiles_x) * 16 + (t >> 4);
-            const size_t p = (size_t)py * F.W + px;
-            const uint32_t r0 = todo_id[e];
-            const uint32_t id = F.refine_flag ? r0 & ~kRefineBit : r0;
-            depth[p] = refine_depth_at(F, pos, rad, bonds, id, px, py, depth[p]);
-            if (F.refine_flag) out_id[p] = id;
-        }
-        return;
-    }
-    for (uint32_t e = (uint32_t)tid; e < total; e += kBlock) {
-        const int s = todo[e] / kBlock, t = todo[e] % kBlock;
-        // the entry's block, one of the workgroup's (no second search)
-        const int j = blk_job[s];
-        const uint32_t tb = blk_tile[s];
-        const Job& J = js.job(j);
-        const Frame& F = J.F;
-        const int tiles_x = (F.W + 15) / 16;
-        const int px = ((int)tb % tiles_x) * 16 + (t & 15), py = ((int)tb / tiles_x) * 16 + (t >> 4);
-        const size_t p = (size_t)py * F.W + px;
-        const uint32_t r0 = todo_id[e];
-        const uint32_t id = F.refine_flag ? r0 & ~kRefineBit : r0;
-        global_t<float>* const depth = to_global(J.depth);
-        depth[p] = refine_depth(J, id, px, py, depth[p]);
-        if (F.refine_flag) to_global(J.id)[p] = id;
-    }
-}
-
-// One workgroup per kRefineBlocks of the 16x16 blocks, the grid rounded up
-// to whole XCD rounds as xcd_contiguous needs.
-template <class JS>
-hipError_t refine_impl(const JS& js, uint32_t blocks, hipStream_t stream) {
-    if (blocks == 0) return hipSuccess;
-    const int grid = xcd_grid((int)((blocks + kRefineBlocks - 1) / kRefineBlocks));
-    return dispatch(k_refine<JS>, (unsigned)grid, kBlock, 0, stream, js, blocks);
-}
-hipError_t launch_refine(const OneJob& js, uint32_t grid, hipStream_t stream) { return refine_impl(js, grid, stream); }
-hipError_t launch_refine(const JobList& js, uint32_t grid, hipStream_t stream) { return refine_impl(js, grid, stream); }
 
 hipError_t launch_resolve(const OneJob& js, int tile, int phase, uint32_t grid, bool count, unsigned long long* ovf,
                           uint32_t* ovf_n, hipStream_t stream) {

@@ -9,6 +9,7 @@
 
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 namespace vtx {
@@ -19,9 +20,9 @@ constexpr int kMaxLdsTiles = 15360;          // tile histogram of one binning wo
 constexpr uint32_t kMaxBinGroups = 512;
 constexpr uint32_t kBackground = 0xFFFFFFFFu;
 // A resolve winner whose FP32 depth may miss the depth tolerance (1e-5 of the
-// depth) carries kRefineBit in its id until the refine pass has recomputed the
-// depth in FP64 and cleared it.  Frames with 2^31 - 1 primitives or more have
-// no room for the bit and refine every hit.
+// depth) carries kRefineBit in its id until the resolve's last pass has
+// recomputed the depth in FP64 and cleared it.  Frames with 2^31 - 1
+// primitives or more have no room for the bit and refine every hit.
 constexpr uint32_t kRefineBit = 0x80000000u;
 // The FP32 sphere root is off by at most about 32 u |c| / (n.V) (u = 2^-24,
 // c the record's view-space centre, rounded once from FP64): the centre's
@@ -478,7 +479,7 @@ struct OneJob {
 // A launch over several renders, described by device tables: job i owns the
 // work blocks [start[i], start[i + 1]).
 struct JobList {
-    static constexpr bool kMany = true;   // a batch launch (see resolve_tile's kInline)
+    static constexpr bool kMany = true;   // a batch launch
     const Job* jobs;
     const SampleKernel* K;
     const uint32_t* start;   // n + 1 entries
@@ -519,6 +520,60 @@ struct JobList {
     }
 };
 
+// A job's constants read where they are used.  A kernel's job is the same
+// for the whole workgroup and no kernel writes it, so it comes by scalar
+// loads, from the kernel arguments (OneJob) or the job table (JobList).  Left
+// to itself the compiler loads everything a kernel uses at its start, more
+// than the 100 scalar registers hold, and moves the overflow through vector
+// registers, or (a job table, after the kernel's first stores) loads it by
+// lanes.  again() is a point such loads are not moved across: the words read
+// through it are loaded there, and the unused ones not at all.
+struct JobRef {
+#if defined(__HIP_DEVICE_COMPILE__)
+    using Word = const __attribute__((address_space(4))) uint32_t;
+#else
+    using Word = const uint32_t;
+#endif
+    Word* at;
+    __device__ JobRef again() const {
+        uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uintptr_t)at);
+        uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint64_t)(uintptr_t)at >> 32));
+        asm volatile("" : "+s"(lo), "+s"(hi));
+        return JobRef{(Word*)(uintptr_t)(((uint64_t)hi << 32) | lo)};
+    }
+    template <class T>
+    __device__ T words(size_t off) const {
+        static_assert(sizeof(T) % 4 == 0, "copied by words");
+        uint32_t w[sizeof(T) / 4];
+#pragma unroll
+        for (unsigned k = 0; k < sizeof(T) / 4; ++k) w[k] = at[off / 4 + k];
+        T v;
+        __builtin_memcpy(&v, w, sizeof(T));
+        return v;
+    }
+    __device__ Frame frame() const { return words<Frame>(offsetof(Job, F)); }
+    __device__ SceneDev scene() const { return words<SceneDev>(offsetof(Job, S)); }
+    __device__ BinBuffers bins() const { return words<BinBuffers>(offsetof(Job, bb)); }
+    __device__ const float* pos() const { return words<const float*>(offsetof(Job, pos)); }
+    __device__ const float* rad() const { return words<const float*>(offsetof(Job, rad)); }
+    __device__ const uint32_t* bonds() const { return words<const uint32_t*>(offsetof(Job, bonds)); }
+    __device__ float* depth() const { return words<float*>(offsetof(Job, depth)); }
+    __device__ uint32_t* id() const { return words<uint32_t*>(offsetof(Job, id)); }
+};
+
+// Job `i` of a launch whose job source is its kernel's first parameter.
+__device__ inline JobRef job_ref(const OneJob&, int) {
+    static_assert(offsetof(OneJob, j) == 0, "the job leads the kernel arguments");
+#if defined(__HIP_DEVICE_COMPILE__)
+    return JobRef{(JobRef::Word*)__builtin_amdgcn_kernarg_segment_ptr()};
+#else
+    return JobRef{nullptr};
+#endif
+}
+__device__ inline JobRef job_ref(const JobList& js, int i) {
+    return JobRef{(JobRef::Word*)(js.jobs + __builtin_amdgcn_readfirstlane(i))};
+}
+
 // Launch wrappers, one overload per job source.  `grid` is the number of
 // work blocks (sum over the jobs); `max_tiles` the largest tile grid of the
 // jobs (LDS of the binning kernels).  `tile` selects the resolve
@@ -555,10 +610,6 @@ hipError_t launch_resolve(const JobList& js, int tile, int phase, uint32_t grid,
 hipError_t launch_downsample(const float* sdepth, const uint32_t* sid, const uint32_t* srgba, int W, int H, int S,
                              float* depth, uint32_t* id, uint32_t* rgba, hipStream_t stream);
 // `noise`: some job asks for the noise form of the ambient occlusion.
-// FP64 depths of the pixels the resolve marked, over the shade's 16x16
-// blocks (resolve.hip); runs after the last resolve of a frame.
-hipError_t launch_refine(const OneJob& js, uint32_t grid, hipStream_t stream);
-hipError_t launch_refine(const JobList& js, uint32_t grid, hipStream_t stream);
 hipError_t launch_shade(const OneJob& js, uint32_t grid, bool noise, hipStream_t stream);
 hipError_t launch_shade(const JobList& js, uint32_t grid, bool noise, hipStream_t stream);
 
