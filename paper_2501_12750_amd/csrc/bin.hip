@@ -49,57 +49,6 @@ __device__ inline bool item_rect(const Frame& F, const Item& it, const double* v
     return bond_rect_fast(F, v, v + 3, r, x0, y0, x1, y1);
 }
 
-// Primitive sources of the count kernel.  Workgroup b owns items
-// [0, items()) (after begin(b)) and the visible-list region
-// [b * chunk, (b + 1) * chunk).
-struct PlainSource {     // the caller's arrays, primitives in their given order
-    const float* pos;
-    const float* rad;
-    const uint32_t* bonds;
-    uint64_t total;
-    uint32_t chunk;
-    uint32_t n_atoms;
-    uint64_t first, count;
-    __device__ void begin(uint32_t b) {
-        first = (uint64_t)b * chunk;
-        count = first < total ? min((uint64_t)chunk, total - first) : 0;
-    }
-    __device__ uint64_t items() const { return count; }
-    __device__ Item fetch(uint64_t k) const {
-        return fetch_plain(to_global(pos), to_global(rad), to_global(bonds), n_atoms, first + k);
-    }
-};
-
-struct SceneSource {     // a resident scene: the clusters that passed the frustum test, by depth class
-    SceneDev S;
-    uint32_t groups;
-};
-
-template <bool kScene>
-struct SourceOf;
-template <>
-struct SourceOf<false> {
-    __device__ static PlainSource make(const Job& J) {
-        PlainSource s;
-        s.pos = J.pos;
-        s.rad = J.rad;
-        s.bonds = J.bonds;
-        s.total = (uint64_t)J.F.n_atoms + J.F.n_bonds;
-        s.chunk = J.bb.chunk;
-        s.n_atoms = J.F.n_atoms;
-        return s;
-    }
-};
-template <>
-struct SourceOf<true> {
-    __device__ static SceneSource make(const Job& J) {
-        SceneSource s;
-        s.S = J.S;
-        s.groups = J.bb.groups;
-        return s;
-    }
-};
-
 // Runs of consecutive lanes whose primitives lie in the same single tile t
 // (t < 0: none); Morton-ordered primitives keep them long.  For such a lane
 // `head` is its run's first lane, and for a head `len` is the run's length
@@ -136,9 +85,9 @@ __device__ inline uint32_t wave_scan_u32(uint32_t v) {
 
 // Tile of entry i of a workgroup's histogram row: the row covers the box of
 // tiles [bx0, bx0 + bw) x [by0, ...) its primitives touch, row-major.
-__device__ inline int box_tile(const Frame& F, uint32_t bx0, uint32_t by0, int bw, int i) {
+__device__ inline int box_tile(int tiles_x, uint32_t bx0, uint32_t by0, int bw, int i) {
     const int q = i / bw;
-    return ((int)by0 + q) * F.tiles_x + (int)bx0 + (i - q * bw);
+    return ((int)by0 + q) * tiles_x + (int)bx0 + (i - q * bw);
 }
 
 // Rest pass of a two-pass frame: true when cluster c cannot win a pixel.
@@ -187,18 +136,12 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_count(JS js, int phase) {
     uint32_t blk;
     const int ji = js.find(blockIdx.x, blk);
     if (ji < 0) return;
-    const Job& J = js.job(ji);
-    const Frame F = J.F;
-    const auto src0 = SourceOf<kScene>::make(J);
-    const uint32_t chunk = J.bb.chunk;
-    global_t<uint32_t>* __restrict__ const vis_src = to_global(J.bb.vis_src);
-    global_t<uint2>* __restrict__ const vis_rect = to_global(J.bb.vis_rect);
-    global_t<uint32_t>* __restrict__ const vis_cnt = to_global(J.bb.vis_cnt);
-    global_t<uint2>* __restrict__ const vis_box = to_global(J.bb.vis_box);
-    global_t<uint32_t>* __restrict__ const hist_out = to_global(J.bb.hist);
-    uint32_t* __restrict__ const tile_cnt = J.bb.tile_cnt;
-    Counters* const ctr = J.bb.ctr;
-    const int T = F.tiles_x * F.tiles_y;
+    const JobRef R = job_ref(js, ji);
+    const BinBuffers bb = R.bins();
+    const uint32_t chunk = bb.chunk;
+    Counters* const ctr = bb.ctr;
+    const int tiles_x = R.frame().tiles_x, tsh = R.frame().tile_shift;
+    const int T = tiles_x * R.frame().tiles_y;
     const int tid = threadIdx.x;
     for (int t = tid; t < T; t += kBinThreads) hist[t] = 0;
     if constexpr (kScene) {
@@ -236,12 +179,9 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_count(JS js, int phase) {
     };
 
     const uint64_t start = (uint64_t)blk * chunk;
-    auto src = src0;
-    if constexpr (!kScene) src.begin(blk);
-    const int tsh = F.tile_shift;
     uint32_t bad_count = 0;
-    global_t<uint32_t>* __restrict__ const my_src = vis_src + start;   // this workgroup's visible list
-    global_t<uint2>* __restrict__ const my_rect = vis_rect + start;
+    global_t<uint32_t>* __restrict__ const my_src = to_global(bb.vis_src) + start;   // this workgroup's visible list
+    global_t<uint2>* __restrict__ const my_rect = to_global(bb.vis_rect) + start;
     // One visible-or-not primitive per lane (every lane of the wave calls
     // it): its slot in the workgroup's visible list, its tile counts.
     auto emit = [&](bool vis, uint32_t sidx, int x0, int y0, int x1, int y1) {
@@ -252,18 +192,18 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_count(JS js, int phase) {
         slot_base = __shfl(slot_base, leader);
         const int tx0 = x0 >> tsh, tx1 = x1 >> tsh, ty0 = y0 >> tsh, ty1 = y1 >> tsh;
         const bool single = vis && tx0 == tx1 && ty0 == ty1;
-        wave_count(hist, single ? ty0 * F.tiles_x + tx0 : -1);
+        wave_count(hist, single ? ty0 * tiles_x + tx0 : -1);
         if (vis) {
             const uint32_t slot = slot_base + (uint32_t)__popcll(vmask & __lanemask_lt());
             my_src[slot] = sidx;
             my_rect[slot] = make_uint2((uint32_t)x0 | ((uint32_t)y0 << 16), (uint32_t)x1 | ((uint32_t)y1 << 16));
             if (!single)
                 for (int ty = ty0; ty <= ty1; ++ty)
-                    for (int tx = tx0; tx <= tx1; ++tx) atomicAdd(&hist[ty * F.tiles_x + tx], 1u);
+                    for (int tx = tx0; tx <= tx1; ++tx) atomicAdd(&hist[ty * tiles_x + tx], 1u);
         }
     };
     // any primitive (the generic path)
-    auto emit_item = [&](const Item& it) {
+    auto emit_item = [&](const Frame& F, const Item& it) {
         int x0 = 0, y0 = 0, x1 = -1, y1 = -1;
         PrimRec rec;
         double v[6], r = 0.0;
@@ -282,7 +222,7 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_count(JS js, int phase) {
         // Workgroup b takes positions [c0, c1) of the visible clusters in
         // depth-class order, so the workgroups run front to back.  A
         // two-pass frame splits the positions at the first 1 / kFrontShare.
-        const SceneDev& S = src.S;
+        const SceneDev S = R.scene();
         const uint32_t stride = S.atom_clusters + S.bond_clusters;
         const uint32_t nvc = cls_end[kDepthBuckets - 1];
         // the front pass ends at a depth-class boundary (the order inside a
@@ -294,7 +234,7 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_count(JS js, int phase) {
             break;
         }
         const uint32_t lo = phase == kPhaseRest ? front : 0u, hi = phase == kPhaseFront ? front : nvc;
-        const uint32_t cpw = (hi - lo + src.groups - 1) / src.groups;
+        const uint32_t cpw = (hi - lo + bb.groups - 1) / bb.groups;
         const uint32_t c0 = min(hi, lo + blk * cpw), c1 = min(hi, c0 + cpw);
         int cls = 0;   // class of the positions this wave reads next (they increase)
         auto cluster_at = [&](uint32_t q) -> uint32_t {
@@ -315,12 +255,13 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_count(JS js, int phase) {
             const bool inside = (ce & kClusterInside) != 0u;   // its atoms need no frustum test
             if (ci + nw < c1) cn = cluster_at(ci + nw);   // the next cluster's id, ahead of its use
             if constexpr (kRest) {
-                if (cluster_hidden(F, S, J.bb, c)) continue;
+                if (cluster_hidden(R.again().frame(), S, bb, c)) continue;
             }
             if (kAtoms || c < S.atom_clusters) {
                 // one quarter at a time: holding more quarters' atoms spills
                 // registers, which costs more than the load latency it hides
                 for (uint32_t q = 0; q < 4u / kPer; ++q) {
+                    const Frame F = R.again().frame();
                     const uint32_t i = c * kCluster + q * 64u + part;
                     float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
                     if (i < S.n_atoms) a = to_global(S.xyzr)[i];
@@ -343,19 +284,26 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_count(JS js, int phase) {
             } else if constexpr (!kAtoms) {
                 for (uint32_t q = 0; q < 4u / kPer; ++q) {
                     const uint32_t j = (c - S.atom_clusters) * kCluster + q * 64u + part;
-                    emit_item(j < S.n_bonds ? fetch_scene(S, S.n_atoms + j) : empty_item());
+                    const JobRef Rq = R.again();
+                    const SceneDev Sq = Rq.scene();
+                    emit_item(Rq.frame(), j < Sq.n_bonds ? fetch_scene(Sq, Sq.n_atoms + j) : empty_item());
                 }
             }
         }
     } else {
-        const uint64_t nitems = src.items();
+        const uint32_t n_atoms = R.frame().n_atoms;
+        const uint64_t total = (uint64_t)n_atoms + R.frame().n_bonds;
+        const uint32_t nitems = start < total ? (uint32_t)min((uint64_t)chunk, total - start) : 0u;
+        auto fetch = [&](uint32_t k) {
+            return fetch_plain(to_global(R.pos()), to_global(R.rad()), to_global(R.bonds()), n_atoms, start + k);
+        };
         Item cur = empty_item();
-        if ((uint64_t)tid < nitems) cur = src.fetch(tid);
-        for (uint64_t base = 0; base < nitems; base += kBinThreads) {
+        if ((uint32_t)tid < nitems) cur = fetch(tid);
+        for (uint32_t base = 0; base < nitems; base += kBinThreads) {
             // the next iteration's inputs are loaded while this one is processed
             Item nxt = empty_item();
-            if (base + kBinThreads + tid < nitems) nxt = src.fetch(base + kBinThreads + tid);
-            emit_item(cur);
+            if (base + kBinThreads + tid < nitems) nxt = fetch(base + kBinThreads + tid);
+            emit_item(R.again().frame(), cur);
             cur = nxt;
         }
     }
@@ -370,7 +318,7 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_count(JS js, int phase) {
         for (int t = tid; t < T; t += kBinThreads) {
             const uint32_t h = hist[t];
             if (h) {
-                const uint32_t ty = (uint32_t)(t / F.tiles_x), tx = (uint32_t)t - ty * (uint32_t)F.tiles_x;
+                const uint32_t ty = (uint32_t)(t / tiles_x), tx = (uint32_t)t - ty * (uint32_t)tiles_x;
                 mx0 = min(mx0, tx);
                 my0 = min(my0, ty);
                 mx1 = max(mx1, tx);
@@ -387,26 +335,26 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_count(JS js, int phase) {
         }
     }
     __syncthreads();
-    global_t<uint32_t>* const row = hist_out + (size_t)blk * T;
+    global_t<uint32_t>* const row = to_global(bb.hist) + (size_t)blk * T;
     // layered lists: per-layer totals (the layer kernel turns them into list
     // starts and tile totals); otherwise the tile totals directly
-    uint32_t* const tot = kScene && J.bb.layers > 1
-                              ? J.bb.layer_sum + (size_t)layer_of(blk, J.bb.groups, J.bb.layers) * T
-                              : tile_cnt;
+    uint32_t* const tot = kScene && bb.layers > 1
+                              ? bb.layer_sum + (size_t)layer_of(blk, bb.groups, bb.layers) * T
+                              : bb.tile_cnt;
     // the histogram row holds the tiles of the workgroup's box only (see
     // box_tile), row-major within the box
     const int bw = bx0 <= bx1 ? (int)(bx1 - bx0) + 1 : 0, nb = bw * (bw ? (int)(by1 - by0) + 1 : 0);
     for (int i = tid; i < nb; i += kBinThreads) {
-        const int t = box_tile(F, bx0, by0, bw, i);
+        const int t = box_tile(tiles_x, bx0, by0, bw, i);
         const uint32_t h = hist[t];
         row[i] = h;
         if (h) atomicAdd(&tot[t], h);
     }
     if (tid == 0) {
-        if (kScene && J.bb.layers > 1 && wg_zlo != 0x7F800000u)
-            atomicMin(&ctr->layer_zlo[phase == kPhaseRest ? 1 : 0][layer_of(blk, J.bb.groups, J.bb.layers)], wg_zlo);
-        vis_cnt[blk] = local_n;
-        vis_box[blk] = make_uint2(bx0 | (by0 << 16), bx1 | (by1 << 16));
+        if (kScene && bb.layers > 1 && wg_zlo != 0x7F800000u)
+            atomicMin(&ctr->layer_zlo[phase == kPhaseRest ? 1 : 0][layer_of(blk, bb.groups, bb.layers)], wg_zlo);
+        bb.vis_cnt[blk] = local_n;
+        bb.vis_box[blk] = make_uint2(bx0 | (by0 << 16), bx1 | (by1 << 16));
         atomicAdd(&ctr->vis_count, local_n);
         if (local_pairs) atomicAdd(&ctr->pairs_counted, local_pairs);
     }
@@ -600,13 +548,13 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_scatter(JS js, int phase) {
 #pragma unroll
         for (int q = 0; q < kTileRows; ++q) {
             const int i = q * kBinThreads + tid;
-            r[q] = h[q] ? atomicAdd(&fill[box_tile(F, bx0, by0, bw, i)], h[q]) : 0u;
+            r[q] = h[q] ? atomicAdd(&fill[box_tile(F.tiles_x, bx0, by0, bw, i)], h[q]) : 0u;
         }
 #pragma unroll
         for (int q = 0; q < kTileRows; ++q) {
             const int i = q * kBinThreads + tid;
             if (i >= nb) break;
-            const int t = box_tile(F, bx0, by0, bw, i);
+            const int t = box_tile(F.tiles_x, bx0, by0, bw, i);
             const uint64_t run = off[t];
             const bool fits = run + cnt[t] <= capacity;   // else the resolve rebuilds this tile from the visible lists
             cur[t] = h[q] && fits ? (uint32_t)(run + (loff ? loff[t] : 0u) + r[q]) : kNoRun;
