@@ -76,7 +76,12 @@ extern "C" {
                                     close whole cells (a dense slab in front of a
                                     deep scene bins ~10x fewer primitives) and costs
                                     a second binning pass when they do not (sparse
-                                    scenes whose cells keep a gap).  Ignored with
+                                    scenes whose cells keep a gap).  Renders of
+                                    scenes without bonds take it unasked when some
+                                    16 million of their atoms are in view and the
+                                    atoms' cross-sections cover a face of their box
+                                    20 times; vtx_stats then counts the primitives
+                                    binned.  Ignored with
                                     VTX_FLAG_STATS, VTX_FLAG_COUNT or
                                     VTX_FLAG_ONE_PASS, with 8-pixel
                                     tiles, for jobs in a batch whose other jobs do
@@ -209,7 +214,8 @@ typedef struct vtx_options {
 
 /* Per-frame counters of the last frame queued on a stream. */
 typedef struct vtx_stats {
-    uint64_t visible;          /* primitives that survived frustum culling */
+    uint64_t visible;          /* primitives that survived frustum culling (two-pass frames:
+                                  of the clusters they binned) */
     uint64_t pairs;            /* (primitive, tile) bin entries */
     uint64_t fragments_tested; /* (primitive, pixel) ray tests run (VTX_FLAG_STATS: every
                                   footprint pixel; VTX_FLAG_COUNT: those the early-outs left) */

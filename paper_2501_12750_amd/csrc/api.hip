@@ -383,8 +383,8 @@ int ensure_bins(Workspace* ws, Bins* b, int T, uint64_t nprim, uint32_t groups, 
         }
         b->bb.hz16_w = (int32_t)cw;
     }
-    if (nc && ((size_t)nc * vtx::kDepthBuckets > b->vc_cap || !b->vis_clusters)) {
-        if ((rc = grow(&b->vis_clusters, b->vc_cap, (size_t)nc * vtx::kDepthBuckets, st, "visible clusters"))) return rc;
+    if (nc && (vtx::vis_cluster_entries(nc) > b->vc_cap || !b->vis_clusters)) {
+        if ((rc = grow(&b->vis_clusters, b->vc_cap, vtx::vis_cluster_entries(nc), st, "visible clusters"))) return rc;
     }
     uint64_t want = ws->fixed_capacity ? ws->fixed_entries : b->want_capacity;
     if (want == 0) {
@@ -682,6 +682,7 @@ struct vtx_scene {
     std::vector<void*> frame_blocks;    // their allocations
     bool have_box = false;              // bounding box of the atoms at creation
     double box_lo[3] = {}, box_hi[3] = {};
+    double r_sum = 0.0, r2_sum = 0.0;   // of the radii given at creation
 };
 
 // Depth classes of a resident scene's render: log-spaced over the view depths
@@ -702,6 +703,44 @@ static void scene_depth_classes(const vtx_scene* sc, Frame* F) {
     if (!(zlo > 0.0 && zhi > zlo * 1.001)) return;
     F->cls_z0 = (float)zlo;
     F->cls_k = (float)(vtx::kDepthBuckets / std::log2(zhi / zlo));
+}
+
+// Whether a resident scene's render is worth the occlusion pre-pass unasked.
+// The pre-pass costs about 90 us (a second binning and a second resolve over
+// the front pass's image) and saves the binning of what the nearest eighth of
+// the visible clusters hides, so it pays when many atoms are in view
+// (estimated: the share of the scene's box in the view volume) and the scene
+// is opaque (its atoms' cross-sections cover a face of its box many times
+// over).  us per frame in one pass and in two, SSAO 16, two views each:
+//   100M compartments (a quarter in view or more, cover 32), 4K: 769 to 1,093
+//     and 599 to 921; 1080p: 471 to 602 and 279 to 332
+//   40M (10M to 16M in view, cover 24), 4K: 559, 577 and 604, 556
+//   20M (cover 19), 4K: 468 to 472 and 556 to 572
+//   ball of 20M (cover 300), 4K: 694 to 701 and 626 to 630; of 5M: 361 and 484
+//   20M atoms and bonds (thin: cells keep gaps): 881 to 1,134 and 920 to 1,336
+constexpr double kPrePassAtoms = 16e6, kPrePassCover = 20.0;
+
+static bool wants_pre_pass(const vtx_scene* sc, const Frame& F) {
+    if (!sc->have_box || F.n_bonds || (double)sc->n < kPrePassAtoms) return false;
+    const double n = (double)sc->n, p = (double)F.probe, rho = (double)F.bond_radius;
+    const double r2 = F.rep == VTX_REP_STICKS ? n * rho * rho
+                      : F.rep == VTX_REP_SAS  ? sc->r2_sum + 2.0 * p * sc->r_sum + n * p * p
+                                              : sc->r2_sum;
+    const double ex = sc->box_hi[0] - sc->box_lo[0], ey = sc->box_hi[1] - sc->box_lo[1], ez = sc->box_hi[2] - sc->box_lo[2];
+    const double face = (ex * ey + ey * ez + ez * ex) / 3.0;
+    if (!(3.14159265 * r2 >= kPrePassCover * face)) return false;
+    constexpr int kGrid = 8;
+    int in = 0;
+    for (int i = 0; i < kGrid * kGrid * kGrid; ++i) {
+        const double x = sc->box_lo[0] + ex * (i % kGrid + 0.5) / kGrid - F.eye[0],
+                     y = sc->box_lo[1] + ey * (i / kGrid % kGrid + 0.5) / kGrid - F.eye[1],
+                     z = sc->box_lo[2] + ez * (i / (kGrid * kGrid) + 0.5) / kGrid - F.eye[2];
+        const double vx = x * F.s[0] + y * F.s[1] + z * F.s[2], vy = x * F.u[0] + y * F.u[1] + z * F.u[2],
+                     vz = x * F.f[0] + y * F.f[1] + z * F.f[2];
+        const double lx = F.proj == 0 ? F.tx * vz : F.hx, ly = F.proj == 0 ? F.ty * vz : F.hy;
+        in += vz >= (double)F.znear && vz <= (double)F.zfar && std::fabs(vx) <= lx && std::fabs(vy) <= ly;
+    }
+    return n * in >= kPrePassAtoms * (kGrid * kGrid * kGrid);
 }
 
 
@@ -804,6 +843,7 @@ struct JobDesc {
     bool scene;
     uint64_t scene_uid;
     uint64_t tuned_capacity = 0;   // tile-list entries the tuner chose for this render's shape (0: none)
+    bool pre_pass = false;         // the render is worth the occlusion pre-pass unasked
     int ss = 1;                    // samples per pixel side: F is S times the outputs' size
     vtx::SceneDev S;
     float* depth;
@@ -956,7 +996,7 @@ int render_locked(std::vector<JobDesc>& d, bool bin, bool shade, hipStream_t str
         Bins* b = ws->slots[i];
         if (capture && (b->dirty || !b->was_sized(nprim, s.F.W, s.F.H) || (size_t)T > b->tiles_cap ||
                         (size_t)groups * chunk > b->vis_cap || (size_t)groups * T > b->hist_cap ||
-                        (nc && (size_t)nc * vtx::kDepthBuckets > b->vc_cap) ||
+                        (nc && vtx::vis_cluster_entries(nc) > b->vc_cap) ||
                         (nc && (size_t)((s.F.W + vtx::kHzCell - 1) / vtx::kHzCell) *
                                        ((s.F.H + vtx::kHzCell - 1) / vtx::kHzCell) > b->hz16_cap)))
             return fail(VTX_EINVAL, "job %zu: scratch not sized for capture", i);
@@ -1071,12 +1111,12 @@ int render_locked(std::vector<JobDesc>& d, bool bin, bool shade, hipStream_t str
             if (!ws->fixed_capacity && !b->was_sized(nprims[i], d[i].F.W, d[i].F.H)) need.push_back(i);
         }
         if (!need.empty() && capture) return fail(VTX_EINVAL, "scratch not sized for capture");
-        // Occlusion pre-pass (asked for by every job, resident scenes with
-        // sized lists): bin and resolve the nearest clusters first, then only
+        // Occlusion pre-pass (asked for by or worth it for every job,
+        // resident scenes with sized lists): bin and resolve the nearest clusters first, then only
         // the clusters not hidden behind that pass's depths.
         bool two_pass = scene && need.empty();
         for (size_t i = 0; i < n && two_pass; ++i)
-            two_pass = d[i].scene && (d[i].F.flags & VTX_FLAG_TWO_PASS) &&
+            two_pass = d[i].scene && ((d[i].F.flags & VTX_FLAG_TWO_PASS) || d[i].pre_pass) &&
                        !(d[i].F.flags & (VTX_FLAG_STATS | VTX_FLAG_COUNT | VTX_FLAG_ONE_PASS)) &&
                        d[i].F.tile >= vtx::kHzCell;
         if (scene) {
@@ -1085,7 +1125,11 @@ int render_locked(std::vector<JobDesc>& d, bool bin, bool shade, hipStream_t str
         }
         for (int pass = 0; pass < (two_pass ? 2 : 1); ++pass) {
             const int phase = two_pass ? (pass == 0 ? vtx::kPhaseFront : vtx::kPhaseRest) : vtx::kPhaseAll;
-            if (pass > 0) VTX_HIP(mark(1));
+            if (pass > 0) {
+                VTX_HIP(mark(1));
+                if (n == 1) VTX_HIP(vtx::launch_cluster_rest(one(g_cull), g_cull, stream));
+                else VTX_HIP(vtx::launch_cluster_rest(list_of(0, n, 0), g_cull, stream));
+            }
             if (n == 1) VTX_HIP(vtx::launch_count(one(g_bin), scene, phase, g_bin, max_tiles, stream));
             else VTX_HIP(vtx::launch_count(list_of(0, n, n + 1), scene, phase, g_bin, max_tiles, stream));
             if (!need.empty()) {
@@ -1475,7 +1519,7 @@ size_t vtx_frame_scratch_bytes(int32_t W, int32_t H, int64_t n_atoms, int64_t n_
     // histograms, lists, visible clusters per depth class, cell depths, counters
     return (size_t)(T * 16 + T * 12 * vtx::kLayers + (uint64_t)groups * chunk * (sizeof(uint32_t) + sizeof(uint2)) +
                     (uint64_t)groups * T * 4 + cap * sizeof(uint2) +
-                    scene_clusters(n_atoms, n_bonds) * 4 * vtx::kDepthBuckets +
+                    vtx::vis_cluster_entries(scene_clusters(n_atoms, n_bonds)) * 4 +
                     (uint64_t)((W + vtx::kHzCell - 1) / vtx::kHzCell) * ((H + vtx::kHzCell - 1) / vtx::kHzCell) * 4 +
                     sizeof(Counters) + 4096);
 }
@@ -1542,9 +1586,9 @@ int vtx_scene_create(vtx_context* ctx, const float* positions, const float* radi
     sc->S.atom_id = sc->atom_id;
     sc->S.bond_rec = sc->bond_rec;
     sc->S.vis_clusters = nullptr;   // per render, in the stream's scratch
-    uint32_t box_bits[6] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0u, 0u, 0u};
+    vtx::SceneExtent ext{};
     hipError_t e = vtx::scene_build(sc->pos, sc->rad, sc->bonds, na, nb, sc->S, sc->xyzr, sc->atom_id, sc->bond_rec,
-                                    sc->cluster_box, tmp, tmp_bytes, &m_valid, &n_bad, box_bits, st);
+                                    sc->cluster_box, tmp, tmp_bytes, &m_valid, &n_bad, &ext, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return bail(fail(VTX_EHIP, "building the scene failed: %s", hipGetErrorString(e)));
     if (na > 0) {
@@ -1555,11 +1599,13 @@ int vtx_scene_create(vtx_context* ctx, const float* positions, const float* radi
             return (double)f;
         };
         for (int k = 0; k < 3; ++k) {
-            sc->box_lo[k] = from_ordered(box_bits[k]);
-            sc->box_hi[k] = from_ordered(box_bits[3 + k]);
+            sc->box_lo[k] = from_ordered(ext.box[k]);
+            sc->box_hi[k] = from_ordered(ext.box[3 + k]);
         }
         sc->have_box = std::isfinite(sc->box_lo[0] + sc->box_lo[1] + sc->box_lo[2] + sc->box_hi[0] + sc->box_hi[1] +
                                      sc->box_hi[2]);
+        sc->r_sum = (double)ext.r_sum / 1024.0;
+        sc->r2_sum = (double)ext.r2_sum / 1024.0;
     }
     hipFree(tmp);
     sc->bad_bonds = n_bad;
@@ -1685,6 +1731,7 @@ int vtx_render_scene(vtx_scene* scene, const vtx_camera* cam, const vtx_options*
     d[0].scene = true;
     d[0].scene_uid = scene->uid;
     d[0].tuned_capacity = tuned_cap;
+    d[0].pre_pass = wants_pre_pass(scene, F);
     d[0].S = scene->S;
     d[0].depth = depth;
     d[0].id = id;
@@ -1741,6 +1788,7 @@ int build_batch(vtx_context* ctx, const vtx_job* jobs, int32_t n_jobs, std::vect
         d[(size_t)i].scene = true;
         d[(size_t)i].scene_uid = sc->uid;
         d[(size_t)i].tuned_capacity = tuned_cap;
+        d[(size_t)i].pre_pass = wants_pre_pass(sc, F);
         d[(size_t)i].S = S;
         d[(size_t)i].depth = j.depth;
         d[(size_t)i].id = j.id;

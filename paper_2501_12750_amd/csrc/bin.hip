@@ -90,40 +90,9 @@ __device__ inline int box_tile(int tiles_x, uint32_t bx0, uint32_t by0, int bw, 
     return ((int)by0 + q) * tiles_x + (int)bx0 + (i - q * bw);
 }
 
-// Rest pass of a two-pass frame: true when cluster c cannot win a pixel.
-// The lower bound of the cull depth of its primitives (the bounding sphere
-// of its box, widened as in the frustum test, with the margin of the
-// per-primitive bound) lies behind the front pass's depth of every 16x16
-// cell under the sphere's footprint; those depths only decrease later.
-// Called by whole waves with a wave-uniform c: the lanes share the cells.
-__device__ inline bool cluster_hidden(const Frame& F, const SceneDev& S, const BinBuffers& bb, uint32_t c) {
-    const float4 lo = S.cluster_box[2 * (size_t)c], hi = S.cluster_box[2 * (size_t)c + 1];
-    const float pad = c < S.atom_clusters ? (F.rep == 2 ? F.bond_radius : F.rep == 3 ? F.probe : 0.0f) : F.bond_radius;
-    const double hx = 0.5 * ((double)hi.x - lo.x), hy = 0.5 * ((double)hi.y - lo.y), hz = 0.5 * ((double)hi.z - lo.z);
-    double vx, vy, vz;
-    to_view(F, (float)(lo.x + hx), (float)(lo.y + hy), (float)(lo.z + hz), vx, vy, vz);
-    const double r = sqrt(hx * hx + hy * hy + hz * hz) + pad +
-                     1e-6 * (fabs((double)lo.x) + fabs((double)lo.y) + fabs((double)lo.z) + 1.0);
-    const float zlo = __double2float_rd(vz - r - 2e-5 * (fabs(vz) + r) - 2e-6);
-    if (!(zlo > 0.0f)) return false;
-    int x0, y0, x1, y1;
-    if (!sphere_rect_fast(F, vx, vy, vz, r, x0, y0, x1, y1)) return true;   // covers no pixel of the image
-    const int cx0 = x0 / kHzCell, cy0 = y0 / kHzCell, cw = x1 / kHzCell - cx0 + 1;
-    const int n = cw * (y1 / kHzCell - cy0 + 1);
-    if (n > 16 * 64) return false;   // a footprint this large is rarely hidden: not worth the reads
-    uint32_t m = 0;
-    for (int k = (int)__lane_id(); k < n; k += 64) {
-        const int q = k / cw;
-        m = max(m, bb.hz16[(size_t)(cy0 + q) * bb.hz16_w + (cx0 + k - q * cw)]);
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o));
-    return __float_as_uint(zlo) > m;
-}
-
 // Count.  Work block b of a job is that job's binning workgroup b.
-// kRest: the rest pass of a two-pass frame (a separate instantiation keeps
-// the cluster test out of the others' registers).  kAtoms: a scene without
+// kRest: the rest pass of a two-pass frame, over the clusters
+// k_cluster_rest kept.  kAtoms: a scene without
 // bonds (no bond path in the loop: fewer live registers).  kQuarters: see
 // quarters() for the scenes that take it.
 template <class JS, bool kScene, bool kRest, bool kAtoms = false, bool kQuarters = false>
@@ -131,7 +100,7 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_count(JS js, int phase) {
     extern __shared__ uint32_t hist[];
     __shared__ uint32_t local_n, bx0, by0, bx1, by1;
     __shared__ unsigned long long local_pairs;
-    __shared__ uint32_t cls_end[kDepthBuckets];
+    __shared__ uint32_t cls_end[kDepthBuckets], cls_all[kRest ? kDepthBuckets : 1];
     __shared__ uint32_t wg_zlo;
     uint32_t blk;
     const int ji = js.find(blockIdx.x, blk);
@@ -145,15 +114,11 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_count(JS js, int phase) {
     const int tid = threadIdx.x;
     for (int t = tid; t < T; t += kBinThreads) hist[t] = 0;
     if constexpr (kScene) {
-        // end of each depth class in the front-to-back order of the visible clusters
+        // end of each depth class in the front-to-back order of the clusters
+        // (rest pass: also where each class's region of the kept ones starts)
         if (tid < 64) {
-            uint32_t v = tid < kDepthBuckets ? ctr->vis_bucket[tid] : 0u;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const uint32_t u = __shfl_up(v, o);
-                if (tid >= o) v += u;
-            }
-            if (tid < kDepthBuckets) cls_end[tid] = v;
+            class_ends(kRest ? ctr->rest_bucket : ctr->vis_bucket, cls_end);
+            if constexpr (kRest) class_ends(ctr->vis_bucket, cls_all);
         }
     }
     if (tid == 0) {
@@ -219,27 +184,19 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_count(JS js, int phase) {
         // Resident scene: each wave takes whole clusters or quarters of them
         // (256 primitives of one kind, so the kind is the same across the wave).  An atom
         // cluster's 64-atom quarters take the sphere-only path.
-        // Workgroup b takes positions [c0, c1) of the visible clusters in
-        // depth-class order, so the workgroups run front to back.  A
-        // two-pass frame splits the positions at the first 1 / kFrontShare.
+        // Workgroup b takes positions [c0, c1) of the pass's clusters in
+        // depth-class order, so the workgroups run front to back.
         const SceneDev S = R.scene();
         const uint32_t stride = S.atom_clusters + S.bond_clusters;
-        const uint32_t nvc = cls_end[kDepthBuckets - 1];
-        // the front pass ends at a depth-class boundary (the order inside a
-        // class is arbitrary), unless that would take more than half
-        uint32_t front = (nvc + kFrontShare - 1) / kFrontShare;
-        for (int k = 0; k < kDepthBuckets; ++k) {
-            if (cls_end[k] < front) continue;
-            if (cls_end[k] <= nvc / 2) front = cls_end[k];
-            break;
-        }
-        const uint32_t lo = phase == kPhaseRest ? front : 0u, hi = phase == kPhaseFront ? front : nvc;
-        const uint32_t cpw = (hi - lo + bb.groups - 1) / bb.groups;
-        const uint32_t c0 = min(hi, lo + blk * cpw), c1 = min(hi, c0 + cpw);
+        const uint32_t n = phase == kPhaseFront ? front_clusters(cls_end) : cls_end[kDepthBuckets - 1];
+        const uint32_t cpw = (n + bb.groups - 1) / bb.groups;
+        const uint32_t c0 = min(n, blk * cpw), c1 = min(n, c0 + cpw);
         int cls = 0;   // class of the positions this wave reads next (they increase)
         auto cluster_at = [&](uint32_t q) -> uint32_t {
             while (cls_end[cls] <= q) ++cls;
-            return S.vis_clusters[(size_t)cls * stride + (q - (cls ? cls_end[cls - 1] : 0u))];
+            const uint32_t in = q - (cls ? cls_end[cls - 1] : 0u);
+            if constexpr (kRest) return S.vis_clusters[(size_t)kDepthBuckets * stride + (cls ? cls_all[cls - 1] : 0u) + in];
+            return S.vis_clusters[(size_t)cls * stride + in];
         };
         // kQuarters: the waves take the clusters' 64-primitive quarters in
         // turn, four waves per cluster, else whole clusters.
@@ -254,9 +211,6 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_count(JS js, int phase) {
             const uint32_t c = ce & ~kClusterInside;
             const bool inside = (ce & kClusterInside) != 0u;   // its atoms need no frustum test
             if (ci + nw < c1) cn = cluster_at(ci + nw);   // the next cluster's id, ahead of its use
-            if constexpr (kRest) {
-                if (cluster_hidden(R.again().frame(), S, bb, c)) continue;
-            }
             if (kAtoms || c < S.atom_clusters) {
                 // one quarter at a time: holding more quarters' atoms spills
                 // registers, which costs more than the load latency it hides
@@ -579,7 +533,7 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_scatter(JS js, int phase) {
             ctr->pairs_counted = 0;
             // the next frame's cluster test adds to these (the rest pass reads them)
             if (phase != kPhaseFront)
-                for (int k = 0; k < kDepthBuckets; ++k) ctr->vis_bucket[k] = 0;
+                for (int k = 0; k < kDepthBuckets; ++k) ctr->vis_bucket[k] = ctr->rest_bucket[k] = 0;
             if (host_ctr && phase == kPhaseRest) {
                 // a two-pass frame: visible primitives and overflowed tiles of
                 // both passes, the larger list total
@@ -730,7 +684,7 @@ hipError_t count_impl(const JS& js, bool scene, int phase, uint32_t grid, int ma
     if (!scene) return dispatch(k_count<JS, false, false>, grid, kBinThreads, lds, stream, js, phase);
     if (phase == kPhaseRest) return dispatch(k_count<JS, true, true>, grid, kBinThreads, lds, stream, js, phase);
     if (!atoms_only(js)) return dispatch(k_count<JS, true, false, false, true>, grid, kBinThreads, lds, stream, js, phase);
-    if (quarters(js)) return dispatch(k_count<JS, true, false, true, true>, grid, kBinThreads, lds, stream, js, phase);
+    if (quarters(js) || phase == kPhaseFront) return dispatch(k_count<JS, true, false, true, true>, grid, kBinThreads, lds, stream, js, phase);
     return dispatch(k_count<JS, true, false, true>, grid, kBinThreads, lds, stream, js, phase);
 }
 

@@ -266,13 +266,12 @@ __device__ inline bool source_record(JobRef R, uint32_t src, PrimRec& pr) {
 // records and their prefix.  Two-pass frames: the front pass also stores the
 // farthest depth of each 16x16 cell of the tile; the rest pass starts from the
 // front pass's depth and id.
-template <int TS, bool kCount, bool kTail, bool kTwo>
-__device__ __forceinline__ void resolve_tile(JobRef R, int t, uint32_t n, uint64_t o, int phase_arg) {
+template <int TS, bool kCount, bool kTail, int kPhase>
+__device__ __forceinline__ void resolve_tile(JobRef R, int t, uint32_t n, uint64_t o, unsigned long long* keys) {
     const JobRef R0 = R.again();
     const Frame F = R0.frame();
     const BinBuffers bb = R0.bins();
-    const int phase = kTwo ? phase_arg : (int)kPhaseAll;   // one-pass instantiations drop the two-pass code
-    __shared__ unsigned long long keys[TS * TS];
+    constexpr int phase = kPhase;
     __shared__ Rec recs[kChunk];
     __shared__ uint32_t pref[kChunk + 1];
     __shared__ uint32_t wsum[kBlock / 64];
@@ -843,6 +842,39 @@ __device__ __forceinline__ void resolve_tile(JobRef R, int t, uint32_t n, uint64
     }
 }
 
+// The rest pass in a tile it adds nothing to: the front pass's marked winners
+// get their FP64 depths, the other pixels stay as they are.
+template <int TS>
+__device__ __forceinline__ void refine_tile(JobRef R, int t, unsigned long long* todo) {
+    __shared__ uint32_t n_todo;
+    const Frame F = R.frame();
+    global_t<float>* __restrict__ const depth = to_global(R.depth());
+    global_t<uint32_t>* __restrict__ const out_id = to_global(R.id());
+    const int px0 = (t % F.tiles_x) * TS, py0 = (t / F.tiles_x) * TS;
+    const int tid = threadIdx.x, lane = __lane_id();
+    if (tid == 0) n_todo = 0u;
+    __syncthreads();
+    for (int i = tid; i < TS * TS; i += kBlock) {
+        const int x = px0 + i % TS, y = py0 + i / TS;
+        const uint32_t id = x < F.W && y < F.H ? out_id[(size_t)y * F.W + x] : kBackground;
+        const bool marked = id != kBackground && (!F.refine_flag || (id & kRefineBit));
+        const unsigned long long mm = __ballot(marked);
+        uint32_t at = 0;
+        if (mm && lane == 0) at = atomicAdd(&n_todo, (uint32_t)__popcll(mm));
+        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + (uint32_t)__popcll(mm & __lanemask_lt());
+        if (marked) todo[at] = ((unsigned long long)i << 32) | (F.refine_flag ? id & ~kRefineBit : id);
+    }
+    __syncthreads();
+    for (uint32_t e = (uint32_t)tid; e < n_todo; e += kBlock) {
+        const int i = (int)(todo[e] >> 32);
+        const uint32_t id = (uint32_t)todo[e];
+        const int x = px0 + i % TS, y = py0 + i / TS;
+        const size_t p = (size_t)y * F.W + x;
+        depth[p] = refine_depth_at(F, to_global(R.pos()), to_global(R.rad()), to_global(R.bonds()), id, x, y, depth[p]);
+        out_id[p] = id;
+    }
+}
+
 // Main launch: work block t of a job is that job's tile t, so consecutive
 // tiles go to different XCDs (the dispatcher deals blocks round-robin).  The
 // costly tiles lie together, around the footprints of the nearest atoms:
@@ -851,10 +883,9 @@ __device__ __forceinline__ void resolve_tile(JobRef R, int t, uint32_t n, uint64
 // is left to the tail launch: it is appended to `ovf` (job << 32 | tile).
 // kCount: the instantiation that can count fragments (jobs with
 // VTX_FLAG_STATS); the other one carries no counters.
-// kTwo: the instantiation for the passes of a two-pass frame.
-template <int TS, class JS, bool kCount, bool kTwo>
-__global__ void __launch_bounds__(kBlock, kCount ? 1 : 7) k_resolve(JS js, unsigned long long* ovf, uint32_t* ovf_n,
-                                                                     int phase) {
+// kPhase: one pass, or one of a two-pass frame's.
+template <int TS, class JS, bool kCount, int kPhase>
+__global__ void __launch_bounds__(kBlock, kCount ? 1 : 7) k_resolve(JS js, unsigned long long* ovf, uint32_t* ovf_n) {
     uint32_t tu;
     const int ji = js.find(blockIdx.x, tu);
     if (ji < 0) return;
@@ -865,7 +896,7 @@ __global__ void __launch_bounds__(kBlock, kCount ? 1 : 7) k_resolve(JS js, unsig
         if (threadIdx.x == 0) ovf[atomicAdd(ovf_n, 1u)] = ((unsigned long long)ji << 32) | tu;
         return;
     }
-    if (!kTwo && n == 0) {   // nothing to cast or to re-arm: background
+    if (kPhase == kPhaseAll && n == 0) {   // nothing to cast or to re-arm: background
         const int W = J.F.W, H = J.F.H, tiles_x = J.F.tiles_x;
         const int px0 = ((int)tu % tiles_x) * TS, py0 = ((int)tu / tiles_x) * TS;
         global_t<float>* __restrict__ const depth = to_global(J.depth);
@@ -879,16 +910,23 @@ __global__ void __launch_bounds__(kBlock, kCount ? 1 : 7) k_resolve(JS js, unsig
         }
         return;
     }
-    resolve_tile<TS, kCount, false, kTwo>(job_ref(js, ji), (int)tu, n, o, phase);
+    __shared__ unsigned long long keys[TS * TS];   // the tile's depth buffer
+    if constexpr (kPhase == kPhaseRest) {
+        if (n == 0) {
+            refine_tile<TS>(job_ref(js, ji), (int)tu, keys);
+            return;
+        }
+    }
+    resolve_tile<TS, kCount, false, kPhase>(job_ref(js, ji), (int)tu, n, o, keys);
 }
 
 // Tail launch (a fixed grid, queued right after the main one): resolves the
 // overflowed tiles the main launch listed, then its last workgroup clears the
 // list and publishes the fragment counters of every counting job.  Keeping the
 // rare overflow path out of the main instantiation keeps its register budget.
-template <int TS, class JS, bool kCount, bool kTwo>
-__global__ void __launch_bounds__(kBlock) k_resolve_tail(JS js, const unsigned long long* ovf, uint32_t* ovf_n,
-                                                          int phase) {
+template <int TS, class JS, bool kCount, int kPhase>
+__global__ void __launch_bounds__(kBlock) k_resolve_tail(JS js, const unsigned long long* ovf, uint32_t* ovf_n) {
+    __shared__ unsigned long long keys[TS * TS];
     const uint32_t total = *(volatile uint32_t*)ovf_n;
     // Nothing overflowed (the usual frame): nothing to clear or publish, and
     // no fences.  The count is the same for every workgroup (it is cleared
@@ -898,7 +936,7 @@ __global__ void __launch_bounds__(kBlock) k_resolve_tail(JS js, const unsigned l
         const unsigned long long v = ovf[e];
         const Job& J = js.job((int)(v >> 32));
         const int t = (int)(v & 0xFFFFFFFFull);
-        resolve_tile<TS, kCount, true, kTwo>(job_ref(js, (int)(v >> 32)), t, J.bb.tile_cnt[t], J.bb.tile_off[t], phase);
+        resolve_tile<TS, kCount, true, kPhase>(job_ref(js, (int)(v >> 32)), t, J.bb.tile_cnt[t], J.bb.tile_off[t], keys);
         __syncthreads();   // the next tile reuses the LDS
     }
     if (threadIdx.x == 0) {
@@ -931,21 +969,22 @@ __global__ void __launch_bounds__(kBlock) k_resolve_tail(JS js, const unsigned l
 
 }  // namespace
 
+template <int TS, class JS, bool kCount, int kPhase>
+hipError_t resolve_pass(const JS& js, unsigned g, unsigned long long* ovf, uint32_t* ovf_n, hipStream_t stream) {
+    const hipError_t e = dispatch(k_resolve<TS, JS, kCount, kPhase>, g, kBlock, 0, stream, js, ovf, ovf_n);
+    if (e) return e;
+    return dispatch(k_resolve_tail<TS, JS, kCount, kPhase>, kTailBlocks, kBlock, 0, stream, js,
+                    (const unsigned long long*)ovf, ovf_n);
+}
+
 template <int TS, class JS, bool kCount>
 hipError_t resolve_launch(const JS& js, int phase, unsigned g, unsigned long long* ovf, uint32_t* ovf_n,
                           hipStream_t stream) {
-    hipError_t e;
     if constexpr (!kCount && TS >= kHzCell) {
-        if (phase != kPhaseAll) {
-            if ((e = dispatch(k_resolve<TS, JS, false, true>, g, kBlock, 0, stream, js, ovf, ovf_n, phase)))
-                return e;
-            return dispatch(k_resolve_tail<TS, JS, false, true>, kTailBlocks, kBlock, 0, stream, js,
-                            (const unsigned long long*)ovf, ovf_n, phase);
-        }
+        if (phase == kPhaseFront) return resolve_pass<TS, JS, false, kPhaseFront>(js, g, ovf, ovf_n, stream);
+        if (phase == kPhaseRest) return resolve_pass<TS, JS, false, kPhaseRest>(js, g, ovf, ovf_n, stream);
     }
-    if ((e = dispatch(k_resolve<TS, JS, kCount, false>, g, kBlock, 0, stream, js, ovf, ovf_n, phase))) return e;
-    return dispatch(k_resolve_tail<TS, JS, kCount, false>, kTailBlocks, kBlock, 0, stream, js,
-                    (const unsigned long long*)ovf, ovf_n, phase);
+    return resolve_pass<TS, JS, kCount, kPhaseAll>(js, g, ovf, ovf_n, stream);
 }
 
 template <class JS, bool kCount>

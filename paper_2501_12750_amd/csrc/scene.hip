@@ -14,7 +14,7 @@
 // clusters of 256 as well.  Both orders come from the stable radix sort of
 // sort.hip, so atoms with equal Morton keys keep their original order, and so
 // do bonds with the same first atom.
-#include "vtx_internal.h"
+#include "prims.h"
 
 namespace vtx {
 
@@ -29,29 +29,50 @@ __device__ inline float from_ordered(uint32_t u) {
     return __uint_as_float((u & 0x80000000u) ? (u & 0x7FFFFFFFu) : ~u);
 }
 
-// Bounding box of the atom positions: box[0..2] min, box[3..5] max (ordered bits).
-__global__ void __launch_bounds__(kBlock) k_bbox(const float* __restrict__ pos, uint32_t n, uint32_t* box) {
+// Bounding box and radius sums of the atoms (*ext initialised by k_extent_init).
+__global__ void __launch_bounds__(kBlock) k_extent(const float* __restrict__ pos, const float* __restrict__ rad,
+                                                   uint32_t n, SceneExtent* ext) {
     __shared__ uint32_t sb[6];
+    __shared__ unsigned long long sr[2];
     if (threadIdx.x < 6) sb[threadIdx.x] = threadIdx.x < 3 ? 0xFFFFFFFFu : 0u;
+    if (threadIdx.x < 2) sr[threadIdx.x] = 0;
     __syncthreads();
     uint32_t lo[3] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, hi[3] = {0u, 0u, 0u};
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
+    unsigned long long r1 = 0, r2 = 0;
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
         for (int k = 0; k < 3; ++k) {
             const uint32_t v = ordered_bits(pos[3 * (size_t)i + k]);
             lo[k] = min(lo[k], v);
             hi[k] = max(hi[k], v);
         }
+        const float r = rad[i];
+        if (r > 0.0f && r <= 1000.0f) {
+            r1 += (unsigned long long)(r * 1024.0f);
+            r2 += (unsigned long long)(r * r * 1024.0f);
+        }
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        r1 += __shfl_xor(r1, o);
+        r2 += __shfl_xor(r2, o);
+    }
+    if (__lane_id() == 0) {
+        atomicAdd(&sr[0], r1);
+        atomicAdd(&sr[1], r2);
+    }
     for (int k = 0; k < 3; ++k) {
         atomicMin(&sb[k], lo[k]);
         atomicMax(&sb[3 + k], hi[k]);
     }
     __syncthreads();
-    if (threadIdx.x < 3) atomicMin(&box[threadIdx.x], sb[threadIdx.x]);
-    else if (threadIdx.x < 6) atomicMax(&box[threadIdx.x], sb[threadIdx.x]);
+    if (threadIdx.x < 3) atomicMin(&ext->box[threadIdx.x], sb[threadIdx.x]);
+    else if (threadIdx.x < 6) atomicMax(&ext->box[threadIdx.x], sb[threadIdx.x]);
+    else if (threadIdx.x == 6) atomicAdd(&ext->r_sum, sr[0]);
+    else if (threadIdx.x == 7) atomicAdd(&ext->r2_sum, sr[1]);
 }
 
-__global__ void k_box_init(uint32_t* box) {
-    if (threadIdx.x < 6) box[threadIdx.x] = threadIdx.x < 3 ? 0xFFFFFFFFu : 0u;
+__global__ void k_extent_init(SceneExtent* ext) {
+    if (threadIdx.x < 6) ext->box[threadIdx.x] = threadIdx.x < 3 ? 0xFFFFFFFFu : 0u;
+    if (threadIdx.x == 0) ext->r_sum = ext->r2_sum = 0;
 }
 
 // 30-bit Morton key (10 bits per axis) of each atom, and the identity payload.
@@ -169,6 +190,47 @@ __global__ void __launch_bounds__(kBlock) k_cluster_boxes(SceneDev S, float4* bo
     }
 }
 
+// Bounding sphere of cluster c's box in view space, widened by what the
+// representation draws past the given radii and by the FP32 rounding of the
+// centre.  False for an empty cluster.
+__device__ inline bool cluster_sphere(const Frame& F, const SceneDev& S, uint32_t c, double& vx, double& vy, double& vz,
+                                      double& r) {
+    const float4 lo = S.cluster_box[2 * (size_t)c], hi = S.cluster_box[2 * (size_t)c + 1];
+    if (!(lo.x <= hi.x)) return false;   // empty clusters have an inverted box
+    // atom boxes hold the given radii: the representation may draw
+    // larger spheres (sticks, solvent-accessible surface)
+    const float pad = c < S.atom_clusters ? (F.rep == 2 ? F.bond_radius : F.rep == 3 ? F.probe : 0.0f) : F.bond_radius;
+    const double hx = 0.5 * ((double)hi.x - lo.x), hy = 0.5 * ((double)hi.y - lo.y), hz = 0.5 * ((double)hi.z - lo.z);
+    to_view(F, (float)(lo.x + hx), (float)(lo.y + hy), (float)(lo.z + hz), vx, vy, vz);
+    r = sqrt(hx * hx + hy * hy + hz * hz) + pad +
+        1e-6 * (fabs((double)lo.x) + fabs((double)lo.y) + fabs((double)lo.z) + 1.0);
+    return true;
+}
+
+// Place of each thread's cluster within the global run of its class cls (< 0:
+// none): lanes sharing a class take one LDS atomic, then the workgroup one
+// global atomic per class on bucket[].  wcnt starts at zero; the place is
+// wbase[cls] plus the returned offset.  Every thread of the workgroup calls it.
+__device__ inline uint32_t class_place(int cls, uint32_t* wcnt, uint32_t* wbase, unsigned int* bucket) {
+    uint32_t off = 0;
+    unsigned long long pend = __ballot(cls >= 0);
+    while (pend) {
+        const int leader = __ffsll((long long)pend) - 1;
+        const int cl = __shfl(cls, leader);
+        const unsigned long long grp = __ballot(cls == cl) & pend;
+        uint32_t base = 0;
+        if ((int)__lane_id() == leader) base = atomicAdd(&wcnt[cl], (uint32_t)__popcll(grp));
+        base = __shfl(base, leader);
+        if ((grp >> __lane_id()) & 1ull) off = base + (uint32_t)__popcll(grp & __lanemask_lt());
+        pend &= ~grp;
+    }
+    __syncthreads();
+    if (threadIdx.x < kDepthBuckets && wcnt[threadIdx.x])
+        wbase[threadIdx.x] = atomicAdd(&bucket[threadIdx.x], wcnt[threadIdx.x]);
+    __syncthreads();
+    return off;
+}
+
 // Per frame: clusters whose bounding sphere meets the view volume, appended
 // (with kClusterInside when the sphere lies wholly inside it) to the region
 // of S.vis_clusters of their depth class: the front depth of
@@ -196,47 +258,104 @@ __global__ void __launch_bounds__(kBlock) k_cluster_cull(JS js) {
     int cls = -1;
     bool inside = false;
     if (c < nc) {
-        const float4 lo = S.cluster_box[2 * (size_t)c], hi = S.cluster_box[2 * (size_t)c + 1];
-        if (lo.x <= hi.x) {   // empty clusters have an inverted box
-            // atom boxes hold the given radii: the representation may draw
-            // larger spheres (sticks, solvent-accessible surface)
-            const float pad = c < S.atom_clusters ? (F.rep == 2 ? F.bond_radius : F.rep == 3 ? F.probe : 0.0f)
-                                                  : F.bond_radius;
-            const double hx = 0.5 * ((double)hi.x - lo.x), hy = 0.5 * ((double)hi.y - lo.y),
-                         hz = 0.5 * ((double)hi.z - lo.z);
-            double vx, vy, vz;
-            to_view(F, (float)(lo.x + hx), (float)(lo.y + hy), (float)(lo.z + hz), vx, vy, vz);
-            // the centre was rounded to FP32: widen by its rounding error
-            const double r = sqrt(hx * hx + hy * hy + hz * hz) + pad +
-                             1e-6 * (fabs((double)lo.x) + fabs((double)lo.y) + fabs((double)lo.z) + 1.0);
-            if (sphere_in_frustum(F, vx, vy, vz, r)) {
-                // only the order of the lists depends on the class, never the image
-                const float zf = fmaxf((float)(vz - r), F.cls_z0);
-                const float q = __log2f(zf / F.cls_z0) * F.cls_k;
-                cls = q >= 0.0f ? (int)fminf(q, (float)(kDepthBuckets - 1)) : 0;   // NaN: class 0
-                inside = sphere_inside_frustum(F, vx, vy, vz, r);
-            }
+        double vx, vy, vz, r;
+        if (cluster_sphere(F, S, c, vx, vy, vz, r) && sphere_in_frustum(F, vx, vy, vz, r)) {
+            // only the order of the lists depends on the class, never the image
+            const float zf = fmaxf((float)(vz - r), F.cls_z0);
+            const float q = __log2f(zf / F.cls_z0) * F.cls_k;
+            cls = q >= 0.0f ? (int)fminf(q, (float)(kDepthBuckets - 1)) : 0;   // NaN: class 0
+            inside = sphere_inside_frustum(F, vx, vy, vz, r);
         }
     }
-    // place within the workgroup's run of the class (lanes sharing a class
-    // take one LDS atomic), then one global atomic per class
-    uint32_t off = 0;
-    unsigned long long pend = __ballot(cls >= 0);
-    while (pend) {
-        const int leader = __ffsll((long long)pend) - 1;
-        const int cl = __shfl(cls, leader);
-        const unsigned long long grp = __ballot(cls == cl) & pend;
-        uint32_t base = 0;
-        if ((int)__lane_id() == leader) base = atomicAdd(&wcnt[cl], (uint32_t)__popcll(grp));
-        base = __shfl(base, leader);
-        if ((grp >> __lane_id()) & 1ull) off = base + (uint32_t)__popcll(grp & __lanemask_lt());
-        pend &= ~grp;
+    const uint32_t off = class_place(cls, wcnt, wbase, ctr->vis_bucket);
+    if (cls >= 0) S.vis_clusters[(size_t)cls * stride + wbase[cls] + off] = c | (inside ? kClusterInside : 0u);
+}
+
+// Two-pass frames, after the front pass: which of the remaining visible
+// clusters can still win a pixel.  One cannot when the lower bound of the
+// cull depth of its primitives (the bounding sphere of its box, widened as in
+// the frustum test, with the margin of the per-primitive bound) lies behind
+// the front pass's depth of every 16x16 cell under the sphere's footprint;
+// those depths only decrease later.  A thread takes each cluster's sphere and
+// rectangle, then half a wave its cells (a hundred or so, up to 1024).
+// The kept clusters go to the last region of S.vis_clusters, each class after
+// the classes before it, so the count shares them evenly among its
+// workgroups: tested inside the count, by the workgroup that held them, the
+// kept ones were nearly all in the first few of its workgroups (100M atoms:
+// 118 to 296 us, depending on the view, for a tenth to a half of the atoms).
+template <class JS>
+__global__ void __launch_bounds__(kBlock) k_cluster_rest(JS js) {
+    constexpr uint32_t kLanes = 32, kTeams = kBlock / kLanes;
+    __shared__ uint32_t cls_end[kDepthBuckets], wcnt[kDepthBuckets], wbase[kDepthBuckets];
+    // the workgroup's clusters: first cell and cell counts of the footprint
+    // (no rows: nothing to read), the depth bound's float bits (0: none), and
+    // whether the front pass hides it
+    __shared__ uint32_t cell0[kBlock], span[kBlock], bound[kBlock], hid[kBlock];
+    uint32_t blk;
+    const int ji = js.find(blockIdx.x, blk);
+    if (ji < 0) return;
+    const JobRef R = job_ref(js, ji);
+    const SceneDev S = R.scene();
+    const uint32_t* const hz16 = R.bins().hz16;
+    const uint32_t hz16_w = (uint32_t)R.bins().hz16_w;
+    Counters* const ctr = R.bins().ctr;
+    const uint32_t stride = S.atom_clusters + S.bond_clusters;
+    const uint32_t tid = threadIdx.x;
+    if (tid < 64) class_ends(ctr->vis_bucket, cls_end);
+    if (tid < kDepthBuckets) wcnt[tid] = 0;
+    __syncthreads();
+    const uint32_t front = front_clusters(cls_end), n = cls_end[kDepthBuckets - 1] - front;
+    // at most kBlock clusters per workgroup: the grid holds a thread per cluster
+    const uint32_t per = min((uint32_t)kBlock, (n + js.work_blocks(ji) - 1) / js.work_blocks(ji));
+    const uint32_t q0 = min(n, blk * per), cnt = min(n, q0 + per) - q0;
+    uint32_t entry = 0, k = 0;
+    if (tid < cnt) {
+        const uint32_t q = front + q0 + tid;
+        uint32_t hi = kDepthBuckets - 1;   // k: the first class that ends past q
+        while (k < hi) {
+            const uint32_t mid = (k + hi) >> 1;
+            if (cls_end[mid] > q) hi = mid;
+            else k = mid + 1;
+        }
+        entry = S.vis_clusters[(size_t)k * stride + (q - (k ? cls_end[k - 1] : 0u))];
+        const Frame F = R.frame();
+        double vx = 0.0, vy = 0.0, vz = 0.0, r = 0.0;
+        (void)cluster_sphere(F, S, entry & ~kClusterInside, vx, vy, vz, r);   // visible: not empty
+        const float zlo = __double2float_rd(vz - r - 2e-5 * (fabs(vz) + r) - 2e-6);
+        uint32_t c0 = 0, sp = 0, zb = 0;
+        int x0, y0, x1, y1;
+        if (zlo > 0.0f) {
+            zb = __float_as_uint(zlo);
+            if (sphere_rect_fast(F, vx, vy, vz, r, x0, y0, x1, y1)) {   // else it covers no pixel of the image
+                const uint32_t cx0 = (uint32_t)x0 / kHzCell, cy0 = (uint32_t)y0 / kHzCell;
+                const uint32_t cw = (uint32_t)x1 / kHzCell - cx0 + 1, ch = (uint32_t)y1 / kHzCell - cy0 + 1;
+                c0 = cy0 * hz16_w + cx0;
+                sp = cw | (ch << 16);
+                if (cw * ch > 16 * 64) zb = 0;   // a footprint this large is rarely hidden: not worth the reads
+            }
+        }
+        cell0[tid] = c0;
+        span[tid] = sp;
+        bound[tid] = zb;
     }
     __syncthreads();
-    if (threadIdx.x < kDepthBuckets && wcnt[threadIdx.x])
-        wbase[threadIdx.x] = atomicAdd(&ctr->vis_bucket[threadIdx.x], wcnt[threadIdx.x]);
+    const uint32_t team = tid / kLanes, lane = tid % kLanes;
+    for (uint32_t base = 0; base < cnt; base += kTeams) {   // uniform over the workgroup: whole waves shuffle
+        const uint32_t c = min(base + team, cnt - 1);
+        const uint32_t zb = bound[c], cw = span[c] & 0xFFFFu, cells = zb ? cw * (span[c] >> 16) : 0u, c0 = cell0[c];
+        uint32_t m = 0;
+        for (uint32_t i = lane; i < cells; i += kLanes) {
+            const uint32_t row = i / cw;
+            m = max(m, hz16[c0 + row * hz16_w + (i - row * cw)]);
+        }
+#pragma unroll
+        for (int o = kLanes / 2; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o));
+        if (lane == 0) hid[c] = zb > m ? 1u : 0u;
+    }
     __syncthreads();
-    if (cls >= 0) S.vis_clusters[(size_t)cls * stride + wbase[cls] + off] = c | (inside ? kClusterInside : 0u);
+    const bool keep = tid < cnt && !hid[tid];
+    const uint32_t off = class_place(keep ? (int)k : -1, wcnt, wbase, ctr->rest_bucket);
+    if (keep) S.vis_clusters[(size_t)kDepthBuckets * stride + (k ? cls_end[k - 1] : 0u) + wbase[k] + off] = entry;
 }
 
 inline unsigned grid_for(uint64_t n) {
@@ -259,7 +378,7 @@ size_t scene_build_temp_bytes(uint64_t n, uint64_t m) {
 
 hipError_t scene_build(const float* pos, const float* rad, const uint32_t* bonds, uint64_t n, uint64_t m,
                        SceneDev& S, float4* xyzr, uint32_t* atom_id, uint4* bond_rec, float4* cluster_box,
-                       void* tmp, size_t tmp_bytes, uint32_t* m_valid, uint32_t* n_bad, uint32_t* box_bits,
+                       void* tmp, size_t tmp_bytes, uint32_t* m_valid, uint32_t* n_bad, SceneExtent* extent,
                        hipStream_t stream) {
     const uint64_t mx = n > m ? n : m;
     char* p = static_cast<char*>(tmp);
@@ -273,16 +392,17 @@ hipError_t scene_build(const float* pos, const float* rad, const uint32_t* bonds
     uint32_t* vin = (uint32_t*)take(sizeof(uint32_t) * (mx ? mx : 1));
     uint32_t* vout = (uint32_t*)take(sizeof(uint32_t) * (mx ? mx : 1));
     uint32_t* inv = (uint32_t*)take(sizeof(uint32_t) * (n ? n : 1));
-    uint32_t* box = (uint32_t*)take(64);
-    uint32_t* bad = box + 8;
+    SceneExtent* ext = (SceneExtent*)take(64);
+    uint32_t* bad = (uint32_t*)(ext + 1);
     uint32_t* sort_tmp = (uint32_t*)take(sizeof(uint32_t) * radix_sort_scratch_words((size_t)mx));
     if ((size_t)(p - static_cast<char*>(tmp)) > tmp_bytes) return hipErrorOutOfMemory;
     hipError_t e;
-    k_box_init<<<1, 64, 0, stream>>>(box);
+    static_assert(sizeof(SceneExtent) + sizeof(uint32_t) <= 64, "taken together");
+    k_extent_init<<<1, 64, 0, stream>>>(ext);
     if ((e = launch_zero(bad, 1, stream)) != hipSuccess) return e;
     if (n) {
-        k_bbox<<<grid_for(n) < 1024 ? grid_for(n) : 1024, kBlock, 0, stream>>>(pos, (uint32_t)n, box);
-        k_morton<<<grid_for(n), kBlock, 0, stream>>>(pos, (uint32_t)n, box, kin, vin);
+        k_extent<<<grid_for(n) < 1024 ? grid_for(n) : 1024, kBlock, 0, stream>>>(pos, rad, (uint32_t)n, ext);
+        k_morton<<<grid_for(n), kBlock, 0, stream>>>(pos, (uint32_t)n, ext->box, kin, vin);
         if ((e = radix_sort_pairs(kin, kout, vin, vout, atom_id, (size_t)n, 30, sort_tmp, stream)) != hipSuccess)
             return e;
         k_gather_atoms<<<grid_for(n), kBlock, 0, stream>>>(pos, rad, atom_id, (uint32_t)n, xyzr, inv);
@@ -306,9 +426,8 @@ hipError_t scene_build(const float* pos, const float* rad, const uint32_t* bonds
     if (nc) k_cluster_boxes<<<grid_for((uint64_t)nc * 64), kBlock, 0, stream>>>(S, cluster_box);
     *m_valid = mv;
     *n_bad = nb;
-    // the atoms' bounding box (order-preserving bits, min xyz then max xyz),
     // host memory, valid once the stream has reached this point
-    if ((e = hipMemcpyAsync(box_bits, box, 6 * sizeof(uint32_t), hipMemcpyDeviceToHost, stream)) != hipSuccess) return e;
+    if ((e = hipMemcpyAsync(extent, ext, sizeof(SceneExtent), hipMemcpyDeviceToHost, stream)) != hipSuccess) return e;
     return hipGetLastError();
 }
 
@@ -347,6 +466,14 @@ hipError_t cull_impl(const JS& js, uint32_t grid, hipStream_t stream) {
     return dispatch(k_cluster_cull<JS>, grid, kBlock, 0, stream, js);
 }
 
+template <class JS>
+hipError_t rest_impl(const JS& js, uint32_t grid, hipStream_t stream) {
+    if (grid == 0) return hipSuccess;
+    return dispatch(k_cluster_rest<JS>, grid, kBlock, 0, stream, js);
+}
+
+hipError_t launch_cluster_rest(const OneJob& js, uint32_t grid, hipStream_t stream) { return rest_impl(js, grid, stream); }
+hipError_t launch_cluster_rest(const JobList& js, uint32_t grid, hipStream_t stream) { return rest_impl(js, grid, stream); }
 hipError_t launch_cluster_cull(const OneJob& js, uint32_t grid, hipStream_t stream) { return cull_impl(js, grid, stream); }
 hipError_t launch_cluster_cull(const JobList& js, uint32_t grid, hipStream_t stream) { return cull_impl(js, grid, stream); }
 

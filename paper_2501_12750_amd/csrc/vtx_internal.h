@@ -122,6 +122,7 @@ struct Counters {
     unsigned long long chunks_stopped;
     unsigned int done_blocks;
     unsigned int vis_bucket[kDepthBuckets];   // resident scenes: clusters that passed the frustum test, per depth class
+    unsigned int rest_bucket[kDepthBuckets];  // two-pass frames: of those past the front pass, the clusters it does not hide
     // resident scenes: per pass (one pass or the front pass; the rest) and
     // layer, float bits of a lower bound of the resolve's cull depth of every
     // primitive its workgroups binned (+inf: none; 0: not positive)
@@ -285,6 +286,32 @@ __device__ inline bool sphere_inside_frustum(const Frame& F, double vx, double v
     }
     return fabs(vx) + r + m <= F.hx && fabs(vy) + r + m <= F.hy;
 }
+// Ends of the depth classes (cls_end[kDepthBuckets - 1] their total) in the
+// front-to-back order of the clusters counted in `bucket`.  Called by one wave.
+__device__ inline void class_ends(const unsigned int* bucket, uint32_t* cls_end) {
+    static_assert(kDepthBuckets == 64, "one lane per class");
+    const int lane = __lane_id();
+    uint32_t v = bucket[lane];
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t u = __shfl_up(v, o);
+        if (lane >= o) v += u;
+    }
+    cls_end[lane] = v;
+}
+// Clusters of a two-pass frame's front pass: the first 1 / kFrontShare of the
+// visible ones, rounded up to the end of a depth class (the order inside one
+// is arbitrary) unless that would take more than half.
+__device__ inline uint32_t front_clusters(const uint32_t* cls_end) {
+    const uint32_t nvc = cls_end[kDepthBuckets - 1];
+    uint32_t front = (nvc + kFrontShare - 1) / kFrontShare;
+    for (int k = 0; k < kDepthBuckets; ++k) {
+        if (cls_end[k] < front) continue;
+        if (cls_end[k] <= nvc / 2) front = cls_end[k];
+        break;
+    }
+    return front;
+}
 // Flag of a visible-cluster entry whose sphere is wholly inside the view
 // volume (cluster indices stay below 2^31).
 constexpr uint32_t kClusterInside = 0x80000000u;
@@ -386,6 +413,9 @@ struct BinBuffers {
 // them to the waves by quarters.
 constexpr uint32_t kFewClusters = 8;
 
+// Entries of a render's visible-cluster scratch (SceneDev::vis_clusters).
+inline size_t vis_cluster_entries(size_t clusters) { return clusters * (kDepthBuckets + 1); }
+
 // Binning grid for n primitives of one of `renders` renders launched together
 // (groups <= kMaxBinGroups, groups * chunk >= n).
 void bin_grid(uint64_t nprim, uint64_t renders, uint32_t* groups, uint32_t* chunk);
@@ -403,7 +433,16 @@ struct SceneDev {
     const uint4* bond_rec;              // n_bonds: (stored index a, stored index b, original bond index, 0)
     const float4* cluster_box;          // 2 per cluster: (min xyz, -), (max xyz, -); bond boxes exclude the radius
     uint32_t* vis_clusters;             // kDepthBuckets regions of atom_clusters + bond_clusters entries:
-                                        // visible cluster ids per depth class (per render)
+                                        // visible cluster ids per depth class (per render), then one such
+                                        // region for the clusters of a two-pass frame's rest pass
+};
+// What the build measures of a scene: the atoms' bounding box
+// (order-preserving bits, min xyz then max xyz) and the sums of their radii
+// and squared radii in 1/1024 (radii outside (0, 1000] left out).
+struct SceneExtent {
+    uint32_t box[6];
+    uint32_t pad[2];
+    unsigned long long r_sum, r2_sum;
 };
 // Stable radix sort (sort.hip) of n (key, value) pairs by the low end_bit
 // bits of the keys, 8 bits per pass.  keys/vals hold the input and are
@@ -419,7 +458,7 @@ hipError_t scene_order(const SceneDev& S, uint32_t* atom_order, uint32_t* bond_o
 size_t scene_build_temp_bytes(uint64_t n, uint64_t m);
 hipError_t scene_build(const float* pos, const float* rad, const uint32_t* bonds, uint64_t n, uint64_t m,
                        SceneDev& S, float4* xyzr, uint32_t* atom_id, uint4* bond_rec, float4* cluster_box,
-                       void* tmp, size_t tmp_bytes, uint32_t* m_valid, uint32_t* n_bad, uint32_t* box_bits,
+                       void* tmp, size_t tmp_bytes, uint32_t* m_valid, uint32_t* n_bad, SceneExtent* extent,
                        hipStream_t stream);
 hipError_t scene_update_positions(const float* pos, SceneDev& S, float4* xyzr, float4* cluster_box,
                                   hipStream_t stream);
@@ -470,6 +509,7 @@ struct OneJob {
     __device__ const Job& job(int) const { return j; }
     __device__ const SampleKernel& samples(int) const { return K; }
     __device__ uint32_t count() const { return 1; }
+    __device__ uint32_t work_blocks(int) const { return blocks; }
     // the work block after (i, local): the next one of the job, else -1
     __device__ void next(int& i, uint32_t& local) const {
         if (i >= 0 && ++local >= blocks) i = -1;
@@ -507,6 +547,7 @@ struct JobList {
     __device__ const Job& job(int i) const { return jobs[i]; }
     __device__ const SampleKernel& samples(int i) const { return K[i]; }
     __device__ uint32_t count() const { return n; }
+    __device__ uint32_t work_blocks(int i) const { return start[i + 1] - start[i]; }
     // the work block after (i, local): the next one of job i, else the first
     // of the next job that has any, else -1 (no search)
     __device__ void next(int& i, uint32_t& local) const {
@@ -582,6 +623,10 @@ __device__ inline JobRef job_ref(const JobList& js, int i) {
 // VTX_FLAG_STATS).
 hipError_t launch_cluster_cull(const OneJob& js, uint32_t grid, hipStream_t stream);
 hipError_t launch_cluster_cull(const JobList& js, uint32_t grid, hipStream_t stream);
+// Two-pass frames, between the passes: the clusters past the front pass that
+// it does not hide (grid as for the cull).
+hipError_t launch_cluster_rest(const OneJob& js, uint32_t grid, hipStream_t stream);
+hipError_t launch_cluster_rest(const JobList& js, uint32_t grid, hipStream_t stream);
 // `phase` (resident scenes): kPhaseAll bins every visible cluster; a
 // two-pass frame runs count to resolve with kPhaseFront, then again with
 // kPhaseRest, whose resolve starts from the front pass's G-buffer.

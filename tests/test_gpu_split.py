@@ -66,3 +66,48 @@ def test_binning_cuts_give_the_oracle_image(vtx, ctx, n, bonded):
     for f in frames:
         assert_identical(f.numpy(), plain, "batch")
     rs.close()
+
+
+def two_ways(vtx, ctx, wl, flags_a, flags_b):
+    """The scene's images and statistics with two sets of flags, once its lists are sized."""
+    import torch
+    rs = vtx.ResidentScene(ctx, vtx.DeviceScene(wl.scene))
+    out = []
+    for flags in (0, flags_a, flags_b):
+        fr = rs.render(wl.camera, dataclasses.replace(wl.options, flags=flags), wl.width, wl.height)
+        torch.cuda.synchronize()
+        out.append((fr.numpy(), vtx.vtx_read_stats()))
+    rs.close()
+    return out[1:]
+
+
+@pytest.mark.parametrize("n", [1, 256, 257, 2049, 4096, 65536 + 255, 300_001])
+@pytest.mark.parametrize("bonded", [False, True])
+def test_pre_pass_at_few_and_odd_cluster_counts(vtx, ctx, n, bonded):
+    wl = workload(n, bonded, 211, 133)
+    (two, st_two), (one, st_one) = two_ways(vtx, ctx, wl, vtx.VTX_FLAG_TWO_PASS, vtx.VTX_FLAG_ONE_PASS)
+    assert_identical(two, one, f"{n} atoms")
+    print("atoms", n, "binned in two passes", st_two["visible"], "in one", st_one["visible"], flush=True)
+    assert st_two["visible"] <= st_one["visible"]
+
+
+def test_a_large_opaque_scene_takes_the_pre_pass_unasked(vtx, ctx):
+    """17M atoms in a ball, seen whole: over 16M in view, its faces covered
+    hundreds of times.  The same scene seen from inside, with an eighth of it
+    in view, keeps to one pass."""
+    n = 17_000_000
+    rng = np.random.default_rng(17)
+    radius = (3.0 * n / (4.0 * np.pi * 0.1)) ** (1.0 / 3.0)
+    d = rng.normal(size=(n, 3)).astype(np.float32)
+    d *= (radius * np.cbrt(rng.uniform(size=n)) / np.linalg.norm(d, axis=1)).astype(np.float32)[:, None]
+    scene = scenes.Scene(d, np.full(n, 1.6, np.float32), np.full(n, scenes.pack_rgba(200, 180, 160), np.uint32),
+                         np.zeros((0, 2), np.uint32))
+    wl = scenes.Workload("ball", scene, scenes.orbit_camera((0.0, 0.0, 0.0), 1.2 * radius, 0.4),
+                         scenes.Options(ssao_samples=8), 640, 480)
+    (auto, st_auto), (one, st_one) = two_ways(vtx, ctx, wl, 0, vtx.VTX_FLAG_ONE_PASS)
+    assert_identical(auto, one, "whole")
+    assert st_auto["visible"] < st_one["visible"] // 2, (st_auto["visible"], st_one["visible"])
+    wl.camera = scenes.Camera(eye=(0.0, 0.0, 0.0), target=(1.0, 0.2, 0.1))
+    (auto, st_auto), (one, st_one) = two_ways(vtx, ctx, wl, 0, vtx.VTX_FLAG_ONE_PASS)
+    assert_identical(auto, one, "inside")
+    assert st_auto["visible"] == st_one["visible"]
