@@ -1456,23 +1456,23 @@ int vtx_ses(const float* positions, const float* radii, int64_t n_atoms, float p
     int rc = get_workspace(st, &ws);
     if (rc) return rc;
     const int dims[3] = {grid->dims[0], grid->dims[1], grid->dims[2]};
-    size_t wm, wg, wc, wb;
-    size_t words = vtx::ses_scratch_words(dims, &wm, &wg, &wc, &wb);
-    const size_t wf = field ? 0 : (size_t)np;
-    words += wf + 64;
+    const vtx::SesWords w = vtx::ses_scratch_words(probe_radius, grid->spacing, dims);
+    const size_t words = w.mark + 2 * w.g + w.sign + w.cnt + w.bsum + (field ? 0 : (size_t)np) + 64;
     if ((rc = grow(&ws->ses, ws->ses_cap, words, st, "surface scratch"))) return rc;
     vtx::SesScratch sc;
     uint32_t* at = ws->ses;
-    sc.mark = reinterpret_cast<uint8_t*>(at);
-    at += wm;
+    sc.mark = reinterpret_cast<unsigned long long*>(at);
+    at += w.mark;
     sc.ga = reinterpret_cast<int32_t*>(at);
-    at += wg;
+    at += w.g;
     sc.gb = reinterpret_cast<int32_t*>(at);
-    at += wg;
+    at += w.g;
+    sc.sign = at;
+    at += w.sign;
     sc.cnt = at;
-    at += wc;
+    at += w.cnt;
     sc.bsum = at;
-    at += wb;
+    at += w.bsum;
     float* f = field ? field : reinterpret_cast<float*>(at);
     VTX_HIP(vtx::ses_run(positions, radii, (uint64_t)n_atoms, probe_radius, grid->origin, grid->spacing, dims, f,
                          triangles, (uint64_t)capacity, reinterpret_cast<unsigned long long*>(n_triangles), sc, st));

@@ -67,6 +67,41 @@ __global__ void __launch_bounds__(kScanBlock) k_scan_top(uint32_t* __restrict__ 
     if (threadIdx.x == 0 && total_out) *total_out = carry;
 }
 
+// A few thousand counts by one workgroup, kOnePer consecutive ones a thread.
+constexpr int kOneBlock = 1024, kOnePer = 8, kOneSpan = kOneBlock * kOnePer;
+
+__global__ void __launch_bounds__(kOneBlock) k_scan_one(uint32_t* __restrict__ v, uint32_t n,
+                                                        unsigned long long* __restrict__ total_out) {
+    __shared__ uint32_t wsum[kOneBlock / 64];
+    const int lane = __lane_id(), wave = threadIdx.x >> 6;
+    const uint32_t base = threadIdx.x * kOnePer;
+    uint32_t x[kOnePer], s = 0;
+#pragma unroll
+    for (int r = 0; r < kOnePer; ++r) {
+        x[r] = base + r < n ? v[base + r] : 0u;
+        s += x[r];
+    }
+    uint32_t incl = s;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t u = __shfl_up(incl, o);
+        if (lane >= o) incl += u;
+    }
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    uint32_t run = incl - s, all = 0;
+    for (int w = 0; w < kOneBlock / 64; ++w) {
+        run += w < wave ? wsum[w] : 0u;
+        all += wsum[w];
+    }
+#pragma unroll
+    for (int r = 0; r < kOnePer; ++r) {
+        if (base + r < n) v[base + r] = run;
+        run += x[r];
+    }
+    if (threadIdx.x == 0 && total_out) *total_out = all;
+}
+
 // Block b's elements, loaded and stored coalesced through LDS: thread t
 // scans the kScanPer consecutive elements t * kScanPer + [0, kScanPer) of
 // the block (the LDS index skips one word every 32 so those reads spread
@@ -113,6 +148,8 @@ size_t scan_scratch_words(size_t n) { return (n + kScanSpan - 1) / kScanSpan + 1
 hipError_t exclusive_scan(uint32_t* v, size_t n, uint32_t* bsum, unsigned long long* total, hipStream_t stream) {
     const size_t nb = (n + kScanSpan - 1) / kScanSpan;
     hipError_t e;
+    // a few thousand counts: one launch in place of three (17 us in all)
+    if (n <= (size_t)kOneSpan) return dispatch(k_scan_one, 1, kOneBlock, 0, stream, v, (uint32_t)n, total);
     if (nb && (e = dispatch(k_scan_sums, (unsigned)nb, kScanBlock, 0, stream, (const uint32_t*)v, n, bsum))) return e;
     if ((e = dispatch(k_scan_top, 1, kScanBlock, 0, stream, bsum, (uint32_t)nb, total))) return e;
     if (nb && (e = dispatch(k_scan_apply, (unsigned)nb, kScanBlock, 0, stream, v, n, (const uint32_t*)bsum))) return e;

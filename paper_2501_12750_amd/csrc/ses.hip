@@ -17,12 +17,13 @@
 //    the outside ones and started at their lowest edge; a 3-edge loop is a
 //    triangle, a longer one a fan around the mean of its vertices.
 //
-// Passes: mark the SAS interior per atom; the exact squared distance to
-// the nearest exterior point within a W-box by three separable 1-D passes
-// in integers (x: nearest exterior point on the row; y and z: the least of
-// g + d^2 over the window); triangle counts per cube; an exclusive scan of
-// the counts (scan.hip); emission of the triangles of the cubes that have
-// any, each at its offset.
+// Passes: mark the SAS interior per atom, one bit per point; the exact
+// squared distance to the nearest exterior point within a W-box by three
+// separable 1-D passes in integers (x: nearest exterior point on the row; y
+// and z: the least of g + d^2 over the window), all three in LDS per brick of
+// points when W is small, then the field and one sign bit per point; triangle
+// counts per run of cubes from the sign bits, an exclusive scan of those
+// (scan.hip), and the triangles of each run's cubes that have any.
 #include <mutex>
 
 #include "vtx_internal.h"
@@ -33,20 +34,20 @@ namespace {
 
 constexpr int kSesBlock = 256;
 constexpr int kSesMarkBlock = 64;      // one wave per atom: its box setup is paid once per wave
+constexpr int kSesRun = 64;            // words of sign bits (up to 32 cubes each) per run of cubes
+constexpr int kMaxFusedW = 12;         // windows up to which a brick's distances fit LDS
 constexpr int32_t kFar = 0x3FFFFFFF;   // no exterior point within the window
 
-// Case table: for each case, its loops as a byte string: loop length, then
-// its edges, ..., then 0.  Edges 0-3 run along x, 4-7 along y, 8-11 along z
-// (corner pairs below); corner c sits at (c & 1, c >> 1 & 1, c >> 2 & 1).
-constexpr int kCaseBytes = 24;
-__constant__ uint8_t c_cases[256 * kCaseBytes];
+// Case table: for each case, one word with its loops' edges in order, 4 bits
+// each from bit 0 (12 at most), and the loops' lengths, 4 bits each from bit
+// 48 (4 loops at most; 0 ends them), so that a cube's thread reads its case
+// at once.  Edges 0-3 run along x, 4-7 along y, 8-11 along z (corner pairs
+// below); corner c sits at (c & 1, c >> 1 & 1, c >> 2 & 1).
+__constant__ unsigned long long c_cases[256];
 __constant__ uint8_t c_case_tris[256];
 
 constexpr int kEdgeA[12] = {0, 2, 4, 6, 0, 1, 4, 5, 0, 1, 2, 3};
 constexpr int kEdgeB[12] = {1, 3, 5, 7, 2, 3, 6, 7, 4, 5, 6, 7};
-__constant__ int8_t c_edge_corner[12][2] = {{0, 1}, {2, 3}, {4, 5}, {6, 7}, {0, 2}, {1, 3},
-                                            {4, 6}, {5, 7}, {0, 4}, {1, 5}, {2, 6}, {3, 7}};
-
 int edge_of(int a, int b) {
     if (a > b) {
         const int t = a;
@@ -59,7 +60,7 @@ int edge_of(int a, int b) {
 }
 
 // The loops of case m, built as the table's rule states.
-void build_case(int m, uint8_t* out, uint8_t* ntri) {
+void build_case(int m, unsigned long long* out, uint8_t* ntri) {
     static const int faces[6][4] = {{0, 2, 6, 4}, {1, 3, 7, 5}, {0, 1, 5, 4}, {2, 3, 7, 6}, {0, 1, 3, 2}, {4, 5, 7, 6}};
     int in[8];
     for (int c = 0; c < 8; ++c) in[c] = (m >> c) & 1;
@@ -84,7 +85,8 @@ void build_case(int m, uint8_t* out, uint8_t* ntri) {
         }
     }
     bool used[12] = {};
-    int pos = 0, tris = 0;
+    int pos = 0, loops = 0, tris = 0;
+    unsigned long long w = 0;
     for (int start = 0; start < 12; ++start) {
         if (deg[start] == 0 || used[start]) continue;
         int loop[12], k = 0;
@@ -125,11 +127,11 @@ void build_case(int m, uint8_t* out, uint8_t* ntri) {
         int lo = 0;
         for (int i = 1; i < k; ++i)
             if (loop[i] < loop[lo]) lo = i;
-        out[pos++] = (uint8_t)k;
-        for (int i = 0; i < k; ++i) out[pos++] = (uint8_t)loop[(lo + i) % k];
+        w |= (unsigned long long)k << (48 + 4 * loops++);
+        for (int i = 0; i < k; ++i) w |= (unsigned long long)loop[(lo + i) % k] << (4 * pos++);
         tris += k == 3 ? 1 : k;
     }
-    out[pos] = 0;
+    *out = w;
     *ntri = (uint8_t)tris;
 }
 
@@ -140,9 +142,9 @@ hipError_t ensure_cases(int device) {
     std::lock_guard<std::mutex> lk(g_case_mu);
     if (device < 0 || device >= 64) return hipErrorInvalidDevice;
     if (g_case_ready[device]) return hipSuccess;
-    static uint8_t cases[256 * kCaseBytes];
+    static unsigned long long cases[256];
     static uint8_t ntri[256];
-    for (int m = 0; m < 256; ++m) build_case(m, cases + m * kCaseBytes, ntri + m);
+    for (int m = 0; m < 256; ++m) build_case(m, cases + m, ntri + m);
     hipError_t e = hipMemcpyToSymbol(HIP_SYMBOL(c_cases), cases, sizeof(cases));
     if (e == hipSuccess) e = hipMemcpyToSymbol(HIP_SYMBOL(c_case_tris), ntri, sizeof(ntri));
     if (e == hipSuccess) g_case_ready[device] = true;
@@ -162,47 +164,89 @@ __device__ inline size_t gidx(const SesGrid& G, int i, int j, int k) {
     return (size_t)i + (size_t)G.nx * ((size_t)j + (size_t)G.ny * k);
 }
 
-// One wave per atom: marks the grid points inside its solvent-accessible
-// sphere (interior = 1; points no atom marks stay 0: exterior).  Each lane
-// takes (i, j) columns of the atom's box and walks them along k with
-// dx^2 + dy^2 computed once per column.
+// The mark of a point is one bit: word (i / 4, j / 4, k / 4) of 64 bits holds
+// a 4 x 4 x 4 cell of points, bit (k & 3) 16 + (j & 3) 4 + (i & 3).
+struct MarkGrid {
+    unsigned long long* bits;
+    int nx, ny;          // cells along x and y
+};
+inline int mark_cells(int n) { return (n + 3) / 4; }
+
+// One wave per atom: sets the bits of the grid points inside its
+// solvent-accessible sphere (points no atom marks stay 0: exterior), one lane
+// per 4 x 4 x 4 cell of the atom's box, one atomic per cell that has any.  The
+// squared offsets and the two sums are rounded as the reading states; each
+// rounding is monotone, so a cell whose nearest (farthest) corner fails
+// (passes) the test is empty (full) without testing its points.  Bounded by
+// the point tests' VALU instructions: 50,000 atoms of reach 2.6 to 3.2 at
+// spacing 0.5 take 45 us, and took 90 with a byte per point (249 MB of
+// write-backs for a 10 MB grid).
 __global__ void __launch_bounds__(kSesMarkBlock) k_ses_mark(const float* __restrict__ pos,
                                                             const float* __restrict__ rad, uint32_t n, SesGrid G,
-                                                            uint8_t* __restrict__ mark) {
+                                                            MarkGrid M) {
 #pragma clang fp contract(off)
     const uint32_t a = blockIdx.x;
     if (a >= n) return;
-    const double cx = pos[3 * (size_t)a], cy = pos[3 * (size_t)a + 1], cz = pos[3 * (size_t)a + 2];
+    const double c[3] = {pos[3 * (size_t)a], pos[3 * (size_t)a + 1], pos[3 * (size_t)a + 2]};
     const double R = (double)rad[a] + G.rp;
     if (!(R > 0.0)) return;
     const double R2 = R * R;
-    int lo[3], hi[3];
-    const double c[3] = {cx, cy, cz};
+    int lo[3], nc[3];
     const int nmax[3] = {G.nx - 1, G.ny - 1, G.nz - 1};
-    // the box only has to hold every point the test can mark: a step of
-    // margin on each side covers the rounding of the product by 1 / h
+    // the box only has to hold every point the test can mark: a thousandth of
+    // a step of margin covers the rounding of the grid coordinates (below
+    // 2^31, so off by less than 2e-6)
     for (int d = 0; d < 3; ++d) {
-        lo[d] = max(0, (int)floor((c[d] - R - G.o[d]) * G.inv_h) - 1);
-        hi[d] = min(nmax[d], (int)ceil((c[d] + R - G.o[d]) * G.inv_h) + 1);
-        if (lo[d] > hi[d]) return;
+        const double from = fmax(0.0, ceil((c[d] - R - G.o[d]) * G.inv_h - 1e-3));
+        const double to = fmin((double)nmax[d], floor((c[d] + R - G.o[d]) * G.inv_h + 1e-3));
+        if (!(from <= to) || !(c[d] - c[d] == 0.0)) return;   // beside the grid, or not a finite position
+        const int l = (int)from, h = (int)to;
+        lo[d] = l >> 2;
+        nc[d] = (h >> 2) - lo[d] + 1;
     }
-    const int bx = hi[0] - lo[0] + 1, ncol = bx * (hi[1] - lo[1] + 1);
-    const size_t plane = (size_t)G.nx * G.ny;
-    for (int q = threadIdx.x; q < ncol; q += kSesMarkBlock) {
-        const int j = lo[1] + q / bx, i = lo[0] + q % bx;
-        const double dx = (G.o[0] + G.h * i) - cx, dy = (G.o[1] + G.h * j) - cy;
-        const double sxy = dx * dx + dy * dy;
-        size_t p = gidx(G, i, j, lo[2]);
-        for (int k = lo[2]; k <= hi[2]; ++k, p += plane) {
-            const double dz = (G.o[2] + G.h * k) - cz;
-            if (sxy + dz * dz < R2) mark[p] = 1;
+    const int cells = nc[0] * nc[1] * nc[2];
+    for (int q = threadIdx.x; q < cells; q += kSesMarkBlock) {
+        const int qz = q / (nc[0] * nc[1]), qr = q - qz * (nc[0] * nc[1]), qy = qr / nc[0], qx = qr - qy * nc[0];
+        const int cell[3] = {lo[0] + qx, lo[1] + qy, lo[2] + qz};
+        double s[3][4], near[3], far[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const double x = (G.o[d] + G.h * (4 * cell[d] + t)) - c[d];
+                s[d][t] = x * x;
+            }
+            near[d] = fmin(fmin(s[d][0], s[d][1]), fmin(s[d][2], s[d][3]));
+            far[d] = fmax(s[d][0], s[d][3]);
         }
+        if (!((near[0] + near[1]) + near[2] < R2)) continue;
+        unsigned long long m = ~0ull;
+        if (!((far[0] + far[1]) + far[2] < R2)) {
+            uint32_t w[2] = {0u, 0u};
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const double sxy = s[0][i] + s[1][j];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        w[k >> 1] |= sxy + s[2][k] < R2 ? 1u << ((k & 1) * 16 + j * 4 + i) : 0u;
+                }
+            m = ((unsigned long long)w[1] << 32) | w[0];
+        }
+        if (m) atomicOr(&M.bits[((size_t)cell[2] * M.ny + cell[1]) * M.nx + cell[0]], m);
     }
 }
 
-// The per-point and per-cube passes run one thread per point (or cube) in
-// x-fastest order; the grid holds fewer than 2^31 points, so the index and
-// its decomposition stay in 32 bits.
+// The mark words' nibble of row (j, k) (points 4 c to 4 c + 3 of it).
+__device__ inline uint32_t mark_nibble(const MarkGrid& M, int c, int j, int k) {
+    const uint32_t* half = reinterpret_cast<const uint32_t*>(M.bits + ((size_t)(k >> 2) * M.ny + (j >> 2)) * M.nx + c) + (k >> 1 & 1);
+    return *half >> ((k & 1) * 16 + (j & 3) * 4) & 15u;
+}
+
+// The per-point passes below run one thread per point in x-fastest order;
+// the grid holds fewer than 2^31 points, so the index and its decomposition
+// stay in 32 bits.
 __device__ inline bool flat_item(uint32_t n, int nx, int ny, int& i, int& j, int& k, uint32_t& p) {
     p = blockIdx.x * (uint32_t)kSesBlock + threadIdx.x;
     if (p >= n) return false;
@@ -213,52 +257,144 @@ __device__ inline bool flat_item(uint32_t n, int nx, int ny, int& i, int& j, int
     return true;
 }
 
+// Field of a squared grid distance g (exterior point farther than the
+// window: any g > W^2).
+__device__ inline float ses_field(const SesGrid& G, int g) {
+    const double cap = G.W * G.h;
+    const double D = g > G.W * G.W ? cap : fmin(G.h * sqrt((double)g), cap);
+    return (float)(D - G.rp);
+}
+
+// The three distance passes of one brick of kBx x kBy x kBz points in LDS
+// (window kW <= kMaxFusedW), the field and the sign bits (f >= 0) of its rows.
+// The points within kW of the brick along y and z are recomputed by each
+// brick that needs them; nothing goes through memory between the passes.
+// Squared distances fit 16 bits (3 kW^2 at most, 127^2 for none on the row),
+// two points to a register:
+// x0 + t and x0 + 16 + t, so that stores of the field are consecutive.  (Three
+// passes over int32 grids: 136 us for 9.75M points and kW = 5, now 36.)
+constexpr int kBx = 32, kBy = 16, kBz = 16;
+constexpr int kEdtBlock = 512;
+typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+
+// out[c] = the least over |d| <= kW of col[c + kW + d] + d^2.
+template <int kW, int kN>
+__device__ inline void window_min(const us2 (&col)[kN + 2 * kW], us2 (&out)[kN]) {
+#pragma unroll
+    for (int c = 0; c < kN; ++c) {
+        us2 best = col[c + kW];
+#pragma unroll
+        for (int d = 1; d <= kW; ++d) {
+            const unsigned short dd = (unsigned short)(d * d);
+            best = __builtin_elementwise_min(best, (us2)(__builtin_elementwise_min(col[c + kW - d], col[c + kW + d]) + (us2){dd, dd}));
+        }
+        out[c] = best;
+    }
+}
+
+template <int kW>
+__global__ void __launch_bounds__(kEdtBlock) k_ses_edt(SesGrid G, MarkGrid M, uint32_t nbx, uint32_t nby,
+                                                       float* __restrict__ field, uint32_t* __restrict__ sign, int nxw) {
+    constexpr int kRows = kBy + 2 * kW, kPlanes = kBz + 2 * kW, kPairs = kBx / 2;
+    constexpr int kLead = (kW + 3) / 4 * 4, kNibbles = (kLead + kBx + kW + 3) / 4;
+    static_assert(kNibbles <= 16, "a row's window fits 64 bits");
+    constexpr int kHalf = kBz / 2;
+    static_assert(kEdtBlock == 2 * kBy * kPairs, "half a z column per thread");
+    __shared__ us2 g[kPlanes][kRows | 1][kPairs];   // an odd row count: a wave's four planes lie in different banks
+    __shared__ unsigned long long ext[kPlanes * kRows];   // bit p of a row: point x0 - kW + p is exterior
+    __shared__ float tab[kW * kW + 2];                    // field by squared distance
+    const int tid = threadIdx.x;
+    const uint32_t b = blockIdx.x, bx = b % nbx, br = b / nbx;
+    const int x0 = (int)bx * kBx, y0 = (int)(br % nby) * kBy, z0 = (int)(br / nby) * kBz;
+    for (int r = tid; r < kPlanes * kRows; r += kEdtBlock) {
+        const int j = y0 - kW + r % kRows, k = z0 - kW + r / kRows;
+        // every load first, at cells clamped to the grid, so they overlap;
+        // points outside the grid are no exterior points
+        const int jc = min(max(j, 0), G.ny - 1), kc = min(max(k, 0), G.nz - 1);
+        const int c0 = (x0 - kLead) / 4;   // exact: both are multiples of 4
+        uint32_t nib[kNibbles], w[2] = {0u, 0u};
+#pragma unroll
+        for (int q = 0; q < kNibbles; ++q) nib[q] = mark_nibble(M, min(max(c0 + q, 0), M.nx - 1), jc, kc);
+#pragma unroll
+        for (int q = 0; q < kNibbles; ++q) w[q >> 3] |= (c0 + q >= 0 && c0 + q < M.nx ? nib[q] : 15u) << (4 * (q & 7));
+        unsigned long long in = (unsigned long long)w[1] << 32 | w[0];
+        const int end = G.nx - (x0 - kLead);   // first position past the row
+        if (end < 64) in |= ~0ull << end;
+        if (j != jc || k != kc) in = ~0ull;
+        ext[r] = ~in >> (kLead - kW);
+    }
+    for (int q = tid; q < kW * kW + 2; q += kEdtBlock) tab[q] = ses_field(G, q);
+    __syncthreads();
+    // x: the nearest exterior point of the row
+    const int t = tid % kPairs;
+    for (int r = tid / kPairs; r < kPlanes * kRows; r += kEdtBlock / kPairs) {
+        us2 v;
+        const uint32_t lo = (uint32_t)ext[r], hi = (uint32_t)(ext[r] >> 32);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const uint32_t w = __builtin_amdgcn_alignbit(hi, lo, t + 16 * h);   // bit kW: the point itself
+            const uint32_t right = w >> kW, left = w << (31 - kW);
+            const uint32_t d = min(right ? (uint32_t)__builtin_ctz(right) : ~0u, left ? (uint32_t)__builtin_clz(left) : ~0u);
+            // a distance past the window squares to more than kW^2: far, whatever it is
+            v[h] = (unsigned short)__umul24(min(d, 127u), min(d, 127u));
+        }
+        g[r / kRows][r % kRows][t] = v;
+    }
+    __syncthreads();
+    // y, in place: a thread reads its whole column first
+    for (int q = tid; q < kPlanes * kPairs; q += kEdtBlock) {
+        const int p = q / kPairs;
+        us2 col[kRows], out[kBy];
+#pragma unroll
+        for (int c = 0; c < kRows; ++c) col[c] = g[p][c][t];
+        window_min<kW, kBy>(col, out);
+#pragma unroll
+        for (int c = 0; c < kBy; ++c) g[p][c][t] = out[c];
+    }
+    __syncthreads();
+    // z, the field and the signs
+    const int y = tid / kPairs % kBy, j = y0 + y, zh = tid / (kPairs * kBy) * kHalf;
+    us2 col[kHalf + 2 * kW], out[kHalf];
+#pragma unroll
+    for (int c = 0; c < kHalf + 2 * kW; ++c) col[c] = g[zh + c][y][t];
+    window_min<kW, kHalf>(col, out);
+    const int lane = __lane_id();
+#pragma unroll
+    for (int c = 0; c < kHalf; ++c) {
+        const int k = z0 + zh + c;
+        if (k >= G.nz) break;   // the same for the whole wave
+        bool pos[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const float f = tab[min((int)out[c][h], kW * kW + 1)];
+            const int x = x0 + t + 16 * h;
+            pos[h] = f >= 0.0f;
+            if (x < G.nx && j < G.ny) field[gidx(G, x, j, k)] = f;
+        }
+        const unsigned long long lo = __ballot(pos[0]), hi = __ballot(pos[1]);
+        if (t == 0 && j < G.ny) {
+            const int sh = lane & ~(kPairs - 1);   // this row's 16 lanes
+            sign[((size_t)k * G.ny + j) * nxw + bx] = (uint32_t)(lo >> sh & 0xFFFFu) | (uint32_t)(hi >> sh & 0xFFFFu) << 16;
+        }
+    }
+}
+
+// The passes of larger windows (or grids of too many bricks), through memory.
 // x pass: squared distance along the row to the nearest exterior point
 // within W steps (kFar if none).
-__global__ void __launch_bounds__(kSesBlock) k_ses_edt_x(SesGrid G, uint32_t np, const uint8_t* __restrict__ mark,
-                                                         int32_t* __restrict__ g) {
+__global__ void __launch_bounds__(kSesBlock) k_ses_edt_x(SesGrid G, uint32_t np, MarkGrid M, int32_t* __restrict__ g) {
     int i, j, k;
     uint32_t p;
     if (!flat_item(np, G.nx, G.ny, i, j, k, p)) return;
+    auto exterior = [&](int x) { return !(mark_nibble(M, x >> 2, j, k) >> (x & 3) & 1u); };
     int32_t best = kFar;
     for (int d = 0; d <= G.W; ++d) {
-        const bool l = i - d >= 0 && !mark[p - d];
-        const bool r = i + d < G.nx && !mark[p + d];
-        if (l || r) {
+        if ((i - d >= 0 && exterior(i - d)) || (i + d < G.nx && exterior(i + d))) {
             best = d * d;
             break;
         }
     }
     g[p] = best;
-}
-
-// The x pass through LDS (W <= kEdtMaxW): work block b takes kSesBlock
-// consecutive points of one row (x block b mod nxb of row b / nxb) and
-// stages their marks and W more on each side.
-template <int kMaxW>
-__global__ void __launch_bounds__(kSesBlock) k_ses_edt_x_lds(SesGrid G, uint32_t nxb,
-                                                             const uint8_t* __restrict__ mark,
-                                                             int32_t* __restrict__ g) {
-    __shared__ uint8_t row[kSesBlock + 2 * kMaxW];
-    const uint32_t r = blockIdx.x / nxb, xb = blockIdx.x - r * nxb;
-    const int W = G.W, x0 = (int)xb * kSesBlock;
-    const size_t base = (size_t)r * G.nx;   // row r = j + ny k starts at r nx
-    for (int t = threadIdx.x; t < kSesBlock + 2 * W; t += kSesBlock) {
-        const int x = x0 - W + t;
-        row[t] = (x >= 0 && x < G.nx) ? mark[base + x] : (uint8_t)2;   // 2: outside the grid
-    }
-    __syncthreads();
-    const int i = x0 + (int)threadIdx.x;
-    if (i >= G.nx) return;
-    int32_t best = kFar;
-    for (int d = 0; d <= W; ++d) {
-        const uint8_t l = row[threadIdx.x + W - d], rr = row[threadIdx.x + W + d];
-        if (l == 0 || rr == 0) {
-            best = d * d;
-            break;
-        }
-    }
-    g[base + i] = best;
 }
 
 // y or z pass: the least of g(p + d e) + d^2 over |d| <= W along the axis.
@@ -283,9 +419,7 @@ __global__ void __launch_bounds__(kSesBlock) k_ses_edt_yz(SesGrid G, uint32_t np
         gout[p] = best;
         return;
     }
-    const double cap = G.W * G.h;
-    const double D = best > G.W * G.W ? cap : fmin(G.h * sqrt((double)best), cap);
-    field[p] = (float)(D - G.rp);
+    field[p] = ses_field(G, best);
 }
 
 // The same passes through LDS (windows of W <= kEdtMaxW): work block b
@@ -328,101 +462,216 @@ __global__ void __launch_bounds__(kSesBlock) k_ses_edt_yz_lds(SesGrid G, uint32_
         if (!kLast) {
             gout[p] = best;
         } else {
-            const double cap = G.W * G.h;
-            const double D = best > G.W * G.W ? cap : fmin(G.h * sqrt((double)best), cap);
-            field[p] = (float)(D - G.rp);
+            field[p] = ses_field(G, best);
         }
     }
 }
 
-__device__ inline int cube_case(const SesGrid& G, const float* __restrict__ f, int i, int j, int k, float v[8]) {
-    int m = 0;
+// Sign bits (f >= 0) of a field the passes through memory wrote: one thread
+// per word of 32 points of a row.
+__global__ void __launch_bounds__(kSesBlock) k_ses_sign(SesGrid G, const float* __restrict__ f, int nxw, uint32_t nw,
+                                                        uint32_t* __restrict__ sign) {
+    const uint32_t w = blockIdx.x * (uint32_t)kSesBlock + threadIdx.x;
+    if (w >= nw) return;
+    const uint32_t row = w / (uint32_t)nxw;
+    const int x0 = (int)(w - row * (uint32_t)nxw) * 32;
+    uint32_t m = 0;
+    for (int q = 0; q < 32 && x0 + q < G.nx; ++q) m |= f[(size_t)row * G.nx + x0 + q] >= 0.0f ? 1u << q : 0u;
+    sign[w] = m;
+}
+
+// The cubes of a word of sign bits: cube q of word wx of cube row (j, k) has
+// its first corner at point (32 wx + q, j, k).  `corner[c]` holds the sign
+// bits of corner c of every cube, `active` the cubes with triangles.
+struct WordCubes {
+    uint32_t corner[8];
+    uint32_t active;
+    int i0, j, k;
+    __device__ uint32_t cube(int q) const {
+        uint32_t m = 0;
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        v[c] = f[gidx(G, i + (c & 1), j + ((c >> 1) & 1), k + ((c >> 2) & 1))];
-        m |= (v[c] >= 0.0f ? 1 : 0) << c;
+        for (int c = 0; c < 8; ++c) m |= (corner[c] >> q & 1u) << c;
+        return m;
     }
-    return m;
+};
+
+// Word w of the cube rows (nw of them), w in x-fastest order.
+__device__ inline WordCubes word_cubes(const SesGrid& G, const uint32_t* __restrict__ sign, int nxw, uint32_t w, uint32_t nw) {
+    WordCubes u;
+    u.active = 0;
+    if (w >= nw) return u;
+    const uint32_t row = w / (uint32_t)nxw;
+    const int wx = (int)(w - row * (uint32_t)nxw);
+    u.i0 = 32 * wx;
+    u.j = (int)(row % (uint32_t)(G.ny - 1));
+    u.k = (int)(row / (uint32_t)(G.ny - 1));
+    uint32_t any = 0, all = ~0u;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const size_t at = ((size_t)(u.k + (c >> 1)) * G.ny + (u.j + (c & 1))) * nxw + wx;
+        const uint32_t a = sign[at], next = wx + 1 < nxw ? sign[at + 1] : 0u;
+        u.corner[2 * c] = a;
+        u.corner[2 * c + 1] = (a >> 1) | (next << 31);
+        any |= u.corner[2 * c] | u.corner[2 * c + 1];
+        all &= u.corner[2 * c] & u.corner[2 * c + 1];
+    }
+    const int cubes = min(32, G.nx - 1 - u.i0);   // the last word may hold none
+    const uint32_t valid = cubes >= 32 ? ~0u : cubes > 0 ? (1u << cubes) - 1u : 0u;
+    u.active = any & ~all & valid;
+    return u;
 }
 
-// Triangles per cube, and per workgroup of kSesBlock cubes the list of its
-// cubes that have any: active[b * kSesBlock + s] for s < n_active[b].
-__global__ void __launch_bounds__(kSesBlock) k_ses_count(SesGrid G, uint32_t nc, const float* __restrict__ f,
-                                                         uint32_t* __restrict__ cnt, uint32_t* __restrict__ active,
-                                                         uint32_t* __restrict__ n_active) {
-    __shared__ uint32_t wave_n[kSesBlock / 64];
-    int i, j, k;
-    uint32_t q;
-    uint32_t nt = 0;
-    if (flat_item(nc, G.nx - 1, G.ny - 1, i, j, k, q)) {
-        float v[8];
-        nt = c_case_tris[cube_case(G, f, i, j, k, v)];
-        cnt[q] = nt;
-    }
-    const unsigned long long act = __ballot(nt != 0);
-    const int wave = threadIdx.x >> 6;
-    if (__lane_id() == 0) wave_n[wave] = (uint32_t)__popcll(act);
+// Triangles of each run of kSesRun words of cubes.
+__global__ void __launch_bounds__(kSesRun) k_ses_count(SesGrid G, const uint32_t* __restrict__ sign, int nxw, uint32_t nw,
+                                                       uint32_t* __restrict__ run_tris) {
+    __shared__ uint8_t tris[256];
+    __shared__ uint32_t sum;
+    const int tid = threadIdx.x;
+    for (int q = tid; q < 64; q += kSesRun) reinterpret_cast<uint32_t*>(tris)[q] = reinterpret_cast<const uint32_t*>(c_case_tris)[q];
+    if (tid == 0) sum = 0;
     __syncthreads();
-    uint32_t before = 0, all = 0;
-    for (int w = 0; w < kSesBlock / 64; ++w) {
-        before += w < wave ? wave_n[w] : 0u;
-        all += wave_n[w];
-    }
-    if (nt) active[(size_t)blockIdx.x * kSesBlock + before + (uint32_t)__popcll(act & __lanemask_lt())] = q;
-    if (threadIdx.x == 0) n_active[blockIdx.x] = all;
+    const WordCubes u = word_cubes(G, sign, nxw, blockIdx.x * (uint32_t)kSesRun + tid, nw);
+    uint32_t nt = 0;
+    for (uint32_t m = u.active; m; m &= m - 1) nt += tris[u.cube(__builtin_ctz(m))];
+    for (int o = 32; o > 0; o >>= 1) nt += (uint32_t)__shfl_xor((int)nt, o);
+    if (__lane_id() == 0 && nt) atomicAdd(&sum, nt);
+    __syncthreads();
+    if (tid == 0) run_tris[blockIdx.x] = sum;
 }
 
-// The triangles of each cube its count workgroup listed, at the cube's
-// offset (those past the capacity are dropped).
-__global__ void __launch_bounds__(kSesBlock) k_ses_emit(SesGrid G, const uint32_t* __restrict__ active,
-                                                        const uint32_t* __restrict__ n_active,
-                                                        const float* __restrict__ f, const uint32_t* __restrict__ off,
-                                                        float* __restrict__ tri, unsigned long long capacity) {
-    if (threadIdx.x >= n_active[blockIdx.x]) return;
-    const uint32_t q = active[(size_t)blockIdx.x * kSesBlock + threadIdx.x];
-    const uint32_t r = q / (uint32_t)(G.nx - 1);
-    const int i = (int)(q - r * (uint32_t)(G.nx - 1)), j = (int)(r % (uint32_t)(G.ny - 1)),
-              k = (int)(r / (uint32_t)(G.ny - 1));
-    float v[8];
-    const int m = cube_case(G, f, i, j, k, v);
-    unsigned long long t = off[q];
-    const float ox = (float)G.o[0], oy = (float)G.o[1], oz = (float)G.o[2], h = (float)G.h;
-    const uint8_t* cs = c_cases + m * kCaseBytes;
-    for (int at = 0; cs[at] != 0;) {
-        const int len = cs[at];
-        float px[8], py[8], pz[8];
-        float sx = 0.f, sy = 0.f, sz = 0.f;
-        for (int e = 0; e < len; ++e) {
-            const int ed = cs[at + 1 + e];
-            const int a = c_edge_corner[ed][0], b = c_edge_corner[ed][1];
-            const float tt = v[a] / (v[a] - v[b]);
-            const float fx = (float)((a & 1) + tt * ((b & 1) - (a & 1)));
-            const float fy = (float)(((a >> 1) & 1) + tt * (((b >> 1) & 1) - ((a >> 1) & 1)));
-            const float fz = (float)(((a >> 2) & 1) + tt * (((b >> 2) & 1) - ((a >> 2) & 1)));
-            px[e] = ox + h * ((float)i + fx);
-            py[e] = oy + h * ((float)j + fy);
-            pz[e] = oz + h * ((float)k + fz);
-            sx += px[e];
-            sy += py[e];
-            sz += pz[e];
-        }
-        auto put = [&](float ax, float ay, float az, int b, int c) {
-            if (t < capacity) {
-                float* o = tri + 9 * t;
-                o[0] = ax; o[1] = ay; o[2] = az;
-                o[3] = px[b]; o[4] = py[b]; o[5] = pz[b];
-                o[6] = px[c]; o[7] = py[c]; o[8] = pz[c];
-            }
-            ++t;
-        };
-        if (len == 3) {
-            put(px[0], py[0], pz[0], 1, 2);
-        } else {
-            const float inv = 1.0f / (float)len;
-            for (int e = 0; e < len; ++e) put(sx * inv, sy * inv, sz * inv, e, (e + 1) % len);
-        }
-        at += 1 + len;
+// The triangles of a run's cubes, from its offset on (those past the capacity
+// are dropped).  One wave per run, 64 cubes with triangles a round, packed
+// from the words: their case comes from the signs of the eight corner values
+// they need anyway, a scan of the triangle counts places them, and the
+// round's triangles are written from LDS in order: 30 us for 770k.  (A thread
+// per cube writing its own triangles, from lists of 256 cubes: 58.)
+__global__ void __launch_bounds__(kSesRun) k_ses_emit(SesGrid G, const uint32_t* __restrict__ sign, int nxw, uint32_t nw,
+                                                      const float* __restrict__ f, const uint32_t* __restrict__ run_off,
+                                                      float* __restrict__ tri, unsigned long long capacity) {
+    static_assert(kSesRun == 64, "one wave");
+    constexpr uint32_t kStage = 288;   // triangles staged at once: a round has 4 a cube or so (8 at most)
+    __shared__ float stage[kStage * 9];
+    __shared__ float corner[8][kSesRun];
+    __shared__ uint16_t list[kSesRun];   // the round's cubes: word of the run * 32 + cube of the word
+    const int lane = threadIdx.x;
+    const uint32_t w0 = blockIdx.x * (uint32_t)kSesRun;
+    uint32_t left = word_cubes(G, sign, nxw, w0 + lane, nw).active;   // this lane's cubes not yet taken
+    const uint32_t mine = (uint32_t)__popc(left);
+    uint32_t rank = mine;   // inclusive, then the rank of this lane's next cube
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t v = (uint32_t)__shfl_up((int)rank, o);
+        if (lane >= o) rank += v;
     }
+    const uint32_t cubes = (uint32_t)__shfl((int)rank, 63);
+    rank -= mine;
+    unsigned long long start = run_off[blockIdx.x];
+    for (uint32_t done = 0; done < cubes; done += kSesRun) {
+        for (; left && rank < done + kSesRun; ++rank, left &= left - 1)
+            list[rank - done] = (uint16_t)(lane * 32 + __builtin_ctz(left));
+        __syncthreads();
+        const bool have = done + lane < cubes;
+        int i = 0, j = 0, k = 0;
+        uint32_t m = 0;
+        if (have) {
+            const uint32_t w = w0 + list[lane] / 32u;
+            const uint32_t row = w / (uint32_t)nxw;
+            i = 32 * (int)(w - row * (uint32_t)nxw) + (int)(list[lane] & 31u);
+            j = (int)(row % (uint32_t)(G.ny - 1));
+            k = (int)(row / (uint32_t)(G.ny - 1));
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                const float v = f[gidx(G, i + (c & 1), j + ((c >> 1) & 1), k + ((c >> 2) & 1))];
+                corner[c][lane] = v;
+                m |= (v >= 0.0f ? 1u : 0u) << c;
+            }
+        }
+        const uint32_t nt = have ? c_case_tris[m] : 0u;
+        uint32_t at = nt;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t v = (uint32_t)__shfl_up((int)at, o);
+            if (lane >= o) at += v;
+        }
+        const uint32_t n_tris = (uint32_t)__shfl((int)at, 63);
+        // as many cubes at once as the staging holds (the usual round: all)
+        for (uint32_t from = 0; from < n_tris;) {
+            const bool now = nt && at - nt >= from && at - from <= kStage;
+            const uint32_t to = (uint32_t)__shfl((int)at, 63 - __clzll((long long)__ballot(now)));
+            if (now) {
+                const float ox = (float)G.o[0], oy = (float)G.o[1], oz = (float)G.o[2], h = (float)G.h;
+                float* t = stage + 9 * (at - nt - from);
+                unsigned long long edges = c_cases[m];
+                for (uint32_t lens = (uint32_t)(edges >> 48); lens; lens >>= 4) {
+                    // vertex e of a fan is the second vertex of its triangle e and
+                    // the third of triangle e - 1; the mean is the first of each
+                    const int len = (int)(lens & 15u);
+                    float sx = 0.f, sy = 0.f, sz = 0.f;
+                    for (int e = 0; e < len; ++e) {
+                        // edge ed: the (ed & 3)-th along axis ed >> 2, from corner a
+                        const int ed = (int)edges & 15, axis = ed >> 2, r = ed & 3;
+                        edges >>= 4;
+                        const int a = axis == 0 ? 2 * r : axis == 1 ? (r & 1) | (r & 2) << 1 : r;
+                        const float va = corner[a][lane], vb = corner[a + (1 << axis)][lane];
+                        const float tt = va / (va - vb);
+                        const float fx = axis == 0 ? tt : (float)(a & 1);
+                        const float fy = axis == 1 ? tt : (float)((a >> 1) & 1);
+                        const float fz = axis == 2 ? tt : (float)((a >> 2) & 1);
+                        const float px = ox + h * ((float)i + fx);
+                        const float py = oy + h * ((float)j + fy);
+                        const float pz = oz + h * ((float)k + fz);
+                        auto put = [&](float* o) {
+                            o[0] = px;
+                            o[1] = py;
+                            o[2] = pz;
+                        };
+                        if (len == 3) {
+                            put(t + 3 * e);
+                        } else {
+                            put(t + 9 * e + 3);
+                            put(t + 9 * (e ? e - 1 : len - 1) + 6);
+                        }
+                        sx += px;
+                        sy += py;
+                        sz += pz;
+                    }
+                    if (len > 3) {
+                        const float inv = 1.0f / (float)len;
+                        for (int e = 0; e < len; ++e) {
+                            t[9 * e] = sx * inv;
+                            t[9 * e + 1] = sy * inv;
+                            t[9 * e + 2] = sz * inv;
+                        }
+                    }
+                    t += 9 * (len == 3 ? 1 : len);
+                }
+            }
+            __syncthreads();
+            const uint32_t room = start < capacity ? (uint32_t)min((unsigned long long)(to - from), capacity - start) : 0u;
+            for (uint32_t q = (uint32_t)lane; q < 9u * room; q += kSesRun) tri[9 * start + q] = stage[q];
+            start += to - from;
+            from = to;
+            __syncthreads();   // the staging, the list and the corners are rewritten next
+        }
+    }
+}
+
+template <int kW>
+hipError_t launch_edt(int W, unsigned blocks, const SesGrid& G, const MarkGrid& M, uint32_t nbx, uint32_t nby, float* field,
+                      uint32_t* sign, int nxw, hipStream_t stream) {
+    if constexpr (kW > kMaxFusedW) return hipErrorInvalidValue;
+    else
+        return W == kW ? dispatch(k_ses_edt<kW>, blocks, kEdtBlock, 0, stream, G, M, nbx, nby, field, sign, nxw)
+                       : launch_edt<kW + 1>(W, blocks, G, M, nbx, nby, field, sign, nxw, stream);
+}
+
+int ses_window(float probe, float spacing) { return (int)ceil((double)probe / (double)spacing) + 2; }
+uint64_t ses_bricks(const int dims[3]) {
+    return ((uint64_t)dims[0] + kBx - 1) / kBx * (((uint64_t)dims[1] + kBy - 1) / kBy) * (((uint64_t)dims[2] + kBz - 1) / kBz);
+}
+// Small windows (and bricks that fit one launch) take the passes in LDS.
+bool ses_fused(float probe, float spacing, const int dims[3]) {
+    return ses_window(probe, spacing) <= kMaxFusedW && ses_bricks(dims) * kEdtBlock < (1ull << 31);
 }
 }  // namespace
 
@@ -441,62 +690,63 @@ hipError_t ses_run(const float* pos, const float* rad, uint64_t n, float probe, 
     G.ny = dims[1];
     G.nz = dims[2];
     G.rp = (double)probe;
-    G.W = (int)ceil(G.rp / G.h) + 2;
+    G.W = ses_window(probe, spacing);
     const size_t np = (size_t)G.nx * G.ny * G.nz;
-    const size_t nc = (size_t)(G.nx - 1) * (G.ny - 1) * (G.nz - 1);
-    if ((e = launch_zero(reinterpret_cast<uint32_t*>(s.mark), (np + 3) / 4, stream)) != hipSuccess) return e;
-    if (n && (e = dispatch(k_ses_mark, (unsigned)n, kSesMarkBlock, 0, stream, pos, rad, (uint32_t)n, G, s.mark)))
-        return e;
-    // rows of points along x (y-z rows), then rows of cubes
-    const unsigned gp = (unsigned)((np + kSesBlock - 1) / kSesBlock);
-    const uint64_t nxr = (uint64_t)(G.nx + kSesBlock - 1) / kSesBlock, gx = nxr * (uint64_t)G.ny * (uint64_t)G.nz;
-    if (G.W <= kEdtMaxW && gx * kSesBlock < (1ull << 31)) {
-        if ((e = dispatch(k_ses_edt_x_lds<kEdtMaxW>, (uint32_t)gx, kSesBlock, 0, stream, G, (uint32_t)nxr,
-                          (const uint8_t*)s.mark, s.ga)))
-            return e;
-    } else if ((e = dispatch(k_ses_edt_x, gp, kSesBlock, 0, stream, G, (uint32_t)np, (const uint8_t*)s.mark, s.ga))) {
-        return e;
-    }
-    const uint64_t nxb = (uint64_t)(G.nx + kEdtX - 1) / kEdtX;
-    const uint64_t gy = nxb * (uint64_t)((G.ny + kEdtRows - 1) / kEdtRows) * (uint64_t)G.nz;
-    const uint64_t gz = nxb * (uint64_t)((G.nz + kEdtRows - 1) / kEdtRows) * (uint64_t)G.ny;
-    if (G.W <= kEdtMaxW && gy * kSesBlock < (1ull << 31) && gz * kSesBlock < (1ull << 31)) {
-        if ((e = dispatch(k_ses_edt_yz_lds<false>, (uint32_t)gy, kSesBlock, 0, stream, G, (uint32_t)nxb,
-                          (uint32_t)((G.ny + kEdtRows - 1) / kEdtRows), (const int32_t*)s.ga, s.gb, (float*)nullptr)))
-            return e;
-        if ((e = dispatch(k_ses_edt_yz_lds<true>, (uint32_t)gz, kSesBlock, 0, stream, G, (uint32_t)nxb,
-                          (uint32_t)((G.nz + kEdtRows - 1) / kEdtRows), (const int32_t*)s.gb, s.ga, field)))
-            return e;
+    MarkGrid M;
+    M.bits = s.mark;
+    M.nx = mark_cells(G.nx);
+    M.ny = mark_cells(G.ny);
+    const size_t mark_words = 2 * (size_t)M.nx * M.ny * mark_cells(G.nz);
+    if ((e = launch_zero(reinterpret_cast<uint32_t*>(s.mark), mark_words, stream)) != hipSuccess) return e;
+    if (n && (e = dispatch(k_ses_mark, (unsigned)n, kSesMarkBlock, 0, stream, pos, rad, (uint32_t)n, G, M))) return e;
+    const int nxw = (G.nx + 31) / 32;
+    const uint32_t sign_words = (uint32_t)((size_t)nxw * G.ny * G.nz);
+    if (ses_fused(probe, spacing, dims)) {
+        const uint32_t nbx = (uint32_t)nxw, nby = (uint32_t)((G.ny + kBy - 1) / kBy);
+        static_assert(kBx == 32, "a brick row is a word of sign bits");
+        if ((e = launch_edt<2>(G.W, (unsigned)ses_bricks(dims), G, M, nbx, nby, field, s.sign, nxw, stream))) return e;
     } else {
-        if ((e = dispatch(k_ses_edt_yz<false>, gp, kSesBlock, 0, stream, G, (uint32_t)np, (const int32_t*)s.ga, s.gb,
-                          (float*)nullptr)))
-            return e;
-        if ((e = dispatch(k_ses_edt_yz<true>, gp, kSesBlock, 0, stream, G, (uint32_t)np, (const int32_t*)s.gb, s.ga,
-                          field)))
+        const unsigned gp = (unsigned)((np + kSesBlock - 1) / kSesBlock);
+        if ((e = dispatch(k_ses_edt_x, gp, kSesBlock, 0, stream, G, (uint32_t)np, M, s.ga))) return e;
+        const uint64_t nxb = (uint64_t)(G.nx + kEdtX - 1) / kEdtX;
+        const uint64_t gy = nxb * (uint64_t)((G.ny + kEdtRows - 1) / kEdtRows) * (uint64_t)G.nz;
+        const uint64_t gz = nxb * (uint64_t)((G.nz + kEdtRows - 1) / kEdtRows) * (uint64_t)G.ny;
+        if (G.W <= kEdtMaxW && gy * kSesBlock < (1ull << 31) && gz * kSesBlock < (1ull << 31)) {
+            if ((e = dispatch(k_ses_edt_yz_lds<false>, (uint32_t)gy, kSesBlock, 0, stream, G, (uint32_t)nxb,
+                              (uint32_t)((G.ny + kEdtRows - 1) / kEdtRows), (const int32_t*)s.ga, s.gb, (float*)nullptr)))
+                return e;
+            if ((e = dispatch(k_ses_edt_yz_lds<true>, (uint32_t)gz, kSesBlock, 0, stream, G, (uint32_t)nxb,
+                              (uint32_t)((G.nz + kEdtRows - 1) / kEdtRows), (const int32_t*)s.gb, s.ga, field)))
+                return e;
+        } else {
+            if ((e = dispatch(k_ses_edt_yz<false>, gp, kSesBlock, 0, stream, G, (uint32_t)np, (const int32_t*)s.ga, s.gb,
+                              (float*)nullptr)))
+                return e;
+            if ((e = dispatch(k_ses_edt_yz<true>, gp, kSesBlock, 0, stream, G, (uint32_t)np, (const int32_t*)s.gb, s.ga,
+                              field)))
+                return e;
+        }
+        if ((e = dispatch(k_ses_sign, (sign_words + kSesBlock - 1) / kSesBlock, kSesBlock, 0, stream, G, (const float*)field,
+                          nxw, sign_words, s.sign)))
             return e;
     }
-    // the distance buffers are free once the z pass has run: the y pass's
-    // holds the per-workgroup lists of cubes with triangles, the other one
-    // their lengths
-    uint32_t* const active = reinterpret_cast<uint32_t*>(s.gb);
-    uint32_t* const n_active = reinterpret_cast<uint32_t*>(s.ga);
-    const unsigned gc = (unsigned)((nc + kSesBlock - 1) / kSesBlock);
-    if ((e = dispatch(k_ses_count, gc, kSesBlock, 0, stream, G, (uint32_t)nc, (const float*)field, s.cnt, active,
-                      n_active)))
-        return e;
-    if ((e = exclusive_scan(s.cnt, nc, s.bsum, n_tri, stream))) return e;
-    return dispatch(k_ses_emit, gc, kSesBlock, 0, stream, G, (const uint32_t*)active, (const uint32_t*)n_active,
-                    (const float*)field, (const uint32_t*)s.cnt, tri, (unsigned long long)capacity);
+    const uint32_t nw = (uint32_t)((size_t)nxw * (G.ny - 1) * (G.nz - 1));
+    const uint32_t runs = (nw + kSesRun - 1) / kSesRun;
+    if ((e = dispatch(k_ses_count, runs, kSesRun, 0, stream, G, (const uint32_t*)s.sign, nxw, nw, s.cnt))) return e;
+    if ((e = exclusive_scan(s.cnt, runs, s.bsum, n_tri, stream))) return e;
+    return dispatch(k_ses_emit, runs, kSesRun, 0, stream, G, (const uint32_t*)s.sign, nxw, nw, (const float*)field,
+                    (const uint32_t*)s.cnt, tri, (unsigned long long)capacity);
 }
 
-size_t ses_scratch_words(const int dims[3], size_t* mark_words, size_t* g_words, size_t* cnt_words, size_t* bsum_words) {
-    const size_t np = (size_t)dims[0] * dims[1] * dims[2];
-    const size_t nc = (size_t)(dims[0] - 1) * (dims[1] - 1) * (dims[2] - 1);
-    *mark_words = (np + 3) / 4;
-    *g_words = np;
-    *cnt_words = nc;
-    *bsum_words = scan_scratch_words(nc);
-    return *mark_words + 2 * *g_words + *cnt_words + *bsum_words;
+SesWords ses_scratch_words(float probe, float spacing, const int dims[3]) {
+    const size_t np = (size_t)dims[0] * dims[1] * dims[2], nxw = ((size_t)dims[0] + 31) / 32;
+    SesWords w;
+    w.mark = 2 * (size_t)mark_cells(dims[0]) * mark_cells(dims[1]) * mark_cells(dims[2]);
+    w.g = ses_fused(probe, spacing, dims) ? 0 : np;
+    w.sign = nxw * dims[1] * dims[2];
+    w.cnt = (nxw * (dims[1] - 1) * (dims[2] - 1) + kSesRun - 1) / kSesRun;
+    w.bsum = scan_scratch_words(w.cnt);
+    return w;
 }
 
 }  // namespace vtx

@@ -663,18 +663,21 @@ hipError_t launch_shade(const JobList& js, uint32_t grid, bool noise, hipStream_
 size_t scan_scratch_words(size_t n);
 hipError_t exclusive_scan(uint32_t* v, size_t n, uint32_t* bsum, unsigned long long* total, hipStream_t stream);
 
-// Solvent excluded surface (ses.hip): scratch of one call, sized by
-// ses_scratch_words, and the passes (queued on `stream`; field may not be
-// null).
+// Solvent excluded surface (ses.hip): scratch of one call, sized in words by
+// ses_scratch_words (`g` for each of ga and gb), and the passes (queued on
+// `stream`; field may not be null).
 struct SesScratch {
-    uint8_t* mark;          // grid points: 1 inside the solvent-accessible region
-    int32_t* ga;            // squared distances, x and z passes
-    int32_t* gb;            // squared distances, y pass
-    uint32_t* cnt;          // triangles per cube, then their offsets
-    uint32_t* bsum;         // block sums of the scan
+    unsigned long long* mark;   // grid points, a bit each: 1 inside the solvent-accessible region
+    int32_t* ga;                // squared distances, x and z passes (large windows only)
+    int32_t* gb;                // squared distances, y pass (large windows only)
+    uint32_t* sign;             // grid points, a bit each, 32 along x to a word: 1 where the field is >= 0
+    uint32_t* cnt;              // triangles per run of cubes, then their offsets
+    uint32_t* bsum;             // block sums of the scan
 };
-size_t ses_scratch_words(const int dims[3], size_t* mark_words, size_t* g_words, size_t* cnt_words,
-                         size_t* bsum_words);
+struct SesWords {
+    size_t mark, g, sign, cnt, bsum;
+};
+SesWords ses_scratch_words(float probe, float spacing, const int dims[3]);
 hipError_t ses_run(const float* pos, const float* rad, uint64_t n, float probe, const float origin[3], float spacing,
                    const int dims[3], float* field, float* tri, uint64_t capacity, unsigned long long* n_tri,
                    SesScratch& s, hipStream_t stream);

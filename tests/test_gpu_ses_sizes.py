@@ -1,0 +1,72 @@
+"""The surface's distance windows, grid remainders and runs of cubes against
+the SES oracle (needs an MI355X): windows on both sides of the one a brick's
+LDS holds, dimensions around the bricks', words' and cells' sizes, grids
+smaller than a window, cuts through atoms, and little or no capacity."""
+import numpy as np
+import pytest
+
+from oracle import oses
+from tests.test_gpu_ses import run_ses
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def vtx():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a visible GPU"
+    from paper_2501_12750_amd import vtx as v
+    return v
+
+
+def atoms(seed, n, extent):
+    rng = np.random.default_rng(seed)
+    return (rng.uniform(0.0, 1.0, size=(n, 3)) * extent).astype(np.float32), rng.uniform(1.1, 1.9, size=n).astype(np.float32)
+
+
+def check(vtx, pos, rad, probe, origin, h, dims, capacity=None):
+    origin = np.asarray(origin, np.float32)
+    h = np.float32(h)
+    ref = oses.ses_field(pos, rad, probe, origin, h, dims)
+    mc = oses.marching_cubes(ref["f"], origin, h)["vertices"]
+    f, tri, n = run_ses(vtx, pos, rad, probe, origin, h, dims, capacity)
+    print("grid", dims, "h", float(h), "probe", probe, "triangles", n, flush=True)
+    assert np.array_equal(f, ref["f"])
+    assert n == mc.shape[0]
+    m = n if capacity is None else min(n, capacity)
+    assert tri.shape[0] == m
+    # the oracle's vertices in FP64 against FP32 arithmetic of a few roundings
+    assert np.all(np.abs(tri.astype(np.float64) - mc[:m]) <= 1e-5 * (np.abs(mc[:m]) + float(h)))
+    return n
+
+
+@pytest.mark.parametrize("window", [2, 3, 4, 5, 8, 11, 12, 13, 32, 33])
+def test_every_kind_of_window(vtx, window):
+    h = 0.3
+    probe = 0.0 if window == 2 else float(np.float32(h)) * (window - 2.5)
+    pos, rad = atoms(window, 9, np.array([5.0, 6.0, 4.0]))
+    check(vtx, pos, rad, probe, (-2.3, -2.1, -2.2), h, (35, 37, 31))
+
+
+@pytest.mark.parametrize("dims", [(2, 2, 2), (3, 70, 5), (31, 15, 17), (32, 16, 16), (33, 17, 16), (34, 18, 33), (64, 5, 4),
+                                  (65, 33, 2), (129, 3, 20), (97, 48, 50)])
+def test_grid_remainders(vtx, dims):
+    h = 0.45
+    pos, rad = atoms(sum(dims), 40, np.array(dims) * h)   # atoms past the border too: it cuts through them
+    assert check(vtx, pos, rad, 1.4, (0.1, -0.2, 0.05), h, dims) >= 0
+
+
+def test_capacity_ends_inside_a_run(vtx):
+    pos, rad = atoms(5, 30, np.array([9.0, 8.0, 7.0]))
+    n = check(vtx, pos, rad, 1.4, (-3.0, -3.0, -3.0), 0.4, (37, 35, 33))
+    assert n > 2000
+    for capacity in (1, 511, 513, n - 1):
+        check(vtx, pos, rad, 1.4, (-3.0, -3.0, -3.0), 0.4, (37, 35, 33), capacity)
+
+
+def test_no_atoms(vtx):
+    import torch
+    dims = (40, 20, 18)
+    f, tri, n = run_ses(vtx, np.zeros((0, 3), np.float32), np.zeros(0, np.float32), 1.4, (0.0, 0.0, 0.0), 0.5, dims, 16)
+    assert n == 0 and np.all(f < 0.0)
+    torch.cuda.synchronize()
