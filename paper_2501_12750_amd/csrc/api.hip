@@ -910,12 +910,16 @@ int render_locked(std::vector<JobDesc>& d, bool bin, bool shade, hipStream_t str
     if (n == 0) return VTX_OK;
     // one resolve launch per tile size: keep the jobs of a size together
     if (n > 1) std::stable_sort(d.begin(), d.end(), [](const JobDesc& a, const JobDesc& b) { return a.F.tile < b.F.tile; });
-    bool timing = false, scene = false, count = false;
+    bool timing = false, scene = false, count = false, noise = false;
+    uint64_t pixels = 0;
     for (const JobDesc& j : d) {
+        noise |= j.K.noise != 0 && j.K.count > 0;
+        pixels += (uint64_t)j.F.W * j.F.H;
         timing |= (j.F.flags & VTX_FLAG_TIMING) != 0;
         count |= (j.F.flags & (VTX_FLAG_STATS | VTX_FLAG_COUNT)) != 0;
         scene |= j.scene;
     }
+    const vtx::ShadeForm form = vtx::shade_form(noise, pixels);
     TimingSlot* tslot = nullptr;
     if (timing && !capture && (rc = timing_slot(ws, &tslot))) return rc;
     // timed frames: each kernel's own start and stop events, filed under the
@@ -979,7 +983,7 @@ int render_locked(std::vector<JobDesc>& d, bool bin, bool shade, hipStream_t str
             J.rgba = b->ss_rgba;
         }
         starts[2 * (n + 1) + i] = g_shade;
-        g_shade += vtx::shade_blocks(s.F);
+        g_shade += vtx::shade_blocks(s.F, form);
         if (!bin) continue;
         const int T = s.F.tiles_x * s.F.tiles_y;
         max_tiles = std::max(max_tiles, T);
@@ -1193,10 +1197,8 @@ int render_locked(std::vector<JobDesc>& d, bool bin, bool shade, hipStream_t str
     }
     VTX_HIP(mark(5));
     if (shade) {
-        bool noise = false;
-        for (size_t i = 0; i < n; ++i) noise |= d[i].K.noise != 0 && d[i].K.count > 0;
-        if (n == 1) VTX_HIP(vtx::launch_shade(one(g_shade), g_shade, noise, stream));
-        else VTX_HIP(vtx::launch_shade(list_of(0, n, 2 * (n + 1)), g_shade, noise, stream));
+        if (n == 1) VTX_HIP(vtx::launch_shade(one(g_shade), g_shade, form, stream));
+        else VTX_HIP(vtx::launch_shade(list_of(0, n, 2 * (n + 1)), g_shade, form, stream));
         for (size_t i = 0; i < n; ++i)
             if (d[i].ss > 1)
                 VTX_HIP(vtx::launch_downsample(jobs[i].depth, jobs[i].id, jobs[i].rgba, d[i].F.W / d[i].ss,
@@ -1428,8 +1430,9 @@ int vtx_render_static(const float* positions, const float* radii, const uint32_t
     VTX_HIP(vtx::launch_scatter(js, vtx::kPhaseAll, groups, T, st));
     js.blocks = (uint32_t)T;
     VTX_HIP(vtx::launch_resolve(js, F.tile, vtx::kPhaseAll, (uint32_t)T, count, ovf, ovf_n, st));
-    js.blocks = vtx::shade_blocks(F);
-    VTX_HIP(vtx::launch_shade(js, js.blocks, js.K.noise != 0 && js.K.count > 0, st));
+    const vtx::ShadeForm form = vtx::shade_form(js.K.noise != 0 && js.K.count > 0, (uint64_t)F.W * F.H);
+    js.blocks = vtx::shade_blocks(F, form);
+    VTX_HIP(vtx::launch_shade(js, js.blocks, form, st));
     return VTX_OK;
 }
 

@@ -52,10 +52,11 @@ struct Surface {
     bool hit;
 };
 
-__device__ inline Surface surface_at(const Job& J, const Frame& F, int x, int y, uint32_t pid, float z) {
-    const global_t<const float>* __restrict__ const pos = to_global(J.pos);
-    const global_t<const uint32_t>* __restrict__ const col = to_global(J.col);
-    const global_t<const uint32_t>* __restrict__ const bonds = to_global(J.bonds);
+__device__ inline Surface surface_at(JobRef R, int x, int y, uint32_t pid, float z) {
+    const Frame F = R.frame();
+    const global_t<const float>* __restrict__ const pos = to_global(R.pos());
+    const global_t<const uint32_t>* __restrict__ const col = to_global(R.col());
+    const global_t<const uint32_t>* __restrict__ const bonds = to_global(R.bonds());
     Surface s;
     const float ndx = fmaf((float)x + 0.5f, F.inv_w2, -1.0f);
     const float ndy = fmaf(-((float)y + 0.5f), F.inv_h2, 1.0f);
@@ -141,8 +142,8 @@ __device__ inline Surface surface_at(const Job& J, const Frame& F, int x, int y,
 // cosine and sine (rc, rs)), each compared with the depth of the pixel it
 // projects to (kPersp: perspective projection, else orthographic).
 template <bool kTurn, bool kPersp>
-__device__ inline float ssao_at_proj(const Frame& F, const SampleKernel& K, const global_t<const float>* depth, int x, int y,
-                                const Surface& s, float rc, float rs) {
+__device__ inline float ssao_at_proj(const Frame& F, SampleRef K, const global_t<const float>* depth, int x, int y,
+                                     const Surface& s, float rc, float rs) {
     const float nx = s.nx, ny = s.ny, nz = s.nz, Px = s.Px, Py = s.Py, Pz = s.Pz;
     // orthonormal basis from the normal (Duff et al., JCGT 2017, branchless
     // form), turned about the normal: T' = rc T + rs B, B' = rc B - rs T
@@ -160,17 +161,22 @@ __device__ inline float ssao_at_proj(const Frame& F, const SampleKernel& K, cons
     // Samples are taken kBatch at a time: every address first, then the
     // loads, then the tests in sample order, so the loads of a batch are
     // in flight together.  Branch-free: an invalid sample (past the count, behind the near
-    // plane, off the image) reads the pixel's own depth and is masked out
-    // (sz = -inf); entries of h past the count exist (zero).  Byte offsets
+    // plane, off the image) reads the pixel's own depth and is masked out;
+    // entries of h past the count exist (zero).  Byte offsets
     // into the depth image fit 32 bits (at most 4^2 x 7680 x 4320 pixels).
     const float hw = 0.5f * (float)F.W, hh = 0.5f * (float)F.H;
     const uint32_t own = (uint32_t)(y * F.W + x) << 2;
-    for (int k0 = 0; k0 < K.count; k0 += kBatch) {
+    const int count = K.count();
+    const float radius = K.radius(), bias = K.bias();
+    for (int k0 = 0; k0 < count; k0 += kBatch) {
         float zq[kBatch], sz[kBatch];
+        bool oks[kBatch];
+        float4 h4[4];
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
             const int k = k0 + u;
-            const float4 h = K.h[k];   // offset in the (T, B, n) frame, scaled
+            if ((u & 3) == 0) K.h4(k, h4);
+            const float4 h = h4[u & 3];   // offset in the (T, B, n) frame, scaled
             const float Sx = fmaf(h.x, Tx, fmaf(h.y, Bx, fmaf(h.z, nx, Px)));
             const float Sy = fmaf(h.x, Ty, fmaf(h.y, By, fmaf(h.z, ny, Py)));
             const float Sz = fmaf(h.x, Tz, fmaf(h.y, Bz, fmaf(h.z, nz, Pz)));
@@ -182,24 +188,26 @@ __device__ inline float ssao_at_proj(const Frame& F, const SampleKernel& K, cons
             // floors' unsigned ranges (the floors are then the pixel's indices)
             const uint32_t ix = (uint32_t)floor_to_int(spx), iy = (uint32_t)floor_to_int(spy);
             // & rather than &&: all tests evaluated, no branches per sample
-            const bool ok = (k < K.count) & (Sz > F.znear) & (ix < (uint32_t)F.W) & (iy < (uint32_t)F.H);
+            const bool ok = (k < count) & (Sz > F.znear) & (ix < (uint32_t)F.W) & (iy < (uint32_t)F.H);
             // a 24-bit multiply (full rate): the pixel indices are below 2^16
             // where ok, and the offset is discarded elsewhere
             const uint32_t off = ok ? (__umul24(iy, (uint32_t)F.W) + ix) << 2 : own;
             zq[u] = *reinterpret_cast<const global_t<const float>*>(reinterpret_cast<const global_t<const char>*>(depth) + off);
-            sz[u] = ok ? Sz : -INFINITY;
+            sz[u] = Sz;
+            oks[u] = ok;
         }
 #pragma unroll
         for (int u = 0; u < kBatch; ++u)
-            if (zq[u] <= sz[u] - K.bias) occ += smooth01(K.radius * __builtin_amdgcn_rcpf(fabsf(Pz - zq[u])));
+            if (oks[u] & (zq[u] <= sz[u] - bias)) occ += smooth01(radius * __builtin_amdgcn_rcpf(fabsf(Pz - zq[u])));
     }
-    return 1.0f - occ / (float)K.count;
+    return 1.0f - occ / (float)count;
 }
 
 // The projection is the frame's (one branch per pixel, none per sample).
 template <bool kTurn>
-__device__ inline float ssao_at(const Frame& F, const SampleKernel& K, const global_t<const float>* depth, int x, int y,
+__device__ inline float ssao_at(JobRef R, SampleRef K, const global_t<const float>* depth, int x, int y,
                                 const Surface& s, float rc, float rs) {
+    const Frame F = R.frame();
     return F.proj == 0 ? ssao_at_proj<kTurn, true>(F, K, depth, x, y, s, rc, rs)
                        : ssao_at_proj<kTurn, false>(F, K, depth, x, y, s, rc, rs);
 }
@@ -211,124 +219,146 @@ __device__ inline int noise_rank(int x, int y) {
     return (int)((kRows[y & 3] >> (4 * (x & 3))) & 15u);
 }
 
-// Work block t of a job is that job's 16x16 tile t.  kNoise: the
-// instantiation that can take the noise form (launched when a job asks for
-// it; the plain one carries none of its code).
-template <class JS, bool kNoise>
+// Work block t of a job is that job's kTW x 16 tile t, taken by its threads
+// 16x16 pixels at a time, the next ones' depth and id loaded meanwhile.
+// kNoise: the instantiation that can take the noise form (launched when a job
+// asks for it; the plain one carries none of its code).
+template <class JS, bool kNoise, int kTW>
 __global__ void __launch_bounds__(kBlock) k_shade(JS js) {
+    static_assert(kTW % kTile == 0 && kBlock == kTile * kTile, "whole 16x16 blocks");
     // noise form: the raw AO of the tile and of the 2 pixels left and above
     // and 1 right and below it that the 4x4 blur reads (-1: not a hit)
-    constexpr int kHalo = kTile + 3;
-    __shared__ float raw[kNoise ? kHalo * kHalo : 1];
+    constexpr int kHaloW = kTW + 3, kHaloH = kTile + 3;
+    __shared__ float raw[kNoise ? kHaloW * kHaloH : 1];
     uint32_t tu;
-    const int ji = js.find((uint32_t)xcd_contiguous(blockIdx.x, gridDim.x), tu);
+    const int ji = js.find((uint32_t)xcd_runs(blockIdx.x), tu);
     if (ji < 0) return;
-    const Job& J = js.job(ji);
-    const Frame F = J.F;
-    const SampleKernel& K = js.samples(ji);
-    const global_t<const float>* __restrict__ const depth = to_global(J.depth);
-    const global_t<const uint32_t>* __restrict__ const ids = to_global(J.id);
-    global_t<uint32_t>* __restrict__ const rgba = to_global(J.rgba);
-    global_t<float>* __restrict__ const normal_out = to_global(J.normal);
-    global_t<uint32_t>* __restrict__ const albedo_out = to_global(J.albedo);
-    global_t<float>* __restrict__ const ao_out = to_global(J.ao);
-    const int tiles_x = (F.W + kTile - 1) / kTile;
+    const JobRef R = job_ref(js, ji);
+    const SampleRef K = sample_ref(js, ji);
+    const int W = R.frame().W, H = R.frame().H;
+    const global_t<const float>* __restrict__ const depth = to_global((const float*)R.depth());
+    const global_t<const uint32_t>* __restrict__ const ids = to_global((const uint32_t*)R.id());
+    const int tiles_x = (W + kTW - 1) / kTW;
     const int t = (int)tu;
     const int tid = threadIdx.x;
-    const int tx0 = (t % tiles_x) * kTile, ty0 = (t / tiles_x) * kTile;
-    const int x = tx0 + (tid & (kTile - 1)), y = ty0 + (tid >> 4);
-    const bool noise = kNoise && K.noise && K.count > 0;   // the same for the whole workgroup (one job)
+    const int tx0 = (t % tiles_x) * kTW, ty0 = (t / tiles_x) * kTile;
+    const bool noise = kNoise && K.noise() && K.count() > 0;   // the same for the whole workgroup (one job)
     if (noise) {
-        for (int i = tid; i < kHalo * kHalo; i += kBlock) {
-            const int qx = tx0 - 2 + i % kHalo, qy = ty0 - 2 + i / kHalo;
+        for (int i = tid; i < kHaloW * kHaloH; i += kBlock) {
+            const int qx = tx0 - 2 + i % kHaloW, qy = ty0 - 2 + i / kHaloW;
             float v = -1.0f;
-            if (qx >= 0 && qx < F.W && qy >= 0 && qy < F.H) {
-                const size_t q = (size_t)qy * F.W + qx;
-                const Surface sq = surface_at(J, F, qx, qy, ids[q], depth[q]);
+            if (qx >= 0 && qx < W && qy >= 0 && qy < H) {
+                const size_t q = (size_t)qy * W + qx;
+                const Surface sq = surface_at(R.again(), qx, qy, ids[q], depth[q]);
                 if (sq.hit) {
-                    const float2 r = K.rot[noise_rank(qx, qy)];
-                    v = ssao_at<true>(F, K, depth, qx, qy, sq, r.x, r.y);
+                    const float2 r = K.rot(noise_rank(qx, qy));
+                    v = ssao_at<true>(R.again(), K.again(), depth, qx, qy, sq, r.x, r.y);
                 }
             }
             raw[i] = v;
         }
         __syncthreads();
     }
-    if (x >= F.W || y >= F.H) return;
-    const size_t p = (size_t)y * F.W + x;
-    const float z = depth[p];
-    const Surface sf = surface_at(J, F, x, y, ids[p], z);
-    const bool hit = sf.hit;
-    const float nx = sf.nx, ny = sf.ny, nz = sf.nz, Vx = sf.Vx, Vy = sf.Vy, Vz = sf.Vz;
-    const uint32_t alb = sf.alb;
+    constexpr int kBlocks = kTW / kTile;
+    const int y = ty0 + (tid >> 4);
+    auto at_x = [&](int s) { return tx0 + s * kTile + (tid & (kTile - 1)); };
+    float z_next = 0.0f;
+    uint32_t id_next = 0u;
+    auto fetch = [&](int s) {
+        const int x = at_x(s);
+        if (x < W && y < H) {
+            const size_t p = (size_t)y * W + x;
+            z_next = depth[p];
+            id_next = ids[p];
+        }
+    };
+    fetch(0);
+#pragma unroll 1
+    for (int s = 0; s < kBlocks; ++s) {
+        const int x = at_x(s);
+        const float z = z_next;
+        const uint32_t pid = id_next;
+        if (s + 1 < kBlocks) fetch(s + 1);
+        if (x >= W || y >= H) continue;
+        const size_t p = (size_t)y * W + x;
+        const Surface sf = surface_at(R.again(), x, y, pid, z);
+        const bool hit = sf.hit;
+        const float nx = sf.nx, ny = sf.ny, nz = sf.nz, Vx = sf.Vx, Vy = sf.Vy, Vz = sf.Vz;
+        const uint32_t alb = sf.alb;
 
-    float ao = 1.0f;
-    if (hit && noise) {
-        // the mean of the raw AO over the hit pixels of the 4x4 block at
-        // offsets -2..1 (the halo holds the ones outside the tile)
-        const int lx = x - tx0 + 2, ly = y - ty0 + 2;
-        float sum = 0.0f;
-        int cnt = 0;
-#pragma unroll
-        for (int dy = -2; dy <= 1; ++dy)
-#pragma unroll
-            for (int dx = -2; dx <= 1; ++dx) {
-                const float v = raw[(ly + dy) * kHalo + (lx + dx)];
-                if (v >= 0.0f) {
-                    sum += v;
-                    ++cnt;
+        float ao = 1.0f;
+        if (hit && noise) {
+            // the mean of the raw AO over the hit pixels of the 4x4 block at
+            // offsets -2..1 (the halo holds the ones outside the tile)
+            const int lx = x - tx0 + 2, ly = y - ty0 + 2;
+            float sum = 0.0f;
+            int cnt = 0;
+    #pragma unroll
+            for (int dy = -2; dy <= 1; ++dy)
+    #pragma unroll
+                for (int dx = -2; dx <= 1; ++dx) {
+                    const float v = raw[(ly + dy) * kHaloW + (lx + dx)];
+                    if (v >= 0.0f) {
+                        sum += v;
+                        ++cnt;
+                    }
+                }
+            ao = sum / (float)cnt;
+        } else if (hit && K.count() > 0) {
+            ao = ssao_at<false>(R.again(), K.again(), depth, x, y, sf, 1.0f, 0.0f);
+        }
+
+        const JobRef Ro = R.again();
+        const Frame F = Ro.frame();
+        uint32_t out = K.background();
+        if (hit) {
+            const float nv = fmaxf(0.0f, fmaf(nx, Vx, fmaf(ny, Vy, nz * Vz)));
+            // shading mode: a diffuse factor on the albedo and a white specular term
+            float diff, spec = 0.0f;
+            if (F.shading == 2) {                                  // flat
+                diff = ao;
+            } else if (F.shading == 3) {                           // toon: four bands of n.V
+                diff = fmaf(kKd, fminf(floorf(4.0f * nv), 3.0f) * (1.0f / 3.0f), kKa) * ao;
+            } else {                                               // glossy, matte
+                diff = fmaf(kKd, nv, kKa) * ao;
+                if (F.shading == 0) {
+                    float sp = fmaxf(0.0f, fmaf(2.0f * nv, nv, -1.0f));
+                    sp *= sp; sp *= sp; sp *= sp; sp *= sp; sp *= sp;     // ^32
+                    spec = kKs * sp;
                 }
             }
-        ao = sum / (float)cnt;
-    } else if (hit && K.count > 0) {
-        ao = ssao_at<false>(F, K, depth, x, y, sf, 1.0f, 0.0f);
-    }
-
-    uint32_t out = K.background;
-    if (hit) {
-        const float nv = fmaxf(0.0f, fmaf(nx, Vx, fmaf(ny, Vy, nz * Vz)));
-        // shading mode: a diffuse factor on the albedo and a white specular term
-        float diff, spec = 0.0f;
-        if (F.shading == 2) {                                  // flat
-            diff = ao;
-        } else if (F.shading == 3) {                           // toon: four bands of n.V
-            diff = fmaf(kKd, fminf(floorf(4.0f * nv), 3.0f) * (1.0f / 3.0f), kKa) * ao;
-        } else {                                               // glossy, matte
-            diff = fmaf(kKd, nv, kKa) * ao;
-            if (F.shading == 0) {
-                float sp = fmaxf(0.0f, fmaf(2.0f * nv, nv, -1.0f));
-                sp *= sp; sp *= sp; sp *= sp; sp *= sp; sp *= sp;     // ^32
-                spec = kKs * sp;
+            float c[3];
+    #pragma unroll
+            for (int ch = 0; ch < 3; ++ch) c[ch] = fmaf((float)((alb >> (8 * ch)) & 255u) * (1.0f / 255.0f), diff, spec);
+            if (F.fog_inv > 0.0f) {
+                const float f = fminf(fmaxf((z - F.fog_start) * F.fog_inv, 0.0f), 1.0f);
+    #pragma unroll
+                for (int ch = 0; ch < 3; ++ch) c[ch] = fmaf(f, F.fog_rgb[ch] - c[ch], c[ch]);
+            }
+            out = quantize(c[0]) | (quantize(c[1]) << 8) | (quantize(c[2]) << 16) | (255u << 24);
+            if (F.outline_t > 0.0f) {
+                // a neighbour in the image that is background or deeper by the step
+                const float zt = z * (1.0f + F.outline_t);
+                bool edge = false;
+                if (x + 1 < W) edge = edge || depth[p + 1] > zt;
+                if (x > 0) edge = edge || depth[p - 1] > zt;
+                if (y + 1 < H) edge = edge || depth[p + (size_t)W] > zt;
+                if (y > 0) edge = edge || depth[p - (size_t)W] > zt;
+                if (edge) out = F.outline_rgba;
             }
         }
-        float c[3];
-#pragma unroll
-        for (int ch = 0; ch < 3; ++ch) c[ch] = fmaf((float)((alb >> (8 * ch)) & 255u) * (1.0f / 255.0f), diff, spec);
-        if (F.fog_inv > 0.0f) {
-            const float f = fminf(fmaxf((z - F.fog_start) * F.fog_inv, 0.0f), 1.0f);
-#pragma unroll
-            for (int ch = 0; ch < 3; ++ch) c[ch] = fmaf(f, F.fog_rgb[ch] - c[ch], c[ch]);
+        to_global(Ro.rgba())[p] = out;
+        global_t<float>* __restrict__ const normal_out = to_global(Ro.normal());
+        global_t<uint32_t>* __restrict__ const albedo_out = to_global(Ro.albedo());
+        global_t<float>* __restrict__ const ao_out = to_global(Ro.ao());
+        if (normal_out) {
+            normal_out[3 * p] = nx;
+            normal_out[3 * p + 1] = ny;
+            normal_out[3 * p + 2] = nz;
         }
-        out = quantize(c[0]) | (quantize(c[1]) << 8) | (quantize(c[2]) << 16) | (255u << 24);
-        if (F.outline_t > 0.0f) {
-            // a neighbour in the image that is background or deeper by the step
-            const float zt = z * (1.0f + F.outline_t);
-            bool edge = false;
-            if (x + 1 < F.W) edge = edge || depth[p + 1] > zt;
-            if (x > 0) edge = edge || depth[p - 1] > zt;
-            if (y + 1 < F.H) edge = edge || depth[p + (size_t)F.W] > zt;
-            if (y > 0) edge = edge || depth[p - (size_t)F.W] > zt;
-            if (edge) out = F.outline_rgba;
-        }
+        if (albedo_out) albedo_out[p] = hit ? alb : 0u;
+        if (ao_out) ao_out[p] = ao;
     }
-    rgba[p] = out;
-    if (normal_out) {
-        normal_out[3 * p] = nx;
-        normal_out[3 * p + 1] = ny;
-        normal_out[3 * p + 2] = nz;
-    }
-    if (albedo_out) albedo_out[p] = hit ? alb : 0u;
-    if (ao_out) ao_out[p] = ao;
 }
 
 // One output pixel per thread: its S x S samples are reduced to the rounded
@@ -373,17 +403,19 @@ hipError_t launch_downsample(const float* sdepth, const uint32_t* sid, const uin
 }
 
 template <class JS>
-hipError_t shade_impl(const JS& js, uint32_t grid, bool noise, hipStream_t stream) {
+hipError_t shade_impl(const JS& js, uint32_t grid, ShadeForm form, hipStream_t stream) {
     if (grid == 0) return hipSuccess;
-    if (noise) return dispatch(k_shade<JS, true>, (unsigned)xcd_grid((int)grid), kBlock, 0, stream, js);
-    return dispatch(k_shade<JS, false>, (unsigned)xcd_grid((int)grid), kBlock, 0, stream, js);
+    const unsigned g = (unsigned)xcd_run_grid((int)grid);
+    if (form.noise) return dispatch(k_shade<JS, true, 16>, g, kBlock, 0, stream, js);
+    if (form.wide) return dispatch(k_shade<JS, false, 64>, g, kBlock, 0, stream, js);
+    return dispatch(k_shade<JS, false, 16>, g, kBlock, 0, stream, js);
 }
 
-hipError_t launch_shade(const OneJob& js, uint32_t grid, bool noise, hipStream_t stream) {
-    return shade_impl(js, grid, noise, stream);
+hipError_t launch_shade(const OneJob& js, uint32_t grid, ShadeForm form, hipStream_t stream) {
+    return shade_impl(js, grid, form, stream);
 }
-hipError_t launch_shade(const JobList& js, uint32_t grid, bool noise, hipStream_t stream) {
-    return shade_impl(js, grid, noise, stream);
+hipError_t launch_shade(const JobList& js, uint32_t grid, ShadeForm form, hipStream_t stream) {
+    return shade_impl(js, grid, form, stream);
 }
 
 }  // namespace vtx

@@ -340,6 +340,19 @@ __device__ inline int xcd_contiguous(int b, int nblocks) {
     return (b & 7) * per + (b >> 3);
 }
 
+// The same with runs of kXcdRun consecutive work items dealt round-robin to
+// the XCDs: neighbours still share an L2, and no XCD is left with a dear part
+// of the work.  One range per XCD gave each a band of the image, and the
+// molecule usually lies in the middle ones: shade of 107,500 atoms at 1080p
+// 26 us against 21, a figure at 3840x2160 387 against 337; single items lose
+// the shared lines (100M atoms at 4K 137 us against 126).  8 to 256 are alike.
+constexpr int kXcdRun = 32;
+__device__ inline int xcd_runs(int b) {
+    const int k = b >> 3;
+    return ((k / kXcdRun) * 8 + (b & 7)) * kXcdRun + k % kXcdRun;
+}
+inline int xcd_run_grid(int nblocks) { return (nblocks + 8 * kXcdRun - 1) / (8 * kXcdRun) * (8 * kXcdRun); }
+
 inline int xcd_grid(int nblocks) { return ((nblocks + 7) >> 3) << 3; }
 
 // Binning workgroup b of `groups` belongs to layer b * layers / groups; layer
@@ -494,7 +507,21 @@ inline uint32_t cull_blocks(const SceneDev& S) {
     const uint32_t nc = S.atom_clusters + S.bond_clusters;
     return (nc + kBlock - 1) / kBlock;
 }
-inline uint32_t shade_blocks(const Frame& F) { return (uint32_t)(((F.W + 15) / 16) * ((F.H + 15) / 16)); }
+// Form of a shade launch: whether a job asks for the noise form of the ambient
+// occlusion, and tiles of 64x16 pixels instead of 16x16.  Wide tiles read
+// their job's constants once for four blocks, which pays where most blocks
+// are background and the launch is long: a trajectory batch of 520M pixels
+// 5.05 ms narrow, 4.87 wide.  One 8.3M-pixel frame is 126 us narrow, 144 wide
+// (fewer, longer workgroups, one wave per SIMD less).
+struct ShadeForm {
+    bool noise, wide;
+};
+constexpr uint64_t kWidePixels = 128u << 20;
+inline ShadeForm shade_form(bool noise, uint64_t pixels) { return ShadeForm{noise, !noise && pixels >= kWidePixels}; }
+inline uint32_t shade_blocks(const Frame& F, ShadeForm form) {
+    const int w = form.wide ? 64 : 16;
+    return (uint32_t)(((F.W + w - 1) / w) * ((F.H + 15) / 16));
+}
 
 // A launch over one render: the job travels in the kernel arguments.
 struct OneJob {
@@ -569,19 +596,20 @@ struct JobList {
 // registers, or (a job table, after the kernel's first stores) loads it by
 // lanes.  again() is a point such loads are not moved across: the words read
 // through it are loaded there, and the unused ones not at all.
-struct JobRef {
 #if defined(__HIP_DEVICE_COMPILE__)
-    using Word = const __attribute__((address_space(4))) uint32_t;
+using Word = const __attribute__((address_space(4))) uint32_t;
 #else
-    using Word = const uint32_t;
+using Word = const uint32_t;
 #endif
+__device__ inline Word* read_again(Word* at) {
+    uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uintptr_t)at);
+    uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint64_t)(uintptr_t)at >> 32));
+    asm volatile("" : "+s"(lo), "+s"(hi));
+    return (Word*)(uintptr_t)(((uint64_t)hi << 32) | lo);
+}
+struct JobRef {
     Word* at;
-    __device__ JobRef again() const {
-        uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uintptr_t)at);
-        uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint64_t)(uintptr_t)at >> 32));
-        asm volatile("" : "+s"(lo), "+s"(hi));
-        return JobRef{(Word*)(uintptr_t)(((uint64_t)hi << 32) | lo)};
-    }
+    __device__ JobRef again() const { return JobRef{read_again(at)}; }
     template <class T>
     __device__ T words(size_t off) const {
         static_assert(sizeof(T) % 4 == 0, "copied by words");
@@ -598,21 +626,61 @@ struct JobRef {
     __device__ const float* pos() const { return words<const float*>(offsetof(Job, pos)); }
     __device__ const float* rad() const { return words<const float*>(offsetof(Job, rad)); }
     __device__ const uint32_t* bonds() const { return words<const uint32_t*>(offsetof(Job, bonds)); }
+    __device__ const uint32_t* col() const { return words<const uint32_t*>(offsetof(Job, col)); }
     __device__ float* depth() const { return words<float*>(offsetof(Job, depth)); }
     __device__ uint32_t* id() const { return words<uint32_t*>(offsetof(Job, id)); }
+    __device__ uint32_t* rgba() const { return words<uint32_t*>(offsetof(Job, rgba)); }
+    __device__ float* normal() const { return words<float*>(offsetof(Job, normal)); }
+    __device__ uint32_t* albedo() const { return words<uint32_t*>(offsetof(Job, albedo)); }
+    __device__ float* ao() const { return words<float*>(offsetof(Job, ao)); }
+};
+// A job's SSAO samples, read the same way.
+struct SampleRef {
+    Word* at;
+    __device__ SampleRef again() const { return SampleRef{read_again(at)}; }
+    __device__ float f(size_t off) const { return __uint_as_float(at[off / 4]); }
+    // samples k to k + 3 (k the same across the wave): one load
+    __device__ void h4(int k, float4 (&out)[4]) const {
+        typedef uint32_t Words16 __attribute__((ext_vector_type(16), aligned(16)));
+        static_assert(offsetof(SampleKernel, h) == 0 && sizeof(out) == sizeof(Words16), "16 words");
+#if defined(__HIP_DEVICE_COMPILE__)
+        const Words16 w = *(const __attribute__((address_space(4))) Words16*)(at + 4 * k);
+#else
+        const Words16 w = *(const Words16*)(at + 4 * k);
+#endif
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            out[q] = make_float4(__uint_as_float(w[4 * q]), __uint_as_float(w[4 * q + 1]), __uint_as_float(w[4 * q + 2]),
+                                 __uint_as_float(w[4 * q + 3]));
+    }
+    __device__ float2 rot(int b) const {
+        const size_t o = offsetof(SampleKernel, rot) + 8 * (size_t)b;
+        return make_float2(f(o), f(o + 4));
+    }
+    __device__ int count() const { return (int)at[offsetof(SampleKernel, count) / 4]; }
+    __device__ float radius() const { return f(offsetof(SampleKernel, radius)); }
+    __device__ float bias() const { return f(offsetof(SampleKernel, bias)); }
+    __device__ uint32_t background() const { return at[offsetof(SampleKernel, background) / 4]; }
+    __device__ int noise() const { return (int)at[offsetof(SampleKernel, noise) / 4]; }
 };
 
 // Job `i` of a launch whose job source is its kernel's first parameter.
 __device__ inline JobRef job_ref(const OneJob&, int) {
     static_assert(offsetof(OneJob, j) == 0, "the job leads the kernel arguments");
 #if defined(__HIP_DEVICE_COMPILE__)
-    return JobRef{(JobRef::Word*)__builtin_amdgcn_kernarg_segment_ptr()};
+    return JobRef{(Word*)__builtin_amdgcn_kernarg_segment_ptr()};
 #else
     return JobRef{nullptr};
 #endif
 }
+__device__ inline SampleRef sample_ref(const OneJob& js, int i) {
+    return SampleRef{job_ref(js, i).at + offsetof(OneJob, K) / 4};
+}
+__device__ inline SampleRef sample_ref(const JobList& js, int i) {
+    return SampleRef{(Word*)(js.K + __builtin_amdgcn_readfirstlane(i))};
+}
 __device__ inline JobRef job_ref(const JobList& js, int i) {
-    return JobRef{(JobRef::Word*)(js.jobs + __builtin_amdgcn_readfirstlane(i))};
+    return JobRef{(Word*)(js.jobs + __builtin_amdgcn_readfirstlane(i))};
 }
 
 // Launch wrappers, one overload per job source.  `grid` is the number of
@@ -654,9 +722,8 @@ hipError_t launch_resolve(const JobList& js, int tile, int phase, uint32_t grid,
 // (depth, id)).
 hipError_t launch_downsample(const float* sdepth, const uint32_t* sid, const uint32_t* srgba, int W, int H, int S,
                              float* depth, uint32_t* id, uint32_t* rgba, hipStream_t stream);
-// `noise`: some job asks for the noise form of the ambient occlusion.
-hipError_t launch_shade(const OneJob& js, uint32_t grid, bool noise, hipStream_t stream);
-hipError_t launch_shade(const JobList& js, uint32_t grid, bool noise, hipStream_t stream);
+hipError_t launch_shade(const OneJob& js, uint32_t grid, ShadeForm form, hipStream_t stream);
+hipError_t launch_shade(const JobList& js, uint32_t grid, ShadeForm form, hipStream_t stream);
 
 // In-place exclusive prefix sum of n counts (scan.hip); bsum needs
 // scan_scratch_words(n) words; *total (may be null) gets the sum.

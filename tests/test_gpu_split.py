@@ -111,3 +111,26 @@ def test_a_large_opaque_scene_takes_the_pre_pass_unasked(vtx, ctx):
     (auto, st_auto), (one, st_one) = two_ways(vtx, ctx, wl, 0, vtx.VTX_FLAG_ONE_PASS)
     assert_identical(auto, one, "inside")
     assert st_auto["visible"] == st_one["visible"]
+
+
+@pytest.mark.parametrize("size", [(3845, 2049), (3840, 2064)])
+def test_wide_shade_tiles_of_a_large_batch(vtx, ctx, size):
+    """Over 128M pixels a launch shades in 64x16 tiles: the images are the
+    single renders', at widths that end inside a tile and inside a block."""
+    import torch
+    W, H = size
+    wl = scenes.plain_small(n_atoms=3000, width=W, height=H, seed=7)
+    opts = dataclasses.replace(wl.options, ssao_samples=8, outline_depth=0.05, outline_color=scenes.pack_rgba(9, 9, 9))
+    rs = vtx.ResidentScene(ctx, vtx.DeviceScene(wl.scene))
+    n = (128 << 20) // (W * H) + 1
+    cams = [scenes.orbit_camera((0.0, 0.0, 0.0), 36.0, 0.3 * k) for k in range(n)]
+    frames = [vtx.Frame(W, H) for _ in range(n)]
+    vtx.vtx_render_batch(ctx, [vtx.make_job(rs.handle, 0, cams[k], opts, W, H, f.rgba, f.depth, f.id)
+                               for k, f in enumerate(frames)])
+    one = vtx.Frame(W, H)
+    for k, f in enumerate(frames):
+        rs.render(cams[k], opts, W, H, one)
+        torch.cuda.synchronize()
+        for name in ("rgba", "depth", "id"):
+            assert torch.equal(getattr(one, name), getattr(f, name)), (k, name)
+    rs.close()
