@@ -919,6 +919,27 @@ int render_locked(std::vector<JobDesc>& d, bool bin, bool shade, hipStream_t str
         count |= (j.F.flags & (VTX_FLAG_STATS | VTX_FLAG_COUNT)) != 0;
         scene |= j.scene;
     }
+    // A launch of small resident scenes bins them in their stored order,
+    // without the cluster test, the depth classes and the layers (three
+    // launches and 12 to 18 us).  The front-to-back lists pay where a tile
+    // holds many primitives, so it needs few per tile, fewer the larger the
+    // launch is.  us by clusters and stored: 4,000 atoms at 256x256 (16 per
+    // tile) 67 and 56, 70,000 at 720p (19) 88 and 70, four views of 40,000
+    // primitives (3 to 11) 205 and 182, 107,500 atoms with bonds at 1080p (26)
+    // 132 and 120, 70,000 at 640x480 (58) 96 and 86; but 200,000 at 720p (56)
+    // 107 and 113, 500,000 at 1080p (61) 145 and 162, and 256 renders of
+    // 50,000 9,530 and 9,740.
+    uint64_t binned = 0, per_tile = 0;
+    bool stored = scene;
+    for (const JobDesc& j : d) {
+        const uint64_t np = (uint64_t)j.F.n_atoms + j.F.n_bonds, tiles = (uint64_t)j.F.tiles_x * j.F.tiles_y;
+        binned += np;
+        per_tile = std::max(per_tile, (np + tiles - 1) / tiles);
+        stored = stored && j.scene && !(j.F.flags & VTX_FLAG_TWO_PASS);
+    }
+    stored = stored && ((binned <= 1u << 17 && per_tile <= 64) || (binned <= 1u << 19 && per_tile <= 32));
+    const bool clusters = scene && !stored;
+    const vtx::BinForm bin_form = !scene ? vtx::kBinArrays : stored ? vtx::kBinStored : vtx::kBinClusters;
     const vtx::ShadeForm form = vtx::shade_form(noise, pixels);
     TimingSlot* tslot = nullptr;
     if (timing && !capture && (rc = timing_slot(ws, &tslot))) return rc;
@@ -991,7 +1012,7 @@ int render_locked(std::vector<JobDesc>& d, bool bin, bool shade, hipStream_t str
         nprims[i] = nprim;
         uint32_t groups, chunk, nc = 0;
         vtx::bin_grid(nprim, n, &groups, &chunk);
-        if (s.scene) {
+        if (s.scene && clusters) {
             // each binning workgroup takes whole clusters
             nc = s.S.atom_clusters + s.S.bond_clusters;
             const uint64_t cpw = ((uint64_t)nc + groups - 1) / groups;
@@ -1024,9 +1045,9 @@ int render_locked(std::vector<JobDesc>& d, bool bin, bool shade, hipStream_t str
         J.bb.layers = 1;
         if (s.scene) {
             J.S = s.S;
-            J.S.vis_clusters = b->vis_clusters;
+            J.S.vis_clusters = clusters ? b->vis_clusters : nullptr;
             // binning workgroups run front to back: keep that order in the lists
-            J.bb.layers = std::min<uint32_t>(vtx::kLayers, groups);
+            if (clusters) J.bb.layers = std::min<uint32_t>(vtx::kLayers, groups);
         }
         starts[i] = g_cull;
         starts[(n + 1) + i] = g_bin;
@@ -1118,12 +1139,12 @@ int render_locked(std::vector<JobDesc>& d, bool bin, bool shade, hipStream_t str
         // Occlusion pre-pass (asked for by or worth it for every job,
         // resident scenes with sized lists): bin and resolve the nearest clusters first, then only
         // the clusters not hidden behind that pass's depths.
-        bool two_pass = scene && need.empty();
+        bool two_pass = clusters && need.empty();
         for (size_t i = 0; i < n && two_pass; ++i)
             two_pass = d[i].scene && ((d[i].F.flags & VTX_FLAG_TWO_PASS) || d[i].pre_pass) &&
                        !(d[i].F.flags & (VTX_FLAG_STATS | VTX_FLAG_COUNT | VTX_FLAG_ONE_PASS)) &&
                        d[i].F.tile >= vtx::kHzCell;
-        if (scene) {
+        if (clusters) {
             if (n == 1) VTX_HIP(vtx::launch_cluster_cull(one(g_cull), g_cull, stream));
             else VTX_HIP(vtx::launch_cluster_cull(list_of(0, n, 0), g_cull, stream));
         }
@@ -1134,8 +1155,8 @@ int render_locked(std::vector<JobDesc>& d, bool bin, bool shade, hipStream_t str
                 if (n == 1) VTX_HIP(vtx::launch_cluster_rest(one(g_cull), g_cull, stream));
                 else VTX_HIP(vtx::launch_cluster_rest(list_of(0, n, 0), g_cull, stream));
             }
-            if (n == 1) VTX_HIP(vtx::launch_count(one(g_bin), scene, phase, g_bin, max_tiles, stream));
-            else VTX_HIP(vtx::launch_count(list_of(0, n, n + 1), scene, phase, g_bin, max_tiles, stream));
+            if (n == 1) VTX_HIP(vtx::launch_count(one(g_bin), bin_form, phase, g_bin, max_tiles, stream));
+            else VTX_HIP(vtx::launch_count(list_of(0, n, n + 1), bin_form, phase, g_bin, max_tiles, stream));
             if (!need.empty()) {
                 std::vector<unsigned long long> counted(n, 0);
                 for (size_t i : need)
@@ -1160,7 +1181,7 @@ int render_locked(std::vector<JobDesc>& d, bool bin, bool shade, hipStream_t str
                 if (n > 1 && (rc = upload_tables(ws, jobs, d, starts, &k_off, &s_off))) return rc;
             }
             VTX_HIP(mark(2));
-            if (scene) {
+            if (clusters) {
                 if (n == 1) VTX_HIP(vtx::launch_layers(one(g_bin), g_bin, stream));
                 else VTX_HIP(vtx::launch_layers(list_of(0, n, n + 1), g_bin, stream));
             }
@@ -1425,7 +1446,7 @@ int vtx_render_static(const float* positions, const float* radii, const uint32_t
     VTX_HIP(vtx::launch_zero(reinterpret_cast<uint32_t*>(base), L.zero_end / sizeof(uint32_t), st));
     const bool count = (F.flags & (VTX_FLAG_STATS | VTX_FLAG_COUNT)) != 0;
     js.blocks = groups;
-    VTX_HIP(vtx::launch_count(js, false, vtx::kPhaseAll, groups, T, st));
+    VTX_HIP(vtx::launch_count(js, vtx::kBinArrays, vtx::kPhaseAll, groups, T, st));
     VTX_HIP(vtx::launch_tile_offsets(js, st));
     VTX_HIP(vtx::launch_scatter(js, vtx::kPhaseAll, groups, T, st));
     js.blocks = (uint32_t)T;

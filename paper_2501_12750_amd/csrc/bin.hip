@@ -92,10 +92,11 @@ __device__ inline int box_tile(int tiles_x, uint32_t bx0, uint32_t by0, int bw, 
 
 // Count.  Work block b of a job is that job's binning workgroup b.
 // kRest: the rest pass of a two-pass frame, over the clusters
-// k_cluster_rest kept.  kAtoms: a scene without
-// bonds (no bond path in the loop: fewer live registers).  kQuarters: see
-// quarters() for the scenes that take it.
-template <class JS, bool kScene, bool kRest, bool kAtoms = false, bool kQuarters = false>
+// k_cluster_rest kept.  kAtoms: a scene without bonds (no bond path in the
+// loop: fewer live registers).  kQuarters: see quarters() for the scenes that
+// take it.  kStored (not kScene): a resident scene's primitives in their
+// stored order, without its clusters.
+template <class JS, bool kScene, bool kRest, bool kAtoms = false, bool kQuarters = false, bool kStored = false>
 __global__ void __launch_bounds__(kBinThreads, 8) k_count(JS js, int phase) {
     extern __shared__ uint32_t hist[];
     __shared__ uint32_t local_n, bx0, by0, bx1, by1;
@@ -249,6 +250,7 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_count(JS js, int phase) {
         const uint64_t total = (uint64_t)n_atoms + R.frame().n_bonds;
         const uint32_t nitems = start < total ? (uint32_t)min((uint64_t)chunk, total - start) : 0u;
         auto fetch = [&](uint32_t k) {
+            if constexpr (kStored) return fetch_scene(R.scene(), (uint32_t)start + k);
             return fetch_plain(to_global(R.pos()), to_global(R.rad()), to_global(R.bonds()), n_atoms, start + k);
         };
         Item cur = empty_item();
@@ -676,11 +678,14 @@ inline bool quarters(const OneJob& js) { return js.j.S.atom_clusters <= kFewClus
 inline bool quarters(const JobList& js) { return js.few_clusters != 0; }
 
 template <class JS>
-hipError_t count_impl(const JS& js, bool scene, int phase, uint32_t grid, int max_tiles, hipStream_t stream) {
+hipError_t count_impl(const JS& js, BinForm form, int phase, uint32_t grid, int max_tiles, hipStream_t stream) {
+    const bool scene = form == kBinClusters;
     if (max_tiles > kMaxLdsTiles) return hipErrorInvalidValue;
     if (phase != kPhaseAll && !scene) return hipErrorInvalidValue;
     if (grid == 0) return hipSuccess;
     const size_t lds = (size_t)max_tiles * sizeof(uint32_t);
+    if (form == kBinStored)
+        return dispatch(k_count<JS, false, false, false, false, true>, grid, kBinThreads, lds, stream, js, phase);
     if (!scene) return dispatch(k_count<JS, false, false>, grid, kBinThreads, lds, stream, js, phase);
     if (phase == kPhaseRest) return dispatch(k_count<JS, true, true>, grid, kBinThreads, lds, stream, js, phase);
     if (!atoms_only(js)) return dispatch(k_count<JS, true, false, false, true>, grid, kBinThreads, lds, stream, js, phase);
@@ -695,11 +700,11 @@ hipError_t scatter_impl(const JS& js, int phase, uint32_t grid, int max_tiles, h
     return dispatch(k_scatter<JS>, grid, kBinThreads, (uint32_t)(max_tiles * sizeof(uint32_t)), stream, js, phase);
 }
 
-hipError_t launch_count(const OneJob& js, bool scene, int phase, uint32_t grid, int max_tiles, hipStream_t stream) {
-    return count_impl(js, scene, phase, grid, max_tiles, stream);
+hipError_t launch_count(const OneJob& js, BinForm form, int phase, uint32_t grid, int max_tiles, hipStream_t stream) {
+    return count_impl(js, form, phase, grid, max_tiles, stream);
 }
-hipError_t launch_count(const JobList& js, bool scene, int phase, uint32_t grid, int max_tiles, hipStream_t stream) {
-    return count_impl(js, scene, phase, grid, max_tiles, stream);
+hipError_t launch_count(const JobList& js, BinForm form, int phase, uint32_t grid, int max_tiles, hipStream_t stream) {
+    return count_impl(js, form, phase, grid, max_tiles, stream);
 }
 hipError_t launch_layers(const OneJob& js, uint32_t grid, hipStream_t stream) {
     return dispatch(k_layers<OneJob>, grid, kBinThreads, 0, stream, js);

@@ -695,11 +695,14 @@ hipError_t launch_cluster_cull(const JobList& js, uint32_t grid, hipStream_t str
 // it does not hide (grid as for the cull).
 hipError_t launch_cluster_rest(const OneJob& js, uint32_t grid, hipStream_t stream);
 hipError_t launch_cluster_rest(const JobList& js, uint32_t grid, hipStream_t stream);
+// What the count bins: the caller's arrays, a resident scene's visible
+// clusters in depth-class order, or its primitives in their stored order.
+enum BinForm : int { kBinArrays = 0, kBinClusters = 1, kBinStored = 2 };
 // `phase` (resident scenes): kPhaseAll bins every visible cluster; a
 // two-pass frame runs count to resolve with kPhaseFront, then again with
 // kPhaseRest, whose resolve starts from the front pass's G-buffer.
-hipError_t launch_count(const OneJob& js, bool scene, int phase, uint32_t grid, int max_tiles, hipStream_t stream);
-hipError_t launch_count(const JobList& js, bool scene, int phase, uint32_t grid, int max_tiles, hipStream_t stream);
+hipError_t launch_count(const OneJob& js, BinForm form, int phase, uint32_t grid, int max_tiles, hipStream_t stream);
+hipError_t launch_count(const JobList& js, BinForm form, int phase, uint32_t grid, int max_tiles, hipStream_t stream);
 // Layer starts of every tile list from the count kernel's histograms (jobs
 // with layers > 1; runs on the binning grid).
 hipError_t launch_layers(const OneJob& js, uint32_t grid, hipStream_t stream);

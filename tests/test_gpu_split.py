@@ -134,3 +134,32 @@ def test_wide_shade_tiles_of_a_large_batch(vtx, ctx, size):
         for name in ("rgba", "depth", "id"):
             assert torch.equal(getattr(one, name), getattr(f, name)), (k, name)
     rs.close()
+
+
+@pytest.mark.parametrize("n,size", [(200, (40, 30)), (5000, (97, 83)), (60_000, (701, 403)), (200_000, (1111, 1017))])
+@pytest.mark.parametrize("representation", [0, 3])
+def test_stored_order_binning_equals_clusters(vtx, ctx, n, size, representation):
+    """Small resident scenes are binned in stored order, without clusters; a
+    two-pass request keeps the clusters.  Bad bonds, trajectory frames and
+    bond-free representations go the same way in both."""
+    import torch
+    wl = workload(n, True, *size)
+    wl.scene.bonds[::7, 1] = n + 5          # out of range: dropped from the scene
+    wl.options = dataclasses.replace(wl.options, representation=representation)
+    rs = vtx.ResidentScene(ctx, vtx.DeviceScene(wl.scene))
+    moved = torch.from_numpy(wl.scene.positions + np.float32(0.25)).cuda()
+    rs.add_frames(moved, 1)
+    out = {}
+    for flags in (0, vtx.VTX_FLAG_TWO_PASS):
+        opts = dataclasses.replace(wl.options, flags=flags)
+        for again in range(2):              # the first sizes the lists
+            frames = [vtx.Frame(*size) for _ in range(2)]
+            vtx.vtx_render_batch(ctx, [vtx.make_job(rs.handle, k, wl.camera, opts, *size, f.rgba, f.depth, f.id)
+                                       for k, f in enumerate(frames)])
+            one = rs.render(wl.camera, opts, *size)
+            torch.cuda.synchronize()
+        out[flags] = [f.numpy() for f in frames + [one]]
+    for a, b in zip(*out.values()):
+        assert_identical(a, b, "stored and clusters")
+    assert_identical(out[0][0], out[0][2], "batch and single")
+    rs.close()
