@@ -1668,24 +1668,20 @@ int vtx_scene_add_frames(vtx_scene* scene, const float* positions, int32_t n_fra
     }
     hipStream_t st = (hipStream_t)stream;
     const int32_t first = (int32_t)scene->frames.size() + 1;
+    const hipError_t e = vtx::scene_store_frames(positions, n_frames, scene->S, per, reinterpret_cast<float*>(block),
+                                                 reinterpret_cast<float4*>(block + pos_b),
+                                                 reinterpret_cast<float4*>(block + pos_b + xyzr_b), st);
+    if (e != hipSuccess) {
+        (void)hipStreamSynchronize(st);
+        (void)hipFree(block);
+        std::lock_guard<std::mutex> lk(ctx->mu);
+        ctx->used -= bytes;
+        return fail(VTX_EHIP, "storing the frames failed: %s", hipGetErrorString(e));
+    }
     for (int32_t f = 0; f < n_frames; ++f) {
-        SceneFrame fr;
         char* base = block + per * (size_t)f;
-        fr.pos = reinterpret_cast<float*>(base);
-        fr.xyzr = reinterpret_cast<float4*>(base + pos_b);
-        fr.cluster_box = reinterpret_cast<float4*>(base + pos_b + xyzr_b);
-        hipError_t e = hipSuccess;
-        if (na) e = hipMemcpyAsync(fr.pos, positions + (size_t)f * na * 3, na * 3 * sizeof(float), hipMemcpyDeviceToDevice, st);
-        if (e == hipSuccess) e = vtx::scene_update_positions(fr.pos, scene->S, fr.xyzr, fr.cluster_box, st);
-        if (e != hipSuccess) {
-            (void)hipStreamSynchronize(st);
-            hipFree(block);
-            scene->frames.resize((size_t)first - 1);
-            std::lock_guard<std::mutex> lk(ctx->mu);
-            ctx->used -= bytes;
-            return fail(VTX_EHIP, "storing frame %d failed: %s", f, hipGetErrorString(e));
-        }
-        scene->frames.push_back(fr);
+        scene->frames.push_back({reinterpret_cast<float*>(base), reinterpret_cast<float4*>(base + pos_b),
+                                 reinterpret_cast<float4*>(base + pos_b + xyzr_b)});
     }
     scene->frame_blocks.push_back(block);
     scene->bytes += bytes;
@@ -1698,9 +1694,7 @@ int32_t vtx_scene_frames(const vtx_scene* scene) { return scene ? (int32_t)scene
 int vtx_scene_update_positions(vtx_scene* scene, const float* positions, void* stream) {
     if (!scene || (scene->n > 0 && !positions)) return fail(VTX_EINVAL, "scene/positions is NULL");
     hipStream_t st = (hipStream_t)stream;
-    if (scene->n)
-        VTX_HIP(hipMemcpyAsync(scene->pos, positions, 3 * (size_t)scene->n * sizeof(float), hipMemcpyDeviceToDevice, st));
-    VTX_HIP(vtx::scene_update_positions(scene->pos, scene->S, scene->xyzr, scene->cluster_box, st));
+    VTX_HIP(vtx::scene_store_frames(positions, 1, scene->S, 0, scene->pos, scene->xyzr, scene->cluster_box, st));
     return VTX_OK;
 }
 

@@ -113,19 +113,6 @@ __global__ void __launch_bounds__(kBlock) k_gather_atoms(const float* __restrict
     if (inv) inv[a] = i;
 }
 
-// New positions for a trajectory frame (radii kept).
-// New positions of the stored atoms; the radii come from the scene's own
-// stream (`rsrc`, which may be `xyzr` itself).
-__global__ void __launch_bounds__(kBlock) k_update_positions(const float* __restrict__ pos,
-                                                             const uint32_t* __restrict__ atom_id, uint32_t n,
-                                                             const float4* rsrc, float4* xyzr) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const uint32_t a = atom_id[i];
-    const float r = rsrc[i].w;
-    xyzr[i] = make_float4(pos[3 * (size_t)a], pos[3 * (size_t)a + 1], pos[3 * (size_t)a + 2], r);
-}
-
 // Sort key of bond b: stored index of its first atom (bonds with an index out
 // of range get the largest key and are dropped).
 __global__ void __launch_bounds__(kBlock) k_bond_keys(const uint32_t* __restrict__ bonds, uint32_t m, uint32_t n,
@@ -446,17 +433,86 @@ hipError_t scene_order(const SceneDev& S, uint32_t* atom_order, uint32_t* bond_o
     return hipGetLastError();
 }
 
-// Writes the atom stream `xyzr` and the cluster boxes of new positions `pos`
-// (caller's order) in the scene's stored order; radii are read from S.xyzr.
-// `xyzr` may be S.xyzr (in-place update) or another frame's stream.
-hipError_t scene_update_positions(const float* pos, SceneDev& S, float4* xyzr, float4* cluster_box,
-                                  hipStream_t stream) {
-    if (S.n_atoms)
-        k_update_positions<<<grid_for(S.n_atoms), kBlock, 0, stream>>>(pos, S.atom_id, S.n_atoms, S.xyzr, xyzr);
+// New positions of a scene's atoms (caller's order), blockIdx.y-th frame: the
+// caller-order copy, the stored atom stream (radii kept) and the cluster boxes
+// in one launch, one wave per cluster.  A bond cluster's wave takes its ends
+// from the given positions, so it needs no atom another wave stores.  (A
+// copy, a gather and the boxes one after the other took 5 us each for
+// 107,500 atoms with bonds.)
+__global__ void __launch_bounds__(kBlock) k_store_frames(SceneDev S, const float* __restrict__ pos, size_t stride,
+                                                         float* pos_out, float4* xyzr, float4* box) {
+    const uint32_t c = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    const int lane = __lane_id();
+    if (c >= S.atom_clusters + S.bond_clusters) return;
+    pos += 3 * (size_t)S.n_atoms * blockIdx.y;
+    auto frame = [&](auto* p) { return reinterpret_cast<decltype(p)>(reinterpret_cast<char*>(p) + stride * blockIdx.y); };
+    float4* const out = frame(xyzr);
+    float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+    auto at = [&](uint32_t atom, float p[3]) {
+        for (int k = 0; k < 3; ++k) p[k] = pos[3 * (size_t)atom + k];
+    };
+    if (c < S.atom_clusters) {
+        // the caller-order copy of as many atoms: every load before the stores
+        constexpr int kCopy = 3 * kCluster / 64;
+        const size_t first = 3 * (size_t)c * kCluster + lane, end = 3 * (size_t)S.n_atoms;
+        float v[kCopy];
+#pragma unroll
+        for (int q = 0; q < kCopy; ++q) v[q] = first + 64 * q < end ? pos[first + 64 * q] : 0.0f;
+#pragma unroll
+        for (int q = 0; q < kCopy; ++q)
+            if (first + 64 * q < end) frame(pos_out)[first + 64 * q] = v[q];
+#pragma unroll
+        for (int s = 0; s < kCluster / 64; ++s) {
+            const uint32_t i = c * kCluster + 64 * s + lane;
+            if (i >= S.n_atoms) continue;
+            float p[3];
+            at(S.atom_id[i], p);
+            const float r = S.xyzr[i].w;
+            out[i] = make_float4(p[0], p[1], p[2], r);
+            for (int k = 0; k < 3; ++k) {
+                lo[k] = fminf(lo[k], p[k] - r);
+                hi[k] = fmaxf(hi[k], p[k] + r);
+            }
+        }
+    } else {
+#pragma unroll
+        for (int s = 0; s < kCluster / 64; ++s) {
+            const uint32_t j = (c - S.atom_clusters) * kCluster + 64 * s + lane;
+            if (j >= S.n_bonds) continue;
+            const uint4 br = S.bond_rec[j];
+            float a[3], b[3];
+            at(S.atom_id[br.x], a);
+            at(S.atom_id[br.y], b);
+            for (int k = 0; k < 3; ++k) {
+                lo[k] = fminf(lo[k], fminf(a[k], b[k]));
+                hi[k] = fmaxf(hi[k], fmaxf(a[k], b[k]));
+            }
+        }
+    }
+    for (int o = 32; o > 0; o >>= 1)
+        for (int k = 0; k < 3; ++k) {
+            lo[k] = fminf(lo[k], __shfl_xor(lo[k], o));
+            hi[k] = fmaxf(hi[k], __shfl_xor(hi[k], o));
+        }
+    if (lane == 0) {
+        frame(box)[2 * (size_t)c] = make_float4(lo[0], lo[1], lo[2], 0.0f);
+        frame(box)[2 * (size_t)c + 1] = make_float4(hi[0], hi[1], hi[2], 0.0f);
+    }
+}
+
+// Stores n_frames frames of positions `pos` (caller's order) of scene S; frame
+// f's arrays lie stride bytes after frame f - 1's.  `xyzr` may be S.xyzr
+// (in-place update of one frame).
+hipError_t scene_store_frames(const float* pos, int32_t n_frames, const SceneDev& S, size_t stride, float* pos_out,
+                              float4* xyzr, float4* box, hipStream_t stream) {
     const uint32_t nc = S.atom_clusters + S.bond_clusters;
-    SceneDev Sf = S;
-    Sf.xyzr = xyzr;
-    if (nc) k_cluster_boxes<<<grid_for((uint64_t)nc * 64), kBlock, 0, stream>>>(Sf, cluster_box);
+    constexpr int32_t kMost = 32768;   // frames per launch (grid y)
+    for (int32_t f = 0; nc && f < n_frames; f += kMost) {
+        auto from = [&](auto* p) { return reinterpret_cast<decltype(p)>(reinterpret_cast<char*>(p) + stride * (size_t)f); };
+        const dim3 grid(grid_for((uint64_t)nc * 64), (unsigned)(n_frames - f < kMost ? n_frames - f : kMost));
+        k_store_frames<<<grid, kBlock, 0, stream>>>(S, pos + 3 * (size_t)S.n_atoms * (size_t)f, stride, from(pos_out),
+                                                    from(xyzr), from(box));
+    }
     return hipGetLastError();
 }
 

@@ -473,8 +473,8 @@ hipError_t scene_build(const float* pos, const float* rad, const uint32_t* bonds
                        SceneDev& S, float4* xyzr, uint32_t* atom_id, uint4* bond_rec, float4* cluster_box,
                        void* tmp, size_t tmp_bytes, uint32_t* m_valid, uint32_t* n_bad, SceneExtent* extent,
                        hipStream_t stream);
-hipError_t scene_update_positions(const float* pos, SceneDev& S, float4* xyzr, float4* cluster_box,
-                                  hipStream_t stream);
+hipError_t scene_store_frames(const float* pos, int32_t n_frames, const SceneDev& S, size_t stride, float* pos_out,
+                              float4* xyzr, float4* box, hipStream_t stream);
 
 // Zeroes n 32-bit words (used when scratch is allocated; the frame kernels
 // leave the tile counts and the counters zeroed for the next frame).
