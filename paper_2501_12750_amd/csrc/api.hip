@@ -122,11 +122,6 @@ struct Workspace {
     int tnext = 0;
     uint64_t tframes = 0;
     double tsum[kTimeCats] = {};
-    // overflowed tiles of a resolve launch (job << 32 | tile) and its two
-    // counters, left zeroed by every launch
-    unsigned long long* d_ovf = nullptr;
-    size_t ovf_cap = 0;
-    uint32_t* d_ovf_n = nullptr;
     // solvent excluded surface calls: scratch words and the field when the
     // caller takes none
     uint32_t* ses = nullptr;
@@ -400,8 +395,6 @@ int ensure_bins(Workspace* ws, Bins* b, int T, uint64_t nprim, uint32_t groups, 
     return VTX_OK;
 }
 
-size_t xcd_round(uint32_t n) { return ((size_t)n + 7) / 8 * 8; }
-
 template <class T>
 int dev_alloc_zeroed(T** p, size_t count, hipStream_t stream) {
     if (hipMalloc(p, count * sizeof(T)) != hipSuccess) {
@@ -427,8 +420,6 @@ void workspace_free(Workspace* ws) {
     hipFree(ws->ses);
     hipFree(ws->d_tab);
     hipHostFree(ws->h_tab);
-    hipFree(ws->d_ovf);
-    hipFree(ws->d_ovf_n);
     hipEventDestroy(ws->done);
     hipEventDestroy(ws->staged);
     delete ws;
@@ -1114,16 +1105,6 @@ int render_locked(std::vector<JobDesc>& d, bool bin, bool shade, hipStream_t str
         return o;
     };
 
-    if (bin) {
-        uint32_t gmax = 0;
-        for (uint32_t gg : groups_grid) gmax = std::max(gmax, gg);
-        if (!ws->d_ovf_n) {
-            if ((rc = dev_alloc_zeroed(&ws->d_ovf_n, 2, stream))) return rc;
-        }
-        if ((size_t)xcd_round(gmax) > ws->ovf_cap || !ws->d_ovf) {
-            if ((rc = grow(&ws->d_ovf, ws->ovf_cap, (size_t)xcd_round(gmax), stream, "overflow tiles"))) return rc;
-        }
-    }
     VTX_HIP(mark(0));
     VTX_HIP(mark(1));
     if (bin) {
@@ -1195,18 +1176,18 @@ int render_locked(std::vector<JobDesc>& d, bool bin, bool shade, hipStream_t str
                 const size_t a = groups_ts[g].first, b = groups_ts[g].second;
                 if (n == 1)
                     VTX_HIP(vtx::launch_resolve(one(groups_grid[g]), d[0].F.tile, phase, groups_grid[g], count,
-                                                ws->d_ovf, ws->d_ovf_n, stream));
+                                                stream));
                 else
                     VTX_HIP(vtx::launch_resolve(list_of(a, b - a, groups_off[g]), d[a].F.tile, phase, groups_grid[g],
-                                                count, ws->d_ovf, ws->d_ovf_n, stream));
+                                                count, stream));
             }
         }
         for (size_t i = 0; i < n; ++i) {
             ws->slots[i]->dirty = false;
             ws->slots[i]->pending_capacity = ws->slots[i]->bb.capacity;
         }
-        // The scatter's first workgroup (and, with statistics on, the
-        // resolve's last one) writes each render's counters into its mapped
+        // The scatter's first workgroup (and, with statistics on,
+        // k_publish) writes each render's counters into its mapped
         // pinned buffer; the host reads them once this event has completed.
         if (!capture) {
             VTX_HIP(hipEventRecord(ws->done, stream));
@@ -1344,12 +1325,11 @@ int static_scratch(int* device, unsigned char** out) {
 
 // Byte layout of one frame's binning scratch in the static array (each
 // buffer 256-aligned).  The first region holds what must start at zero and
-// is cleared by a fill kernel at every call: the tile counts and cursors,
-// the frame counters and the overflow counters.  The tile lists take what is
-// left.
+// is cleared by a fill kernel at every call: the tile counts and cursors and
+// the frame counters.  The tile lists take what is left.
 struct StaticLayout {
-    size_t tile_cnt, tile_fill, ctr, ovf_n, zero_end;
-    size_t tile_off, vis_cnt, vis_box, vis_src, vis_rect, hist, ovf, list, fixed_end;
+    size_t tile_cnt, tile_fill, ctr, zero_end;
+    size_t tile_off, vis_cnt, vis_box, vis_src, vis_rect, hist, list, fixed_end;
     uint64_t list_entries;
 };
 
@@ -1364,7 +1344,6 @@ StaticLayout static_layout(int T, uint32_t groups, uint32_t chunk) {
     L.tile_cnt = take((size_t)T * sizeof(uint32_t));
     L.tile_fill = take((size_t)T * sizeof(uint32_t));
     L.ctr = take(sizeof(Counters));
-    L.ovf_n = take(2 * sizeof(uint32_t));
     L.zero_end = at;
     L.tile_off = take((size_t)T * sizeof(uint64_t));
     L.vis_cnt = take((size_t)vtx::kMaxBinGroups * sizeof(uint32_t));
@@ -1373,7 +1352,6 @@ StaticLayout static_layout(int T, uint32_t groups, uint32_t chunk) {
     L.vis_src = take(nv * sizeof(uint32_t));
     L.vis_rect = take(nv * sizeof(uint2));
     L.hist = take((size_t)groups * T * sizeof(uint32_t));
-    L.ovf = take(xcd_round((uint32_t)T) * sizeof(unsigned long long));
     L.list = at;
     L.fixed_end = at;
     L.list_entries = at < kStaticScratchBytes ? (kStaticScratchBytes - at) / sizeof(uint2) : 0;
@@ -1439,8 +1417,6 @@ int vtx_render_static(const float* positions, const float* radii, const uint32_t
     bb.groups = groups;
     bb.chunk = chunk;
     bb.layers = 1;   // the caller's primitive order: one layer, no layer tables
-    unsigned long long* ovf = reinterpret_cast<unsigned long long*>(base + L.ovf);
-    uint32_t* ovf_n = reinterpret_cast<uint32_t*>(base + L.ovf_n);
     // the array keeps the last call's contents: clear the counts, cursors
     // and counters this frame adds to (a fill kernel, no memset node)
     VTX_HIP(vtx::launch_zero(reinterpret_cast<uint32_t*>(base), L.zero_end / sizeof(uint32_t), st));
@@ -1450,7 +1426,7 @@ int vtx_render_static(const float* positions, const float* radii, const uint32_t
     VTX_HIP(vtx::launch_tile_offsets(js, st));
     VTX_HIP(vtx::launch_scatter(js, vtx::kPhaseAll, groups, T, st));
     js.blocks = (uint32_t)T;
-    VTX_HIP(vtx::launch_resolve(js, F.tile, vtx::kPhaseAll, (uint32_t)T, count, ovf, ovf_n, st));
+    VTX_HIP(vtx::launch_resolve(js, F.tile, vtx::kPhaseAll, (uint32_t)T, count, st));
     const vtx::ShadeForm form = vtx::shade_form(js.K.noise != 0 && js.K.count > 0, (uint64_t)F.W * F.H);
     js.blocks = vtx::shade_blocks(F, form);
     VTX_HIP(vtx::launch_shade(js, js.blocks, form, st));

@@ -435,7 +435,7 @@ __global__ void __launch_bounds__(kBinThreads) k_tile_offsets(JS js) {
         if (t < T) {
             const uint64_t o = wpre[r * kWaves + wave] + (incl[r] - v[r]);
             off[t] = o;
-            n_over += o + v[r] > J.bb.capacity ? 1u : 0u;   // lists the scatter leaves to the resolve's tail
+            n_over += o + v[r] > J.bb.capacity ? 1u : 0u;   // lists the scatter leaves out
         }
     }
     const unsigned long long base = wpre[kRows * kWaves];

@@ -29,7 +29,6 @@ namespace vtx {
 namespace {
 
 constexpr int kChunk = kBlock;
-constexpr unsigned kTailBlocks = 256;   // grid of the overflow (tail) launch
 constexpr int kBuckets = 64;      // depth buckets of the front-to-back record order
 static_assert(kBuckets <= 64, "one wave scans and searches the buckets");
 constexpr int kSortArea = 64;     // order a chunk when its kept records average more pixels than this
@@ -260,14 +259,15 @@ __device__ inline bool source_record(JobRef R, uint32_t src, PrimRec& pr) {
 }
 
 // Resolves tile t of job J, whose list holds n records from offset o
-// (kTail: the list overflowed and the tile is rebuilt from every binning
-// workgroup's visible list).  Re-arms the tile's count and cursor for the next
+// (over: the list overflowed and the tile is rebuilt from every binning
+// workgroup's visible list; the same for the whole workgroup).  Re-arms the tile's count and cursor for the next
 // frame.  The workgroup's LDS holds the tile's depth buffer, one chunk of
 // records and their prefix.  Two-pass frames: the front pass also stores the
 // farthest depth of each 16x16 cell of the tile; the rest pass starts from the
 // front pass's depth and id.
-template <int TS, bool kCount, bool kTail, int kPhase>
-__device__ __forceinline__ void resolve_tile(JobRef R, int t, uint32_t n, uint64_t o, unsigned long long* keys) {
+template <int TS, bool kCount, int kPhase>
+__device__ __forceinline__ void resolve_tile(JobRef R, int t, uint32_t n, uint64_t o, bool over,
+                                             unsigned long long* keys) {
     const JobRef R0 = R.again();
     const Frame F = R0.frame();
     const BinBuffers bb = R0.bins();
@@ -294,11 +294,6 @@ __device__ __forceinline__ void resolve_tile(JobRef R, int t, uint32_t n, uint64
     };
     uint32_t* __restrict__ const cnt = bb.tile_cnt;
     const global_t<const uint2>* __restrict__ const list = to_global(bb.list);
-    const global_t<const uint32_t>* __restrict__ const vis_src = to_global(bb.vis_src);
-    const global_t<const uint2>* __restrict__ const vis_rect = to_global(bb.vis_rect);
-    const uint32_t* __restrict__ const vis_cnt = bb.vis_cnt;
-    const uint2* __restrict__ const vis_box = bb.vis_box;
-    const uint32_t chunk = bb.chunk, groups = bb.groups;
     uint32_t* __restrict__ const fill = bb.tile_fill;
     Counters* const ctr = bb.ctr;
     global_t<float>* __restrict__ const depth = to_global(R0.depth());
@@ -328,7 +323,7 @@ __device__ __forceinline__ void resolve_tile(JobRef R, int t, uint32_t n, uint64
             keys[i] = k0;
         }
         if (tid < kChunk / 4) reinterpret_cast<uint32_t*>(ord)[tid] = 0u;
-        const uint64_t nsrc = kTail ? (uint64_t)groups * chunk : n;
+        const uint64_t nsrc = over ? (uint64_t)bb.groups * bb.chunk : n;
         const bool persp = F.proj == 0;
         __syncthreads();
         // every wave has read the tile's count (it sets the trip count of the
@@ -373,23 +368,23 @@ __device__ __forceinline__ void resolve_tile(JobRef R, int t, uint32_t n, uint64
                 atomicMin(&keys[slot], ((unsigned long long)__float_as_uint(z) << 32) |
                                            (rc.id | (graze && F.refine_flag ? kRefineBit : 0u)));
         };
-        // entry k of the visible lists (tiles whose list overflowed): the
-        // record is rebuilt from its source
-        auto fetch_overflow = [&](uint64_t k, PrimRec& pr) -> bool {
-            if constexpr (!kTail) return false;
-            const uint32_t g = (uint32_t)(k / chunk);
-            if ((uint32_t)(k - (uint64_t)g * chunk) >= vis_cnt[g]) return false;
-            const uint2 gb = vis_box[g];    // skip workgroups whose primitives cannot touch this tile
+        // entry k of the visible lists (tiles whose list overflowed), as the
+        // list entry it would have been
+        auto fetch_overflow = [&](uint64_t k, uint2& e) -> bool {
+            const BinBuffers vb = R.again().bins();
+            const uint32_t g = (uint32_t)(k / vb.chunk);
+            if ((uint32_t)(k - (uint64_t)g * vb.chunk) >= vb.vis_cnt[g]) return false;
+            const uint2 gb = vb.vis_box[g];    // skip workgroups whose primitives cannot touch this tile
             if (tx < (int)(gb.x & 0xFFFF) || tx > (int)(gb.y & 0xFFFF) || ty < (int)(gb.x >> 16) ||
                 ty > (int)(gb.y >> 16))
                 return false;
-            const uint2 r = vis_rect[k];
+            const uint2 r = vb.vis_rect[k];
             const int x0 = max((int)(r.x & 0xFFFF), px0) - px0, y0 = max((int)(r.x >> 16), py0) - py0;
             const int x1 = min((int)(r.y & 0xFFFF), px0 + TS - 1) - px0;
             const int y1 = min((int)(r.y >> 16), py0 + TS - 1) - py0;
             if (x0 > x1 || y0 > y1) return false;
-            if (!source_record(R.again(), vis_src[k], pr)) return false;
-            pr.g1.w = (uint32_t)x0 | ((uint32_t)y0 << 8) | ((uint32_t)(x1 - x0 + 1) << 16) |
+            e.x = vb.vis_src[k];
+            e.y = (uint32_t)x0 | ((uint32_t)y0 << 8) | ((uint32_t)(x1 - x0 + 1) << 16) |
                       ((uint32_t)(y1 - y0 + 1) << 24);
             return true;
         };
@@ -403,7 +398,7 @@ __device__ __forceinline__ void resolve_tile(JobRef R, int t, uint32_t n, uint64
         // A list's next chunk is loaded while this one is resolved; the
         // overflow path loads each chunk when it starts.
         uint2 nxt = make_uint2(0u, 0u);
-        bool nxt_ok = !kTail && (uint64_t)tid < nsrc;
+        bool nxt_ok = !over && (uint64_t)tid < nsrc;
         if (nxt_ok) nxt = list[o + tid];
         __syncthreads();
         // record cull against the block depths: its nearest possible depth
@@ -627,7 +622,7 @@ __device__ __forceinline__ void resolve_tile(JobRef R, int t, uint32_t n, uint64
         // Layered lists (resident scenes) run front to back by layer: once
         // every record from a layer on lies behind all block depths of the
         // tile, the rest of the list is culled whole, unread.
-        const uint32_t L = kTail || stats || n <= (uint32_t)kChunk ? 1u : bb.layers;   // one chunk: nothing to stop
+        const uint32_t L = over || stats || n <= (uint32_t)kChunk ? 1u : bb.layers;   // one chunk: nothing to stop
         if (L > 1 && wave == 0) {
             uint32_t zr = lane < (int)L ? ctr->layer_zlo[phase == kPhaseRest ? 1 : 0][lane] : 0x7F800000u;
 #pragma unroll
@@ -660,15 +655,13 @@ __device__ __forceinline__ void resolve_tile(JobRef R, int t, uint32_t n, uint64
             }
             PrimRec pr;
             bool have;
-            if constexpr (kTail) {
-                have = base + tid < nsrc && fetch_overflow(base + tid, pr);
-            } else {
-                const uint2 e = nxt;
-                have = nxt_ok && source_record(R.again(), e.x, pr);
-                pr.g1.w = e.y;
-                nxt_ok = base + kChunk + tid < nsrc;
-                if (nxt_ok) nxt = list[o + base + kChunk + tid];
-            }
+            uint2 e = nxt;
+            if (over) have = base + tid < nsrc && fetch_overflow(base + tid, e);
+            else have = nxt_ok;
+            have = have && source_record(R.again(), e.x, pr);
+            pr.g1.w = e.y;
+            nxt_ok = !over && base + kChunk + tid < nsrc;
+            if (nxt_ok) nxt = list[o + base + kChunk + tid];
             bool keep = false;
             uint32_t area = 0;
             float zc = INFINITY;
@@ -880,22 +873,22 @@ __device__ __forceinline__ void refine_tile(JobRef R, int t, unsigned long long*
 // costly tiles lie together, around the footprints of the nearest atoms:
 // contiguous tile ranges per XCD left one XCD with most of them (20 % longer
 // on the whole-cell frame).  A tile whose list overflowed the bins
-// is left to the tail launch: it is appended to `ovf` (job << 32 | tile).
+// is rebuilt from the visible lists by the same code: a second launch for
+// those tiles costs every frame that has none 1.4 to 2 us (4,096 atoms at
+// 256x256: 53.1 us with it, 51.7 without; 1M atoms and bonds at 1080p: 172.9
+// and 170.2; four views in a batch: 179.1 and 173.7).
 // kCount: the instantiation that can count fragments (jobs with
 // VTX_FLAG_STATS); the other one carries no counters.
 // kPhase: one pass, or one of a two-pass frame's.
 template <int TS, class JS, bool kCount, int kPhase>
-__global__ void __launch_bounds__(kBlock, kCount ? 1 : 7) k_resolve(JS js, unsigned long long* ovf, uint32_t* ovf_n) {
+__global__ void __launch_bounds__(kBlock, kCount ? 1 : 7) k_resolve(JS js) {
     uint32_t tu;
     const int ji = js.find(blockIdx.x, tu);
     if (ji < 0) return;
     const Job& J = js.job(ji);
     const uint32_t n = J.bb.tile_cnt[tu];
     const uint64_t o = J.bb.tile_off[tu];
-    if (o + n > J.bb.capacity) {
-        if (threadIdx.x == 0) ovf[atomicAdd(ovf_n, 1u)] = ((unsigned long long)ji << 32) | tu;
-        return;
-    }
+    const bool over = o + n > J.bb.capacity;
     if (kPhase == kPhaseAll && n == 0) {   // nothing to cast or to re-arm: background
         const int W = J.F.W, H = J.F.H, tiles_x = J.F.tiles_x;
         const int px0 = ((int)tu % tiles_x) * TS, py0 = ((int)tu / tiles_x) * TS;
@@ -917,100 +910,67 @@ __global__ void __launch_bounds__(kBlock, kCount ? 1 : 7) k_resolve(JS js, unsig
             return;
         }
     }
-    resolve_tile<TS, kCount, false, kPhase>(job_ref(js, ji), (int)tu, n, o, keys);
+    resolve_tile<TS, kCount, kPhase>(job_ref(js, ji), (int)tu, n, o, over, keys);
 }
 
-// Tail launch (a fixed grid, queued right after the main one): resolves the
-// overflowed tiles the main launch listed, then its last workgroup clears the
-// list and publishes the fragment counters of every counting job.  Keeping the
-// rare overflow path out of the main instantiation keeps its register budget.
-template <int TS, class JS, bool kCount, int kPhase>
-__global__ void __launch_bounds__(kBlock) k_resolve_tail(JS js, const unsigned long long* ovf, uint32_t* ovf_n) {
-    __shared__ unsigned long long keys[TS * TS];
-    const uint32_t total = *(volatile uint32_t*)ovf_n;
-    // Nothing overflowed (the usual frame): nothing to clear or publish, and
-    // no fences.  The count is the same for every workgroup (it is cleared
-    // only after all of them have taken a ticket, which none does here).
-    if (!kCount && total == 0) return;
-    for (uint32_t e = blockIdx.x; e < total; e += gridDim.x) {
-        const unsigned long long v = ovf[e];
-        const Job& J = js.job((int)(v >> 32));
-        const int t = (int)(v & 0xFFFFFFFFull);
-        resolve_tile<TS, kCount, true, kPhase>(job_ref(js, (int)(v >> 32)), t, J.bb.tile_cnt[t], J.bb.tile_off[t], keys);
-        __syncthreads();   // the next tile reuses the LDS
-    }
-    if (threadIdx.x == 0) {
-        __threadfence();
-        const unsigned int ticket = atomicAdd(&ovf_n[1], 1u);
-        if (ticket == gridDim.x - 1) {
-            __threadfence();
-            ovf_n[0] = 0;
-            ovf_n[1] = 0;
-            if (kCount) {
-                for (uint32_t j = 0; j < js.count(); ++j) {
-                    const Job& Jj = js.job((int)j);
-                    if (!(Jj.F.flags & (1u | 16u)) || !Jj.bb.host_ctr) continue;
-                    const volatile Counters* src = Jj.bb.ctr;
-                    Jj.bb.host_ctr->frag_tested = src->frag_tested;
-                    Jj.bb.host_ctr->frag_hit = src->frag_hit;
-                    Jj.bb.host_ctr->frag_hit_bond = src->frag_hit_bond;
-                    Jj.bb.host_ctr->frag_tested_bond = src->frag_tested_bond;
-                    Jj.bb.host_ctr->frag_skipped = src->frag_skipped;
-                    Jj.bb.host_ctr->rec_culled = src->rec_culled;
-                    Jj.bb.host_ctr->lists_stopped = src->lists_stopped;
-                    Jj.bb.host_ctr->chunks_stopped = src->chunks_stopped;
-                }
-            }
-            __threadfence_system();
-        }
+// Counting frames: the resolve's fragment counters, to every counting job's
+// host buffer (one workgroup, queued after the resolve).
+template <class JS>
+__global__ void __launch_bounds__(kBlock) k_publish(JS js) {
+    for (uint32_t j = threadIdx.x; j < js.count(); j += kBlock) {
+        const Job& J = js.job((int)j);
+        if (!(J.F.flags & (1u | 16u)) || !J.bb.host_ctr) continue;
+        const Counters* const src = J.bb.ctr;
+        J.bb.host_ctr->frag_tested = src->frag_tested;
+        J.bb.host_ctr->frag_hit = src->frag_hit;
+        J.bb.host_ctr->frag_hit_bond = src->frag_hit_bond;
+        J.bb.host_ctr->frag_tested_bond = src->frag_tested_bond;
+        J.bb.host_ctr->frag_skipped = src->frag_skipped;
+        J.bb.host_ctr->rec_culled = src->rec_culled;
+        J.bb.host_ctr->lists_stopped = src->lists_stopped;
+        J.bb.host_ctr->chunks_stopped = src->chunks_stopped;
     }
 }
-
 
 }  // namespace
 
 template <int TS, class JS, bool kCount, int kPhase>
-hipError_t resolve_pass(const JS& js, unsigned g, unsigned long long* ovf, uint32_t* ovf_n, hipStream_t stream) {
-    const hipError_t e = dispatch(k_resolve<TS, JS, kCount, kPhase>, g, kBlock, 0, stream, js, ovf, ovf_n);
-    if (e) return e;
-    return dispatch(k_resolve_tail<TS, JS, kCount, kPhase>, kTailBlocks, kBlock, 0, stream, js,
-                    (const unsigned long long*)ovf, ovf_n);
+hipError_t resolve_pass(const JS& js, unsigned g, hipStream_t stream) {
+    const hipError_t e = dispatch(k_resolve<TS, JS, kCount, kPhase>, g, kBlock, 0, stream, js);
+    if (e || !kCount) return e;
+    return dispatch(k_publish<JS>, 1, kBlock, 0, stream, js);
 }
 
 template <int TS, class JS, bool kCount>
-hipError_t resolve_launch(const JS& js, int phase, unsigned g, unsigned long long* ovf, uint32_t* ovf_n,
-                          hipStream_t stream) {
+hipError_t resolve_launch(const JS& js, int phase, unsigned g, hipStream_t stream) {
     if constexpr (!kCount && TS >= kHzCell) {
-        if (phase == kPhaseFront) return resolve_pass<TS, JS, false, kPhaseFront>(js, g, ovf, ovf_n, stream);
-        if (phase == kPhaseRest) return resolve_pass<TS, JS, false, kPhaseRest>(js, g, ovf, ovf_n, stream);
+        if (phase == kPhaseFront) return resolve_pass<TS, JS, false, kPhaseFront>(js, g, stream);
+        if (phase == kPhaseRest) return resolve_pass<TS, JS, false, kPhaseRest>(js, g, stream);
     }
-    return resolve_pass<TS, JS, kCount, kPhaseAll>(js, g, ovf, ovf_n, stream);
+    return resolve_pass<TS, JS, kCount, kPhaseAll>(js, g, stream);
 }
 
 template <class JS, bool kCount>
-hipError_t resolve_impl(const JS& js, int tile, int phase, uint32_t grid, unsigned long long* ovf, uint32_t* ovf_n,
-                        hipStream_t stream) {
+hipError_t resolve_impl(const JS& js, int tile, int phase, uint32_t grid, hipStream_t stream) {
     if (grid == 0) return hipSuccess;
     if (phase != kPhaseAll && (kCount || tile < kHzCell)) return hipErrorInvalidValue;
     const unsigned g = (unsigned)xcd_grid((int)grid);
     switch (tile) {
-        case 8: return resolve_launch<8, JS, kCount>(js, phase, g, ovf, ovf_n, stream);
-        case 16: return resolve_launch<16, JS, kCount>(js, phase, g, ovf, ovf_n, stream);
-        case 32: return resolve_launch<32, JS, kCount>(js, phase, g, ovf, ovf_n, stream);
-        case 64: return resolve_launch<64, JS, kCount>(js, phase, g, ovf, ovf_n, stream);
+        case 8: return resolve_launch<8, JS, kCount>(js, phase, g, stream);
+        case 16: return resolve_launch<16, JS, kCount>(js, phase, g, stream);
+        case 32: return resolve_launch<32, JS, kCount>(js, phase, g, stream);
+        case 64: return resolve_launch<64, JS, kCount>(js, phase, g, stream);
         default: return hipErrorInvalidValue;
     }
 }
 
-hipError_t launch_resolve(const OneJob& js, int tile, int phase, uint32_t grid, bool count, unsigned long long* ovf,
-                          uint32_t* ovf_n, hipStream_t stream) {
-    return count ? resolve_impl<OneJob, true>(js, tile, phase, grid, ovf, ovf_n, stream)
-                 : resolve_impl<OneJob, false>(js, tile, phase, grid, ovf, ovf_n, stream);
+hipError_t launch_resolve(const OneJob& js, int tile, int phase, uint32_t grid, bool count, hipStream_t stream) {
+    return count ? resolve_impl<OneJob, true>(js, tile, phase, grid, stream)
+                 : resolve_impl<OneJob, false>(js, tile, phase, grid, stream);
 }
-hipError_t launch_resolve(const JobList& js, int tile, int phase, uint32_t grid, bool count, unsigned long long* ovf,
-                          uint32_t* ovf_n, hipStream_t stream) {
-    return count ? resolve_impl<JobList, true>(js, tile, phase, grid, ovf, ovf_n, stream)
-                 : resolve_impl<JobList, false>(js, tile, phase, grid, ovf, ovf_n, stream);
+hipError_t launch_resolve(const JobList& js, int tile, int phase, uint32_t grid, bool count, hipStream_t stream) {
+    return count ? resolve_impl<JobList, true>(js, tile, phase, grid, stream)
+                 : resolve_impl<JobList, false>(js, tile, phase, grid, stream);
 }
 
 }  // namespace vtx

@@ -102,7 +102,7 @@ struct SampleKernel {
 
 // Device-side counters of one frame.  The scatter's first workgroup
 // publishes the binning counters to host-mapped memory; on counting frames
-// the resolve's tail launch publishes the fragment counters.
+// a counting frame's k_publish publishes the fragment counters.
 struct Counters {
     unsigned int vis_count;
     unsigned int overflow;
@@ -713,13 +713,10 @@ hipError_t launch_tile_offsets(const OneJob& js, hipStream_t stream);
 hipError_t launch_tile_offsets(const JobList& js, hipStream_t stream);
 hipError_t launch_scatter(const OneJob& js, int phase, uint32_t grid, int max_tiles, hipStream_t stream);
 hipError_t launch_scatter(const JobList& js, int phase, uint32_t grid, int max_tiles, hipStream_t stream);
-// The resolve is a main launch plus a small tail launch for the tiles whose
-// lists overflowed: `ovf` holds at least `grid` entries and ovf_n two zeroed
-// counters (both left zeroed again).
-hipError_t launch_resolve(const OneJob& js, int tile, int phase, uint32_t grid, bool count, unsigned long long* ovf,
-                          uint32_t* ovf_n, hipStream_t stream);
-hipError_t launch_resolve(const JobList& js, int tile, int phase, uint32_t grid, bool count, unsigned long long* ovf,
-                          uint32_t* ovf_n, hipStream_t stream);
+// One workgroup per tile; with `count`, a second launch publishes the
+// fragment counters.
+hipError_t launch_resolve(const OneJob& js, int tile, int phase, uint32_t grid, bool count, hipStream_t stream);
+hipError_t launch_resolve(const JobList& js, int tile, int phase, uint32_t grid, bool count, hipStream_t stream);
 // Supersampled render: output pixel (x, y) of W x H from its S x S samples
 // of the (S W) x (S H) images (channel means rounded half up, nearest
 // (depth, id)).
