@@ -365,36 +365,21 @@ __global__ void __launch_bounds__(kBinThreads) k_layers(JS js) {
 // 2^28, and adding at most a workgroup's pairs keeps the flag bit set.
 constexpr uint32_t kNoRun = 0x80000000u;
 
-// List offsets: the exclusive prefix sum of the tile counts, once per job
-// (work block j of the launch scans job j's counts), with the list total and
-// the overflow flag in the frame counters.  The counts are read as up to
-// kMaxLdsTiles / 1024 rows of 1024 consecutive tiles, every load issued
+// Exclusive prefix sum of the counts of T <= kRows * 1024 tiles by one
+// workgroup: put(t, start, count) for every tile, and the list total.  The
+// counts are read as kRows rows of 1024 consecutive tiles, every load issued
 // before the first is used (coalesced, all in flight); each wave scans its
 // 64 lanes of every row with DPP steps, and one wave scans the (row, wave)
 // totals, which gives every (row, wave) its start.
-template <class JS>
-__global__ void __launch_bounds__(kBinThreads) k_tile_offsets(JS js) {
-    constexpr int kRows = (kMaxLdsTiles + kBinThreads - 1) / kBinThreads;
+template <int kRows, class Put>
+__device__ __forceinline__ unsigned long long tile_starts(const uint32_t (&v)[kRows], int T, Put put) {
     constexpr int kWaves = kBinThreads / 64;
     constexpr int kPre = (kRows * kWaves + 63) / 64;
     __shared__ uint32_t wsum[kRows][kWaves];
     __shared__ unsigned long long wpre[kRows * kWaves + 1];
-    __shared__ uint32_t over_sum;
-    if (blockIdx.x >= js.count()) return;
-    const Job& J = js.job((int)blockIdx.x);
-    const int T = J.F.tiles_x * J.F.tiles_y;
-    const uint32_t* __restrict__ const cnt = J.bb.tile_cnt;
-    uint64_t* __restrict__ const off = J.bb.tile_off;
     const int tid = threadIdx.x, lane = __lane_id(), wave = tid >> 6;
     const int rows = (T + kBinThreads - 1) / kBinThreads;
-    uint32_t v[kRows], incl[kRows];
-    uint32_t n_over = 0;
-    if (tid == 0) over_sum = 0;
-#pragma unroll
-    for (int r = 0; r < kRows; ++r) {
-        const int t = r * kBinThreads + tid;
-        v[r] = r < rows && t < T ? cnt[t] : 0u;
-    }
+    uint32_t incl[kRows];
 #pragma unroll
     for (int r = 0; r < kRows; ++r) {
         incl[r] = wave_scan_u32(v[r]);
@@ -432,21 +417,51 @@ __global__ void __launch_bounds__(kBinThreads) k_tile_offsets(JS js) {
     for (int r = 0; r < kRows; ++r) {
         if (r >= rows) break;
         const int t = r * kBinThreads + tid;
-        if (t < T) {
-            const uint64_t o = wpre[r * kWaves + wave] + (incl[r] - v[r]);
-            off[t] = o;
-            n_over += o + v[r] > J.bb.capacity ? 1u : 0u;   // lists the scatter leaves out
-        }
+        if (t < T) put(t, (uint64_t)(wpre[r * kWaves + wave] + (incl[r] - v[r])), v[r]);
     }
-    const unsigned long long base = wpre[kRows * kWaves];
-    for (int o = 32; o > 0; o >>= 1) n_over += (uint32_t)__shfl_xor((int)n_over, o);
-    if (lane == 0 && n_over) atomicAdd(&over_sum, n_over);
+    return wpre[kRows * kWaves];
+}
+
+// The frame counters of a job's lists: their total, whether it passes the
+// capacity, and how many tiles' lists do (n_over, per thread; the scatter
+// leaves those out).  The whole workgroup.
+__device__ __forceinline__ void publish_lists(const Job& J, unsigned long long total, uint32_t n_over) {
+    __shared__ uint32_t over_sum;
+    if (threadIdx.x == 0) over_sum = 0;
     __syncthreads();
-    if (tid == 0) {
-        J.bb.ctr->pairs = base;
-        J.bb.ctr->overflow = base > J.bb.capacity ? 1u : 0u;
+    for (int o = 32; o > 0; o >>= 1) n_over += (uint32_t)__shfl_xor((int)n_over, o);
+    if (__lane_id() == 0 && n_over) atomicAdd(&over_sum, n_over);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        J.bb.ctr->pairs = total;
+        J.bb.ctr->overflow = total > J.bb.capacity ? 1u : 0u;
         J.bb.ctr->overflow_tiles = over_sum;
     }
+}
+
+// List offsets in a launch of their own, one workgroup per job, for images
+// of more tiles than the scatter scans (see scatter_scans).
+template <class JS>
+__global__ void __launch_bounds__(kBinThreads) k_tile_offsets(JS js) {
+    constexpr int kRows = (kMaxLdsTiles + kBinThreads - 1) / kBinThreads;
+    if (blockIdx.x >= js.count()) return;
+    const Job& J = js.job((int)blockIdx.x);
+    const int T = J.F.tiles_x * J.F.tiles_y;
+    const uint32_t* __restrict__ const cnt = J.bb.tile_cnt;
+    uint64_t* __restrict__ const off = J.bb.tile_off;
+    const uint64_t capacity = J.bb.capacity;
+    uint32_t v[kRows];
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+        const int t = r * kBinThreads + (int)threadIdx.x;
+        v[r] = t < T ? cnt[t] : 0u;
+    }
+    uint32_t n_over = 0;
+    const unsigned long long total = tile_starts<kRows>(v, T, [&](int t, uint64_t o, uint32_t n) {
+        off[t] = o;
+        n_over += o + n > capacity ? 1u : 0u;
+    });
+    publish_lists(J, total, n_over);
 }
 
 // Scatter.  Every workgroup reserves, for each tile its primitives touch,
@@ -457,11 +472,15 @@ __global__ void __launch_bounds__(kBinThreads) k_tile_offsets(JS js) {
 // atomic per run, in one instruction for the wave).  Primitives spanning
 // several tiles take one LDS atomic per tile.  Workgroup 0 also publishes
 // the frame counters.
+// kScan (see scatter_scans): every workgroup scans the tile counts for itself
+// while its reservations are in flight, and workgroup 0 stores the offsets
+// for the resolve.
 constexpr int kScatterPer = 4;
+constexpr int kScanTiles = 8 * kBinThreads;
 
-template <class JS>
+template <class JS, bool kScan>
 __global__ void __launch_bounds__(kBinThreads, 8) k_scatter(JS js, int phase) {
-    constexpr int kTileRows = (kMaxLdsTiles + kBinThreads - 1) / kBinThreads;
+    constexpr int kTileRows = ((kScan ? kScanTiles : kMaxLdsTiles) + kBinThreads - 1) / kBinThreads;
     extern __shared__ uint32_t cur[];
     uint32_t blk;
     const int ji = js.find(blockIdx.x, blk);
@@ -474,7 +493,7 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_scatter(JS js, int phase) {
     const global_t<const uint32_t>* __restrict__ const vis_cnt = to_global(J.bb.vis_cnt);
     const global_t<const uint32_t>* __restrict__ const hist_in = to_global(J.bb.hist);
     const global_t<const uint32_t>* __restrict__ const cnt = to_global(J.bb.tile_cnt);
-    const global_t<const uint64_t>* __restrict__ const off = to_global(J.bb.tile_off);
+    global_t<uint64_t>* __restrict__ const off = to_global(J.bb.tile_off);
     global_t<uint2>* __restrict__ const list = to_global(J.bb.list);
     const uint64_t capacity = J.bb.capacity;
     Counters* const ctr = J.bb.ctr;
@@ -496,21 +515,39 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_scatter(JS js, int phase) {
         const uint32_t bx0 = box.x & 0xFFFFu, by0 = box.x >> 16, bx1 = box.y & 0xFFFFu, by1 = box.y >> 16;
         const int bw = bx0 <= bx1 ? (int)(bx1 - bx0) + 1 : 0, nb = bw * (bw ? (int)(by1 - by0) + 1 : 0);
         uint32_t h[kTileRows], r[kTileRows];
+        uint32_t v[kScan ? kTileRows : 1];
 #pragma unroll
         for (int q = 0; q < kTileRows; ++q) {
             const int i = q * kBinThreads + tid;
             h[q] = i < nb ? row[i] : 0u;
+            if constexpr (kScan) v[q] = i < T ? cnt[i] : 0u;
         }
 #pragma unroll
         for (int q = 0; q < kTileRows; ++q) {
             const int i = q * kBinThreads + tid;
             r[q] = h[q] ? atomicAdd(&fill[box_tile(F.tiles_x, bx0, by0, bw, i)], h[q]) : 0u;
         }
+        if constexpr (kScan) {
+            uint32_t n_over = 0;
+            const unsigned long long total = tile_starts<kTileRows>(v, T, [&](int t, uint64_t o, uint32_t n) {
+                const bool fits = o + n <= capacity;
+                cur[t] = fits ? (uint32_t)o : kNoRun;
+                if (lead) off[t] = o;
+                n_over += fits ? 0u : 1u;
+            });
+            if (lead) publish_lists(J, total, n_over);
+            __syncthreads();   // every tile's start is in LDS
+        }
 #pragma unroll
         for (int q = 0; q < kTileRows; ++q) {
             const int i = q * kBinThreads + tid;
             if (i >= nb) break;
             const int t = box_tile(F.tiles_x, bx0, by0, bw, i);
+            if constexpr (kScan) {
+                const uint32_t run = cur[t];
+                if (h[q] && run != kNoRun) cur[t] = run + (loff ? loff[t] : 0u) + r[q];
+                continue;
+            }
             const uint64_t run = off[t];
             const bool fits = run + cnt[t] <= capacity;   // else the resolve rebuilds this tile from the visible lists
             cur[t] = h[q] && fits ? (uint32_t)(run + (loff ? loff[t] : 0u) + r[q]) : kNoRun;
@@ -519,8 +556,8 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_scatter(JS js, int phase) {
     if (lead) {
         if (tid == 0) {
             const unsigned int vis = ctr->vis_count, bad = ctr->bad_bonds;
-            const unsigned long long total = ctr->pairs;
-            const unsigned int n_over = ctr->overflow_tiles;   // from k_tile_offsets
+            const unsigned long long total = ctr->pairs;   // from publish_lists
+            const unsigned int n_over = ctr->overflow_tiles;
             ctr->vis_count = 0;            // the next frame's count kernel adds to these
             ctr->bad_bonds = 0;
             ctr->frag_tested = 0;          // this frame's resolve adds to these
@@ -693,11 +730,24 @@ hipError_t count_impl(const JS& js, BinForm form, int phase, uint32_t grid, int 
     return dispatch(k_count<JS, true, false, true>, grid, kBinThreads, lds, stream, js, phase);
 }
 
+// The scatter's workgroups each scan the tile counts, instead of a launch of
+// one workgroup per job before it: the counts come from L2 while the
+// reservations are in flight, which costs less than the launch's 4 to 5 us on
+// small frames (4,096 atoms at 256x256: 51.5 us with the launch, 48.3
+// without; 1M atoms and bonds at 1080p: 170.2 and 167.1) and as much on large
+// ones (11M spheres at 4K, 2,048 workgroups: 640 both; 256 renders of 50,000
+// atoms: 9,430 to 9,445 both).  Past kScanTiles the counts no longer fit the
+// scatter's 64 registers beside the reservations (16 rows spill 49).
+bool scatter_scans(int max_tiles) { return max_tiles <= kScanTiles; }
+
 template <class JS>
 hipError_t scatter_impl(const JS& js, int phase, uint32_t grid, int max_tiles, hipStream_t stream) {
     if (max_tiles > kMaxLdsTiles) return hipErrorInvalidValue;
     if (grid == 0) return hipSuccess;
-    return dispatch(k_scatter<JS>, grid, kBinThreads, (uint32_t)(max_tiles * sizeof(uint32_t)), stream, js, phase);
+    const uint32_t lds = (uint32_t)(max_tiles * sizeof(uint32_t));
+    if (scatter_scans(max_tiles))
+        return dispatch(k_scatter<JS, true>, grid, kBinThreads, lds, stream, js, phase);
+    return dispatch(k_scatter<JS, false>, grid, kBinThreads, lds, stream, js, phase);
 }
 
 hipError_t launch_count(const OneJob& js, BinForm form, int phase, uint32_t grid, int max_tiles, hipStream_t stream) {
@@ -712,10 +762,12 @@ hipError_t launch_layers(const OneJob& js, uint32_t grid, hipStream_t stream) {
 hipError_t launch_layers(const JobList& js, uint32_t grid, hipStream_t stream) {
     return dispatch(k_layers<JobList>, grid, kBinThreads, 0, stream, js);
 }
-hipError_t launch_tile_offsets(const OneJob& js, hipStream_t stream) {
+hipError_t launch_tile_offsets(const OneJob& js, int max_tiles, hipStream_t stream) {
+    if (scatter_scans(max_tiles)) return hipSuccess;
     return dispatch(k_tile_offsets<OneJob>, 1, kBinThreads, 0, stream, js);
 }
-hipError_t launch_tile_offsets(const JobList& js, hipStream_t stream) {
+hipError_t launch_tile_offsets(const JobList& js, int max_tiles, hipStream_t stream) {
+    if (scatter_scans(max_tiles)) return hipSuccess;
     return dispatch(k_tile_offsets<JobList>, js.n, kBinThreads, 0, stream, js);
 }
 hipError_t launch_scatter(const OneJob& js, int phase, uint32_t grid, int max_tiles, hipStream_t stream) {

@@ -163,3 +163,25 @@ def test_stored_order_binning_equals_clusters(vtx, ctx, n, size, representation)
         assert_identical(a, b, "stored and clusters")
     assert_identical(out[0][0], out[0][2], "batch and single")
     rs.close()
+
+
+@pytest.mark.parametrize("size", [(8, 8), (1016, 64), (1024, 64), (1032, 64), (1024, 512), (1032, 512)])
+@pytest.mark.parametrize("capacity", [0, 3000])
+def test_list_offsets_at_the_edges_of_their_scan(vtx, size, capacity):
+    """Up to 8192 tiles the scatter scans the tile counts itself, in rows of
+    1024: the image is the one of 64-pixel tiles (at most 144 of them), also
+    where part of the lists overflows."""
+    import torch
+    wl = workload(20_000, True, *size)
+    ds = vtx.DeviceScene(wl.scene)
+    s = torch.cuda.Stream()
+    out = {}
+    for tile in (64, 8):
+        vtx.vtx_set_bin_capacity(capacity if tile == 8 else 0, s)
+        opts = dataclasses.replace(wl.options, tile_size=tile)
+        out[tile] = run_render(vtx, ds, wl.camera, opts, *size, stream=s)
+        st = vtx.vtx_read_stats(s)
+        if tile == 8:
+            assert (st["overflow_tiles"] > 0) == (0 < capacity < st["pairs"]), st
+    vtx.vtx_set_bin_capacity(0, s)
+    assert_identical(out[8], out[64], "8-pixel tiles")
