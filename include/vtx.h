@@ -228,9 +228,9 @@ typedef struct vtx_stats {
     uint64_t fragments_tested_bond; /* of the ray tests, those on bond cylinders */
     /* VTX_FLAG_COUNT frames: the depth early-outs of the resolve */
     uint64_t fragments_skipped; /* footprint pixels not ray-tested: the pixel held a nearer hit */
-    uint64_t records_culled;   /* tile-list records dropped whole: behind every 4x4 block under them */
+    uint64_t records_culled;   /* tile-list records dropped whole: behind all that the pixels under them hold */
     uint64_t lists_stopped;    /* tile lists ended early: every layer left lay behind the tile */
-    uint64_t chunks_stopped;   /* depth-ordered chunks ended early by their depth-bucket bound */
+    uint64_t chunks_stopped;   /* depth-ordered chunks whose farthest records were dropped whole */
 } vtx_stats;
 
 /* Average device time per kernel of the frames rendered with VTX_FLAG_TIMING. */

@@ -18,9 +18,9 @@
 // Depth early-outs, all conservative (statistics frames switch them off):
 // a record whose nearest possible depth lies behind everything the 4x4-pixel
 // blocks under its footprint hold is dropped; a fragment whose pixel holds a
-// nearer hit is skipped; chunks of large footprints run front to back in
-// small sub-chunks and end once the depth bucket they reached lies behind the
-// whole tile; a resident scene's list, ordered front to back by layers, ends
+// nearer hit is skipped; chunks of large footprints run front to back, each
+// 8x8-pixel block on its own, without the records behind everything the block
+// holds; a resident scene's list, ordered front to back by layers, ends
 // once every layer left lies behind the whole tile.
 #include "prims.h"
 
@@ -31,10 +31,19 @@ namespace {
 constexpr int kChunk = kBlock;
 constexpr int kBuckets = 64;      // depth buckets of the front-to-back record order
 static_assert(kBuckets <= 64, "one wave scans and searches the buckets");
-constexpr int kSortArea = 64;     // order a chunk when its kept records average more pixels than this
+// A chunk is ordered and resolved by blocks (resolve_blocks) when its kept
+// records average more than kSortArea pixels and cover the tile more than
+// kSortDepth times: a block's wave spends a pass of 64 lanes on a record
+// however few of its pixels the footprint has, which pays only where the
+// order hides records behind it.  kSortArea 20 to 40 measure the same on
+// spheres (4,096 at 256x256, 16-pixel tiles: 9.9 us of resolve; 64: 22); on
+// bonds small areas lose (107,500 atoms with bonds at 1080p: 58 us with 32,
+// 69 to 79 with 16; 1M dust with bonds: 96 with 32, 103 with 16, 153 with 8).
+// kSortDepth 2, 4, 8: 191, 192, 207 us on 11M spheres at 4K.
+constexpr int kSortArea = 32;
+constexpr int kSortDepth = 2;
 constexpr int kKeptShift = 21;    // packed scan: footprint area (<= 256 * 64 * 64) below, kept count above
 constexpr uint32_t kAreaMask = (1u << kKeptShift) - 1u;
-constexpr int kLaterSub = 8;      // records per depth-ordered sub-chunk after the first (4 to 64, a power of 2)
 static_assert(kBlock == kChunk, "one 64-slot window per wave in the order array");
 template <int TS>
 struct HzGrid {
@@ -49,12 +58,6 @@ struct Rec {
     uint32_t rect;     // tile-local x0 | y0 << 8 | w << 16 | h << 24
     float inv_w;       // 1 / w (hardware reciprocal): splits a footprint offset into row and column
 };
-
-__device__ inline float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-    return v;
-}
 
 // Inclusive max-scan over the 64 lanes of a wave by DPP row shifts and row
 // broadcasts (lanes shifted in from outside a row read 0, the identity).
@@ -515,109 +518,108 @@ __device__ __forceinline__ void resolve_tile(JobRef R, int t, uint32_t n, uint64
             }
             __syncthreads();
         };
-        // The kept records of a chunk in depth order (ord), resolved `sub`
-        // at a time, front to back.  Every wave culls the sub-chunk against
-        // the block depths (2 or 4 lanes per record; all waves read the same
-        // depths, so they agree) and takes the prefix of the survivors'
-        // footprints in its own slots; the workgroup resolves their
-        // fragments, then refreshes the blocks under them before the next
-        // sub-chunk is culled.
-        // zlo, bstep: the depth buckets' origin and width (bucket b holds cull
-        // depths from zlo + b * bstep on; bstep 0: one bucket)
-        auto resolve_sorted = [&](uint32_t nk, int sub0, bool more, float zlo, float bstep) {
-            // All waves compute the same prefix (from the same block depths),
-            // so they share one array, the chunk's prefix, which is no longer
-            // needed: every wave writes it whole before reading it.
-            uint32_t* const wp = pref;
-            uint32_t rbase = 0;
-            for (uint32_t sc = 0; rbase < nk; ++sc) {
-                if (sc > 0) {
-                    // every record from rbase on lies in rbase's bucket or a later
-                    // one: once that bucket's start (less a rounding margin) is
-                    // behind every block depth of the tile, all of them would be
-                    // culled.  Every wave reads the same LDS: a uniform decision.
-                    const unsigned long long in = __ballot(lane < kBuckets && bbase[lane] <= rbase);
-                    const float zb = fmaf((float)(63 - __clzll((long long)in)), bstep, zlo);
-                    const float bound = zb - 1e-5f * (fabsf(zlo) + fabsf(zb));
-                    uint32_t mt = 0;
-                    for (int b = lane; b < kHzBlocks; b += 64) mt = max(mt, hz[b]);
-                    mt = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_max(mt), 63);
-                    if (bound > 0.0f && __float_as_uint(bound) > mt) {
-                        if (counting && tid == 0) ++n_chunk_stop;
-                        break;
+        // The kept records of a chunk in depth order (ord), resolved by 8x8
+        // blocks: a wave holds a block's depth buffer in registers, one pixel
+        // per lane, and takes the records whose footprint meets the block
+        // front to back, one at a time, on the pixels that lie in the
+        // footprint and hold nothing nearer.  After each hit the records
+        // behind the block's farthest depth leave the wave's list at once.
+        // Nothing is shared until the chunk is done, so no wave waits for
+        // another, no pixel is searched for its record and no depth goes
+        // through an atomic; the rays' reciprocals are taken once per pixel.
+        // VALU-bound on batches.  Dealing the fragments of 8 records at a
+        // time to the whole workgroup, with a barrier on both sides of a
+        // refresh of 4x4 block depths, took (resolve of 4,096 spheres at
+        // 256x256 / 11M at 4K / 256 renders of 50,000) 22 us / 275 us / 4.01
+        // ms; this takes 10 / 191 / 3.21.  Looking at the farthest depth only
+        // after every 8th record: 4.47 ms, 4th: 4.32; of each 4x4 quarter:
+        // 3.84 against 3.40; record data through scalar registers instead of
+        // one LDS read the lanes share: 3.34 against 3.24.
+        auto resolve_blocks = [&](uint32_t nk) {
+            constexpr int kSide = TS / 8;
+            for (int b = wave; b < kSide * kSide; b += kBlock / 64) {
+                const int by = b / kSide, bx = (b + by) % kSide;   // a wave's blocks lie on diagonals
+                if (bx * 8 >= tw || by * 8 >= th) continue;
+                const int lx = bx * 8 + (lane & 7), ly = by * 8 + (lane >> 3);
+                const bool in = lx < tw && ly < th;
+                const int slot = ly * TS + lx;
+                unsigned long long cur = in ? keys[slot] : 0ull;   // outside the image: nothing is nearer
+                const float ndx = fmaf((float)(px0 + lx) + 0.5f, F.inv_w2, -1.0f);
+                const float ndy = fmaf(-((float)(py0 + ly) + 0.5f), F.inv_h2, 1.0f);
+                float ox, oy, Dx, Dy;
+                if (persp) {
+                    ox = 0.f; oy = 0.f; Dx = ndx * F.txf; Dy = ndy * F.tyf;
+                } else {
+                    ox = ndx * F.hxf; oy = ndy * F.hyf; Dx = 0.f; Dy = 0.f;
+                }
+                // farthest depth the block holds (all ones while a pixel is empty)
+                auto block_max = [&]() -> uint32_t {
+                    return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_max((uint32_t)(cur >> 32)), 63);
+                };
+                for (uint32_t base = 0; base < nk; base += 64) {
+                    const uint32_t zmax0 = block_max();
+                    const uint32_t i = base + (uint32_t)lane;
+                    // this lane's record: its pixels of the block (bit = lane)
+                    unsigned long long m = 0ull;
+                    uint32_t rj = 0, rid = 0, zcb = 0;
+                    if (i < nk) {
+                        rj = ord[i];
+                        const Rec& r = rec_at(rj);
+                        zcb = r.zcull > 0.0f ? __float_as_uint(r.zcull) : 0u;
+                        rid = r.id;
+                        const uint32_t rect = r.rect;
+                        const int x0 = (int)(rect & 0xFF) - bx * 8, y0 = (int)((rect >> 8) & 0xFF) - by * 8;
+                        const int x1 = x0 + (int)((rect >> 16) & 0xFF), y1 = y0 + (int)(rect >> 24);
+                        if (zcb <= zmax0 && x0 < 8 && y0 < 8 && x1 > 0 && y1 > 0) {
+                            const uint32_t row = (1u << min(x1, 8)) - (1u << max(x0, 0));
+                            const uint32_t rows4 = row * 0x01010101u;
+                            m = (((unsigned long long)rows4 << 32) | rows4) & (~0ull << (8 * max(y0, 0))) &
+                                (~0ull >> (64 - 8 * min(y1, 8)));
+                        }
+                    }
+                    unsigned long long live = __ballot(m != 0ull);
+                    const unsigned long long spheres = __ballot(rid < F.n_atoms);
+                    while (live) {
+                        const int s = __builtin_ctzll(live);
+                        live &= live - 1ull;
+                        const unsigned long long px =
+                            ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(m >> 32), s) << 32) |
+                            (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)m, s);
+                        const uint32_t zcs = (uint32_t)__builtin_amdgcn_readlane((int)zcb, s);
+                        const unsigned long long open = px & __ballot((uint32_t)(cur >> 32) >= zcs);
+                        if (counting && __builtin_amdgcn_inverse_ballot_w64(px & ~open)) n_skipped += 1;
+                        if (open == 0ull) continue;
+                        if (counting) pref[(uint32_t)__builtin_amdgcn_readlane((int)rj, s)] = 1u;
+                        bool better = false;
+                        const Rec& rs = rec_at((uint32_t)__builtin_amdgcn_readlane((int)rj, s));
+                        const float4 a = rs.a;
+                        const uint32_t id = rs.id;
+                        const bool sphere = (spheres >> s) & 1ull;
+                        if (__builtin_amdgcn_inverse_ballot_w64(open)) {
+                            bool graze = true;
+                            float z;
+                            if (sphere) z = hit_sphere(a, ox, oy, Dx, Dy, graze);
+                            else z = hit_cylinder(a, rs.b, ox, oy, Dx, Dy);
+                            bool hit = z >= F.znear && z <= F.zfar;
+                            if (F.clip_on && hit)
+                                hit = fmaf(F.clip[0], fmaf(z, Dx, ox), fmaf(F.clip[1], fmaf(z, Dy, oy), fmaf(F.clip[2], z, F.clip[3]))) >= 0.0f;
+                            if (counting) {
+                                n_tested += 1;
+                                n_tested_bond += sphere ? 0 : 1;
+                                n_hit += hit ? 1 : 0;
+                                n_hit_bond += (hit && !sphere) ? 1 : 0;
+                            }
+                            const unsigned long long k = ((unsigned long long)__float_as_uint(z) << 32) |
+                                                         (id | (graze && F.refine_flag ? kRefineBit : 0u));
+                            better = hit && k < cur;
+                            if (better) cur = k;
+                        }
+                        if (__ballot(better)) live &= __ballot(zcb <= block_max());
                     }
                 }
-                // later sub-chunks stay small too: the finer the steps, the
-                // sooner the bucket bound above ends the chunk
-                const int sub = sc == 0 ? sub0 : kLaterSub;
-                const int lg = sub == 4 ? 4 : sub == 8 ? 3 : sub == 16 ? 2 : sub == 32 ? 1 : 0;   // log2 of the lanes per record
-                const uint32_t i = (uint32_t)lane >> lg;
-                const bool real = rbase + i < nk;
-                uint32_t rect = 0;
-                float zcull = 0.0f;
-                if (real) {
-                    const Rec& r = recs[ord[rbase + i]];
-                    rect = r.rect;
-                    zcull = r.zcull;
-                }
-                const int bx0 = (int)(rect & 0xFF) >> 2, by0 = (int)((rect >> 8) & 0xFF) >> 2;
-                const int bx1 = ((int)(rect & 0xFF) + (int)((rect >> 16) & 0xFF) - 1) >> 2;
-                const int by1 = ((int)((rect >> 8) & 0xFF) + (int)(rect >> 24) - 1) >> 2;
-                // the first sub-chunk was culled with the chunk, against the
-                // same block depths
-                uint32_t m = 0;
-                if (real && sc > 0)
-                    for (int by = by0 + (lane & ((1 << lg) - 1)); by <= by1; by += 1 << lg)
-                        for (int bx = bx0; bx <= bx1; ++bx) m = max(m, hz[by * (TS / 4) + bx]);
-                if (lg >= 1) m = max(m, (uint32_t)__shfl_xor((int)m, 1));
-                if (lg >= 2) m = max(m, (uint32_t)__shfl_xor((int)m, 2));
-                if (lg >= 3) m = max(m, (uint32_t)__shfl_xor((int)m, 4));
-                if (lg >= 4) m = max(m, (uint32_t)__shfl_xor((int)m, 8));
-                const bool live = real && !(sc > 0 && __float_as_uint(zcull) > m && zcull > 0.0f);
-                // every wave takes the same decisions: wave 0 counts them, one lane per record
-                if (counting && wave == 0 && real && !live && (lane & ((1 << lg) - 1)) == 0) n_culled += 1;
-                // blocks under the live records (their union rectangle)
-                const uint32_t ux0 = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_max(live ? 255u - bx0 : 0u), 63);
-                const uint32_t uy0 = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_max(live ? 255u - by0 : 0u), 63);
-                const uint32_t ux1 = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_max(live ? bx1 + 1u : 0u), 63);
-                const uint32_t uy1 = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_max(live ? by1 + 1u : 0u), 63);
-                // record i's footprint to lane i, then its prefix
-                const uint32_t ag = (uint32_t)__shfl((int)(live ? rect_area(rect) : 0u), (lane << lg) & 63);
-                const uint32_t incl = wave_incl_scan(lane < sub ? ag : 0u);
-                if (lane < sub) wp[lane + 1] = incl;
-                if (lane == 0) wp[0] = 0u;
-                const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, sub - 1);
-                __builtin_amdgcn_wave_barrier();
-                for (uint32_t f = (uint32_t)tid; f < total; f += kBlock) {
-                    int lo = 0, hi = sub;
-                    while (hi - lo > 1) {
-                        const int mid = (lo + hi) >> 1;
-                        if (wp[mid] <= f) lo = mid;
-                        else hi = mid;
-                    }
-                    const Rec& rr = rec_at(ord[rbase + (uint32_t)lo]);
-                    const uint32_t local = f - wp[lo];
-                    const uint32_t rw = (rr.rect >> 16) & 0xFF;
-                    const uint32_t dy = (uint32_t)(((float)local + 0.5f) * rr.inv_w);
-                    const uint32_t dx = local - __umul24(dy, rw);
-                    test_pixel(rr, (int)(rr.rect & 0xFF) + (int)dx, (int)((rr.rect >> 8) & 0xFF) + (int)dy);
-                }
-                rbase += (uint32_t)sub;
-                if (rbase >= nk && !more) break;
-                __syncthreads();   // the sub-chunk's hits are in the depth buffer
-                if (ux1 > 0) {
-                    const int cx0 = 255 - (int)ux0, cy0 = 255 - (int)uy0;
-                    const int bw = (int)ux1 - cx0, nb = bw * ((int)uy1 - cy0);
-                    for (int k = tid; k < 4 * nb; k += kBlock) {
-                        const int b = k >> 2, by = cy0 + b / bw, bx = cx0 + b % bw;
-                        uint32_t z = row_zmax(bx, by, k & 3);
-                        z = max(z, (uint32_t)__shfl_xor((int)z, 1));
-                        z = max(z, (uint32_t)__shfl_xor((int)z, 2));
-                        if ((k & 3) == 0) hz[by * (TS / 4) + bx] = z;
-                    }
-                }
-                __syncthreads();   // refreshed block depths are in LDS
+                if (in) keys[slot] = cur;
             }
+            __syncthreads();
         };
         // Layered lists (resident scenes) run front to back by layer: once
         // every record from a layer on lies behind all block depths of the
@@ -683,13 +685,10 @@ __device__ __forceinline__ void resolve_tile(JobRef R, int t, uint32_t n, uint64
             const uint32_t atot = packed & kAreaMask, nk = packed >> kKeptShift;
             // Large footprints (many records cover each pixel): order the
             // kept records front to back by a counting sort over depth
-            // buckets and resolve them in sub-chunks, refreshing the block
-            // depths in between, so records behind the first layers are
-            // culled whole before any of their pixels is tested.  Sub-chunks
-            // are small (8 records): the block depths are refreshed, and the
-            // bucket bound can end the chunk, after every few records.
-            const int sub = atot >= 64u * nk ? 8 : 32;
-            const bool sorted = !stats && nk > (uint32_t)sub && atot > (uint32_t)kSortArea * nk;
+            // buckets and resolve them block by block, so records behind the
+            // first layers are dropped before any of their pixels is tested.
+            const bool sorted = TS > 8 && !stats && atot > (uint32_t)kSortArea * nk &&
+                                atot > (uint32_t)(kSortDepth * TS * TS);
             if (!sorted) {
                 resolve_fragments();
                 if (!stats && more) {
@@ -728,10 +727,18 @@ __device__ __forceinline__ void resolve_tile(JobRef R, int t, uint32_t n, uint64
             }
             __syncthreads();
             if (keep) ord[bbase[bk] + atomicAdd(&bcnt[bk], 1u)] = (uint8_t)tid;
+            if (counting) pref[tid] = 0u;   // marks the records that some pixel tests
             __syncthreads();   // the order is in LDS
-            resolve_sorted(nk, sub, more, zlo, span > 0.0f ? span * (1.0f / (float)kBuckets) : 0.0f);
-            hz_set = true;
-            __syncthreads();   // every wave is done with this chunk's records
+            resolve_blocks(nk);
+            if (counting && keep && pref[tid] == 0u) {
+                n_culled += 1;
+                if ((int)ord[nk - 1] == tid) ++n_chunk_stop;
+            }
+            if (more) {
+                hz_refresh();
+                hz_set = true;
+            }
+            if (counting) __syncthreads();   // every thread has read the order
             if (tid < kChunk / 4) reinterpret_cast<uint32_t*>(ord)[tid] = 0u;
         }
         __syncthreads();

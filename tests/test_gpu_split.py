@@ -185,3 +185,35 @@ def test_list_offsets_at_the_edges_of_their_scan(vtx, size, capacity):
             assert (st["overflow_tiles"] > 0) == (0 < capacity < st["pairs"]), st
     vtx.vtx_set_bin_capacity(0, s)
     assert_identical(out[8], out[64], "8-pixel tiles")
+
+
+@pytest.mark.parametrize("n", [9, 63, 64, 65, 255, 256, 257, 700])
+@pytest.mark.parametrize("tile,size", [(16, (45, 27)), (16, (8, 5)), (32, (45, 27)), (64, (149, 75))])
+@pytest.mark.parametrize("view", ["perspective", "orthographic", "clipped"])
+def test_blocks_front_to_back_equal_all_fragments(vtx, ctx, n, tile, size, view):
+    """Deep tiles of large footprints go front to back by 8x8 blocks: the
+    image is the one of a statistics frame, which tests every fragment, with
+    coinciding atoms (equal depths), bonds, and images that end inside a
+    tile and a block; counting frames see early-outs."""
+    import torch
+    rng = np.random.default_rng(n)
+    wl = workload(n, True, *size)
+    pos = rng.uniform(-3.0, 3.0, size=(n, 3)).astype(np.float32)
+    pos[1::5] = pos[0::5][: len(pos[1::5])]
+    wl.scene = dataclasses.replace(wl.scene, positions=pos, radii=rng.uniform(0.3, 1.8, n).astype(np.float32))
+    wl.camera = scenes.Camera(eye=(0.5, 0.25, 14.0), target=(0.0, 0.0, 0.0), projection=1 if view == "orthographic" else 0,
+                              ortho_half_height=5.0)
+    wl.options = dataclasses.replace(wl.options, tile_size=tile, bond_radius=0.6,
+                                     clip_plane=(0.2, 0.1, -1.0, 1.0) if view == "clipped" else (0.0,) * 4)
+    ds = vtx.DeviceScene(wl.scene)
+    out, tested = {}, {}
+    for flags in (0, vtx.VTX_FLAG_STATS, vtx.VTX_FLAG_COUNT):
+        out[flags] = run_render(vtx, ds, wl.camera, dataclasses.replace(wl.options, flags=flags), *size)
+        tested[flags] = vtx.vtx_read_stats()["fragments_tested"]
+    assert_identical(out[0], out[vtx.VTX_FLAG_STATS], "all fragments")
+    assert_identical(out[0], out[vtx.VTX_FLAG_COUNT], "counted")
+    assert 0 < tested[vtx.VTX_FLAG_COUNT] <= tested[vtx.VTX_FLAG_STATS]
+    if n >= 256:
+        assert tested[vtx.VTX_FLAG_COUNT] < tested[vtx.VTX_FLAG_STATS]
+    ref = osplat.render(wl.scene, wl.camera, wl.options, *size)
+    assert_clean(compare.check_gbuffer(out[0]["depth"], out[0]["id"], ref), f"{n} atoms")
