@@ -83,6 +83,17 @@ __device__ inline uint32_t wave_scan_u32(uint32_t v) {
     return v;
 }
 
+// Maximum over the 64 lanes of a wave, the same steps, in every lane.
+__device__ inline uint32_t wave_max_u32(uint32_t v) {
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false));
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false));
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false));
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false));
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
 // Tile of entry i of a workgroup's histogram row: the row covers the box of
 // tiles [bx0, bx0 + bw) x [by0, ...) its primitives touch, row-major.
 __device__ inline int box_tile(int tiles_x, uint32_t bx0, uint32_t by0, int bw, int i) {
@@ -264,11 +275,17 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_count(JS js, int phase) {
         }
     }
     if (bad_count) atomicAdd(&ctr->bad_bonds, bad_count);
-    if (kScene && my_zlo != 0x7F800000u) atomicMin(&wg_zlo, my_zlo);
+    if constexpr (kScene) {
+        const uint32_t zlo = ~wave_max_u32(~my_zlo);   // the wave's least
+        if (__lane_id() == 0 && zlo != 0x7F800000u) atomicMin(&wg_zlo, zlo);
+    }
     __syncthreads();   // the histogram is complete
     {
         // the workgroup's box of touched tiles and its pair count, read from
-        // the histogram once rather than tracked per primitive
+        // the histogram once rather than tracked per primitive; reduced over
+        // each wave first (an LDS atomic to one address takes its lanes in
+        // turn: with one per thread 4,096 atoms at 256x256 took 16.6 us in
+        // this kernel, 6.6 so; 11M spheres at 4K 120 and 94)
         uint32_t mx0 = 0xFFFF, my0 = 0xFFFF, mx1 = 0, my1 = 0;
         unsigned long long my_pairs = 0;
         for (int t = tid; t < T; t += kBinThreads) {
@@ -282,12 +299,21 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_count(JS js, int phase) {
                 my_pairs += h;
             }
         }
-        if (my_pairs) {
-            atomicMin(&bx0, mx0);
-            atomicMin(&by0, my0);
-            atomicMax(&bx1, mx1);
-            atomicMax(&by1, my1);
-            atomicAdd(&local_pairs, my_pairs);
+        if (__ballot(my_pairs != 0ull)) {
+            // minima as maxima of the complements
+            mx0 = 0xFFFFu - wave_max_u32(0xFFFFu - mx0);
+            my0 = 0xFFFFu - wave_max_u32(0xFFFFu - my0);
+            mx1 = wave_max_u32(mx1);
+            my1 = wave_max_u32(my1);
+            // 16-bit halves, so that 64 lanes cannot overflow
+            const uint32_t lo = wave_scan_u32((uint32_t)my_pairs & 0xFFFFu), hi = wave_scan_u32((uint32_t)(my_pairs >> 16));
+            if (__lane_id() == 63) {
+                atomicMin(&bx0, mx0);
+                atomicMin(&by0, my0);
+                atomicMax(&bx1, mx1);
+                atomicMax(&by1, my1);
+                atomicAdd(&local_pairs, ((unsigned long long)hi << 16) + lo);
+            }
         }
     }
     __syncthreads();

@@ -54,14 +54,18 @@ __global__ void __launch_bounds__(kBlock) k_extent(const float* __restrict__ pos
     for (int o = 32; o > 0; o >>= 1) {
         r1 += __shfl_xor(r1, o);
         r2 += __shfl_xor(r2, o);
+        for (int k = 0; k < 3; ++k) {
+            lo[k] = min(lo[k], (uint32_t)__shfl_xor((int)lo[k], o));
+            hi[k] = max(hi[k], (uint32_t)__shfl_xor((int)hi[k], o));
+        }
     }
     if (__lane_id() == 0) {
         atomicAdd(&sr[0], r1);
         atomicAdd(&sr[1], r2);
-    }
-    for (int k = 0; k < 3; ++k) {
-        atomicMin(&sb[k], lo[k]);
-        atomicMax(&sb[3 + k], hi[k]);
+        for (int k = 0; k < 3; ++k) {
+            atomicMin(&sb[k], lo[k]);
+            atomicMax(&sb[3 + k], hi[k]);
+        }
     }
     __syncthreads();
     if (threadIdx.x < 3) atomicMin(&ext->box[threadIdx.x], sb[threadIdx.x]);
