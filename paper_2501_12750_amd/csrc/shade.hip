@@ -219,16 +219,16 @@ __device__ inline int noise_rank(int x, int y) {
     return (int)((kRows[y & 3] >> (4 * (x & 3))) & 15u);
 }
 
-// Work block t of a job is that job's kTW x 16 tile t, taken by its threads
+// Work block t of a job is that job's kTW x kTH tile t, taken by its threads
 // 16x16 pixels at a time, the next ones' depth and id loaded meanwhile.
 // kNoise: the instantiation that can take the noise form (launched when a job
 // asks for it; the plain one carries none of its code).
-template <class JS, bool kNoise, int kTW>
+template <class JS, bool kNoise, int kTW, int kTH>
 __global__ void __launch_bounds__(kBlock) k_shade(JS js) {
-    static_assert(kTW % kTile == 0 && kBlock == kTile * kTile, "whole 16x16 blocks");
+    static_assert(kTW % kTile == 0 && kTH % kTile == 0 && kBlock == kTile * kTile, "whole 16x16 blocks");
     // noise form: the raw AO of the tile and of the 2 pixels left and above
     // and 1 right and below it that the 4x4 blur reads (-1: not a hit)
-    constexpr int kHaloW = kTW + 3, kHaloH = kTile + 3;
+    constexpr int kHaloW = kTW + 3, kHaloH = kTH + 3;
     __shared__ float raw[kNoise ? kHaloW * kHaloH : 1];
     uint32_t tu;
     const int ji = js.find((uint32_t)xcd_runs(blockIdx.x), tu);
@@ -241,7 +241,7 @@ __global__ void __launch_bounds__(kBlock) k_shade(JS js) {
     const int tiles_x = (W + kTW - 1) / kTW;
     const int t = (int)tu;
     const int tid = threadIdx.x;
-    const int tx0 = (t % tiles_x) * kTW, ty0 = (t / tiles_x) * kTile;
+    const int tx0 = (t % tiles_x) * kTW, ty0 = (t / tiles_x) * kTH;
     const bool noise = kNoise && K.noise() && K.count() > 0;   // the same for the whole workgroup (one job)
     if (noise) {
         for (int i = tid; i < kHaloW * kHaloH; i += kBlock) {
@@ -259,13 +259,13 @@ __global__ void __launch_bounds__(kBlock) k_shade(JS js) {
         }
         __syncthreads();
     }
-    constexpr int kBlocks = kTW / kTile;
-    const int y = ty0 + (tid >> 4);
-    auto at_x = [&](int s) { return tx0 + s * kTile + (tid & (kTile - 1)); };
+    constexpr int kRow = kTW / kTile, kBlocks = kRow * (kTH / kTile);
+    auto at_x = [&](int s) { return tx0 + s % kRow * kTile + (tid & (kTile - 1)); };
+    auto at_y = [&](int s) { return ty0 + s / kRow * kTile + (tid >> 4); };
     float z_next = 0.0f;
     uint32_t id_next = 0u;
     auto fetch = [&](int s) {
-        const int x = at_x(s);
+        const int x = at_x(s), y = at_y(s);
         if (x < W && y < H) {
             const size_t p = (size_t)y * W + x;
             z_next = depth[p];
@@ -275,7 +275,7 @@ __global__ void __launch_bounds__(kBlock) k_shade(JS js) {
     fetch(0);
 #pragma unroll 1
     for (int s = 0; s < kBlocks; ++s) {
-        const int x = at_x(s);
+        const int x = at_x(s), y = at_y(s);
         const float z = z_next;
         const uint32_t pid = id_next;
         if (s + 1 < kBlocks) fetch(s + 1);
@@ -406,9 +406,11 @@ template <class JS>
 hipError_t shade_impl(const JS& js, uint32_t grid, ShadeForm form, hipStream_t stream) {
     if (grid == 0) return hipSuccess;
     const unsigned g = (unsigned)xcd_run_grid((int)grid);
-    if (form.noise) return dispatch(k_shade<JS, true, 16>, g, kBlock, 0, stream, js);
-    if (form.wide) return dispatch(k_shade<JS, false, 64>, g, kBlock, 0, stream, js);
-    return dispatch(k_shade<JS, false, 16>, g, kBlock, 0, stream, js);
+    if (form.noise)
+        return form.wide ? dispatch(k_shade<JS, true, 32, 32>, g, kBlock, 0, stream, js)
+                         : dispatch(k_shade<JS, true, 16, 16>, g, kBlock, 0, stream, js);
+    return form.wide ? dispatch(k_shade<JS, false, 64, 16>, g, kBlock, 0, stream, js)
+                     : dispatch(k_shade<JS, false, 16, 16>, g, kBlock, 0, stream, js);
 }
 
 hipError_t launch_shade(const OneJob& js, uint32_t grid, ShadeForm form, hipStream_t stream) {

@@ -508,19 +508,27 @@ inline uint32_t cull_blocks(const SceneDev& S) {
     return (nc + kBlock - 1) / kBlock;
 }
 // Form of a shade launch: whether a job asks for the noise form of the ambient
-// occlusion, and tiles of 64x16 pixels instead of 16x16.  Wide tiles read
-// their job's constants once for four blocks, which pays where most blocks
-// are background and the launch is long: a trajectory batch of 520M pixels
-// 5.05 ms narrow, 4.87 wide.  One 8.3M-pixel frame is 126 us narrow, 144 wide
-// (fewer, longer workgroups, one wave per SIMD less).
+// occlusion, and tiles of several 16x16-pixel blocks instead of one.
+// Plain: 64x16 tiles read their job's constants once for four blocks, which
+// pays where most blocks are background and the launch is long: a trajectory
+// batch of 520M pixels 5.05 ms narrow, 4.87 wide.  One 8.3M-pixel frame is 126
+// us narrow, 144 wide (fewer, longer workgroups, one wave per SIMD less).
+// Noise: the occlusion is VALU-bound, and a 32x32 tile's halo has 20 % more
+// pixels than the tile (16x16: 41 %): 8.3M pixels of two samples a side 338 us
+// in 16x16, 304 in 32x32 (64x16 326, 32x16 315, 64x64 429: too few workgroups).
+// Below 3M pixels the 32x32 tiles are too few for the 256 CUs: whole frames of
+// 20,000 spheres 43 against 55 us at 256x256, 128 and 130 at 1080p, 215 and
+// 207 at 1440p, 357 and 320 at 4K.
 struct ShadeForm {
     bool noise, wide;
 };
-constexpr uint64_t kWidePixels = 128u << 20;
-inline ShadeForm shade_form(bool noise, uint64_t pixels) { return ShadeForm{noise, !noise && pixels >= kWidePixels}; }
+constexpr uint64_t kWidePixels = 128u << 20, kWideNoisePixels = 3u << 20;
+inline ShadeForm shade_form(bool noise, uint64_t pixels) {
+    return ShadeForm{noise, pixels >= (noise ? kWideNoisePixels : kWidePixels)};
+}
 inline uint32_t shade_blocks(const Frame& F, ShadeForm form) {
-    const int w = form.wide ? 64 : 16;
-    return (uint32_t)(((F.W + w - 1) / w) * ((F.H + 15) / 16));
+    const int w = !form.wide ? 16 : form.noise ? 32 : 64, h = form.wide && form.noise ? 32 : 16;
+    return (uint32_t)(((F.W + w - 1) / w) * ((F.H + h - 1) / h));
 }
 
 // A launch over one render: the job travels in the kernel arguments.

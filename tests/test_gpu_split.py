@@ -217,3 +217,27 @@ def test_blocks_front_to_back_equal_all_fragments(vtx, ctx, n, tile, size, view)
         assert tested[vtx.VTX_FLAG_COUNT] < tested[vtx.VTX_FLAG_STATS]
     ref = osplat.render(wl.scene, wl.camera, wl.options, *size)
     assert_clean(compare.check_gbuffer(out[0]["depth"], out[0]["id"], ref), f"{n} atoms")
+
+
+@pytest.mark.parametrize("size", [(1024, 768), (701, 403), (257, 33)])
+def test_noise_tiles_of_a_large_launch(vtx, ctx, size):
+    """From 3M pixels on, a launch with the noise form of the ambient
+    occlusion shades in 32x32 tiles: its images are the single renders', with
+    and without the noise, at sizes that end inside a tile and a block."""
+    import torch
+    W, H = size
+    wl = scenes.plain_small(n_atoms=3000, width=W, height=H, seed=7, eye_distance=60.0)
+    rs = vtx.ResidentScene(ctx, vtx.DeviceScene(wl.scene))
+    n = (3 << 20) // (W * H) + 1
+    opts = [dataclasses.replace(wl.options, ssao_samples=8, ssao_noise=1 if k % 3 else 0) for k in range(n)]
+    cams = [scenes.orbit_camera((0.0, 0.0, 0.0), 60.0, 0.3 * k) for k in range(n)]
+    frames = [vtx.Frame(W, H) for _ in range(n)]
+    vtx.vtx_render_batch(ctx, [vtx.make_job(rs.handle, 0, cams[k], opts[k], W, H, f.rgba, f.depth, f.id)
+                               for k, f in enumerate(frames)])
+    one = vtx.Frame(W, H)
+    for k, f in enumerate(frames):
+        rs.render(cams[k], opts[k], W, H, one)
+        torch.cuda.synchronize()
+        for name in ("rgba", "depth", "id"):
+            assert torch.equal(getattr(one, name), getattr(f, name)), (k, name)
+    rs.close()
