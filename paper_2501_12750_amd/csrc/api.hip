@@ -334,7 +334,7 @@ int ensure_bins(Workspace* ws, Bins* b, int T, uint64_t nprim, uint32_t groups, 
     if ((size_t)T > b->tiles_cap || !b->bb.tile_cnt) {
         size_t c1 = b->tiles_cap, c2 = b->tiles_cap, c3 = b->tiles_cap * vtx::kLayers, c4 = c3;
         if ((rc = grow(&b->bb.tile_cnt, c1, (size_t)T, st, "tile counts"))) return rc;
-        if ((rc = grow(&b->bb.tile_off, c2, (size_t)T, st, "tile offsets"))) return rc;
+        if ((rc = grow(&b->bb.tile_off, c2, vtx::tile_off_entries((size_t)T), st, "tile offsets"))) return rc;
         if ((rc = grow(&b->bb.tile_fill, c3, (size_t)T * vtx::kLayers, st, "tile cursors"))) return rc;
         if ((rc = grow(&b->bb.layer_off, c4, (size_t)T * vtx::kLayers, st, "tile layer starts"))) return rc;
         size_t c5 = b->tiles_cap * vtx::kLayers;
@@ -1345,7 +1345,7 @@ StaticLayout static_layout(int T, uint32_t groups, uint32_t chunk) {
     L.tile_fill = take((size_t)T * sizeof(uint32_t));
     L.ctr = take(sizeof(Counters));
     L.zero_end = at;
-    L.tile_off = take((size_t)T * sizeof(uint64_t));
+    L.tile_off = take(vtx::tile_off_entries((size_t)T) * sizeof(uint64_t));
     L.vis_cnt = take((size_t)vtx::kMaxBinGroups * sizeof(uint32_t));
     L.vis_box = take((size_t)vtx::kMaxBinGroups * sizeof(uint2));
     const size_t nv = (size_t)groups * chunk;

@@ -448,6 +448,66 @@ __device__ __forceinline__ unsigned long long tile_starts(const uint32_t (&v)[kR
     return wpre[kRows * kWaves];
 }
 
+// The tiles by falling list length (4 classes per octave, in any order within
+// one; no list: last), by one workgroup beside those of the launch that finds
+// the offsets.  A class has kCopies counters, so that fewer lanes of a wave
+// meet in one.
+__device__ __forceinline__ void order_tiles(const Job& J) {
+    constexpr int kClasses = 64, kCopies = 4, kLoads = 4;
+    __shared__ uint32_t next[kCopies][kClasses];
+    const int T = J.F.tiles_x * J.F.tiles_y;
+    const global_t<const uint32_t>* __restrict__ const cnt = to_global((const uint32_t*)J.bb.tile_cnt);
+    global_t<uint32_t>* __restrict__ const order = to_global(tile_order(J.bb, T));
+    const int tid = threadIdx.x, lane = __lane_id();
+    uint32_t* const mine = next[lane & (kCopies - 1)];
+    // exponent and two bits of the mantissa, from 1 on
+    auto class_of = [](uint32_t n) { return (int)min((__float_as_uint((float)n) >> 21) - (127u << 2) + 1u, (uint32_t)kClasses - 1u); };
+    if (tid < kClasses * kCopies) next[tid / kClasses][tid % kClasses] = 0u;
+    __syncthreads();
+    // every tile's count, kLoads at a time: f(tile, count, whether it exists)
+    auto each = [&](auto f) {
+        for (int t0 = 0; t0 < T; t0 += kLoads * kBinThreads) {
+            uint32_t v[kLoads];
+#pragma unroll
+            for (int k = 0; k < kLoads; ++k) {
+                const int t = t0 + k * kBinThreads + tid;
+                v[k] = t < T ? cnt[t] : 0u;
+            }
+#pragma unroll
+            for (int k = 0; k < kLoads; ++k) f(t0 + k * kBinThreads + tid, v[k], t0 + k * kBinThreads + tid < T);
+        }
+    };
+    // the empty tiles, most of many images, are counted once per wave
+    uint32_t empty = 0;
+    each([&](int, uint32_t n, bool in) {
+        if (n) atomicAdd(&mine[class_of(n)], 1u);
+        empty += (uint32_t)__popcll(__ballot(in && n == 0u));
+    });
+    if (empty && lane == 0) atomicAdd(&next[0][0], empty);
+    __syncthreads();
+    if (tid < 64) {
+        uint32_t c[kCopies], sum = 0;
+#pragma unroll
+        for (int k = 0; k < kCopies; ++k) {
+            c[k] = sum;
+            sum += next[k][kClasses - 1 - tid];
+        }
+        const uint32_t start = wave_scan_u32(sum) - sum;
+#pragma unroll
+        for (int k = 0; k < kCopies; ++k) next[k][kClasses - 1 - tid] = start + c[k];
+    }
+    __syncthreads();
+    uint32_t at = 0;
+    if (empty && lane == 0) at = atomicAdd(&next[0][0], empty);
+    at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+    each([&](int t, uint32_t n, bool in) {
+        const unsigned long long none = __ballot(in && n == 0u);
+        if (n) order[atomicAdd(&mine[class_of(n)], 1u)] = (uint32_t)t;
+        else if (in) order[at + (uint32_t)__popcll(none & __lanemask_lt())] = (uint32_t)t;
+        at += (uint32_t)__popcll(none);
+    });
+}
+
 // The frame counters of a job's lists: their total, whether it passes the
 // capacity, and how many tiles' lists do (n_over, per thread; the scatter
 // leaves those out).  The whole workgroup.
@@ -470,7 +530,10 @@ __device__ __forceinline__ void publish_lists(const Job& J, unsigned long long t
 template <class JS>
 __global__ void __launch_bounds__(kBinThreads) k_tile_offsets(JS js) {
     constexpr int kRows = (kMaxLdsTiles + kBinThreads - 1) / kBinThreads;
-    if (blockIdx.x >= js.count()) return;
+    if (blockIdx.x >= js.count()) {
+        if (JS::kOrdered) order_tiles(js.job(0));
+        return;
+    }
     const Job& J = js.job((int)blockIdx.x);
     const int T = J.F.tiles_x * J.F.tiles_y;
     const uint32_t* __restrict__ const cnt = J.bb.tile_cnt;
@@ -510,7 +573,10 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_scatter(JS js, int phase) {
     extern __shared__ uint32_t cur[];
     uint32_t blk;
     const int ji = js.find(blockIdx.x, blk);
-    if (ji < 0) return;
+    if (ji < 0) {
+        if (kScan && JS::kOrdered) order_tiles(js.job(0));
+        return;
+    }
     const Job& J = js.job(ji);
     const Frame F = J.F;
     const uint32_t chunk = J.bb.chunk;
@@ -771,8 +837,11 @@ hipError_t scatter_impl(const JS& js, int phase, uint32_t grid, int max_tiles, h
     if (max_tiles > kMaxLdsTiles) return hipErrorInvalidValue;
     if (grid == 0) return hipSuccess;
     const uint32_t lds = (uint32_t)(max_tiles * sizeof(uint32_t));
+    // the workgroup that orders the tiles comes after the others: it takes
+    // less time than they do, also where it has to wait for a CU
+    const uint32_t extra = JS::kOrdered && max_tiles > kOrderTiles ? 1u : 0u;
     if (scatter_scans(max_tiles))
-        return dispatch(k_scatter<JS, true>, grid, kBinThreads, lds, stream, js, phase);
+        return dispatch(k_scatter<JS, true>, grid + extra, kBinThreads, lds, stream, js, phase);
     return dispatch(k_scatter<JS, false>, grid, kBinThreads, lds, stream, js, phase);
 }
 
@@ -790,7 +859,7 @@ hipError_t launch_layers(const JobList& js, uint32_t grid, hipStream_t stream) {
 }
 hipError_t launch_tile_offsets(const OneJob& js, int max_tiles, hipStream_t stream) {
     if (scatter_scans(max_tiles)) return hipSuccess;
-    return dispatch(k_tile_offsets<OneJob>, 1, kBinThreads, 0, stream, js);
+    return dispatch(k_tile_offsets<OneJob>, 2, kBinThreads, 0, stream, js);
 }
 hipError_t launch_tile_offsets(const JobList& js, int max_tiles, hipStream_t stream) {
     if (scatter_scans(max_tiles)) return hipSuccess;

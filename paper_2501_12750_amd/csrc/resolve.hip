@@ -875,7 +875,8 @@ __device__ __forceinline__ void refine_tile(JobRef R, int t, unsigned long long*
     }
 }
 
-// Main launch: work block t of a job is that job's tile t, so consecutive
+// Main launch: work block t of a job is that job's tile t, or the t-th of its
+// tile order (see kOrderTiles), so consecutive
 // tiles go to different XCDs (the dispatcher deals blocks round-robin).  The
 // costly tiles lie together, around the footprints of the nearest atoms:
 // contiguous tile ranges per XCD left one XCD with most of them (20 % longer
@@ -893,6 +894,8 @@ __global__ void __launch_bounds__(kBlock, kCount ? 1 : 7) k_resolve(JS js) {
     const int ji = js.find(blockIdx.x, tu);
     if (ji < 0) return;
     const Job& J = js.job(ji);
+    const int T = J.F.tiles_x * J.F.tiles_y;
+    if (JS::kOrdered && T > kOrderTiles) tu = (uint32_t)__builtin_amdgcn_readfirstlane((int)tile_order(J.bb, T)[tu]);
     const uint32_t n = J.bb.tile_cnt[tu];
     const uint64_t o = J.bb.tile_off[tu];
     const bool over = o + n > J.bb.capacity;

@@ -400,7 +400,7 @@ hipError_t dispatch(void (*k)(Params...), dim3 grid, dim3 block, uint32_t lds, h
 // consecutive primitives and the same range of the visible-list arrays.
 struct BinBuffers {
     uint32_t* tile_cnt;     // T
-    uint64_t* tile_off;     // T
+    uint64_t* tile_off;     // T, then the tile order's T words (see tile_order)
     uint32_t* tile_fill;    // layers * T: next free entry of each layer's run of each tile list
     uint32_t* layer_off;    // layers * T: start of each layer's run within each tile list
     uint32_t* layer_sum;    // layers * T: entries of each layer in each tile list, added up by the
@@ -421,6 +421,23 @@ struct BinBuffers {
     Counters* ctr;
     Counters* host_ctr;     // device address of host-mapped counters (may be null)
 };
+
+// Images of more tiles than the device holds resolve workgroups (7 on each of
+// 256 CUs) resolve them longest list first: in image order the launch ends
+// with the few long lists that happen to start last (1M atoms and bonds at
+// 1080p: every tile has started after 57 of 107 us, and half the device is
+// idle from 68 us on).  Resolve in image order and ordered: 98 and 78 us
+// there, 58 and 47 for 107,500 atoms with bonds at 1080p, 104 and 94 for a
+// 4K figure.  Single renders only (JS::kOrdered): a batch of one scene's
+// views has the next render's tiles to fill the end with, and loses the
+// neighbours' shared records instead (256 renders of 50,000 atoms, 3.20 ms in
+// image order, 3.50 ordered; 8 views 374 and 386 us).
+constexpr int kOrderTiles = 1792;
+constexpr size_t tile_off_entries(size_t T) { return T + (T + 1) / 2; }
+// The order's T tile numbers, written with the offsets (T > kOrderTiles).
+__host__ __device__ inline uint32_t* tile_order(const BinBuffers& bb, int T) {
+    return reinterpret_cast<uint32_t*>(bb.tile_off + T);
+}
 
 // Clusters per binning workgroup up to which an atom-only scene's count deals
 // them to the waves by quarters.
@@ -544,6 +561,7 @@ struct OneJob {
     __device__ const Job& job(int) const { return j; }
     __device__ const SampleKernel& samples(int) const { return K; }
     __device__ uint32_t count() const { return 1; }
+    static constexpr bool kOrdered = true;   // see kOrderTiles
     __device__ uint32_t work_blocks(int) const { return blocks; }
     // the work block after (i, local): the next one of the job, else -1
     __device__ void next(int& i, uint32_t& local) const {
@@ -582,6 +600,7 @@ struct JobList {
     __device__ const Job& job(int i) const { return jobs[i]; }
     __device__ const SampleKernel& samples(int i) const { return K[i]; }
     __device__ uint32_t count() const { return n; }
+    static constexpr bool kOrdered = false;
     __device__ uint32_t work_blocks(int i) const { return start[i + 1] - start[i]; }
     // the work block after (i, local): the next one of job i, else the first
     // of the next job that has any, else -1 (no search)

@@ -165,12 +165,14 @@ def test_stored_order_binning_equals_clusters(vtx, ctx, n, size, representation)
     rs.close()
 
 
-@pytest.mark.parametrize("size", [(8, 8), (1016, 64), (1024, 64), (1032, 64), (1024, 512), (1032, 512)])
+@pytest.mark.parametrize("size", [(8, 8), (1016, 64), (1024, 64), (1032, 64), (448, 256), (456, 256), (1024, 512),
+                                  (1032, 512)])
 @pytest.mark.parametrize("capacity", [0, 3000])
 def test_list_offsets_at_the_edges_of_their_scan(vtx, size, capacity):
     """Up to 8192 tiles the scatter scans the tile counts itself, in rows of
-    1024: the image is the one of 64-pixel tiles (at most 144 of them), also
-    where part of the lists overflows."""
+    1024, and past 1792 tiles they are resolved by falling list length: the
+    image is the one of 64-pixel tiles (at most 144 of them), also where part
+    of the lists overflows."""
     import torch
     wl = workload(20_000, True, *size)
     ds = vtx.DeviceScene(wl.scene)
