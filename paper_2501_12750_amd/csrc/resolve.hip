@@ -30,7 +30,7 @@ namespace {
 
 constexpr int kChunk = kBlock;
 constexpr int kBuckets = 64;      // depth buckets of the front-to-back record order
-static_assert(kBuckets <= 64, "one wave scans and searches the buckets");
+static_assert(kBuckets == 64, "a wave scans the buckets, one per lane");
 // A chunk is ordered and resolved by blocks (resolve_blocks) when its kept
 // records average more than kSortArea pixels and cover the tile more than
 // kSortDepth times: a block's wave spends a pass of 64 lanes on a record
@@ -280,8 +280,7 @@ __device__ __forceinline__ void resolve_tile(JobRef R, int t, uint32_t n, uint64
     __shared__ uint32_t wsum[kBlock / 64];
     constexpr int kHzBlocks = HzGrid<TS>::kBlocks;
     __shared__ uint32_t hz[kHzBlocks];
-    __shared__ float red_lo[kBlock / 64], red_hi[kBlock / 64];
-    __shared__ uint32_t bcnt[kBuckets], bbase[kBuckets];
+    __shared__ uint32_t red_lo[kBlock / 64], red_hi[kBlock / 64], bcnt[kBuckets];
     // resident scenes: list position where each layer starts, and the least
     // cull depth (float bits) of the layers from there on
     __shared__ uint32_t lay_start[kLayers], lay_zrest[kLayers];
@@ -679,6 +678,19 @@ __device__ __forceinline__ void resolve_tile(JobRef R, int t, uint32_t n, uint64
                 }
             }
             const bool more = base + kChunk < nsrc;
+            // the kept records' depth range, per wave (as bits: depths before
+            // the eye count as 0, the order need not be exact), and the
+            // buckets cleared, for a chunk that gets ordered
+            const float zord = fmaxf(zc, 0.0f);
+            {
+                const uint32_t zb = __float_as_uint(zord);
+                const uint32_t hi = wave_incl_max(keep ? zb : 0u), lo = wave_incl_max(keep ? ~zb : 0u);
+                if (lane == 63) {
+                    red_hi[wave] = hi;
+                    red_lo[wave] = ~lo;
+                }
+                if (tid < kBuckets) bcnt[tid] = 0u;
+            }
             // prefix of the footprint areas, with the kept records counted in
             // the high bits
             const uint32_t packed = block_scan(area | (keep ? 1u << kKeptShift : 0u));
@@ -697,36 +709,23 @@ __device__ __forceinline__ void resolve_tile(JobRef R, int t, uint32_t n, uint64
                 }
                 continue;
             }
-            // depth range of the kept records
-            float zlo = zc, zhi = keep ? zc : -INFINITY;
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) {
-                zlo = fminf(zlo, __shfl_xor(zlo, o));
-                zhi = fmaxf(zhi, __shfl_xor(zhi, o));
-            }
-            if (lane == 0) {
-                red_lo[wave] = zlo;
-                red_hi[wave] = zhi;
-            }
-            if (tid < kBuckets) bcnt[tid] = 0u;
-            __syncthreads();
-            zlo = fminf(fminf(red_lo[0], red_lo[1]), fminf(red_lo[2], red_lo[3]));
-            zhi = fmaxf(fmaxf(red_hi[0], red_hi[1]), fmaxf(red_hi[2], red_hi[3]));
+            // A record's rank in its bucket, then (every wave for itself) the
+            // buckets' starts: two barriers (with the depth range by shuffles,
+            // one wave's scan and a second atomic five, and the resolve of 256
+            // renders of 50,000 atoms 3.21 ms instead of 3.12).
+            const float zlo = __uint_as_float(min(min(red_lo[0], red_lo[1]), min(red_lo[2], red_lo[3])));
+            const float zhi = __uint_as_float(max(max(red_hi[0], red_hi[1]), max(red_hi[2], red_hi[3])));
             const float span = zhi - zlo;
             const float scale = span > 0.0f ? (float)kBuckets / span : 0.0f;
-            const int bk = keep ? min(kBuckets - 1, (int)((zc - zlo) * scale)) : 0;
-            if (keep) atomicAdd(&bcnt[bk], 1u);
+            const int bk = keep ? min(kBuckets - 1, (int)((zord - zlo) * scale)) : 0;
+            uint32_t rank = 0;
+            if (keep) rank = atomicAdd(&bcnt[bk], 1u);
             __syncthreads();
-            if (wave == 0) {
-                const uint32_t c = lane < kBuckets ? bcnt[lane] : 0u;
-                const uint32_t inc = wave_incl_scan(c);
-                if (lane < kBuckets) {
-                    bbase[lane] = inc - c;
-                    bcnt[lane] = 0u;
-                }
+            {
+                const uint32_t c = bcnt[lane];
+                const uint32_t at = (uint32_t)__shfl((int)(wave_incl_scan(c) - c), bk) + rank;
+                if (keep) ord[at] = (uint8_t)tid;
             }
-            __syncthreads();
-            if (keep) ord[bbase[bk] + atomicAdd(&bcnt[bk], 1u)] = (uint8_t)tid;
             if (counting) pref[tid] = 0u;   // marks the records that some pixel tests
             __syncthreads();   // the order is in LDS
             resolve_blocks(nk);
