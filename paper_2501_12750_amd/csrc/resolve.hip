@@ -37,8 +37,8 @@ static_assert(kBuckets == 64, "a wave scans the buckets, one per lane");
 // however few of its pixels the footprint has, which pays only where the
 // order hides records behind it.  kSortArea 20 to 40 measure the same on
 // spheres (4,096 at 256x256, 16-pixel tiles: 9.9 us of resolve; 64: 22); on
-// bonds small areas lose (107,500 atoms with bonds at 1080p: 58 us with 32,
-// 69 to 79 with 16; 1M dust with bonds: 96 with 32, 103 with 16, 153 with 8).
+// bonds small areas lose (in image order, 107,500 atoms with bonds at 1080p:
+// 58 us with 32, 69 to 79 with 16; 1M dust with bonds: 96 with 32, 103 with 16, 153 with 8).
 // kSortDepth 2, 4, 8: 191, 192, 207 us on 11M spheres at 4K.
 constexpr int kSortArea = 32;
 constexpr int kSortDepth = 2;
@@ -774,20 +774,18 @@ __device__ __forceinline__ void resolve_tile(JobRef R, int t, uint32_t n, uint64
                                             __uint_as_float((uint32_t)(kk >> 32)));
             return ((unsigned long long)__float_as_uint(z) << 32) | id;
         };
-        // Several pixels per thread: about one winner in five is marked, in
-        // nearly every wave, so the marked pixels are packed into a list first
-        // and only as many waves as they fill run the FP64 code (a trajectory
-        // batch of 256 renders, 32-pixel tiles: 3.98 ms; with a pass of its
-        // own over the ids after the resolve 5.14 ms).  With one pixel per
-        // thread the list's barriers cost more than the waves it saves (1M
-        // atoms and bonds at 1080p, 16-pixel tiles: 86 us packed, 80 not).
-        constexpr bool kPacked = TS * TS > kBlock;
-        if (kPacked && finish) {
+        // About one winner in five is marked, in nearly every wave, so the
+        // marked pixels are packed into a list first and only as many waves
+        // as they fill run the FP64 code (256 renders of 50,000 atoms, 32-pixel
+        // tiles: 3.12 ms, with each thread refining its own pixels 3.39; with
+        // one pixel per thread, 16-pixel tiles, the list and its barriers cost
+        // as much as they save: 1M atoms and bonds at 1080p 60.5 and 60.9 us).
+        if (finish) {
             uint16_t* const todo = reinterpret_cast<uint16_t*>(recs);   // the records are done with
             static_assert(TS * TS * sizeof(uint16_t) <= sizeof(recs), "one list entry per pixel of the tile");
             if (tid == 0) wsum[0] = 0u;
             __syncthreads();
-            for (int i = tid; i < TS * TS; i += kBlock) {   // whole waves: TS * TS is a multiple of kBlock
+            for (int i = tid; i < TS * TS; i += kBlock) {   // whole waves: TS * TS is a multiple of 64
                 const unsigned long long kk = keys[i];
                 const unsigned long long mm = __ballot(is_marked(kk));
                 uint32_t at = 0;
@@ -808,9 +806,8 @@ __device__ __forceinline__ void resolve_tile(JobRef R, int t, uint32_t n, uint64
         for (int i = tid; i < TS * TS; i += kBlock) {
             const int ly = i / TS, lx = i - ly * TS;
             if (lx < tw && ly < th) {
-                unsigned long long kk = keys[i];
+                const unsigned long long kk = keys[i];
                 const size_t p = (size_t)(py0 + ly) * F.W + (px0 + lx);
-                if (!kPacked && finish && is_marked(kk)) kk = refined(kk, i);
                 depth[p] = kk == ~0ull ? INFINITY : __uint_as_float((uint32_t)(kk >> 32));
                 out_id[p] = (uint32_t)kk;   // no hit: kBackground, the key's low word
             }
