@@ -709,12 +709,13 @@ static void scene_depth_classes(const vtx_scene* sc, Frame* F) {
 // the visible clusters hides, so it pays when many atoms are in view
 // (estimated: the share of the scene's box in the view volume) and the scene
 // is opaque (its atoms' cross-sections cover a face of its box many times
-// over).  us per frame in one pass and in two, SSAO 16, two views each:
-//   100M compartments (a quarter in view or more, cover 32), 4K: 769 to 1,093
-//     and 599 to 921; 1080p: 471 to 602 and 279 to 332
-//   40M (10M to 16M in view, cover 24), 4K: 559, 577 and 604, 556
-//   20M (cover 19), 4K: 468 to 472 and 556 to 572
-//   ball of 20M (cover 300), 4K: 694 to 701 and 626 to 630; of 5M: 361 and 484
+// over).  us per frame in one pass and in two, SSAO 16, one to five views each:
+//   100M compartments (a quarter in view or more, cover 32), 4K: 650 to 1,070
+//     and 452 to 792; 1080p: 524 to 591 and 297 to 300
+//   40M (10M to 16M in view, cover 24), 4K: 456 to 483 and 442 to 476; 1080p:
+//     322 to 358 and 271 to 302
+//   20M (cover 19), 4K: 373 to 383 and 439 to 450; 1080p: 243 to 261 and 281 to 289
+//   ball of 20M (cover 300), 4K: 524 to 529 and 392 to 394; of 5M: 264 and 327
 //   20M atoms and bonds (thin: cells keep gaps): 881 to 1,134 and 920 to 1,336
 constexpr double kPrePassAtoms = 16e6, kPrePassCover = 20.0;
 
@@ -919,14 +920,15 @@ int render_locked(std::vector<JobDesc>& d, bool bin, bool shade, hipStream_t str
     }
     // A launch of small resident scenes bins them in their stored order,
     // without the cluster test, the depth classes and the layers (three
-    // launches and 12 to 18 us).  The front-to-back lists pay where a tile
-    // holds many primitives, so it needs few per tile, fewer the larger the
-    // launch is.  us by clusters and stored: 4,000 atoms at 256x256 (16 per
-    // tile) 67 and 56, 70,000 at 720p (19) 88 and 70, four views of 40,000
-    // primitives (3 to 11) 205 and 182, 107,500 atoms with bonds at 1080p (26)
-    // 132 and 120, 70,000 at 640x480 (58) 96 and 86; but 200,000 at 720p (56)
-    // 107 and 113, 500,000 at 1080p (61) 145 and 162, and 256 renders of
-    // 50,000 9,530 and 9,740.
+    // launches and 9 to 16 us).  The front-to-back lists pay where a tile
+    // holds many primitives, and in launches long enough for what they hide
+    // to outweigh those.  us by clusters and stored: 4,000 atoms at 256x256 (16
+    // per tile) 42 and 33, 70,000 at 720p (19) 62 and 49, 70,000 at 640x480
+    // (58) 52 and 45, 200,000 at 720p (56) 65 and 58, 200,000 at 1440p (14)
+    // 126 and 111, 500,000 at 1080p (61) 95 and 94, four views of 40,000
+    // primitives (3 to 11) 186 and 166, 107,500 atoms with bonds at 1080p (26)
+    // 103 and 94; but 200,000 at 640x480 (167) 56 and 75, 900,000 at 1080p
+    // (110) 102 and 112, and 256 renders of 50,000 8,560 and 8,700.
     uint64_t binned = 0, per_tile = 0;
     bool stored = scene;
     for (const JobDesc& j : d) {
@@ -935,7 +937,7 @@ int render_locked(std::vector<JobDesc>& d, bool bin, bool shade, hipStream_t str
         per_tile = std::max(per_tile, (np + tiles - 1) / tiles);
         stored = stored && j.scene && !(j.F.flags & VTX_FLAG_TWO_PASS);
     }
-    stored = stored && ((binned <= 1u << 17 && per_tile <= 64) || (binned <= 1u << 19 && per_tile <= 32));
+    stored = stored && binned <= 1u << 19 && per_tile <= 64;
     const bool clusters = scene && !stored;
     const vtx::BinForm bin_form = !scene ? vtx::kBinArrays : stored ? vtx::kBinStored : vtx::kBinClusters;
     const vtx::ShadeForm form = vtx::shade_form(noise, pixels);

@@ -766,11 +766,10 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_scatter(JS js, int phase) {
 // workgroup's primitives are a serial chain (four rounds of 1024 threads for
 // 4096), so a single render cuts them finer: 512 primitives each up to 128
 // workgroups, 1024 up to 256.  Past those the finer cut loses: every
-// workgroup adds to, and reserves a run in, each tile it touches, and 107,640
-// large spheres at 3840x2160 took 604 us in 210 workgroups against 594 in
-// 106.  (4,096 atoms at 256x256: 73 us in one workgroup, 58 in 8; 50,000 at
-// 720p: 98 in 13, 82 in 98; 214,785 primitives at 1080p: 162 in 53, 146 in
-// 210.)  A batch's renders share the device: 512 workgroups over all of them
+// workgroup adds to, and reserves a run in, each tile it touches (count and
+// scatter of a figure of large spheres at 3840x2160: 36 us in 128 workgroups,
+// 44 in 256).  4,096 atoms at 256x256 take 29 us in one workgroup and 14 in 8;
+// 50,000 at 720p 34 us in 13 and 18 in 98.  A batch's renders share the device: 512 workgroups over all of them
 // are enough, and 256 renders of 50,000 atoms lose 8 % with 98 each.
 void bin_grid(uint64_t nprim, uint64_t renders, uint32_t* groups, uint32_t* chunk) {
     const uint64_t share = std::max<uint64_t>(1, kMaxBinGroups / std::max<uint64_t>(1, renders));
@@ -798,11 +797,11 @@ inline bool atoms_only(const JobList& js) { return js.no_bonds != 0; }
 
 // A scene of few clusters per binning workgroup is dealt by quarters: whole
 // clusters would leave most of the workgroup's 16 waves without work
-// (107,500 atoms with bonds, two clusters per workgroup: 29 us by clusters,
-// 23 by quarters).  So is any scene with bonds (1M atoms and bonds: 48 us by
-// clusters, 46 by quarters); large atom-only scenes are not, whose waves then
-// wait on a cluster id per quarter (100M atoms: 180 us by clusters, 199 by
-// quarters).
+// (107,500 atoms with bonds, two clusters per workgroup: 16.6 us by clusters,
+// 10.7 by quarters).  So is any scene with bonds (1M atoms and bonds: 32 us
+// either way); large atom-only scenes are not, whose waves then wait on a
+// cluster id per quarter (100M atoms: 170 us by clusters, 185 by quarters;
+// 256 renders of 50,000 atoms 121 and 129).
 inline bool quarters(const OneJob& js) { return js.j.S.atom_clusters <= kFewClusters * js.j.bb.groups; }
 inline bool quarters(const JobList& js) { return js.few_clusters != 0; }
 
