@@ -55,12 +55,10 @@ TRAFFIC_FILES = {"ball_and_stick_1000k_1920x1080": "hbm_traffic_ball_and_stick_1
                  "whole_cell_100M_3840x2160": "hbm_traffic_whole_cell_100M_4k.txt",
                  "trajectory_50k_64x4": "hbm_traffic_trajectory_50k_64x4.txt",
                  "ses_globule_50k_h0.5": "hbm_traffic_ses_globule_50k_h0.5.txt"}
-KERNEL_SOURCES = {"k_resolve": "resolve.hip", "k_resolve_tail": "resolve.hip", "k_refine": "resolve.hip",
-                  "k_count": "bin.hip", "k_layers": "bin.hip", "k_tile_offsets": "bin.hip",
+KERNEL_SOURCES = {"k_resolve": "resolve.hip", "k_cluster_rest": "scene.hip", "k_count": "bin.hip", "k_layers": "bin.hip", "k_tile_offsets": "bin.hip",
                   "k_scatter": "bin.hip", "k_shade": "shade.hip", "k_cluster_cull": "scene.hip",
-                  "k_ses_mark": "ses.hip", "k_ses_edt_x_lds": "ses.hip", "k_ses_edt_yz_lds": "ses.hip",
-                  "k_ses_count": "ses.hip", "k_ses_emit": "ses.hip", "k_scan_sums": "scan.hip",
-                  "k_scan_top": "scan.hip", "k_scan_apply": "scan.hip"}
+                  "k_ses_mark": "ses.hip", "k_ses_edt": "ses.hip", "k_ses_count": "ses.hip", "k_ses_emit": "ses.hip",
+                  "k_scan_one": "scan.hip", "k_zero": "bin.hip"}
 # the launches of one vtx_ses call on the benchmark's grid (windows of at
 # most 32 steps: the distance passes staged through LDS)
 SES_KERNELS = ["k_ses_mark", "k_ses_edt_x_lds<32>", "k_ses_edt_yz_lds<false>", "k_ses_edt_yz_lds<true>",
@@ -689,19 +687,32 @@ def run_workload(args, workload, vtx, scenes, torch, stream, steps_arg, warmup_a
     scene_path = batch or runner.path == "scene"
     res_tiles = sorted({eff_tile(r) for r in runner.renders})
     # the launches of each stage, named as the kernel trace names them (template
-    # arguments: launch form; count: scene, rest pass, atoms only; resolve:
-    # tile, counting, two-pass; shade: noise)
+    # arguments: launch form; count: scene, rest pass, atoms only, quarters,
+    # stored order; scatter: scans the tile counts; resolve: tile, counting,
+    # pass; shade: noise, tile)
     form = "JobList" if batch else "OneJob"
-    atoms_only = "true" if M == 0 else "false"
-    noise = "true" if getattr(runner.renders[0].options, "ssao_noise", 0) else "false"
-    launched = {"project": ([f"k_cluster_cull<{form}>", f"k_count<{form},true,false,{atoms_only}>"] if scene_path
-                            else [f"k_count<{form},false,false,false>"]),
-                "scatter": [f"k_scatter<{form}>"],
-                "resolve": ([k for t in res_tiles for k in (f"k_resolve<{t},{form},false,false>",
-                                                             f"k_resolve_tail<{t},{form},false,false>")] +
-                            (["k_refine<JobList>"] if batch else [])),
-                "shade": [f"k_shade<{form},{noise}>"],
-                "scan": []}
+    pixels = sum(r.W * r.H for r in runner.renders)
+    prims = (N + M) * len(runner.renders)
+    per_tile = max((N + M) * t * t / (r.W * r.H) for r in runner.renders for t in res_tiles)
+    noise = bool(getattr(runner.renders[0].options, "ssao_noise", 0))
+    two_pass = scene_path and not batch and M == 0 and N >= 64_000_000   # the whole cell takes the pre-pass unasked
+    stored = scene_path and prims <= 1 << 19 and per_tile <= 64
+    clusters = scene_path and not stored
+    counts = {"two_pass": [f"k_count<{form},true,false,true,true,false>", f"k_cluster_rest<{form}>",
+                           f"k_count<{form},true,true,false,false,false>"],
+              "stored": [f"k_count<{form},false,false,false,false,true>"],
+              "bonds": [f"k_count<{form},true,false,false,true,false>"],
+              "atoms": [f"k_count<{form},true,false,true,false,false>"],
+              "arrays": [f"k_count<{form},false,false,false,false,false>"]}
+    count_form = ("arrays" if not scene_path else "stored" if stored else "two_pass" if two_pass
+                  else "bonds" if M else "atoms")
+    passes = [1, 2] if two_pass else [0]
+    shade_tile = "16,16" if pixels < (3 << 20 if noise else 128 << 20) else "32,32" if noise else "64,16"
+    launched = {"project": ([f"k_cluster_cull<{form}>"] if clusters else []) + counts[count_form],
+                "scatter": [f"k_scatter<{form},true>"] * len(passes),
+                "resolve": [f"k_resolve<{t},{form},false,{ph}>" for t in res_tiles for ph in passes],
+                "shade": [f"k_shade<{form},{'true' if noise else 'false'},{shade_tile}>"],
+                "scan": [f"k_layers<{form}>"] * len(passes) if clusters else []}
     traffic = measured_traffic(name, launched[dom]) if (launched[dom] and scene_path) else None
     roof = {"kernel": dom, "launches": launched[dom], **roof, "traffic": None if traffic is None else round(traffic),
             "timing": "per-kernel dispatch events (hipExtLaunchKernel start/stop), mean over the timed steps"}
@@ -711,8 +722,7 @@ def run_workload(args, workload, vtx, scenes, torch, stream, steps_arg, warmup_a
     frame_rl = frame_roofline(N, M, st, K, runner.renders, ms_per_step)
     frame_valu = None
     if scene_path:
-        step_kernels = (launched["project"] + [f"k_layers<{form}>", f"k_tile_offsets<{form}>"] + launched["scatter"] +
-                        launched["resolve"] + launched["shade"])
+        step_kernels = [k for stage in ("project", "scan", "scatter", "resolve", "shade") for k in launched[stage]]
         v = measured_valu(name, step_kernels)
         if v is not None:
             frame_valu = {"valu_wave_instr": round(v), "issue_frac": round(v * 4 / (ms_per_step * 1e-3 * 1024 * 2.4e9), 4),
@@ -787,7 +797,8 @@ def run_ses(args, vtx, scenes, torch, stream, cpu=True):
         step()
     torch.cuda.synchronize()
     ms = (time.perf_counter() - a) / steps * 1e3
-    # algorithmic bytes: the mark (1 B), three distance passes (4 B written
+    # algorithmic bytes of separable passes through memory (the kernels keep
+    # theirs in LDS): the mark (1 B), three distance passes (4 B written
     # each, 1 + 4 + 4 B read), the field read by the count and the emission
     # (4 B each), per cube the count written, scanned and read (12 B), and
     # 36 B per triangle written; the atoms (16 B each)

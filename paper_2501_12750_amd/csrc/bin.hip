@@ -15,7 +15,9 @@
 //            of the workgroups), one atomic per touched tile;
 //   layers   resident scenes: the per-layer totals become the start of each
 //            layer's run in every tile list, and the tile totals;
-//   offsets  one exclusive scan of the tile totals per job: the list offsets;
+//   offsets  one exclusive scan of the tile totals per job: the list offsets
+//            (up to 8192 tiles by the scatter's workgroups themselves), and
+//            for a single render the order the resolve takes the tiles in;
 //   scatter  each workgroup reserves, per touched tile, one run of the tile's
 //            list inside its layer's run (one atomic), then places its
 //            primitives with LDS atomics (one per run of lanes with the same
