@@ -55,14 +55,13 @@ TRAFFIC_FILES = {"ball_and_stick_1000k_1920x1080": "hbm_traffic_ball_and_stick_1
                  "whole_cell_100M_3840x2160": "hbm_traffic_whole_cell_100M_4k.txt",
                  "trajectory_50k_64x4": "hbm_traffic_trajectory_50k_64x4.txt",
                  "ses_globule_50k_h0.5": "hbm_traffic_ses_globule_50k_h0.5.txt"}
-KERNEL_SOURCES = {"k_resolve": "resolve.hip", "k_cluster_rest": "scene.hip", "k_count": "bin.hip", "k_layers": "bin.hip", "k_tile_offsets": "bin.hip",
+KERNEL_SOURCES = {"k_resolve": "resolve.hip", "k_cluster_rest": "scene.hip", "k_count": "bin.hip", "k_layers": "bin.hip",
                   "k_scatter": "bin.hip", "k_shade": "shade.hip", "k_cluster_cull": "scene.hip",
                   "k_ses_mark": "ses.hip", "k_ses_edt": "ses.hip", "k_ses_count": "ses.hip", "k_ses_emit": "ses.hip",
                   "k_scan_one": "scan.hip", "k_zero": "bin.hip"}
-# the launches of one vtx_ses call on the benchmark's grid (windows of at
-# most 32 steps: the distance passes staged through LDS)
-SES_KERNELS = ["k_ses_mark", "k_ses_edt_x_lds<32>", "k_ses_edt_yz_lds<false>", "k_ses_edt_yz_lds<true>",
-               "k_ses_count", "k_scan_sums", "k_scan_top", "k_scan_apply", "k_ses_emit"]
+# the launches of one vtx_ses call on the benchmark's grid (a window of 5
+# steps: the distance passes of a brick in LDS; up to 8192 cube runs: one scan)
+SES_KERNELS = ["k_zero", "k_ses_mark", "k_ses_edt<5>", "k_ses_count", "k_scan_one", "k_ses_emit"]
 
 
 def log(msg):
@@ -688,7 +687,7 @@ def run_workload(args, workload, vtx, scenes, torch, stream, steps_arg, warmup_a
     res_tiles = sorted({eff_tile(r) for r in runner.renders})
     # the launches of each stage, named as the kernel trace names them (template
     # arguments: launch form; count: scene, rest pass, atoms only, quarters,
-    # stored order; scatter: scans the tile counts; resolve: tile, counting,
+    # stored order; scatter: parts of the tile counts; resolve: tile, counting,
     # pass; shade: noise, tile)
     form = "JobList" if batch else "OneJob"
     pixels = sum(r.W * r.H for r in runner.renders)
@@ -709,7 +708,7 @@ def run_workload(args, workload, vtx, scenes, torch, stream, steps_arg, warmup_a
     passes = [1, 2] if two_pass else [0]
     shade_tile = "16,16" if pixels < (3 << 20 if noise else 128 << 20) else "32,32" if noise else "64,16"
     launched = {"project": ([f"k_cluster_cull<{form}>"] if clusters else []) + counts[count_form],
-                "scatter": [f"k_scatter<{form},true>"] * len(passes),
+                "scatter": [f"k_scatter<{form},1>"] * len(passes),
                 "resolve": [f"k_resolve<{t},{form},false,{ph}>" for t in res_tiles for ph in passes],
                 "shade": [f"k_shade<{form},{'true' if noise else 'false'},{shade_tile}>"],
                 "scan": [f"k_layers<{form}>"] * len(passes) if clusters else []}

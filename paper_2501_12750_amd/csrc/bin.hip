@@ -15,10 +15,8 @@
 //            of the workgroups), one atomic per touched tile;
 //   layers   resident scenes: the per-layer totals become the start of each
 //            layer's run in every tile list, and the tile totals;
-//   offsets  one exclusive scan of the tile totals per job: the list offsets
-//            (up to 8192 tiles by the scatter's workgroups themselves), and
-//            for a single render the order the resolve takes the tiles in;
-//   scatter  each workgroup reserves, per touched tile, one run of the tile's
+//   scatter  each workgroup takes the exclusive scan of the tile totals (the
+//            list offsets) and reserves, per touched tile, one run of the tile's
 //            list inside its layer's run (one atomic), then places its
 //            primitives with LDS atomics (one per run of lanes with the same
 //            tile): 8 bytes per (primitive, tile), the source index and the
@@ -527,34 +525,6 @@ __device__ __forceinline__ void publish_lists(const Job& J, unsigned long long t
     }
 }
 
-// List offsets in a launch of their own, one workgroup per job, for images
-// of more tiles than the scatter scans (see scatter_scans).
-template <class JS>
-__global__ void __launch_bounds__(kBinThreads) k_tile_offsets(JS js) {
-    constexpr int kRows = (kMaxLdsTiles + kBinThreads - 1) / kBinThreads;
-    if (blockIdx.x >= js.count()) {
-        if (JS::kOrdered) order_tiles(js.job(0));
-        return;
-    }
-    const Job& J = js.job((int)blockIdx.x);
-    const int T = J.F.tiles_x * J.F.tiles_y;
-    const uint32_t* __restrict__ const cnt = J.bb.tile_cnt;
-    uint64_t* __restrict__ const off = J.bb.tile_off;
-    const uint64_t capacity = J.bb.capacity;
-    uint32_t v[kRows];
-#pragma unroll
-    for (int r = 0; r < kRows; ++r) {
-        const int t = r * kBinThreads + (int)threadIdx.x;
-        v[r] = t < T ? cnt[t] : 0u;
-    }
-    uint32_t n_over = 0;
-    const unsigned long long total = tile_starts<kRows>(v, T, [&](int t, uint64_t o, uint32_t n) {
-        off[t] = o;
-        n_over += o + n > capacity ? 1u : 0u;
-    });
-    publish_lists(J, total, n_over);
-}
-
 // Scatter.  Every workgroup reserves, for each tile its primitives touch,
 // one run of that tile's list (one global atomic), then places its visible
 // primitives kScatterPer per thread at a time, all their loads issued
@@ -563,20 +533,29 @@ __global__ void __launch_bounds__(kBinThreads) k_tile_offsets(JS js) {
 // atomic per run, in one instruction for the wave).  Primitives spanning
 // several tiles take one LDS atomic per tile.  Workgroup 0 also publishes
 // the frame counters.
-// kScan (see scatter_scans): every workgroup scans the tile counts for itself
-// while its reservations are in flight, and workgroup 0 stores the offsets
-// for the resolve.
+// List offsets: every workgroup scans the tile counts for itself while its
+// reservations are in flight, and workgroup 0 stores the offsets for the
+// resolve.  The counts come from L2, which costs less than the 4 to 5 us of a
+// launch of one workgroup per job on small frames (4,096 atoms at 256x256:
+// 51.5 us with the launch, 48.3 without; 1M atoms and bonds at 1080p: 170.2
+// and 167.1) and as much on large ones (four views up to 1440p 158 both; 11M
+// spheres at 4K, 512 workgroups: 640 both; 256 renders of 50,000 atoms: 9,430
+// to 9,445 both).
+// kParts: parts of kScanTiles tiles.  With two the reservations follow the
+// scan, part by part: 16 rows of both at once do not fit the 64 registers (44
+// to 49 spilled).
 constexpr int kScatterPer = 4;
 constexpr int kScanTiles = 8 * kBinThreads;
+static_assert(kMaxLdsTiles <= 2 * kScanTiles, "one or two parts");
 
-template <class JS, bool kScan>
+template <class JS, int kParts>
 __global__ void __launch_bounds__(kBinThreads, 8) k_scatter(JS js, int phase) {
-    constexpr int kTileRows = ((kScan ? kScanTiles : kMaxLdsTiles) + kBinThreads - 1) / kBinThreads;
+    constexpr int kRows = kScanTiles / kBinThreads;
     extern __shared__ uint32_t cur[];
     uint32_t blk;
     const int ji = js.find(blockIdx.x, blk);
     if (ji < 0) {
-        if (kScan && JS::kOrdered) order_tiles(js.job(0));
+        if (JS::kOrdered) order_tiles(js.job(0));
         return;
     }
     const Job& J = js.job(ji);
@@ -608,44 +587,62 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_scatter(JS js, int phase) {
         const uint2 box = to_global(J.bb.vis_box)[blk];
         const uint32_t bx0 = box.x & 0xFFFFu, by0 = box.x >> 16, bx1 = box.y & 0xFFFFu, by1 = box.y >> 16;
         const int bw = bx0 <= bx1 ? (int)(bx1 - bx0) + 1 : 0, nb = bw * (bw ? (int)(by1 - by0) + 1 : 0);
-        uint32_t h[kTileRows], r[kTileRows];
-        uint32_t v[kScan ? kTileRows : 1];
+        uint32_t h[kRows], r[kRows], v[kRows];
+        // kRows rows of the box from row q0 on: their reservations, and then
+        // their cursors
+        auto reserve = [&](int q0) {
 #pragma unroll
-        for (int q = 0; q < kTileRows; ++q) {
-            const int i = q * kBinThreads + tid;
-            h[q] = i < nb ? row[i] : 0u;
-            if constexpr (kScan) v[q] = i < T ? cnt[i] : 0u;
-        }
+            for (int q = 0; q < kRows; ++q) {
+                const int i = (q0 + q) * kBinThreads + tid;
+                h[q] = i < nb ? row[i] : 0u;
+                if (kParts == 1) v[q] = i < T ? cnt[i] : 0u;
+            }
 #pragma unroll
-        for (int q = 0; q < kTileRows; ++q) {
-            const int i = q * kBinThreads + tid;
-            r[q] = h[q] ? atomicAdd(&fill[box_tile(F.tiles_x, bx0, by0, bw, i)], h[q]) : 0u;
-        }
-        if constexpr (kScan) {
-            uint32_t n_over = 0;
-            const unsigned long long total = tile_starts<kTileRows>(v, T, [&](int t, uint64_t o, uint32_t n) {
-                const bool fits = o + n <= capacity;
-                cur[t] = fits ? (uint32_t)o : kNoRun;
-                if (lead) off[t] = o;
-                n_over += fits ? 0u : 1u;
-            });
-            if (lead) publish_lists(J, total, n_over);
-            __syncthreads();   // every tile's start is in LDS
-        }
+            for (int q = 0; q < kRows; ++q) {
+                const int i = (q0 + q) * kBinThreads + tid;
+                r[q] = h[q] ? atomicAdd(&fill[box_tile(F.tiles_x, bx0, by0, bw, i)], h[q]) : 0u;
+            }
+        };
+        auto place = [&](int q0) {
 #pragma unroll
-        for (int q = 0; q < kTileRows; ++q) {
-            const int i = q * kBinThreads + tid;
-            if (i >= nb) break;
-            const int t = box_tile(F.tiles_x, bx0, by0, bw, i);
-            if constexpr (kScan) {
+            for (int q = 0; q < kRows; ++q) {
+                const int i = (q0 + q) * kBinThreads + tid;
+                if (i >= nb) break;
+                const int t = box_tile(F.tiles_x, bx0, by0, bw, i);
                 const uint32_t run = cur[t];
                 if (h[q] && run != kNoRun) cur[t] = run + (loff ? loff[t] : 0u) + r[q];
-                continue;
             }
-            const uint64_t run = off[t];
-            const bool fits = run + cnt[t] <= capacity;   // else the resolve rebuilds this tile from the visible lists
-            cur[t] = h[q] && fits ? (uint32_t)(run + (loff ? loff[t] : 0u) + r[q]) : kNoRun;
+        };
+        if (kParts == 1) reserve(0);   // in flight during the scan
+        uint32_t n_over = 0;
+        unsigned long long total = 0;
+#pragma unroll 1
+        for (int part = 0; part < kParts; ++part) {
+            const int t0 = part * kScanTiles;
+            if (kParts > 1) {
+#pragma unroll
+                for (int q = 0; q < kRows; ++q) {
+                    const int t = t0 + q * kBinThreads + tid;
+                    v[q] = t < T ? cnt[t] : 0u;
+                }
+            }
+            total += tile_starts<kRows>(v, T - t0, [&](int t, uint64_t in, uint32_t n) {
+                const uint64_t o = total + in;
+                const bool fits = o + n <= capacity;   // else the resolve rebuilds this tile from the visible lists
+                cur[t0 + t] = fits ? (uint32_t)o : kNoRun;
+                if (lead) off[t0 + t] = o;
+                n_over += fits ? 0u : 1u;
+            });
         }
+        if (lead) publish_lists(J, total, n_over);
+        __syncthreads();   // every tile's start is in LDS
+        if (kParts == 1) place(0);
+        else
+#pragma unroll 1
+            for (int q0 = 0; q0 < kParts * kRows; q0 += kRows) {
+                reserve(q0);
+                place(q0);
+            }
     }
     if (lead) {
         if (tid == 0) {
@@ -823,16 +820,6 @@ hipError_t count_impl(const JS& js, BinForm form, int phase, uint32_t grid, int 
     return dispatch(k_count<JS, true, false, true>, grid, kBinThreads, lds, stream, js, phase);
 }
 
-// The scatter's workgroups each scan the tile counts, instead of a launch of
-// one workgroup per job before it: the counts come from L2 while the
-// reservations are in flight, which costs less than the launch's 4 to 5 us on
-// small frames (4,096 atoms at 256x256: 51.5 us with the launch, 48.3
-// without; 1M atoms and bonds at 1080p: 170.2 and 167.1) and as much on large
-// ones (11M spheres at 4K, 2,048 workgroups: 640 both; 256 renders of 50,000
-// atoms: 9,430 to 9,445 both).  Past kScanTiles the counts no longer fit the
-// scatter's 64 registers beside the reservations (16 rows spill 49).
-bool scatter_scans(int max_tiles) { return max_tiles <= kScanTiles; }
-
 template <class JS>
 hipError_t scatter_impl(const JS& js, int phase, uint32_t grid, int max_tiles, hipStream_t stream) {
     if (max_tiles > kMaxLdsTiles) return hipErrorInvalidValue;
@@ -841,9 +828,8 @@ hipError_t scatter_impl(const JS& js, int phase, uint32_t grid, int max_tiles, h
     // the workgroup that orders the tiles comes after the others: it takes
     // less time than they do, also where it has to wait for a CU
     const uint32_t extra = JS::kOrdered && max_tiles > kOrderTiles ? 1u : 0u;
-    if (scatter_scans(max_tiles))
-        return dispatch(k_scatter<JS, true>, grid + extra, kBinThreads, lds, stream, js, phase);
-    return dispatch(k_scatter<JS, false>, grid, kBinThreads, lds, stream, js, phase);
+    if (max_tiles <= kScanTiles) return dispatch(k_scatter<JS, 1>, grid + extra, kBinThreads, lds, stream, js, phase);
+    return dispatch(k_scatter<JS, 2>, grid + extra, kBinThreads, lds, stream, js, phase);
 }
 
 hipError_t launch_count(const OneJob& js, BinForm form, int phase, uint32_t grid, int max_tiles, hipStream_t stream) {
@@ -857,14 +843,6 @@ hipError_t launch_layers(const OneJob& js, uint32_t grid, hipStream_t stream) {
 }
 hipError_t launch_layers(const JobList& js, uint32_t grid, hipStream_t stream) {
     return dispatch(k_layers<JobList>, grid, kBinThreads, 0, stream, js);
-}
-hipError_t launch_tile_offsets(const OneJob& js, int max_tiles, hipStream_t stream) {
-    if (scatter_scans(max_tiles)) return hipSuccess;
-    return dispatch(k_tile_offsets<OneJob>, 2, kBinThreads, 0, stream, js);
-}
-hipError_t launch_tile_offsets(const JobList& js, int max_tiles, hipStream_t stream) {
-    if (scatter_scans(max_tiles)) return hipSuccess;
-    return dispatch(k_tile_offsets<JobList>, js.n, kBinThreads, 0, stream, js);
 }
 hipError_t launch_scatter(const OneJob& js, int phase, uint32_t grid, int max_tiles, hipStream_t stream) {
     return scatter_impl(js, phase, grid, max_tiles, stream);

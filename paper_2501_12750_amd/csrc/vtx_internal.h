@@ -735,10 +735,7 @@ hipError_t launch_count(const JobList& js, BinForm form, int phase, uint32_t gri
 hipError_t launch_layers(const OneJob& js, uint32_t grid, hipStream_t stream);
 hipError_t launch_layers(const JobList& js, uint32_t grid, hipStream_t stream);
 // List offsets of every tile (exclusive prefix sum of the counts), the list
-// total and the overflow flag, one workgroup per job; nothing where the
-// scatter takes them itself (up to 8192 tiles).
-hipError_t launch_tile_offsets(const OneJob& js, int max_tiles, hipStream_t stream);
-hipError_t launch_tile_offsets(const JobList& js, int max_tiles, hipStream_t stream);
+// total, the overflow flag and the entries.
 hipError_t launch_scatter(const OneJob& js, int phase, uint32_t grid, int max_tiles, hipStream_t stream);
 hipError_t launch_scatter(const JobList& js, int phase, uint32_t grid, int max_tiles, hipStream_t stream);
 // One workgroup per tile; with `count`, a second launch publishes the
