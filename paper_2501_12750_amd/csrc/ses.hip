@@ -193,12 +193,14 @@ __global__ void __launch_bounds__(kSesMarkBlock) k_ses_mark(const float* __restr
     const double R2 = R * R;
     int lo[3], nc[3];
     const int nmax[3] = {G.nx - 1, G.ny - 1, G.nz - 1};
-    // the box only has to hold every point the test can mark: a thousandth of
-    // a step of margin covers the rounding of the grid coordinates (below
-    // 2^31, so off by less than 2e-6)
+    // the box only has to hold every point the test can mark.  Its ends and the
+    // points' coordinates are rounded at the magnitude of the positions (eight
+    // roundings of 2^-53 at most in all, in steps of the grid), the product by
+    // 1 / h at that of the grid coordinates (below 2^31, so by less than 2e-6).
     for (int d = 0; d < 3; ++d) {
-        const double from = fmax(0.0, ceil((c[d] - R - G.o[d]) * G.inv_h - 1e-3));
-        const double to = fmin((double)nmax[d], floor((c[d] + R - G.o[d]) * G.inv_h + 1e-3));
+        const double margin = 1e-3 + (fabs(c[d]) + R + fabs(G.o[d])) * G.inv_h * 0x1p-50;
+        const double from = fmax(0.0, ceil((c[d] - R - G.o[d]) * G.inv_h - margin));
+        const double to = fmin((double)nmax[d], floor((c[d] + R - G.o[d]) * G.inv_h + margin));
         if (!(from <= to) || !(c[d] - c[d] == 0.0)) return;   // beside the grid, or not a finite position
         const int l = (int)from, h = (int)to;
         lo[d] = l >> 2;

@@ -70,3 +70,20 @@ def test_no_atoms(vtx):
     f, tri, n = run_ses(vtx, np.zeros((0, 3), np.float32), np.zeros(0, np.float32), 1.4, (0.0, 0.0, 0.0), 0.5, dims, 16)
     assert n == 0 and np.all(f < 0.0)
     torch.cuda.synchronize()
+
+
+def test_positions_far_beyond_the_spacing(vtx):
+    """Coordinates of 2^27 at a spacing of 1e-6: their rounding is 0.03 steps,
+    so a point that the rounded sphere holds can lie past the rounded end of
+    the atom's box by more than any fixed margin."""
+    rng = np.random.default_rng(0)
+    o = 2.0 ** 27
+    left_out = 0
+    for _ in range(2000):
+        h = float(np.float32(1e-6 * rng.uniform(0.5, 2.0)))
+        r = float(np.float32(h * rng.uniform(2.0, 9.0)))
+        x = (o + h * np.arange(14)) - o
+        if np.flatnonzero(x * x < r * r).max() > np.floor((o + r - o) * (1.0 / h) + 1e-3):
+            left_out += 1
+            check(vtx, np.full((1, 3), o, np.float32), np.array([r], np.float32), 0.0, (o, o, o), h, (14, 14, 14))
+    assert left_out > 5
