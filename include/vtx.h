@@ -521,7 +521,10 @@ typedef struct vtx_tuning {
                                  (-1: no sample job asked for them) */
     uint64_t bin_capacity;    /* tile-list entries reserved for a render of this shape:
                                  5/4 of the most (primitive, tile) pairs of a sample
-                                 job at the chosen tile size, plus 1024 */
+                                 job at the chosen tile size in one pass, plus 1024
+                                 (0: read from a cache file that does not say the
+                                 pairs were one pass's, for a shape whose renders may
+                                 take two; its renders count first) */
     float ms_by_samples[9];   /* per-render device time with 64, 48, 32, 24, 16, 12, 8, 4, 0
                                  samples (0 = not timed) */
 } vtx_tuning;
@@ -541,9 +544,10 @@ typedef struct vtx_tuning {
  *    images accept; the fastest is used by renders of those shapes that leave
  *    options.tile_size at 0 (vtx_render_scene, vtx_render_batch).  Images do
  *    not depend on the tile size.
- *  - bin capacity: the (primitive, tile) pairs of each sample job are read
- *    back at the chosen size; a render of the shape whose scratch is new sizes
- *    its lists from them instead of counting first and waiting for the count.
+ *  - bin capacity: the (primitive, tile) pairs of each sample job, drawn in
+ *    one pass, are read back at the chosen size; a render of the shape whose
+ *    scratch is new sizes its lists from them instead of counting first and
+ *    waiting for the count.
  *    Images do not depend on it either (a frame that outgrows its lists is
  *    resolved exactly from the visible lists).
  *  - SSAO samples, only when a sample job's options ask for VTX_SSAO_AUTO:

@@ -641,6 +641,7 @@ struct TunedShape {
     int tile = 0;            // tile size (0: none)
     int ssao = -1;           // SSAO samples of VTX_SSAO_AUTO renders (-1: none chosen)
     uint64_t capacity = 0;   // tile-list entries for a render's new scratch (0: none)
+    bool one_pass = false;   // the capacity holds a one-pass frame's pairs
 };
 constexpr int kAutoSsaoDefault = 16;
 
@@ -806,6 +807,10 @@ std::string shape_key(int32_t W, int32_t H, int64_t n, int64_t m, int32_t projec
     return buf;
 }
 
+// Whether a shape's renders may take the pre-pass unasked (the keys' classes of
+// primitive counts from the one that holds kPrePassAtoms on).
+bool may_pre_pass(int64_t n, int64_t m) { return n + m >= (int64_t)1 << std::ilogb(kPrePassAtoms); }
+
 // Options with the choices the context tuned for this shape where the
 // caller left them to the library (tile size 0, VTX_SSAO_AUTO samples), and
 // the tuned tile-list capacity (0: none).
@@ -818,7 +823,7 @@ vtx_options tuned_options(vtx_context* ctx, vtx_options o, const vtx_camera* cam
         if (it != ctx->tuned.end()) {
             if (o.tile_size == 0) o.tile_size = it->second.tile;
             if (o.ssao_samples == VTX_SSAO_AUTO && it->second.ssao >= 0) o.ssao_samples = it->second.ssao;
-            if (capacity) *capacity = it->second.capacity;
+            if (capacity && (it->second.one_pass || !may_pre_pass(n, m))) *capacity = it->second.capacity;
         }
     }
     if (o.ssao_samples == VTX_SSAO_AUTO) o.ssao_samples = kAutoSsaoDefault;
@@ -1134,6 +1139,9 @@ int render_locked(std::vector<JobDesc>& d, bool bin, bool shade, hipStream_t str
             two_pass = d[i].scene && ((d[i].F.flags & VTX_FLAG_TWO_PASS) || d[i].pre_pass) &&
                        !(d[i].F.flags & (VTX_FLAG_STATS | VTX_FLAG_COUNT | VTX_FLAG_ONE_PASS)) &&
                        d[i].F.tile >= vtx::kHzCell;
+        // its counters hold the larger pass's pairs, which say nothing of a
+        // one-pass frame's: they are not noted for the scene
+        for (size_t i = 0; i < n && two_pass; ++i) ws->slots[i]->pending_uid = 0;
         if (clusters) {
             if (n == 1) VTX_HIP(vtx::launch_cluster_cull(one(g_cull), g_cull, stream));
             else VTX_HIP(vtx::launch_cluster_cull(list_of(0, n, 0), g_cull, stream));
@@ -1920,17 +1928,20 @@ int vtx_autotune(vtx_context* ctx, const vtx_job* jobs, int32_t n_jobs, const ch
     t.frame_budget_ms = budget;
     t.ssao_samples = -1;
     // cached choices: one line per shape
-    //   {"key": K, "tile_size": T, "ssao_samples": S, "bin_capacity": C, "ms_per_batch": M}
+    //   {"key": K, "tile_size": T, "ssao_samples": S, "bin_capacity": C, "one_pass": 1, "ms_per_batch": M}
+    // An entry without "one_pass" may hold what one pass of a two-pass frame
+    // binned, about half a one-pass frame's pairs: where a shape's renders may
+    // take two passes, its capacity is left to the first frame's count.
     std::vector<std::pair<std::string, std::string>> lines;   // key -> its cache line
     if (cache_path && *cache_path) {
         if (FILE* fh = std::fopen(cache_path, "r")) {
             char buf[512];
             while (std::fgets(buf, sizeof(buf), fh)) {
                 char k[160];
-                int tile = 0, ssao = -1;
+                int tile = 0, ssao = -1, one_pass = 0;
                 unsigned long long cap = 0;
-                if (std::sscanf(buf, " {\"key\": \"%159[^\"]\", \"tile_size\": %d, \"ssao_samples\": %d, \"bin_capacity\": %llu",
-                                k, &tile, &ssao, &cap) >= 2) {
+                if (std::sscanf(buf, " {\"key\": \"%159[^\"]\", \"tile_size\": %d, \"ssao_samples\": %d, \"bin_capacity\": %llu, \"one_pass\": %d",
+                                k, &tile, &ssao, &cap, &one_pass) >= 2) {
                     std::string line(buf);
                     while (!line.empty() && (line.back() == '\n' || line.back() == ',' || line.back() == ' '))
                         line.pop_back();
@@ -1940,6 +1951,7 @@ int vtx_autotune(vtx_context* ctx, const vtx_job* jobs, int32_t n_jobs, const ch
                         ts.tile = tile;
                         ts.ssao = ssao >= 0 && ssao <= VTX_MAX_SSAO_SAMPLES ? ssao : -1;
                         ts.capacity = cap <= kMaxCapacity ? (uint64_t)cap : 0;
+                        ts.one_pass = one_pass == 1;
                         cached[k] = ts;
                     }
                 }
@@ -1954,7 +1966,8 @@ int vtx_autotune(vtx_context* ctx, const vtx_job* jobs, int32_t n_jobs, const ch
         t.from_cache = 1;
         t.tile_size = cached[key].tile;
         t.ssao_samples = want_ssao ? cached[key].ssao : -1;
-        t.bin_capacity = cached[key].capacity;
+        t.bin_capacity =
+            cached[key].one_pass || !may_pre_pass(jobs[0].scene->n, jobs[0].scene->m) ? cached[key].capacity : 0;
     } else {
         hipStream_t st = (hipStream_t)stream;
         hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -2004,9 +2017,12 @@ int vtx_autotune(vtx_context* ctx, const vtx_job* jobs, int32_t n_jobs, const ch
             t.ms_per_batch = best;
             for (vtx_job& j : trial) j.options.tile_size = t.tile_size;
         }
-        // 2. bin capacity: the pairs of each sample job at that size
+        // 2. bin capacity: the pairs of each sample job at that size, in one
+        // pass (of a two-pass frame the counters hold the larger pass's)
         std::map<std::string, uint64_t> cap;
+        for (vtx_job& j : trial) j.options.flags = VTX_FLAG_ONE_PASS;
         if (rc == VTX_OK) rc = vtx_render_batch(ctx, trial.data(), n_jobs, stream);
+        for (vtx_job& j : trial) j.options.flags = 0;
         if (rc == VTX_OK && hipStreamSynchronize(st) != hipSuccess) rc = fail(VTX_EHIP, "hipStreamSynchronize failed");
         if (rc == VTX_OK) {
             std::lock_guard<std::mutex> lk(g_mu);
@@ -2052,6 +2068,7 @@ int vtx_autotune(vtx_context* ctx, const vtx_job* jobs, int32_t n_jobs, const ch
             ts.tile = t.tile_size;
             ts.ssao = ssao >= 0 ? ssao : (cached.count(k) ? cached[k].ssao : -1);
             ts.capacity = cap[k];
+            ts.one_pass = true;
             cached[k] = ts;
         }
         if (cache_path && *cache_path) {
@@ -2059,7 +2076,7 @@ int vtx_autotune(vtx_context* ctx, const vtx_job* jobs, int32_t n_jobs, const ch
                 char line[320];
                 std::snprintf(line, sizeof(line),
                               "  {\"key\": \"%s\", \"tile_size\": %d, \"ssao_samples\": %d, \"bin_capacity\": %llu, "
-                              "\"ms_per_batch\": %.6f}",
+                              "\"one_pass\": 1, \"ms_per_batch\": %.6f}",
                               k.c_str(), cached[k].tile, cached[k].ssao, (unsigned long long)cached[k].capacity,
                               (double)best);
                 bool replaced = false;

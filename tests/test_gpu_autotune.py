@@ -146,3 +146,109 @@ def test_autotune_picks_ssao_samples_within_a_budget(vtx, tmp_path):
     rs.close()
     vtx.vtx_context_destroy(ctx)
     vtx.vtx_context_destroy(ctx2)
+
+
+# ---------------------------------------------------------------------------
+# Scenes large and opaque enough to take the occlusion pre-pass unasked
+# ---------------------------------------------------------------------------
+W_BALL, H_BALL = 1280, 960   # too many 8-pixel tiles, which keep to one pass
+
+
+@pytest.fixture(scope="module")
+def ball():
+    """17M atoms in a ball seen whole: its frames take two passes once their lists are sized."""
+    n = 17_000_000
+    rng = np.random.default_rng(17)
+    radius = (3.0 * n / (4.0 * np.pi * 0.1)) ** (1.0 / 3.0)
+    d = rng.normal(size=(n, 3)).astype(np.float32)
+    d *= (radius * np.cbrt(rng.uniform(size=n)) / np.linalg.norm(d, axis=1)).astype(np.float32)[:, None]
+    scene = scenes.Scene(d, np.full(n, 1.6, np.float32), np.full(n, scenes.pack_rgba(200, 180, 160), np.uint32),
+                         np.zeros((0, 2), np.uint32))
+    return scenes.Workload("ball", scene, scenes.orbit_camera((0.0, 0.0, 0.0), 1.2 * radius, 0.4),
+                           scenes.Options(ssao_samples=0), W_BALL, H_BALL)
+
+
+def _fresh_stream(vtx):
+    """A stream without scratch (torch hands the same streams out again)."""
+    import torch
+    stream = torch.cuda.Stream()
+    vtx.vtx_release_scratch(stream)
+    return stream
+
+
+def _frame_stats(vtx, rs, wl, flags, stream):
+    """Statistics of the scene's next frame on the stream."""
+    import torch
+    with torch.cuda.stream(stream):
+        rs.render(wl.camera, with_opts(wl.options, flags=flags), wl.width, wl.height, stream=stream)
+    stream.synchronize()
+    return vtx.vtx_read_stats(stream)
+
+
+def _ball_job(vtx, rs, wl):
+    fr = vtx.Frame(wl.width, wl.height)
+    return fr, vtx.make_job(rs.handle, 0, wl.camera, wl.options, wl.width, wl.height, fr.rgba, fr.depth, fr.id)
+
+
+def test_tuned_lists_hold_the_one_pass_frames_of_a_pre_pass_scene(vtx, ball, tmp_path):
+    ctx = vtx.vtx_context_create(0, 0)
+    rs = vtx.ResidentScene(ctx, vtx.DeviceScene(ball.scene))
+    fr, job = _ball_job(vtx, rs, ball)
+    t = vtx.vtx_autotune(ctx, [job], tmp_path / "t.json")
+    two = _frame_stats(vtx, rs, ball, 0, _fresh_stream(vtx))
+    for flags in (vtx.VTX_FLAG_ONE_PASS, vtx.VTX_FLAG_STATS):
+        st = _frame_stats(vtx, rs, ball, flags, _fresh_stream(vtx))
+        print("capacity", t["bin_capacity"], "pairs in one pass", st["pairs"], "the larger of two", two["pairs"], flush=True)
+        assert two["pairs"] < st["pairs"] and st["bin_capacity"] == t["bin_capacity"]
+        assert st["overflow_tiles"] == 0
+        assert t["bin_capacity"] == st["pairs"] + st["pairs"] // 4 + 1024
+    # read back from the cache, the capacity is the same
+    ctx2 = vtx.vtx_context_create(0, 0)
+    t2 = vtx.vtx_autotune(ctx2, [job], tmp_path / "t.json")
+    assert t2["from_cache"] and t2["bin_capacity"] == t["bin_capacity"]
+    rs.close()
+    vtx.vtx_context_destroy(ctx)
+    vtx.vtx_context_destroy(ctx2)
+
+
+def test_a_cache_entry_of_unknown_passes_is_counted_anew(vtx, ball, tmp_path):
+    """A cache that does not say its pairs were one pass's: the tile size is
+    taken, the capacity is not, so that the first frame counts its pairs.  A
+    shape too small for the pre-pass keeps its capacity."""
+    ctx = vtx.vtx_context_create(0, 0)
+    rs = vtx.ResidentScene(ctx, vtx.DeviceScene(ball.scene))
+    fr, job = _ball_job(vtx, rs, ball)
+    small, cams, opts = _setup(vtx, ctx)
+    jobs, _ = _batch(vtx, ctx, small, cams, opts, 16)
+    cache = tmp_path / "old.json"
+    cache.write_text('{"vtx_tuning": [\n'
+                     '  {"key": "1280x960/p24/persp", "tile_size": 32, "ssao_samples": -1, "bin_capacity": 2000, "ms_per_batch": 0.5},\n'
+                     '  {"key": "480x270/p11/persp", "tile_size": 32, "ssao_samples": -1, "bin_capacity": 70000, "ms_per_batch": 0.5}\n'
+                     ']}\n')
+    t = vtx.vtx_autotune(ctx, [job], cache)
+    assert t["from_cache"] and t["tile_size"] == 32 and t["bin_capacity"] == 0
+    st = _frame_stats(vtx, rs, ball, vtx.VTX_FLAG_ONE_PASS, _fresh_stream(vtx))
+    assert st["overflow_tiles"] == 0 and st["bin_capacity"] > st["pairs"] > 2000
+    t = vtx.vtx_autotune(ctx, jobs, cache)
+    assert t["from_cache"] and t["tile_size"] == 32 and t["bin_capacity"] == 70000
+    rs.close()
+    small.close()
+    vtx.vtx_context_destroy(ctx)
+
+
+def test_two_pass_pairs_size_no_other_stream(vtx, ball):
+    """Frames of a fixed capacity take two passes without a count: what they
+    bin is not taken for the pairs of the scene on another stream."""
+    ctx = vtx.vtx_context_create(0, 0)
+    rs = vtx.ResidentScene(ctx, vtx.DeviceScene(ball.scene))
+    fixed, other = _fresh_stream(vtx), _fresh_stream(vtx)
+    vtx.vtx_set_bin_capacity(60_000_000, fixed)
+    for _ in range(2):
+        two = _frame_stats(vtx, rs, ball, 0, fixed)
+    st = _frame_stats(vtx, rs, ball, vtx.VTX_FLAG_ONE_PASS, other)
+    print("two passes", two, "one", st, flush=True)
+    assert two["overflow_tiles"] == 0 and two["pairs"] < st["pairs"]
+    assert st["overflow_tiles"] == 0 and st["bin_capacity"] >= st["pairs"]
+    rs.close()
+    vtx.vtx_release_scratch(fixed)
+    vtx.vtx_context_destroy(ctx)
