@@ -80,8 +80,9 @@ extern "C" {
                                     scenes without bonds take it unasked when some
                                     16 million of their atoms are in view and the
                                     atoms' cross-sections cover a face of their box
-                                    20 times; vtx_stats then counts the primitives
-                                    binned.  Ignored with
+                                    20 times (and a clip plane does not cut the
+                                    nearest of them away); vtx_stats then counts the
+                                    primitives binned.  Ignored with
                                     VTX_FLAG_STATS, VTX_FLAG_COUNT or
                                     VTX_FLAG_ONE_PASS, with 8-pixel
                                     tiles, for jobs in a batch whose other jobs do

@@ -718,7 +718,17 @@ static void scene_depth_classes(const vtx_scene* sc, Frame* F) {
 //   20M (cover 19), 4K: 373 to 383 and 439 to 450; 1080p: 243 to 261 and 281 to 289
 //   ball of 20M (cover 300), 4K: 524 to 529 and 392 to 394; of 5M: 264 and 327
 //   20M atoms and bonds (thin: cells keep gaps): 881 to 1,134 and 920 to 1,336
-constexpr double kPrePassAtoms = 16e6, kPrePassCover = 20.0;
+// A clip plane can leave the front pass nothing to draw, and then the second
+// binning is for nothing: 264 clipped views of which the rule above takes the
+// pre-pass (100M compartments and a ball of 20M, 1080p and 4K; the plane
+// across, along and askew to the view) take 401 ms in one pass and 372 in two,
+// 76 of them longer in two (1 to 14 %).  They are the ones whose nearest part
+// is cut: with two passes only where a third of the nearest sixteenth of the
+// sample points in view is kept, 369 ms, 9 longer (by 7 % at most), the best
+// choice for each view 367.  (A third of the nearest eighth: 368, 12 longer,
+// by up to 11 %.)
+constexpr double kPrePassAtoms = 16e6, kPrePassCover = 20.0, kPrePassKept = 1.0 / 3.0;
+constexpr int kPrePassNearest = 16;
 
 static bool wants_pre_pass(const vtx_scene* sc, const Frame& F) {
     if (!sc->have_box || F.n_bonds || (double)sc->n < kPrePassAtoms) return false;
@@ -730,6 +740,11 @@ static bool wants_pre_pass(const vtx_scene* sc, const Frame& F) {
     const double face = (ex * ey + ey * ez + ez * ex) / 3.0;
     if (!(3.14159265 * r2 >= kPrePassCover * face)) return false;
     constexpr int kGrid = 8;
+    struct Point {
+        double z;
+        bool kept;
+    };
+    Point seen[kGrid * kGrid * kGrid];
     int in = 0;
     for (int i = 0; i < kGrid * kGrid * kGrid; ++i) {
         const double x = sc->box_lo[0] + ex * (i % kGrid + 0.5) / kGrid - F.eye[0],
@@ -738,9 +753,15 @@ static bool wants_pre_pass(const vtx_scene* sc, const Frame& F) {
         const double vx = x * F.s[0] + y * F.s[1] + z * F.s[2], vy = x * F.u[0] + y * F.u[1] + z * F.u[2],
                      vz = x * F.f[0] + y * F.f[1] + z * F.f[2];
         const double lx = F.proj == 0 ? F.tx * vz : F.hx, ly = F.proj == 0 ? F.ty * vz : F.hy;
-        in += vz >= (double)F.znear && vz <= (double)F.zfar && std::fabs(vx) <= lx && std::fabs(vy) <= ly;
+        if (vz >= (double)F.znear && vz <= (double)F.zfar && std::fabs(vx) <= lx && std::fabs(vy) <= ly)
+            seen[in++] = {vz, !F.clip_on || F.clip[0] * vx + F.clip[1] * vy + F.clip[2] * vz + F.clip[3] >= 0.0};
     }
-    return n * in >= kPrePassAtoms * (kGrid * kGrid * kGrid);
+    if (n * in < kPrePassAtoms * (kGrid * kGrid * kGrid)) return false;
+    if (!F.clip_on) return true;
+    const int near = std::max(1, in / kPrePassNearest);
+    std::nth_element(seen, seen + (near - 1), seen + in, [](const Point& a, const Point& b) { return a.z < b.z; });
+    const auto kept = std::count_if(seen, seen + near, [](const Point& p) { return p.kept; });
+    return (double)kept >= kPrePassKept * near;
 }
 
 

@@ -113,6 +113,33 @@ def test_a_large_opaque_scene_takes_the_pre_pass_unasked(vtx, ctx):
     assert st_auto["visible"] == st_one["visible"]
 
 
+def test_a_clip_plane_on_the_near_side_keeps_to_one_pass(vtx, ctx):
+    """The scene of the test above, cut: where the nearest part of it goes,
+    the front pass would have nothing to draw, and the frame stays in one
+    pass; a cut of the far half or of a rim leaves it the pre-pass."""
+    n = 17_000_000
+    rng = np.random.default_rng(18)
+    radius = (3.0 * n / (4.0 * np.pi * 0.1)) ** (1.0 / 3.0)
+    d = rng.normal(size=(n, 3)).astype(np.float32)
+    d *= (radius * np.cbrt(rng.uniform(size=n)) / np.linalg.norm(d, axis=1)).astype(np.float32)[:, None]
+    scene = scenes.Scene(d, np.full(n, 1.6, np.float32), np.full(n, scenes.pack_rgba(200, 180, 160), np.uint32),
+                         np.zeros((0, 2), np.uint32))
+    cam = scenes.orbit_camera((0.0, 0.0, 0.0), 1.2 * radius, 0.4)
+    view = np.asarray(cam.target, float) - np.asarray(cam.eye, float)
+    view /= np.linalg.norm(view)
+    side = np.cross(view, cam.up)
+    side /= np.linalg.norm(side)
+    for name, normal, d0, one_pass in (("near half", view, 0.0, True), ("nearest fifth", view, 0.45 * radius, True),
+                                       ("far half", -view, 0.0, False), ("rim", side, 0.6 * radius, False)):
+        wl = scenes.Workload("ball", scene, cam, scenes.Options(clip_plane=tuple(float(v) for v in normal) + (float(d0),)),
+                             640, 480)
+        (auto, st_auto), (one, st_one) = two_ways(vtx, ctx, wl, 0, vtx.VTX_FLAG_ONE_PASS)
+        print(name, "pairs", st_auto["pairs"], "in one pass", st_one["pairs"], flush=True)
+        assert_identical(auto, one, name)
+        # of two passes the counters hold the larger one's pairs
+        assert (st_auto["pairs"] == st_one["pairs"]) == one_pass, name
+
+
 @pytest.mark.parametrize("size", [(3845, 2049), (3840, 2064)])
 def test_wide_shade_tiles_of_a_large_batch(vtx, ctx, size):
     """Over 128M pixels a launch shades in 64x16 tiles: the images are the
