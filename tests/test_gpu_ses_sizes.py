@@ -87,3 +87,25 @@ def test_positions_far_beyond_the_spacing(vtx):
             left_out += 1
             check(vtx, np.full((1, 3), o, np.float32), np.array([r], np.float32), 0.0, (o, o, o), h, (14, 14, 14))
     assert left_out > 5
+
+
+@pytest.mark.parametrize("n", [1, 2, 7, 8, 9, 15, 63, 65, 520, 4099])
+@pytest.mark.parametrize("dims,h,scale", [((6, 5, 4), 1.5, 1.0), ((5, 5, 8), 0.7, 1.0), ((17, 9, 33), 2.5, 1.0), ((34, 18, 6), 0.4, 6.0)])
+def test_many_atoms_per_wave(vtx, n, dims, h, scale):
+    """Grids on both sides of 100 points per atom, below which a wave takes
+    several atoms: remainders of the wave's atoms, boxes of one cell and of
+    many, atoms beside the grid, and ones that mark nothing (no radius, no
+    finite position) between them."""
+    pos, rad = atoms(n, n, np.array(dims) * h * 1.5)
+    pos -= np.float32(0.25) * np.array(dims, np.float32) * np.float32(h)
+    rad *= np.float32(scale)
+    origin = (0.1, -0.2, 0.05)
+    ref = oses.ses_field(pos, rad, 0.6, origin, h, dims)
+    k = n // 3
+    pos_all = np.insert(pos, [0, k, k, n], [[np.nan, 0, 0], [1, np.inf, 1], [2, 2, 2], [3, 3, -np.inf]], axis=0).astype(np.float32)
+    rad_all = np.insert(rad, [0, k, k, n], [2.0, 2.0, -1.0, 2.0]).astype(np.float32)
+    for p, r in ((pos, rad), (pos_all, rad_all)):
+        f, tri, count = run_ses(vtx, p, r, 0.6, np.asarray(origin, np.float32), np.float32(h), dims)
+        assert np.array_equal(f, ref["f"])
+        assert count == oses.marching_cubes(ref["f"], origin, h)["vertices"].shape[0]
+    print("atoms", n, "points per atom", np.prod(dims) / n, "inside", int(np.count_nonzero(~ref["exterior"])), flush=True)
