@@ -158,6 +158,13 @@ struct SesGrid {
     int nx, ny, nz;
     int W;              // distance window in grid steps
     double rp;
+    // Margin of an atom's box in steps: slack0 + reach slack.  The box's ends
+    // and the points' coordinates are rounded at the magnitude of the origin,
+    // the points, the atom and its reach (eight roundings of 2^-53 at most in
+    // all); an atom that reaches the grid is no further than the grid's
+    // farthest point and its reach.  The product by 1 / h is rounded at the
+    // magnitude of the grid coordinates (below 2^31, so by less than 2e-6).
+    double slack0, slack;
 };
 
 __device__ inline size_t gidx(const SesGrid& G, int i, int j, int k) {
@@ -186,20 +193,17 @@ struct AtomBox {
     double c[3], R2;   // centre, squared reach
     int lo[3], nc[3];  // first cell, cells
 };
-__device__ inline bool atom_box(const SesGrid& G, const float* __restrict__ pos, const float* __restrict__ rad, size_t a,
+__device__ __forceinline__ bool atom_box(const SesGrid& G, const float* __restrict__ pos, const float* __restrict__ rad, size_t a,
                                 AtomBox& B) {
 #pragma clang fp contract(off)
     const double R = (double)rad[a] + G.rp;
     if (!(R > 0.0)) return false;
     B.R2 = R * R;
     const int nmax[3] = {G.nx - 1, G.ny - 1, G.nz - 1};
-    // the box only has to hold every point the test can mark.  Its ends and the
-    // points' coordinates are rounded at the magnitude of the positions (eight
-    // roundings of 2^-53 at most in all, in steps of the grid), the product by
-    // 1 / h at that of the grid coordinates (below 2^31, so by less than 2e-6).
+    // the box only has to hold every point the test can mark: see SesGrid::slack
+    const double margin = fma(R, G.slack, G.slack0);
     for (int d = 0; d < 3; ++d) {
         B.c[d] = pos[3 * a + d];
-        const double margin = 1e-3 + (fabs(B.c[d]) + R + fabs(G.o[d])) * G.inv_h * 0x1p-50;
         const double from = fmax(0.0, ceil((B.c[d] - R - G.o[d]) * G.inv_h - margin));
         const double to = fmin((double)nmax[d], floor((B.c[d] + R - G.o[d]) * G.inv_h + margin));
         if (!(from <= to) || !(B.c[d] - B.c[d] == 0.0)) return false;   // beside the grid, or not a finite position
@@ -211,7 +215,7 @@ __device__ inline bool atom_box(const SesGrid& G, const float* __restrict__ pos,
 }
 
 // Marks cell q (x fastest) of a box.
-__device__ inline void mark_cell(const SesGrid& G, const MarkGrid& M, const AtomBox& B, int q) {
+__device__ __forceinline__ void mark_cell(const SesGrid& G, const MarkGrid& M, const AtomBox& B, int q) {
 #pragma clang fp contract(off)
     const int qz = q / (B.nc[0] * B.nc[1]), qr = q - qz * (B.nc[0] * B.nc[1]), qy = qr / B.nc[0], qx = qr - qy * B.nc[0];
     const int cell[3] = {B.lo[0] + qx, B.lo[1] + qy, B.lo[2] + qz};
@@ -750,6 +754,10 @@ hipError_t ses_run(const float* pos, const float* rad, uint64_t n, float probe, 
     G.nz = dims[2];
     G.rp = (double)probe;
     G.W = ses_window(probe, spacing);
+    double far = 0.0;   // the grid's largest coordinate
+    for (int d = 0; d < 3; ++d) far = fmax(far, fmax(fabs(G.o[d]), fabs(G.o[d] + G.h * (dims[d] - 1))));
+    G.slack = G.inv_h * 0x1p-48;
+    G.slack0 = 1e-3 + far * G.inv_h * 0x1p-48;
     const size_t np = (size_t)G.nx * G.ny * G.nz;
     MarkGrid M;
     M.bits = s.mark;
