@@ -35,7 +35,10 @@ namespace {
 constexpr int kSesBlock = 256;
 constexpr int kSesMarkBlock = 64;      // one wave per atom: its box setup is paid once per wave
 constexpr int kSesRun = 64;            // words of sign bits (up to 32 cubes each) per run of cubes
-constexpr int kMaxFusedW = 12;         // windows up to which a brick's distances fit LDS
+// Windows up to which a brick's distances fit LDS, which is also where they
+// pay: the whole call for 9.4M points and W = 7, 9, 11, 12 in LDS 116, 153, 176,
+// 160 us, through memory 251, 250, 273, 270 (and 288 for 13).
+constexpr int kMaxFusedW = 12;
 constexpr int32_t kFar = 0x3FFFFFFF;   // no exterior point within the window
 
 // Case table: for each case, one word with its loops' edges in order, 4 bits
@@ -444,20 +447,73 @@ __global__ void __launch_bounds__(kEdtBlock) k_ses_edt(SesGrid G, MarkGrid M, ui
 
 // The passes of larger windows (or grids of too many bricks), through memory.
 // x pass: squared distance along the row to the nearest exterior point
-// within W steps (kFar if none).
+// within W steps (kFar if none).  Cells of four points outwards from the
+// point's own, so a load serves four steps (9.4M points, W = 33: 260 us with a
+// byte per point and step, 312 with a cell per step, 97 so).
 __global__ void __launch_bounds__(kSesBlock) k_ses_edt_x(SesGrid G, uint32_t np, MarkGrid M, int32_t* __restrict__ g) {
     int i, j, k;
     uint32_t p;
     if (!flat_item(np, G.nx, G.ny, i, j, k, p)) return;
-    auto exterior = [&](int x) { return !(mark_nibble(M, x >> 2, j, k) >> (x & 3) & 1u); };
-    int32_t best = kFar;
-    for (int d = 0; d <= G.W; ++d) {
-        if ((i - d >= 0 && exterior(i - d)) || (i + d < G.nx && exterior(i + d))) {
-            best = d * d;
-            break;
+    // exterior points of cell c of the row (points past the row's end are none)
+    auto exterior = [&](int c) -> uint32_t {
+        const int end = G.nx - 4 * c;
+        return ~mark_nibble(M, c, j, k) & (end < 4 ? (1u << end) - 1u : 15u);
+    };
+    const int own = i >> 2, at = i & 3;
+    const uint32_t e = exterior(own);
+    int d = G.W + 1;
+    const uint32_t right = e >> at, left = e << (31 - at);
+    if (right) d = __builtin_ctz(right);
+    if (left) d = min(d, __builtin_clz(left));
+    // the nearest point of the cells c steps out is 4 c - at to the left at
+    // most, 4 c + at - 3 to the right
+    for (int c = 1; 4 * c - 3 <= min(d - 1, G.W) && (own + c < M.nx || own - c >= 0); ++c) {
+        if (own + c < M.nx) {
+            const uint32_t r = exterior(own + c);
+            if (r) d = min(d, 4 * c - at + __builtin_ctz(r));
+        }
+        if (own - c >= 0) {
+            const uint32_t l = exterior(own - c);
+            if (l) d = min(d, 4 * c + at - 31 + __builtin_clz(l));
         }
     }
-    g[p] = best;
+    g[p] = d <= G.W ? d * d : kFar;
+}
+
+constexpr int kEdtMaxW = 32;   // windows the passes through LDS take
+
+// The x pass through LDS (W <= kEdtMaxW): work block b takes kSesBlock
+// consecutive points of one row (x block b mod nxb of row b / nxb) and stages
+// their exterior bits and a word of them more on each side; a point's nearest
+// ones are the first and last bits of the words that start and end at it.
+// 9.4M points: 28 us for W = 13 to 32; a point's marks one after another from
+// memory 146 and 301, from bytes in LDS 105 and 219.
+__global__ void __launch_bounds__(kSesBlock) k_ses_edt_x_lds(SesGrid G, uint32_t nxb, MarkGrid M, int32_t* __restrict__ g) {
+    static_assert(kEdtMaxW == 32, "a word of bits on each side");
+    constexpr int kWords = kSesBlock / 32 + 2;
+    static_assert(kWords * 8 <= kSesBlock, "a thread per nibble");
+    __shared__ uint32_t ext[kWords];
+    const uint32_t r = blockIdx.x / nxb, xb = blockIdx.x - r * nxb;
+    const int t = threadIdx.x, x0 = (int)xb * kSesBlock;
+    const int j = (int)(r % (uint32_t)G.ny), k = (int)(r / (uint32_t)G.ny);
+    const int c = x0 / 4 - 8 + t, end = G.nx - 4 * c;   // points of the row from cell c on
+    uint32_t w = 0;
+    if (t < kWords * 8 && c >= 0 && end > 0) w = ~mark_nibble(M, c, j, k) & (end < 4 ? (1u << end) - 1u : 15u);
+    w <<= 4 * (t & 7);
+    w |= (uint32_t)__shfl_xor((int)w, 1);
+    w |= (uint32_t)__shfl_xor((int)w, 2);
+    w |= (uint32_t)__shfl_xor((int)w, 4);
+    if (t < kWords * 8 && (t & 7) == 0) ext[t >> 3] = w;
+    __syncthreads();
+    const int i = x0 + t;
+    if (i >= G.nx) return;
+    const int q = t >> 5, s = t & 31;   // the point is bit s of word q + 1
+    const uint32_t right = __builtin_amdgcn_alignbit(ext[q + 2], ext[q + 1], s);   // bit 0: the point
+    const uint32_t left = s == 31 ? ext[q + 1] : __builtin_amdgcn_alignbit(ext[q + 1], ext[q], s + 1);   // bit 31: the point
+    uint32_t d = (ext[q + 2] | ext[q]) >> s & 1u ? 32u : ~0u;
+    if (right) d = min(d, (uint32_t)__builtin_ctz(right));
+    if (left) d = min(d, (uint32_t)__builtin_clz(left));
+    g[(size_t)r * G.nx + i] = d <= (uint32_t)G.W ? (int32_t)(d * d) : kFar;
 }
 
 // y or z pass: the least of g(p + d e) + d^2 over |d| <= W along the axis.
@@ -490,7 +546,7 @@ __global__ void __launch_bounds__(kSesBlock) k_ses_edt_yz(SesGrid G, uint32_t np
 // and kEdtRows consecutive positions along the axis, stages those rows and
 // W more on each side in LDS (one load per staged value), and each thread
 // then takes the window minima of its column from LDS.
-constexpr int kEdtX = 64, kEdtRows = 32, kEdtMaxW = 32;
+constexpr int kEdtX = 64, kEdtRows = 32;
 
 template <bool kLast>
 __global__ void __launch_bounds__(kSesBlock) k_ses_edt_yz_lds(SesGrid G, uint32_t nxb, uint32_t nrb,
@@ -783,7 +839,12 @@ hipError_t ses_run(const float* pos, const float* rad, uint64_t n, float probe, 
         if ((e = launch_edt<2>(G.W, (unsigned)ses_bricks(dims), G, M, nbx, nby, field, s.sign, nxw, stream))) return e;
     } else {
         const unsigned gp = (unsigned)((np + kSesBlock - 1) / kSesBlock);
-        if ((e = dispatch(k_ses_edt_x, gp, kSesBlock, 0, stream, G, (uint32_t)np, M, s.ga))) return e;
+        const uint64_t nxr = (uint64_t)(G.nx + kSesBlock - 1) / kSesBlock, gx = nxr * (uint64_t)G.ny * (uint64_t)G.nz;
+        if (G.W <= kEdtMaxW && gx * kSesBlock < (1ull << 31)) {
+            if ((e = dispatch(k_ses_edt_x_lds, (uint32_t)gx, kSesBlock, 0, stream, G, (uint32_t)nxr, M, s.ga))) return e;
+        } else if ((e = dispatch(k_ses_edt_x, gp, kSesBlock, 0, stream, G, (uint32_t)np, M, s.ga))) {
+            return e;
+        }
         const uint64_t nxb = (uint64_t)(G.nx + kEdtX - 1) / kEdtX;
         const uint64_t gy = nxb * (uint64_t)((G.ny + kEdtRows - 1) / kEdtRows) * (uint64_t)G.nz;
         const uint64_t gz = nxb * (uint64_t)((G.nz + kEdtRows - 1) / kEdtRows) * (uint64_t)G.ny;

@@ -109,3 +109,22 @@ def test_many_atoms_per_wave(vtx, n, dims, h, scale):
         assert np.array_equal(f, ref["f"])
         assert count == oses.marching_cubes(ref["f"], origin, h)["vertices"].shape[0]
     print("atoms", n, "points per atom", np.prod(dims) / n, "inside", int(np.count_nonzero(~ref["exterior"])), flush=True)
+
+
+@pytest.mark.parametrize("window", [13, 32, 33, 50])
+@pytest.mark.parametrize("dims", [(2, 3, 2), (5, 4, 3), (63, 4, 3), (64, 3, 4), (65, 2, 2), (255, 4, 3), (256, 3, 3), (257, 3, 4), (515, 3, 2)])
+def test_rows_through_memory(vtx, window, dims):
+    """The x pass of windows too large for a brick in LDS: rows around the
+    sizes of its cells, words and blocks, with exterior points at every
+    distance up to the window and past it."""
+    h = 0.25
+    probe = float(np.float32(h)) * (window - 2.5)
+    rng = np.random.default_rng(window + dims[0])
+    centre, reach, x = [], [], rng.uniform(-5.0, 3.0)
+    while x < dims[0]:   # spheres along the row with gaps of a point or two between them
+        r = rng.uniform(2.0, 1.5 * window)
+        centre.append([x + r, (dims[1] - 1) / 2, (dims[2] - 1) / 2])
+        reach.append(r)
+        x += 2.0 * r + rng.uniform(0.3, 2.5)
+    pos, rad = np.array(centre, np.float32) * np.float32(h), np.array(reach, np.float32) * np.float32(h) - np.float32(probe)
+    check(vtx, pos, rad, probe, (0.0, 0.0, 0.0), h, dims)
