@@ -402,17 +402,6 @@ int ensure_bins(Workspace* ws, Bins* b, int T, uint64_t nprim, uint32_t groups, 
     return VTX_OK;
 }
 
-template <class T>
-int dev_alloc_zeroed(T** p, size_t count, hipStream_t stream) {
-    if (hipMalloc(p, count * sizeof(T)) != hipSuccess) {
-        (void)hipGetLastError();
-        *p = nullptr;
-        return fail(VTX_ENOMEM, "cannot allocate %zu bytes", count * sizeof(T));
-    }
-    VTX_HIP(vtx::launch_zero(reinterpret_cast<uint32_t*>(*p), count * sizeof(T) / sizeof(uint32_t), stream));
-    return VTX_OK;
-}
-
 void workspace_free(Workspace* ws) {
     for (Bins* b : ws->slots) bins_free(b);
     ws->slots.clear();

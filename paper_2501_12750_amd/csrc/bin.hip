@@ -659,7 +659,6 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_scatter(JS js, int phase) {
             ctr->rec_culled = 0;
             ctr->lists_stopped = 0;
             ctr->chunks_stopped = 0;
-            ctr->done_blocks = 0;
             ctr->pairs_counted = 0;
             // the next frame's cluster test adds to these (the rest pass reads them)
             if (phase != kPhaseFront)

@@ -13,7 +13,7 @@ struct Item {
     float4 a;          // atom: centre and radius | bond: end A (w unused)
     float4 b;          // bond: end B
     uint32_t id;       // primitive id (atoms i, bonds n_atoms + b, in the caller's numbering)
-    uint32_t src;      // source index the primitive is fetched by again (see fetch_src)
+    uint32_t src;      // source index the primitive is fetched by again (by the resolve's source_record)
     uint32_t kind;     // kNone, kAtom, kBond, kBadBond
 };
 constexpr uint32_t kNone = 0, kAtom = 1, kBond = 2, kBadBond = 3;
@@ -68,12 +68,6 @@ __device__ inline Item fetch_scene(const SceneDev& S, uint32_t src) {
     it.id = S.n_atoms + br.z;
     it.kind = kBond;
     return it;
-}
-
-// A job's primitive by source index (resident scene or the caller's arrays).
-__device__ inline Item fetch_src(const Job& J, uint32_t src) {
-    if (J.S.xyzr) return fetch_scene(J.S, src);
-    return fetch_plain(to_global(J.pos), to_global(J.rad), to_global(J.bonds), J.F.n_atoms, src);
 }
 
 // View-space record of an item (FP64 view transform rounded once to FP32,

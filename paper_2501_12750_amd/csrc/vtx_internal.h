@@ -120,7 +120,6 @@ struct Counters {
     unsigned long long rec_culled;
     unsigned long long lists_stopped;
     unsigned long long chunks_stopped;
-    unsigned int done_blocks;
     unsigned int vis_bucket[kDepthBuckets];   // resident scenes: clusters that passed the frustum test, per depth class
     unsigned int rest_bucket[kDepthBuckets];  // two-pass frames: of those past the front pass, the clusters it does not hide
     // resident scenes: per pass (one pass or the front pass; the rest) and
@@ -333,19 +332,13 @@ using global_t = T;
 template <class T>
 __device__ inline global_t<T>* to_global(T* p) { return (global_t<T>*)p; }
 
-// Hardware dispatch places workgroup b on XCD (b mod 8).  Give each XCD one
-// contiguous range of work items so neighbouring tiles share an L2.
-__device__ inline int xcd_contiguous(int b, int nblocks) {
-    const int per = (nblocks + 7) >> 3;
-    return (b & 7) * per + (b >> 3);
-}
-
-// The same with runs of kXcdRun consecutive work items dealt round-robin to
-// the XCDs: neighbours still share an L2, and no XCD is left with a dear part
-// of the work.  One range per XCD gave each a band of the image, and the
-// molecule usually lies in the middle ones: shade of 107,500 atoms at 1080p
-// 26 us against 21, a figure at 3840x2160 387 against 337; single items lose
-// the shared lines (100M atoms at 4K 137 us against 126).  8 to 256 are alike.
+// Hardware dispatch places workgroup b on XCD (b mod 8).  Runs of kXcdRun
+// consecutive work items are dealt round-robin to the XCDs, so that neighbours
+// share an L2 and no XCD is left with a dear part of the work.  One range per
+// XCD gave each a band of the image, and the molecule usually lies in the
+// middle ones: shade of 107,500 atoms at 1080p 26 us against 21, a figure at
+// 3840x2160 387 against 337; single items lose the shared lines (100M atoms at
+// 4K 137 us against 126).  8 to 256 are alike.
 constexpr int kXcdRun = 32;
 __device__ inline int xcd_runs(int b) {
     const int k = b >> 3;
@@ -355,13 +348,9 @@ inline int xcd_run_grid(int nblocks) { return (nblocks + 8 * kXcdRun - 1) / (8 *
 
 inline int xcd_grid(int nblocks) { return ((nblocks + 7) >> 3) << 3; }
 
-// Binning workgroup b of `groups` belongs to layer b * layers / groups; layer
-// g holds the workgroups [layer_first(g), layer_first(g + 1)).
+// The layer of binning workgroup b of `groups`.
 __device__ inline uint32_t layer_of(uint32_t b, uint32_t groups, uint32_t layers) {
     return (uint32_t)(((uint64_t)b * layers) / groups);
-}
-__device__ inline uint32_t layer_first(uint32_t g, uint32_t groups, uint32_t layers) {
-    return (uint32_t)(((uint64_t)g * groups + layers - 1) / layers);
 }
 
 // ---------------------------------------------------------------------------
@@ -552,27 +541,20 @@ inline uint32_t shade_blocks(const Frame& F, ShadeForm form) {
 struct OneJob {
     Job j;
     SampleKernel K;
-    static constexpr bool kMany = false;
     uint32_t blocks;         // work blocks of the launch (the grid may be padded past it)
     __device__ int find(uint32_t g, uint32_t& local) const {
         local = g;
         return g < blocks ? 0 : -1;
     }
     __device__ const Job& job(int) const { return j; }
-    __device__ const SampleKernel& samples(int) const { return K; }
     __device__ uint32_t count() const { return 1; }
     static constexpr bool kOrdered = true;   // see kOrderTiles
     __device__ uint32_t work_blocks(int) const { return blocks; }
-    // the work block after (i, local): the next one of the job, else -1
-    __device__ void next(int& i, uint32_t& local) const {
-        if (i >= 0 && ++local >= blocks) i = -1;
-    }
 };
 
 // A launch over several renders, described by device tables: job i owns the
 // work blocks [start[i], start[i + 1]).
 struct JobList {
-    static constexpr bool kMany = true;   // a batch launch
     const Job* jobs;
     const SampleKernel* K;
     const uint32_t* start;   // n + 1 entries
@@ -598,21 +580,9 @@ struct JobList {
         return (int)lo;
     }
     __device__ const Job& job(int i) const { return jobs[i]; }
-    __device__ const SampleKernel& samples(int i) const { return K[i]; }
     __device__ uint32_t count() const { return n; }
     static constexpr bool kOrdered = false;
     __device__ uint32_t work_blocks(int i) const { return start[i + 1] - start[i]; }
-    // the work block after (i, local): the next one of job i, else the first
-    // of the next job that has any, else -1 (no search)
-    __device__ void next(int& i, uint32_t& local) const {
-        if (i < 0) return;
-        ++local;
-        while ((uint32_t)i < n && local >= (per ? per : start[i + 1] - start[i])) {
-            ++i;
-            local = 0;
-        }
-        if ((uint32_t)i >= n) i = -1;
-    }
 };
 
 // A job's constants read where they are used.  A kernel's job is the same
