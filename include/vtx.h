@@ -351,8 +351,9 @@ typedef struct vtx_ses_grid {
  *              cube (x fastest), then by loop and position in the loop.
  *   n_triangles one uint64 out (device): the surface's triangle count; those
  *              past `capacity` are not written (call again with more)
- * Queued on `stream`; library scratch ~ 13 B per grid point.  VTX_EINVAL for
- * bad sizes or pointers, VTX_ENOMEM, VTX_EHIP.
+ * Queued on `stream`; library scratch ~ 0.3 B per grid point, 4 B more if
+ * field is NULL and 8 B more where ceil(probe_radius / spacing) is above 10.
+ * VTX_EINVAL for bad sizes or pointers, VTX_ENOMEM, VTX_EHIP.
  */
 int vtx_ses(const float* positions, const float* radii, int64_t n_atoms, float probe_radius,
             const vtx_ses_grid* grid, float* field, float* triangles, int64_t capacity, uint64_t* n_triangles,

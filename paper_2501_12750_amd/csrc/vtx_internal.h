@@ -102,7 +102,7 @@ struct SampleKernel {
 
 // Device-side counters of one frame.  The scatter's first workgroup
 // publishes the binning counters to host-mapped memory; on counting frames
-// a counting frame's k_publish publishes the fragment counters.
+// k_publish publishes the fragment counters.
 struct Counters {
     unsigned int vis_count;
     unsigned int overflow;
@@ -415,7 +415,10 @@ struct BinBuffers {
 // 256 CUs) resolve them longest list first: in image order the launch ends
 // with the few long lists that happen to start last (1M atoms and bonds at
 // 1080p: every tile has started after 57 of 107 us, and half the device is
-// idle from 68 us on).  Resolve in image order and ordered: 98 and 78 us
+// idle from 68 us on).  That many workgroups fit for tiles of up to 32 pixels;
+// a 64-pixel tile's takes 48 KB of LDS, so 3 fit a CU, and images of 769 to
+// 1,792 such tiles (1440p has 920) keep the image order although they do not
+// all run at once.  Resolve in image order and ordered: 98 and 78 us
 // there, 58 and 47 for 107,500 atoms with bonds at 1080p, 104 and 94 for a
 // 4K figure.  Single renders only (JS::kOrdered): a batch of one scene's
 // views has the next render's tiles to fill the end with, and loses the

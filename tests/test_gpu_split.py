@@ -192,6 +192,8 @@ def test_stored_order_binning_equals_clusters(vtx, ctx, n, size, representation)
     rs.close()
 
 
+# The scatter scans the tile counts at every size: in one part up to 8192
+# tiles, in two parts of 8192 above.
 @pytest.mark.parametrize("size", [(8, 8), (1016, 64), (1024, 64), (1032, 64), (448, 256), (456, 256), (1024, 512),
                                   (1032, 512)])
 @pytest.mark.parametrize("capacity", [0, 3000])
