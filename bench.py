@@ -652,11 +652,20 @@ def run_workload(args, workload, vtx, scenes, torch, stream, steps_arg, warmup_a
     def eff_tile(r):
         return frame_tile(getattr(r, "tuned_tile", 0) or r.options.tile_size, r.W, r.H)
     tiles = sum(n_tiles(eff_tile(r), r.W, r.H) for r in runner.renders)
+    scene_path = batch or runner.path == "scene"
+    # the timed frames took the occlusion pre-pass if they binned fewer
+    # primitives than a statistics frame, which goes in one pass: they are then
+    # priced on what their passes binned (the primitives and pairs of both
+    # passes; of the pairs the library reports the larger pass's, so that the
+    # scatter's bytes are a lower bound) and on the cluster boxes
+    two_pass = scene_path and st_after["visible"] < st["visible"]
+    binned = st_after if two_pass else st
+    read = 16.0 * binned["visible"] + 32.0 * (N + 255) // 256 if two_pass else (16.0 * N + 8.0 * M) * R
     per_kernel = {
-        "project": ("hbm", (16.0 * N + 8.0 * M) * R, timings["ms_project"]),
+        "project": ("hbm", read, timings["ms_project"]),
         "resolve": ("alu", float(OPS_SPHERE_FRAG * f_sph + OPS_CYL_FRAG * f_cyl), timings["ms_resolve"]),
         "shade": ("alu", float((OPS_PIXEL + OPS_SAMPLE * K) * hit_px), timings["ms_shade"]),
-        "scatter": ("hbm", 12.0 * st["visible"] + 4.0 * st["pairs"], timings["ms_scatter"]),
+        "scatter": ("hbm", 12.0 * binned["visible"] + 4.0 * binned["pairs"], timings["ms_scatter"]),
         "scan": ("hbm", 12.0 * tiles, timings["ms_scan"]),
     }
     kern = {}
@@ -670,12 +679,15 @@ def run_workload(args, workload, vtx, scenes, torch, stream, steps_arg, warmup_a
         kern[k] = {"bound": bound, "ms": round(ms, 5), "achieved": round(ach, 3), "peak": round(peak, 2),
                    "unit": unit, "frac": round(ach / peak, 4)}
     if "resolve" in kern:
-        # the resolve priced on the ray tests the timed frames run (early-outs
-        # on), beside the plain z-buffer pricing above
+        # the resolve priced on the ray tests run with the early-outs on,
+        # beside the plain z-buffer pricing above.  Counting frames go in one
+        # pass: of two-pass frames the counts are not the timed frames' own,
+        # and no rate is made of them
         done = float(OPS_SPHERE_FRAG * t_sph + OPS_CYL_FRAG * t_cyl)
         ach = done / (timings["ms_resolve"] * 1e-3) / 1e12
         kern["resolve"].update({
-            "frac_work_done": round(ach / ALU_PEAK_TOPS, 4),
+            "frac_work_done": None if two_pass else round(ach / ALU_PEAK_TOPS, 4),
+            "tests_counted": "in one pass; the timed frames take two" if two_pass else "as timed",
             "tests_all": st["fragments_tested"], "tests_done": stc["fragments_tested"],
             "skip_rate": round(1.0 - stc["fragments_tested"] / max(1, st["fragments_tested"]), 4),
             "tests_done_per_atom_fragment": round(stc["fragments_tested"] / max(1, f_total), 4),
@@ -683,7 +695,6 @@ def run_workload(args, workload, vtx, scenes, torch, stream, steps_arg, warmup_a
                                                "chunks_stopped")}})
     dom = max(kern, key=lambda k: kern[k]["ms"])
     roof = {k: v for k, v in kern[dom].items() if k in ("bound", "achieved", "peak", "unit", "frac")}
-    scene_path = batch or runner.path == "scene"
     res_tiles = sorted({eff_tile(r) for r in runner.renders})
     # the launches of each stage, named as the kernel trace names them (template
     # arguments: launch form; count: scene, rest pass, atoms only, quarters,
@@ -694,7 +705,6 @@ def run_workload(args, workload, vtx, scenes, torch, stream, steps_arg, warmup_a
     prims = (N + M) * len(runner.renders)
     per_tile = max((N + M) * t * t / (r.W * r.H) for r in runner.renders for t in res_tiles)
     noise = bool(getattr(runner.renders[0].options, "ssao_noise", 0))
-    two_pass = scene_path and not batch and M == 0 and N >= 64_000_000   # the whole cell takes the pre-pass unasked
     stored = scene_path and prims <= 1 << 19 and per_tile <= 64
     clusters = scene_path and not stored
     counts = {"two_pass": [f"k_count<{form},true,false,true,true,false>", f"k_cluster_rest<{form}>",
@@ -706,9 +716,10 @@ def run_workload(args, workload, vtx, scenes, torch, stream, steps_arg, warmup_a
     count_form = ("arrays" if not scene_path else "stored" if stored else "two_pass" if two_pass
                   else "bonds" if M else "atoms")
     passes = [1, 2] if two_pass else [0]
+    parts = 2 if max(n_tiles(eff_tile(r), r.W, r.H) for r in runner.renders) > 8192 else 1
     shade_tile = "16,16" if pixels < (3 << 20 if noise else 128 << 20) else "32,32" if noise else "64,16"
     launched = {"project": ([f"k_cluster_cull<{form}>"] if clusters else []) + counts[count_form],
-                "scatter": [f"k_scatter<{form},1>"] * len(passes),
+                "scatter": [f"k_scatter<{form},{parts}>"] * len(passes),
                 "resolve": [f"k_resolve<{t},{form},false,{ph}>" for t in res_tiles for ph in passes],
                 "shade": [f"k_shade<{form},{'true' if noise else 'false'},{shade_tile}>"],
                 "scan": [f"k_layers<{form}>"] * len(passes) if clusters else []}
@@ -753,7 +764,9 @@ def run_workload(args, workload, vtx, scenes, torch, stream, steps_arg, warmup_a
         "roofline": roof,
         "frame_roofline": frame_rl,
         "frame_valu": frame_valu,
-        "bins": {"visible": st["visible"], "pairs": st["pairs"], "overflow_tiles": st_after["overflow_tiles"]},
+        # one pass's; and the primitives the timed frames binned
+        "bins": {"visible": st["visible"], "pairs": st["pairs"], "overflow_tiles": st_after["overflow_tiles"],
+                 "two_pass": two_pass, "visible_binned": st_after["visible"]},
     }
     if cpu and not args.no_cpu_baseline:
         log("cpu baseline (oracle) ...")
