@@ -85,6 +85,7 @@ struct Bins {
     uint32_t* ss_rgba = nullptr;
     size_t ss_cap = 0;
     Counters* host_ctr = nullptr;       // host view of the mapped counters
+    uint32_t stamp = 0;                 // of the last render queued in this slot (see Counters::stamp)
     uint64_t want_capacity = 0;
     uint64_t pending_capacity = 0;
     uint64_t pending_uid = 0;       // resident scene of the render queued in this slot (0: none)
@@ -108,9 +109,9 @@ struct Bins {
 
 // The event that a frame's counters are complete lies between its resolve and
 // its shade, where a system-scope fence would hold the shade up (4,096 atoms
-// at 256x256: 31.3 us with it, 29.6 without).  What the host reads after it,
-// Bins::host_ctr, is coherent host memory, which needs no fence; images are
-// not covered by it.
+// at 256x256: 31.3 us with it, 29.6 without).  Without the fence the event
+// alone does not order the counters before the host's reads: what does is the
+// stamp that follows them (Counters::stamp).  Images are not covered by it.
 constexpr unsigned kDoneEvent = hipEventDisableTiming | hipEventDisableSystemFence;
 
 // Scratch of one (device, stream).
@@ -217,10 +218,15 @@ int bins_new(Bins** out) {
 }
 
 // Reads the counters of a completed call into ws->last (sums over its renders)
-// and grows the bins of any render whose lists overflowed.
-void harvest(Workspace* ws) {
+// and grows the bins of any render whose lists overflowed.  Leaves them for
+// later while they have not all arrived, unless the stream is known to be idle.
+void harvest(Workspace* ws, bool idle = false) {
     if (!ws->pending) return;
     if (hipEventQuery(ws->done) != hipSuccess) return;
+    for (int i = 0; i < ws->pending_n && !idle; ++i) {
+        const Bins* b = ws->slots[i];
+        if (__atomic_load_n(&b->host_ctr->stamp, __ATOMIC_ACQUIRE) != b->stamp) return;
+    }
     vtx_stats s{};
     for (int i = 0; i < ws->pending_n; ++i) {
         Bins* b = ws->slots[i];
@@ -1052,6 +1058,8 @@ int render_locked(std::vector<JobDesc>& d, bool bin, bool shade, hipStream_t str
             }
         }
         if ((rc = ensure_bins(ws, b, T, nprim, groups, chunk, nc, s.F.W, s.F.H))) return rc;
+        if (!capture) ++b->stamp;   // a captured launch keeps the sizing call's: the job tables must be the same
+        b->bb.stamp = b->stamp;
         b->pending_uid = s.scene_uid;
         b->pending_w = s.F.W;
         b->pending_h = s.F.H;
@@ -2124,6 +2132,10 @@ int vtx_read_stats(void* stream, vtx_stats* out) {
     Workspace* ws = it->second;
     if (ws->pending) VTX_HIP(hipEventSynchronize(ws->done));
     harvest(ws);
+    if (ws->pending) {   // the counters were still on their way
+        VTX_HIP(hipStreamSynchronize(ws->stream));
+        harvest(ws, true);
+    }
     if (!ws->have_stats) return fail(VTX_EINVAL, "no frame was rendered on this stream");
     *out = ws->last;
     return VTX_OK;
@@ -2136,7 +2148,7 @@ int vtx_set_bin_capacity(void* stream, uint64_t entries) {
     int rc = get_workspace((hipStream_t)stream, &ws);
     if (rc) return rc;
     VTX_HIP(hipStreamSynchronize(ws->stream));
-    harvest(ws);
+    harvest(ws, true);
     ws->fixed_capacity = entries > 0;
     ws->fixed_entries = entries;
     for (Bins* b : ws->slots) {

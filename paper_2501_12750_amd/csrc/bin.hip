@@ -689,8 +689,17 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_scatter(JS js, int phase) {
         }
     }
     __syncthreads();
+    // at the end of the workgroup's work, when the counters' stores are long
+    // done; a counting frame's follow the fragment counters (k_publish)
+    auto stamp = [&]() {
+        if (lead && tid == 0 && host_ctr && phase != kPhaseFront && !(F.flags & (1u | 16u)))
+            stamp_counters(host_ctr, J.bb.stamp);
+    };
     const uint32_t n = vis_cnt[blk];
-    if (n == 0) return;
+    if (n == 0) {
+        stamp();
+        return;
+    }
     const global_t<const uint32_t>* __restrict__ const my_src = vis_src + (size_t)blk * chunk;
     const global_t<const uint2>* __restrict__ const my_rect = vis_rect + (size_t)blk * chunk;
     const int ts = F.tile, tsh = F.tile_shift;
@@ -755,6 +764,7 @@ __global__ void __launch_bounds__(kBinThreads, 8) k_scatter(JS js, int phase) {
             }
         }
     }
+    stamp();
 }
 
 }  // namespace

@@ -935,6 +935,7 @@ __global__ void __launch_bounds__(kBlock) k_publish(JS js) {
         J.bb.host_ctr->rec_culled = src->rec_culled;
         J.bb.host_ctr->lists_stopped = src->lists_stopped;
         J.bb.host_ctr->chunks_stopped = src->chunks_stopped;
+        stamp_counters(J.bb.host_ctr, J.bb.stamp);
     }
 }
 

@@ -127,7 +127,16 @@ struct Counters {
     // primitive its workgroups binned (+inf: none; 0: not positive)
     unsigned int layer_zlo[2][kLayers];
     unsigned long long pairs_counted;   // total of the tile counts, added by the count kernel
+    unsigned int stamp;                 // host copy: the job's stamp, written once the frame's counters are there
 };
+
+// Stores a job's stamp after its counters, all by one thread: the stores
+// before it have reached the (coherent, uncached) host memory when they no
+// longer count as outstanding.
+__device__ inline void stamp_counters(Counters* host_ctr, unsigned int stamp) {
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    host_ctr->stamp = stamp;
+}
 
 // View-space record of one visible primitive (32 bytes), computed from FP64
 // and rounded to FP32; the resolve rebuilds it from the 8-byte tile-list
@@ -409,6 +418,7 @@ struct BinBuffers {
     int32_t hz16_w;
     Counters* ctr;
     Counters* host_ctr;     // device address of host-mapped counters (may be null)
+    uint32_t stamp;         // see Counters::stamp
 };
 
 // Images of more tiles than the device holds resolve workgroups (7 on each of
