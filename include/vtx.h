@@ -217,7 +217,9 @@ typedef struct vtx_options {
 typedef struct vtx_stats {
     uint64_t visible;          /* primitives that survived frustum culling (two-pass frames:
                                   of the clusters they binned) */
-    uint64_t pairs;            /* (primitive, tile) bin entries */
+    uint64_t pairs;            /* (primitive, tile) bin entries (two-pass frames: of the pass
+                                  with more; VTX_FLAG_ONE_PASS, STATS or COUNT give the
+                                  frame's whole numbers) */
     uint64_t fragments_tested; /* (primitive, pixel) ray tests run (VTX_FLAG_STATS: every
                                   footprint pixel; VTX_FLAG_COUNT: those the early-outs left) */
     uint64_t fragments_hit;    /* tests that hit: atom-fragments (VTX_FLAG_STATS) */
