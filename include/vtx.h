@@ -86,7 +86,7 @@ extern "C" {
                                     VTX_FLAG_STATS, VTX_FLAG_COUNT or
                                     VTX_FLAG_ONE_PASS, with 8-pixel
                                     tiles, for jobs in a batch whose other jobs do
-                                    not all set it, and on the first frame of a new
+                                    not all take it, and on the first frame of a new
                                     scene or image size in a render slot */
 #define VTX_FLAG_ONE_PASS 4u     /* resident scenes: never take the pre-pass */
 #define VTX_FLAG_COUNT 16u       /* count the ray tests the frame runs with its depth
@@ -241,8 +241,8 @@ typedef struct vtx_timings {
     uint64_t frames;        /* frames averaged */
     double ms_clear;        /* clear the tile counters */
     double ms_project;      /* project, cull, count per tile */
-    double ms_scan;         /* prefix sum of the tile counts */
-    double ms_scatter;      /* fill the tile lists */
+    double ms_scan;         /* starts of the layers of each tile list (resident scenes) */
+    double ms_scatter;      /* prefix sum of the tile counts, fill the tile lists */
     double ms_resolve;      /* per-tile ray casting into the G-buffer */
     double ms_shade;        /* SSAO and shading */
 } vtx_timings;
