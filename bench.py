@@ -61,7 +61,7 @@ KERNEL_SOURCES = {"k_resolve": "resolve.hip", "k_cluster_rest": "scene.hip", "k_
                   "k_scan_one": "scan.hip", "k_zero": "bin.hip"}
 # the launches of one vtx_ses call on the benchmark's grid (a window of 5
 # steps: the distance passes of a brick in LDS; up to 8192 cube runs: one scan)
-SES_KERNELS = ["k_zero", "k_ses_mark", "k_ses_edt<5>", "k_ses_count", "k_scan_one", "k_ses_emit"]
+SES_KERNELS = ["k_zero", "k_ses_mark<1>", "k_ses_edt<5>", "k_ses_count", "k_scan_one", "k_ses_emit"]
 
 
 def log(msg):

@@ -182,125 +182,119 @@ struct MarkGrid {
 };
 inline int mark_cells(int n) { return (n + 3) / 4; }
 
-// Sets the bits of the grid points inside an atom's solvent-accessible sphere
-// (points no atom marks stay 0: exterior), one lane per 4 x 4 x 4 cell of the
-// atom's box, one atomic per cell that has any.  The squared offsets and the
-// two sums are rounded as the reading states; each rounding is monotone, so a
-// cell whose nearest (farthest) corner fails (passes) the test is empty (full)
-// without testing its points.  Bounded by the point tests' VALU instructions:
-// 50,000 atoms of reach 2.6 to 3.2 at spacing 0.5 take 45 us, and took 90 with
-// a byte per point (249 MB of write-backs for a 10 MB grid).
+// Several atoms per wave (k_ses_mark), for grids with few points per atom,
+// whose boxes of some eight cells leave most of a wave's lanes idle: the lanes
+// take the cells of all its atoms in turn.  The wave's atoms lie a grid's width
+// apart in the input, so neighbours in space, which often are neighbours there,
+// do not meet in one wave.  1M atoms of reach 2.6 to 3.2, the whole call with a
+// wave per atom and per 8: spacing 0.7 1,010 and 593 us, 1.4 845 and 214, 5 733
+// and 150 (lanes by (x, y) columns of a byte grid: 2,727, 663 and 376).
+constexpr int kMarkAtoms = 8;
+constexpr uint64_t kManyPoints = 100;   // grid points per atom below which it is done
 
-// The cells of an atom's box: false if it has none.
+// An atom's box: centre, squared reach, first cell and cells.
 struct AtomBox {
-    double c[3], R2;   // centre, squared reach
-    int lo[3], nc[3];  // first cell, cells
+    double c[3], R2;
+    int lo[3], nc[3];
 };
-__device__ __forceinline__ bool atom_box(const SesGrid& G, const float* __restrict__ pos, const float* __restrict__ rad, size_t a,
-                                AtomBox& B) {
-#pragma clang fp contract(off)
-    const double R = (double)rad[a] + G.rp;
-    if (!(R > 0.0)) return false;
-    B.R2 = R * R;
-    const int nmax[3] = {G.nx - 1, G.ny - 1, G.nz - 1};
-    // the box only has to hold every point the test can mark: see SesGrid::slack
-    const double margin = fma(R, G.slack, G.slack0);
-    for (int d = 0; d < 3; ++d) {
-        B.c[d] = pos[3 * a + d];
-        const double from = fmax(0.0, ceil((B.c[d] - R - G.o[d]) * G.inv_h - margin));
-        const double to = fmin((double)nmax[d], floor((B.c[d] + R - G.o[d]) * G.inv_h + margin));
-        if (!(from <= to) || !(B.c[d] - B.c[d] == 0.0)) return false;   // beside the grid, or not a finite position
-        const int l = (int)from, h = (int)to;
-        B.lo[d] = l >> 2;
-        B.nc[d] = (h >> 2) - B.lo[d] + 1;
-    }
-    return true;
-}
 
-// Marks cell q (x fastest) of a box.
-__device__ __forceinline__ void mark_cell(const SesGrid& G, const MarkGrid& M, const AtomBox& B, int q) {
-#pragma clang fp contract(off)
-    const int qz = q / (B.nc[0] * B.nc[1]), qr = q - qz * (B.nc[0] * B.nc[1]), qy = qr / B.nc[0], qx = qr - qy * B.nc[0];
-    const int cell[3] = {B.lo[0] + qx, B.lo[1] + qy, B.lo[2] + qz};
-    double s[3][4], near[3], far[3];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const double x = (G.o[d] + G.h * (4 * cell[d] + t)) - B.c[d];
-            s[d][t] = x * x;
-        }
-        near[d] = fmin(fmin(s[d][0], s[d][1]), fmin(s[d][2], s[d][3]));
-        far[d] = fmax(s[d][0], s[d][3]);
-    }
-    if (!((near[0] + near[1]) + near[2] < B.R2)) return;
-    unsigned long long m = ~0ull;
-    if (!((far[0] + far[1]) + far[2] < B.R2)) {
-        uint32_t w[2] = {0u, 0u};
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const double sxy = s[0][i] + s[1][j];
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    w[k >> 1] |= sxy + s[2][k] < B.R2 ? 1u << ((k & 1) * 16 + j * 4 + i) : 0u;
-            }
-        m = ((unsigned long long)w[1] << 32) | w[0];
-    }
-    if (m) atomicOr(&M.bits[((size_t)cell[2] * M.ny + cell[1]) * M.nx + cell[0]], m);
-}
-
-// One wave per atom.
+// kAtoms atoms per wave: sets the bits of the grid points inside their
+// solvent-accessible spheres (points no atom marks stay 0: exterior), one lane
+// per 4 x 4 x 4 cell of an atom's box, one atomic per cell that has any.  The
+// squared offsets and the two sums are rounded as the reading states; each
+// rounding is monotone, so a cell whose nearest (farthest) corner fails
+// (passes) the test is empty (full) without testing its points.  Bounded by
+// the point tests' VALU instructions: 50,000 atoms of reach 2.6 to 3.2 at
+// spacing 0.5 take 45 us, and took 90 with a byte per point (249 MB of
+// write-backs for a 10 MB grid).  One atom's box stays in registers and the
+// cell's test in the kernel itself: as functions of the box it was 1 to 3 us
+// slower.
+template <int kAtoms>
 __global__ void __launch_bounds__(kSesMarkBlock) k_ses_mark(const float* __restrict__ pos,
                                                             const float* __restrict__ rad, uint32_t n, SesGrid G,
                                                             MarkGrid M) {
-    if (blockIdx.x >= n) return;
-    AtomBox B;
-    if (!atom_box(G, pos, rad, blockIdx.x, B)) return;
-    const int cells = B.nc[0] * B.nc[1] * B.nc[2];
-    for (int q = threadIdx.x; q < cells; q += kSesMarkBlock) mark_cell(G, M, B, q);
-}
-
-// kMarkAtoms atoms per wave, for grids with few points per atom, whose boxes of
-// some eight cells leave most of a wave's lanes idle: the lanes take the cells
-// of all its atoms in turn.  The wave's atoms lie a grid's width apart in the
-// input, so neighbours in space, which often are neighbours there, do not meet
-// in one wave.  1M atoms of reach 2.6 to 3.2, the whole call with a wave per
-// atom and per 8: spacing 0.7 1,011 and 596 us, 1.4 845 and 211, 5 732 and 149
-// (lanes by (x, y) columns of a byte grid: 2,727, 661 and 375).
-constexpr int kMarkAtoms = 8;
-constexpr uint64_t kManyPoints = 100;   // grid points per atom below which it is taken
-
-__global__ void __launch_bounds__(kSesMarkBlock) k_ses_mark_many(const float* __restrict__ pos,
-                                                                 const float* __restrict__ rad, uint32_t n, SesGrid G,
-                                                                 MarkGrid M) {
-    __shared__ AtomBox box[kMarkAtoms];
-    __shared__ uint32_t first[kMarkAtoms + 1];   // where each box's cells start among the wave's
+#pragma clang fp contract(off)
+    constexpr bool kMany = kAtoms > 1;
+    __shared__ AtomBox box[kMany ? kAtoms : 1];
+    __shared__ uint32_t first[kAtoms + 1];   // where each box's cells start among the wave's
     const int lane = threadIdx.x;
-    if (lane < kMarkAtoms) {
-        const uint64_t a = blockIdx.x + (uint64_t)lane * gridDim.x;
-        AtomBox B;
-        uint32_t end = 0;
-        if (a < n && atom_box(G, pos, rad, (size_t)a, B)) {
-            box[lane] = B;
-            end = (uint32_t)B.nc[0] * (uint32_t)B.nc[1] * (uint32_t)B.nc[2];
+    AtomBox B;
+    uint32_t cells = 0;
+    if (!kMany || lane < kAtoms) {
+        const uint64_t a = blockIdx.x + (kMany ? (uint64_t)lane * gridDim.x : 0u);
+        bool ok = a < n;
+        if (ok) {
+            for (int d = 0; d < 3; ++d) B.c[d] = pos[3 * a + d];
+            const double R = (double)rad[a] + G.rp;
+            ok = R > 0.0;
+            B.R2 = R * R;
+            const int nmax[3] = {G.nx - 1, G.ny - 1, G.nz - 1};
+            // the box only has to hold every point the test can mark: see SesGrid::slack
+            const double margin = fma(R, G.slack, G.slack0);
+            for (int d = 0; d < 3; ++d) {
+                const double from = fmax(0.0, ceil((B.c[d] - R - G.o[d]) * G.inv_h - margin));
+                const double to = fmin((double)nmax[d], floor((B.c[d] + R - G.o[d]) * G.inv_h + margin));
+                ok = ok && from <= to && B.c[d] - B.c[d] == 0.0;   // else beside the grid, or not a finite position
+                const int l = (int)from, h = (int)to;
+                B.lo[d] = l >> 2;
+                B.nc[d] = (h >> 2) - B.lo[d] + 1;
+            }
         }
+        if (ok) cells = (uint32_t)B.nc[0] * (uint32_t)B.nc[1] * (uint32_t)B.nc[2];
+        if (kMany) {
+            box[kMany ? lane : 0] = B;
+            uint32_t end = cells;
 #pragma unroll
-        for (int o = 1; o < kMarkAtoms; o <<= 1) {
-            const uint32_t u = (uint32_t)__shfl_up((int)end, o);
-            if (lane >= o) end += u;
+            for (int o = 1; o < kAtoms; o <<= 1) {
+                const uint32_t u = (uint32_t)__shfl_up((int)end, o);
+                if (lane >= o) end += u;
+            }
+            first[lane + 1] = end;
+            if (lane == 0) first[0] = 0;
         }
-        first[lane + 1] = end;
-        if (lane == 0) first[0] = 0;
     }
-    __syncthreads();
-    const uint32_t cells = first[kMarkAtoms];   // at most 2^27 of a box: fewer than 2^31 points, 2 or more a side
+    if (kMany) {
+        __syncthreads();
+        cells = first[kAtoms];   // at most 2^27 of a box: fewer than 2^31 points, 2 or more a side
+    }
     for (uint32_t q = (uint32_t)lane; q < cells; q += kSesMarkBlock) {
-        int a = 0;
+        int at = (int)q;
+        if (kMany) {
+            int a = 0;
 #pragma unroll
-        for (int k = 1; k < kMarkAtoms; ++k) a = q >= first[k] ? k : a;
-        mark_cell(G, M, box[a], (int)(q - first[a]));
+            for (int k = 1; k < kAtoms; ++k) a = q >= first[k] ? k : a;
+            B = box[kMany ? a : 0];
+            at = (int)(q - first[a]);
+        }
+        const int qz = at / (B.nc[0] * B.nc[1]), qr = at - qz * (B.nc[0] * B.nc[1]), qy = qr / B.nc[0], qx = qr - qy * B.nc[0];
+        const int cell[3] = {B.lo[0] + qx, B.lo[1] + qy, B.lo[2] + qz};
+        double s[3][4], near[3], far[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const double x = (G.o[d] + G.h * (4 * cell[d] + t)) - B.c[d];
+                s[d][t] = x * x;
+            }
+            near[d] = fmin(fmin(s[d][0], s[d][1]), fmin(s[d][2], s[d][3]));
+            far[d] = fmax(s[d][0], s[d][3]);
+        }
+        if (!((near[0] + near[1]) + near[2] < B.R2)) continue;
+        unsigned long long m = ~0ull;
+        if (!((far[0] + far[1]) + far[2] < B.R2)) {
+            uint32_t w[2] = {0u, 0u};
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const double sxy = s[0][i] + s[1][j];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        w[k >> 1] |= sxy + s[2][k] < B.R2 ? 1u << ((k & 1) * 16 + j * 4 + i) : 0u;
+                }
+            m = ((unsigned long long)w[1] << 32) | w[0];
+        }
+        if (m) atomicOr(&M.bits[((size_t)cell[2] * M.ny + cell[1]) * M.nx + cell[0]], m);
     }
 }
 
@@ -827,8 +821,8 @@ hipError_t ses_run(const float* pos, const float* rad, uint64_t n, float probe, 
     // and 52; 200 atoms of 300,000 220 and 843.
     if (np < kManyPoints * n) {
         const unsigned waves = (unsigned)((n + kMarkAtoms - 1) / kMarkAtoms);
-        if ((e = dispatch(k_ses_mark_many, waves, kSesMarkBlock, 0, stream, pos, rad, (uint32_t)n, G, M))) return e;
-    } else if (n && (e = dispatch(k_ses_mark, (unsigned)n, kSesMarkBlock, 0, stream, pos, rad, (uint32_t)n, G, M))) {
+        if ((e = dispatch(k_ses_mark<kMarkAtoms>, waves, kSesMarkBlock, 0, stream, pos, rad, (uint32_t)n, G, M))) return e;
+    } else if (n && (e = dispatch(k_ses_mark<1>, (unsigned)n, kSesMarkBlock, 0, stream, pos, rad, (uint32_t)n, G, M))) {
         return e;
     }
     const int nxw = (G.nx + 31) / 32;
